@@ -517,8 +517,29 @@ int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *
     if (!q_start) return KVC_ERR_NULL;
     rc = check_attn_args(q, k_cache, v_cache, block_tables, context_lens, scale, out);
     if (rc != KVC_OK) return rc;
-    const bool on_mfma = desc->dtype == KVC_BF16 && desc->head_dim == 128 &&
-                         desc->num_q_heads / desc->num_kv_heads <= 16;
+    kvc::PrefillParams p;
+    p.num_seqs = desc->num_seqs;
+    p.num_q_heads = desc->num_q_heads;
+    p.num_kv_heads = desc->num_kv_heads;
+    p.group = desc->num_q_heads / desc->num_kv_heads;
+    p.heads_per_chunk = p.group % 2 == 0 ? 2 : 1;
+    p.block_size = desc->block_size;
+    p.block_size_log2 = ilog2(desc->block_size);
+    p.tiles_per_block_log2 = desc->block_size >= 16 ? ilog2(desc->block_size / 16) : 0;
+    p.max_blocks_per_seq = desc->max_blocks_per_seq;
+    p.max_query_tiles = int(ceil_div(max_query_len, 64));
+    p.scale_log2e = float(double(scale) * 1.4426950408889634);
+    const int64_t tile_grid = int64_t(p.num_q_heads / p.heads_per_chunk) * p.num_seqs * p.max_query_tiles;
+    const bool on_mfma = desc->dtype == KVC_BF16 && desc->head_dim == 128 && p.group <= 16;
+    // head_dim 64 has a matrix-core kernel of its own, for every group size and scale.  Calls of one query row per
+    // sequence stay on the vector ALUs, which take 4 or 8 heads per workgroup and read K and V less often (64
+    // sequences of 500 to 1000 tokens, 32 / 8 heads: 27 us against 40 us; with two rows 43 us against 40 us), and so
+    // does a grid beyond the launch limit (very many sequences with a loose max_query_len; that one counts rows).
+    if (desc->dtype == KVC_BF16 && desc->head_dim == 64 && max_query_len > 1 && tile_grid <= kMaxGrid) {
+        const hipError_t e = kvc::launch_prefill_d64(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p,
+                                                     max_query_len, static_cast<hipStream_t>(hip_stream));
+        return e == hipSuccess ? KVC_OK : hip_failed(e);
+    }
     if (!on_mfma) {
         // vector-ALU kernel, one query row per "sequence" of its grid, one partition, no workspace
         kvc::AttnParams vp = make_params(*desc, pl, scale);
@@ -533,20 +554,7 @@ int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *
                                                       desc->head_dim, int(grid), static_cast<hipStream_t>(hip_stream));
         return e == hipSuccess ? KVC_OK : hip_failed(e);
     }
-    kvc::PrefillParams p;
-    p.num_seqs = desc->num_seqs;
-    p.num_q_heads = desc->num_q_heads;
-    p.num_kv_heads = desc->num_kv_heads;
-    p.group = desc->num_q_heads / desc->num_kv_heads;
-    p.heads_per_chunk = p.group % 2 == 0 ? 2 : 1;
-    p.block_size = desc->block_size;
-    p.block_size_log2 = ilog2(desc->block_size);
-    p.tiles_per_block_log2 = desc->block_size >= 16 ? ilog2(desc->block_size / 16) : 0;
-    p.max_blocks_per_seq = desc->max_blocks_per_seq;
-    p.max_query_tiles = int(ceil_div(max_query_len, 64));
-    p.scale_log2e = float(double(scale) * 1.4426950408889634);
-    if (int64_t(p.num_q_heads / p.heads_per_chunk) * p.num_seqs * p.max_query_tiles > kMaxGrid)
-        return KVC_ERR_BAD_SHAPE;
+    if (tile_grid > kMaxGrid) return KVC_ERR_BAD_SHAPE;
     // 32x32 tiles need a positive scale (their max is taken over raw scores); KVC_KERNEL_MFMA asks
     // for the 16x16-tile kernel whatever the shape
     const bool tiles32 = p.scale_log2e > 0.0f && desc->kernel != KVC_KERNEL_MFMA;
