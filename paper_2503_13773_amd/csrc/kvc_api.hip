@@ -80,6 +80,20 @@ bool balanced_ok(const kvc_attn_desc &d, int max_ctx) {
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 16) < (int64_t(1) << 31);
 }
 
+// At head_dim 64 the balanced kernel serves the calls that KVC_KERNEL_AUTO brings with a context bound
+// above 256 tokens and no split of the caller's own.  Up to 256 tokens the vector-ALU kernel is one launch
+// without a workspace as well, and a caller may rely on that.  Small batches stay on the vector ALUs too: the
+// line lies where the two meet in back-to-back launches (kv heads x tokens of the bound; vector ALUs / balanced
+// in us: 16 k 8.1 / 9.8, 51 k 10.9 / 14.2, 102 k 9.7 / 11.9, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
+bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
+    return d.kernel == KVC_KERNEL_AUTO && d.dtype == KVC_BF16 && d.head_dim == 64 && d.block_size >= 4 &&
+           d.partition_tokens == 0 && max_ctx > 256 && d.num_q_heads / d.num_kv_heads <= 16 &&
+           d.num_seqs <= kvc::kMaxStreamSeqs &&
+           int64_t(d.num_seqs) * d.num_kv_heads * max_ctx >= (1 << 17) &&
+           int64_t(d.num_seqs) * d.num_kv_heads * (ceil_div(max_ctx, 32) + 1) < (int64_t(1) << 30) &&
+           int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
+}
+
 int make_plan(const kvc_attn_desc *d, Plan *pl) {
     if (!d) return KVC_ERR_NULL;
     if (d->num_seqs < 0 || d->num_q_heads <= 0 || d->num_kv_heads <= 0 || d->head_dim <= 0 ||
@@ -101,24 +115,26 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
     int kernel = d->kernel;
     if (kernel < KVC_KERNEL_AUTO || kernel > KVC_KERNEL_MFMA_BALANCED) return KVC_ERR_BAD_SHAPE;
     if (kernel == KVC_KERNEL_AUTO)
-        kernel = balanced_ok(*d, max_ctx) ? KVC_KERNEL_MFMA_BALANCED
+        kernel = balanced_ok(*d, max_ctx) || balanced64_ok(*d, max_ctx) ? KVC_KERNEL_MFMA_BALANCED
                  : mfma_ok(*d)            ? KVC_KERNEL_MFMA
                                           : KVC_KERNEL_VALU;
     if ((kernel == KVC_KERNEL_MFMA || kernel == KVC_KERNEL_MFMA_LDS) && !mfma_ok(*d)) return KVC_ERR_UNSUPPORTED;
-    if (kernel == KVC_KERNEL_MFMA_BALANCED && !balanced_ok(*d, max_ctx)) return KVC_ERR_UNSUPPORTED;
+    if (kernel == KVC_KERNEL_MFMA_BALANCED && !balanced_ok(*d, max_ctx) && !balanced64_ok(*d, max_ctx))
+        return KVC_ERR_UNSUPPORTED;
 
     const int64_t rows = int64_t(d->num_seqs) * d->num_q_heads;
     constexpr uint64_t kHeader = kvc::kWorkspaceHeaderBytes;
     if (kernel == KVC_KERNEL_MFMA_BALANCED) {
         // One launch: cut rows are merged by the last worker to arrive.  A wavefront never takes
         // fewer than min_chunk tiles; the workspace is two partial slots per wavefront.
-        const int64_t max_tiles = ceil_div(max_ctx, 16);
-        const int min_chunk = d->partition_tokens ? d->partition_tokens / 16
+        const int tile_tokens = d->head_dim == 64 ? 32 : 16;  // 8 KiB of K and V
+        const int64_t max_tiles = ceil_div(max_ctx, tile_tokens);
+        const int min_chunk = d->partition_tokens ? d->partition_tokens / tile_tokens
                                                   : int(std::max<int64_t>(4, ceil_div(max_tiles, 32)));
         const int group = d->num_q_heads / d->num_kv_heads;
         const uint64_t slots = uint64_t(kvc::kNumCUs) * kvc::kWaves * 2;
         pl->kernel = kernel;
-        pl->partition_tokens = min_chunk * 16;
+        pl->partition_tokens = min_chunk * tile_tokens;
         pl->min_chunk_tiles = min_chunk;
         pl->max_partitions = 2;           // partial slots per worker
         pl->partial_grid = kvc::kNumCUs;  // 4 wavefronts per CU: one worker per SIMD
@@ -211,7 +227,7 @@ int run_partial(const void *q, const void *k_cache, const void *v_cache, const i
                                      desc->dtype, desc->head_dim, int(pl.partial_grid), stream);
     else if (pl.kernel == KVC_KERNEL_MFMA_BALANCED)
         e = kvc::launch_partial_mfma_stream(q, k_cache, v_cache, block_tables, context_lens, out,
-                                            ws, p, int(pl.partial_grid), 0, kvc::Schedule{}, stream);
+                                            ws, p, desc->head_dim, int(pl.partial_grid), 0, kvc::Schedule{}, stream);
     else
         e = kvc::launch_partial_mfma(q, k_cache, v_cache, block_tables, context_lens, out, ws, p,
                                      int(pl.partial_grid), stream);
@@ -234,7 +250,7 @@ struct ScheduleLayout {
 };
 
 bool schedule_layout(const kvc_attn_desc &d, const Plan &pl, ScheduleLayout *L) {
-    if (pl.kernel != KVC_KERNEL_MFMA_BALANCED) return false;
+    if (pl.kernel != KVC_KERNEL_MFMA_BALANCED || d.head_dim != 128) return false;
     const int64_t workers = int64_t(kvc::kNumCUs) * kvc::kWaves;
     const int64_t units_per_tile = d.block_size >= 16 ? 1 : 16 / d.block_size;
     // no worker takes more flat units than this, whatever the context lengths turn out to be
@@ -444,7 +460,7 @@ int kvc_attn_schedule_build(const int32_t *block_tables, const int32_t *context_
     if (!block_tables || !context_lens) return KVC_ERR_NULL;
     const kvc::AttnParams p = make_params(*desc, pl, 1.0f);
     const hipError_t e = kvc::launch_partial_mfma_stream(nullptr, nullptr, nullptr, block_tables, context_lens,
-                                                         nullptr, kvc::Workspace{}, p, int(pl.partial_grid), 1,
+                                                         nullptr, kvc::Workspace{}, p, desc->head_dim, int(pl.partial_grid), 1,
                                                          schedule_view(schedule, L),
                                                          static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? KVC_OK : hip_failed(e);
@@ -470,7 +486,7 @@ int kvc_paged_attention_decode_scheduled(const void *q, const void *k_cache, con
     if (rc != KVC_OK) return rc;
     const kvc::AttnParams p = make_params(*desc, pl, scale);
     const hipError_t e = kvc::launch_partial_mfma_stream(q, k_cache, v_cache, nullptr, nullptr, out, ws, p,
-                                                         int(pl.partial_grid), 2,
+                                                         desc->head_dim, int(pl.partial_grid), 2,
                                                          schedule_view(const_cast<void *>(schedule), L),
                                                          static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? KVC_OK : hip_failed(e);

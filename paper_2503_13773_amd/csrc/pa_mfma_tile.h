@@ -23,6 +23,7 @@
 // or Inf stored there cannot reach the output.
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -53,16 +54,18 @@ __device__ inline uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
 }
 
-// Online-softmax state of the (up to 16) heads of one KV head, as held by one wavefront.
-struct HeadState {
-    floatx4 acc[8];
+// Online-softmax state of the (up to 16) heads of one KV head, as held by one wavefront: lane
+// (quad, r) holds head r's dims N * 4 * quad + N * i + e in acc[e][i] (N = head_dim / 16).
+template <int N>
+struct HeadStateN {
+    floatx4 acc[N];
     float m;  // running max of the scaled scores (base-2 units) of head r
     float l;  // running sum of weights; partial over this lane's tokens until finish()
 
     __device__ inline void reset() {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
-        m = -INFINITY;
+        for (int e = 0; e < N; ++e) acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+        m = N == 8 ? -INFINITY : -FLT_MAX;  // head_dim 64: scores may be -inf (see below)
         l = 0.f;
     }
     // sum l over the 4 quads (the max is already common to them)
@@ -71,12 +74,14 @@ struct HeadState {
         l += __shfl_xor(l, 32);
     }
 };
+using HeadState = HeadStateN<8>;
 
 // Q as the B operand of S = K.Q^T: lane (quad, r) holds Q[head r][32j + 8*quad .. +7].
 // `qrow` points at Q[head r of this KV head's group]; lanes with active == false get zeros.
-__device__ inline void load_q_operand(bf16x8 (&qb)[4], const uint16_t *qrow, int quad, bool active) {
+template <int N>
+__device__ inline void load_q_operand(bf16x8 (&qb)[N], const uint16_t *qrow, int quad, bool active) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < N; ++j) {
         uint4 w = {0u, 0u, 0u, 0u};
         if (active) w = *reinterpret_cast<const uint4 *>(qrow + 32 * j + 8 * quad);
         qb[j] = __builtin_bit_cast(bf16x8, w);
@@ -155,6 +160,90 @@ __device__ inline void compute_tile(HeadState &st, const bf16x8 (&ka)[4], uint4 
                           __builtin_amdgcn_perm(v3[w], v2[w], 0x07060302u)};
         st.acc[2 * w] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, lo), pb, st.acc[2 * w], 0, 0, 0);
         st.acc[2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, hi), pb, st.acc[2 * w + 1], 0, 0, 0);
+    }
+}
+
+// ---- head_dim 64: a tile is 32 tokens, so that a tile's loads are 8 KiB as at head_dim 128.
+//
+//   S[token][head]   2 x 2 x v_mfma_f32_16x16x32_bf16: sub-tile h holds tokens 16h .. 16h + 15.
+//   O^T[dim][head]   4 dim blocks x 2 x v_mfma_f32_16x16x32_bf16, depth = the 32 tokens in the order
+//                    the scores lie in: depth slot 8*quad + 4h + i is token 16h + 4*quad + i.  V is loaded
+//                    row-wise, 8 bytes (dims 4r .. 4r+3) of a token per lane, 16 lanes read one 128-byte
+//                    row; MFMA number e yields dims {4*row + e}.
+//
+// The weights keep fp32 accuracy: a weight enters the product as the sum of two bf16 values (its
+// upper bits and the rounded rest, 2^-16 relative) and the normaliser sums the fp32 weights.  The upper part
+// is cut off and the rest made positive by 2^-23 of the weight (a factor all weights share), so that
+// an infinity in V keeps its sign, which a rest of 0 or of the other sign would turn into NaN.  A score of
+// -inf weighs nothing: the running max starts at the lowest finite value.
+constexpr int kTileTokens64 = 32;
+
+__device__ inline uint2 load8_stream(const uint16_t *p) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint2, __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p)));
+}
+
+// `valid` = tokens of the tile inside the context (wavefront-uniform); kr[2h + j] = K[token 16h + r][32j + 8*quad ..],
+// vr[4h + i] = V[token 16h + 4*quad + i][4r ..].
+__device__ inline void compute_tile(HeadStateN<4> &st, const uint4 (&kr)[4], uint2 (&vr)[8], const bf16x8 (&qb)[2],
+                                    float scale_log2e, int valid, int quad) {
+    float sv[8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[2 * h + j]), qb[j], s, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sv[4 * h + i] = s[i] * scale_log2e;
+    }
+    if (valid < kTileTokens64) {  // ragged tile
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (16 * (t >> 2) + 4 * quad + (t & 3) >= valid) {
+                sv[t] = -INFINITY;
+                vr[t] = uint2{0u, 0u};
+            }
+        }
+    }
+    float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(st.m, mx);
+    const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
+    st.m = m_new;
+    float psum = 0.f;
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float p0 = __builtin_amdgcn_exp2f(sv[2 * i] - m_new), p1 = __builtin_amdgcn_exp2f(sv[2 * i + 1] - m_new);
+        psum += p0 + p1;
+        const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+        hi[i] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+        lo[i] = pack_bf16(__builtin_fmaf(p0, 1.f + FLT_EPSILON, -__uint_as_float(u0 & 0xffff0000u)),
+                          __builtin_fmaf(p1, 1.f + FLT_EPSILON, -__uint_as_float(u1 & 0xffff0000u)));
+    }
+    st.l = fmaf(st.l, alpha, psum);
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st.acc[e] *= alpha;
+    }
+    const bf16x8 ph = __builtin_bit_cast(bf16x8, uint4{hi[0], hi[1], hi[2], hi[3]});
+    const bf16x8 pl = __builtin_bit_cast(bf16x8, uint4{lo[0], lo[1], lo[2], lo[3]});
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {  // dword w of a row: dims 4r + 2w (low half) and 4r + 2w + 1 (high half)
+        uint32_t d[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) d[t] = w == 0 ? vr[t].x : vr[t].y;
+        const uint4 even = {__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u),
+                            __builtin_amdgcn_perm(d[5], d[4], 0x05040100u), __builtin_amdgcn_perm(d[7], d[6], 0x05040100u)};
+        const uint4 odd = {__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u),
+                           __builtin_amdgcn_perm(d[5], d[4], 0x07060302u), __builtin_amdgcn_perm(d[7], d[6], 0x07060302u)};
+        const bf16x8 ae = __builtin_bit_cast(bf16x8, even), ao = __builtin_bit_cast(bf16x8, odd);
+        st.acc[2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ae, ph, st.acc[2 * w], 0, 0, 0);
+        st.acc[2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao, ph, st.acc[2 * w + 1], 0, 0, 0);
+        st.acc[2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ae, pl, st.acc[2 * w], 0, 0, 0);
+        st.acc[2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao, pl, st.acc[2 * w + 1], 0, 0, 0);
     }
 }
 

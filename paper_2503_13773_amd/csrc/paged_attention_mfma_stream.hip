@@ -1,5 +1,9 @@
 // Load-balanced persistent kernel of paged decode attention on the matrix cores, one launch
-// (gfx950, bf16, head_dim 128, block_size >= 4, group <= 16, <= 4096 sequences).
+// (gfx950, bf16, head_dim 128 or 64, block_size >= 4, group <= 16, <= 4096 sequences).
+//
+// Written for head_dim 128 and 16-token tiles below; at head_dim 64 a tile is 32 tokens, the same 8 KiB of
+// K and V, so ranges, loads in flight and row costs are the same (48 sequences, lognormal, 32 / 8 heads, 73 MB:
+// 19.9 us; on the vector ALUs with a merge launch 32.9 us).
 //
 // The serving traces this path sees have heavily skewed context lengths (a lognormal mix:
 // median ~700 tokens, tail to 4096), and the whole batch is only ~30 us of HBM streaming.
@@ -100,10 +104,26 @@ __device__ inline float2 load2_device_scope(__amdgpu_buffer_rsrc_t b, uint32_t b
 }
 
 constexpr int kStageTiles = 256;  // tiles whose addresses are staged in LDS per wavefront at a time
-constexpr int kMaxUnits = 4;      // a 16-token tile spans up to 4 blocks (block_size 4)
 constexpr int kRowCost = 1;       // flat units charged for leaving a row
 static_assert(size_t(kNumCUs) * kWaves * sizeof(int32_t) <= kWorkspaceHeaderBytes,
               "one arrival counter per worker must fit the workspace header");
+
+// What depends on the head dimension: tokens of a tile (8 KiB of K and V either way), the registers a
+// tile is loaded into, Q operands, softmax state, dims a lane holds of its head.
+template <int HD>
+struct Shape;
+template <>
+struct Shape<128> {
+    static constexpr int kTokens = kTileTokens, kTokensLog2 = 4, kQ = 4, kVecs = 8;
+    using State = HeadStateN<8>;
+    struct Tile { uint4 k[4], v[4]; };
+};
+template <>
+struct Shape<64> {
+    static constexpr int kTokens = kTileTokens64, kTokensLog2 = 5, kQ = 2, kVecs = 4;
+    using State = HeadStateN<4>;
+    struct Tile { uint4 k[4]; uint2 v[8]; };
+};
 
 // ---- finishing cut rows --------------------------------------------------------------------
 // A cut row as seen by the worker that arrived last at it.
@@ -115,38 +135,43 @@ struct CutRow {
 };
 
 
-// Partial slot layout (fp32): [8 vectors][quad][head][4]; vector v of (quad, head) = dims
-// 32*quad + 4v .. +3 of the head's accumulator; (max, sum) per head in a second array.  One
+// Partial slot layout (fp32): [HD / 16 vectors][quad][head][4]; vector v of (quad, head) = dims
+// HD/4 * quad + 4v .. +3 of the head's accumulator; (max, sum) per head in a second array.  One
 // store or load instruction of a wavefront then covers whole 128-byte lines.  Offsets in bytes.
+template <int HD>
 __device__ inline uint32_t slot_vec(int slot, int G, int v, int quad, int head) {
-    return (uint32_t(slot) * uint32_t(G * mfma::D) + uint32_t(((v * 4 + quad) * G + head) * 4)) * 4u;
+    return (uint32_t(slot) * uint32_t(G * HD) + uint32_t(((v * 4 + quad) * G + head) * 4)) * 4u;
 }
 __device__ inline uint32_t slot_ml(int slot, int G, int head) { return uint32_t(slot * G + head) * 8u; }
 __device__ inline int slot_of_partial(int j0, int i) { return i == 0 ? 2 * j0 + 1 : 2 * (j0 + i); }
-// vector v of a lane's accumulator registers: dims 4v .. 4v+3 of its 32-dim slice
-__device__ inline float4 acc_vec(const mfma::HeadState &x, int v) {
+// vector v of a lane's accumulator registers: dims 4v .. 4v+3 of its slice of HD / 4 dims
+__device__ inline float4 acc_vec(const mfma::HeadStateN<8> &x, int v) {
     const int e = 4 * (v & 1), i = v >> 1;
     return float4{x.acc[e][i], x.acc[e + 1][i], x.acc[e + 2][i], x.acc[e + 3][i]};
+}
+__device__ inline float4 acc_vec(const mfma::HeadStateN<4> &x, int v) {
+    return float4{x.acc[0][v], x.acc[1][v], x.acc[2][v], x.acc[3][v]};
 }
 
 // Log-sum-exp merge of the partials of up to two cut rows, in slot order, and the write of the
 // rows.  The loads of both rows are issued before anything is consumed (device-scope loads
 // are slow, ~40 ns each per wavefront when measured, so only partials that exist and are not
-// the worker's own are fetched).  PV = 4-dim vectors per lane: with PV = 8 lane (quad, r)
-// merges all 32 dims of head r (lanes r >= G idle); with PV = 2 or 4 (G <= 2 PV) the 32 dims
-// are spread over the 8 / PV lanes (quad, head + 2 PV * sub), so all lanes work and a lane has
-// 8 / PV times fewer loads in flight.  The worker's own partial comes from its registers
-// (`mine`, re-distributed through `lds`, >= 128 * G floats private to the wavefront, when
-// PV < 8): the same values its slot holds, so the result does not depend on which worker merges.
-template <int PV, typename Await>
+// the worker's own are fetched).  PV = 4-dim vectors per lane: with PV = HD / 16 lane (quad, r)
+// merges all HD / 4 dims of head r (lanes r >= G idle); with 1/2 or 1/4 of that (G <= 8 or 4) the dims
+// are spread over the 2 or 4 lanes (quad, head + 8 or 4 * sub), so all lanes work and a lane has
+// 2 or 4 times fewer loads in flight.  The worker's own partial comes from its registers
+// (`mine`, re-distributed through `lds`, >= HD * G floats private to the wavefront, when
+// PV < HD / 16): the same values its slot holds, so the result does not depend on which worker merges.
+template <int HD, int PV, typename Await>
 __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_buffer_rsrc_t ml_buf,
                                       uint16_t *out, int G, int num_q_heads, int lane, float *lds,
-                                      const CutRow (&row)[2], const mfma::HeadState &mine0,
-                                      const mfma::HeadState &mine1, Await await_row) {
+                                      const CutRow (&row)[2], const typename Shape<HD>::State &mine0,
+                                      const typename Shape<HD>::State &mine1, Await await_row) {
     using namespace mfma;
-    constexpr int HP = 2 * PV;  // heads a quad row of 16 lanes can carry: 4, 8 or 16
+    constexpr int NV = Shape<HD>::kVecs;
+    constexpr int HP = 16 * PV / NV;  // heads a quad row of 16 lanes can carry: 4, 8 or 16
     const int quad = lane >> 4, r = lane & 15;
-    const int head = PV == 8 ? r : (r & (HP - 1)), sub = PV == 8 ? 0 : r / HP;
+    const int head = PV == NV ? r : (r & (HP - 1)), sub = PV == NV ? 0 : r / HP;
     const bool active = head < G;
     const int hd = active ? head : 0;
 
@@ -154,23 +179,23 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
     float2 own_ml[2];
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
-        const HeadState &mine = w == 0 ? mine0 : mine1;
+        const auto &mine = w == 0 ? mine0 : mine1;
         if (!row[w].active) continue;
-        if constexpr (PV == 8) {
+        if constexpr (PV == NV) {
 #pragma unroll
-            for (int v = 0; v < 8; ++v) own_x[w][v] = acc_vec(mine, v);
+            for (int v = 0; v < NV; ++v) own_x[w][v] = acc_vec(mine, v);
             own_ml[w] = float2{mine.m, mine.l};
         } else {
             if (r < G) {
 #pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    *reinterpret_cast<float4 *>(lds + slot_vec(0, G, v, quad, r) / 4) = acc_vec(mine, v);
+                for (int v = 0; v < NV; ++v)
+                    *reinterpret_cast<float4 *>(lds + slot_vec<HD>(0, G, v, quad, r) / 4) = acc_vec(mine, v);
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int vv = 0; vv < PV; ++vv)
-                own_x[w][vv] = *reinterpret_cast<const float4 *>(lds + slot_vec(0, G, PV * sub + vv, quad, hd) / 4);
+                own_x[w][vv] = *reinterpret_cast<const float4 *>(lds + slot_vec<HD>(0, G, PV * sub + vv, quad, hd) / 4);
             own_ml[w] = float2{__shfl(mine.m, (lane & 48) | hd), __shfl(mine.l, (lane & 48) | hd)};
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -190,7 +215,7 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
                 ml[w][u] = load2_device_scope(ml_buf, slot_ml(slot, G, hd));
 #pragma unroll
                 for (int vv = 0; vv < PV; ++vv)
-                    x[w][u][vv] = load4_device_scope(acc_buf, slot_vec(slot, G, PV * sub + vv, quad, hd));
+                    x[w][u][vv] = load4_device_scope(acc_buf, slot_vec<HD>(slot, G, PV * sub + vv, quad, hd));
             }
         }
     };
@@ -248,7 +273,9 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
         }
         if (active) {
             const float inv = 1.0f / L;
-            uint16_t *dst = out + (size_t(row[w].n) * num_q_heads + row[w].kvh * G + head) * D + 32 * quad + 4 * PV * sub;
+            uint16_t *dst = out + (size_t(row[w].n) * num_q_heads + row[w].kvh * G + head) * HD + HD / 4 * quad + 4 * PV * sub;
+            if constexpr (PV == 1)
+                *reinterpret_cast<uint2 *>(dst) = uint2{pack_bf16(a[0].x * inv, a[0].y * inv), pack_bf16(a[0].z * inv, a[0].w * inv)};
 #pragma unroll
             for (int v = 0; v < PV / 2; ++v) {
                 uint4 o;
@@ -282,12 +309,15 @@ constexpr int kPlanInts = 16;  // a worker's plan in the schedule buffer
 
 // MAXSPT: sequences per thread in the start-up prefix sum (batches up to MAXSPT * 256 sequences);
 // the small instance keeps the start-up of ordinary batches short.
-template <int MAXSPT, int MODE>
+template <int HD, int MAXSPT, int MODE>
 __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, uint16_t *__restrict__ out, Workspace ws,
     AttnParams p, int unit_log2, int units_per_block_log2, Schedule sched) {
+    using TS = Shape<HD>;
+    constexpr int kTokens = TS::kTokens;
+    constexpr int kMaxUnits = kTokens / 4;  // a tile spans up to that many blocks (block_size 4)
     constexpr int kSeqs = MAXSPT * kThreads;
     __shared__ int s_pref[kSeqs + 2];  // exclusive prefix of flat units (tiles + row cost) per sequence (+ guard)
     __shared__ int s_ctx[kSeqs];       // context length per sequence
@@ -300,7 +330,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     const int nseq = p.num_seqs;
 
     const int worker = blockIdx.x * kWaves + wave;
-    const int U_log2 = 4 - unit_log2;                 // log2(units per tile)
+    const int U_log2 = TS::kTokensLog2 - unit_log2;                 // log2(units per tile)
     int plan_word = 0;                                // kScheduled: lane i < kPlanInts holds word i of the plan
     if constexpr (MODE == kScheduled) {
         // one round trip: the worker's plan, its first tile addresses (as many as the staging
@@ -326,7 +356,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
             if (i < spt && n < nseq) {
                 const int c = min(max(context_lens[n], 0), p.max_context_len);
                 s_ctx[n] = c;
-                t = (c + kTileTokens - 1) >> 4;
+                t = (c + kTokens - 1) >> TS::kTokensLog2;
                 if (t > 0) t += kRowCost;
             }
             local[i] = sum;
@@ -364,8 +394,8 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         // empty contexts give rows of zeros; workgroup b looks after sequences b, b + grid, ...
         for (int n = blockIdx.x; n < nseq; n += gridDim.x) {
             if (s_ctx[n] == 0) {
-                uint4 *row = reinterpret_cast<uint4 *>(out + size_t(n) * p.num_q_heads * D);
-                for (int i = tid; i < p.num_q_heads * (D / 8); i += kThreads) row[i] = uint4{0u, 0u, 0u, 0u};
+                uint4 *row = reinterpret_cast<uint4 *>(out + size_t(n) * p.num_q_heads * HD);
+                for (int i = tid; i < p.num_q_heads * (HD / 8); i += kThreads) row[i] = uint4{0u, 0u, 0u, 0u};
             }
         }
     }
@@ -400,10 +430,10 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         }
         return o;
     };
-    auto load_q = [&](bf16x8(&qb)[4], const RowCursor &c) __attribute__((always_inline)) {
+    auto load_q = [&](bf16x8(&qb)[TS::kQ], const RowCursor &c) __attribute__((always_inline)) {
         const bool active = r < G && c.n < nseq;
         const int n = c.n < nseq ? c.n : 0;
-        load_q_operand(qb, q + (size_t(n) * p.num_q_heads + c.kvh * G + (r < G ? r : 0)) * D, quad, active);
+        load_q_operand(qb, q + (size_t(n) * p.num_q_heads + c.kvh * G + (r < G ? r : 0)) * HD, quad, active);
     };
 
     // ---- place the worker: largest n with s_pref[n] * Hkv <= f0 (that sequence is not empty)
@@ -558,23 +588,35 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     }
     if constexpr (MODE == kDirect) stage_tiles(0);  // kScheduled: the first window came with the plan
 
-    // Per-lane constants of the tile loads: K wants token r, V wants tokens 4*quad + i.
-    const size_t unit_elems = size_t(unit_tokens) * D;
-    const int k_unit = r >> unit_log2, k_row = r & (unit_tokens - 1);
-    const int v_unit = (4 * quad) >> unit_log2, v_row = (4 * quad) & (unit_tokens - 1);
-    const uint16_t *k_lane = k_cache + k_row * D + 8 * quad;
-    const uint16_t *v_lane = v_cache + v_row * D + 8 * r;
+    // Per-lane constants of the tile loads: K wants token r (of every 16), V wants tokens 4*quad + i (of every 16).
+    const size_t unit_elems = size_t(unit_tokens) * HD;
+    constexpr int kSubs = kTokens / 16;
+    const int k_row = r & (unit_tokens - 1), v_row = (4 * quad) & (unit_tokens - 1);
+    const uint16_t *k_lane = k_cache + k_row * HD + 8 * quad;
+    const uint16_t *v_lane = v_cache + v_row * HD + HD / 16 * r;
 
     int ki = 0;  // worker-relative index of the next tile to load
-    auto issue_next = [&](uint4(&kr)[4], uint4(&vr)[4]) __attribute__((always_inline)) {
+    auto issue_next = [&](typename TS::Tile &t) __attribute__((always_inline)) {
         if (ki - staged_base == kStageTiles) stage_tiles(ki);  // very long ranges only
         const int *e = &s_tile[wave][(ki - staged_base) << U_log2];
-        const uint16_t *kp = k_lane + size_t(e[k_unit]) * unit_elems;
-        const uint16_t *vp = v_lane + size_t(e[v_unit]) * unit_elems;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) kr[j] = load16_stream(kp + 32 * j);
+        for (int h = 0; h < kSubs; ++h) {
+            // sub-tile h: its unit, or with units of 32 tokens the second half of the one unit
+            const int in_unit = kSubs == 2 && unit_log2 == 5 ? 16 * h * HD : 0;
+            const uint16_t *kp = k_lane + size_t(e[(16 * h + r) >> unit_log2]) * unit_elems + in_unit;
+            const uint16_t *vp = v_lane + size_t(e[(16 * h + 4 * quad) >> unit_log2]) * unit_elems + in_unit;
+            if constexpr (HD == 128) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vr[i] = load16_stream(vp + i * D);
+                for (int j = 0; j < 4; ++j) t.k[j] = load16_stream(kp + 32 * j);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t.v[i] = load16_stream(vp + i * HD);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) t.k[2 * h + j] = load16_stream(kp + 32 * j);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t.v[4 * h + i] = load8_stream(vp + i * HD);
+            }
+        }
         ++ki;
     };
 
@@ -583,14 +625,14 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     int tc = first_tile;             // next tile of row rc to consume
     int seg_first = first_tile;      // first tile of the current segment
     int ctx_c = uniform(s_ctx[rc.n]);
-    bf16x8 qb[4], qb_next[4];
+    bf16x8 qb[TS::kQ], qb_next[TS::kQ];
     load_q(qb, rc);
     load_q(qb_next, next_row(rc));
-    HeadState st;
+    typename TS::State st;
     st.reset();
 
     // The H partial is parked in `hp` until the worker's end; the T partial is still in `st` then.
-    HeadState hp;
+    typename TS::State hp;
     hp.reset();
 
     // The segment [seg_first, tc) of row rc is finished: a whole row goes to `out`, a piece of a
@@ -600,32 +642,33 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         if (seg_first > 0) {            // H piece
             hp = st;
         } else if (tc == rc.tiles) {    // whole row
-            if (r < G) {  // lane (quad, r) holds O[head r][32*quad .. +31]
+            if (r < G) {  // lane (quad, r) holds O[head r][HD/4 * quad ..]
                 const size_t orow = size_t(rc.n) * p.num_q_heads + rc.kvh * G + r;
                 const float inv = 1.0f / st.l;
-                uint16_t *dst = out + orow * D + 32 * quad;
+                uint16_t *dst = out + orow * HD + HD / 4 * quad;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int v = 0; v < TS::kVecs; v += 2) {
+                    const float4 x = acc_vec(st, v), y = acc_vec(st, v + 1);
                     uint4 w;
-                    w.x = pack_bf16(st.acc[0][i] * inv, st.acc[1][i] * inv);
-                    w.y = pack_bf16(st.acc[2][i] * inv, st.acc[3][i] * inv);
-                    w.z = pack_bf16(st.acc[4][i] * inv, st.acc[5][i] * inv);
-                    w.w = pack_bf16(st.acc[6][i] * inv, st.acc[7][i] * inv);
-                    *reinterpret_cast<uint4 *>(dst + 8 * i) = w;
+                    w.x = pack_bf16(x.x * inv, x.y * inv);
+                    w.y = pack_bf16(x.z * inv, x.w * inv);
+                    w.z = pack_bf16(y.x * inv, y.y * inv);
+                    w.w = pack_bf16(y.z * inv, y.w * inv);
+                    *reinterpret_cast<uint4 *>(dst + 4 * v) = w;
                 }
             }
         }                               // else: T piece, stays in `st`
     };
 
     const uint32_t slots = 2u * gridDim.x * kWaves;
-    const __amdgpu_buffer_rsrc_t acc_buf = raw_buffer(ws.acc, slots * uint32_t(G * D) * 4u);
+    const __amdgpu_buffer_rsrc_t acc_buf = raw_buffer(ws.acc, slots * uint32_t(G * HD) * 4u);
     const __amdgpu_buffer_rsrc_t ml_buf = raw_buffer(ws.ml, slots * uint32_t(G) * 8u);
-    auto store_partial = [&](int slot, const HeadState &x) __attribute__((always_inline)) {
+    auto store_partial = [&](int slot, const typename TS::State &x) __attribute__((always_inline)) {
         if (r < G) {
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
+            for (int v = 0; v < TS::kVecs; ++v) {
                 const float4 f = acc_vec(x, v);
-                store4_device_scope(acc_buf, slot_vec(slot, G, v, quad, r), f.x, f.y, f.z, f.w);
+                store4_device_scope(acc_buf, slot_vec<HD>(slot, G, v, quad, r), f.x, f.y, f.z, f.w);
             }
             if (quad == 0) store2_device_scope(ml_buf, slot_ml(slot, G, r), x.m, x.l);
         }
@@ -657,11 +700,15 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     // Consumes the tile under the compute cursor.  When it was the last tile of the row the
     // segment is written and the state switches to the next row at once: the stores and the
     // Q prefetch are then issued as early as possible before the next wait on tile data.
-    auto compute_next = [&](uint4(&kr)[4], uint4(&vr)[4], bool more) __attribute__((always_inline)) {
-        bf16x8 ka[4];
+    auto compute_next = [&](typename TS::Tile &t, bool more) __attribute__((always_inline)) {
+        if constexpr (HD == 128) {
+            bf16x8 ka[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ka[j] = __builtin_bit_cast(bf16x8, kr[j]);
-        compute_tile(st, ka, vr, qb, p.scale_log2e, ctx_c - tc * kTileTokens, quad);
+            for (int j = 0; j < 4; ++j) ka[j] = __builtin_bit_cast(bf16x8, t.k[j]);
+            compute_tile(st, ka, t.v, qb, p.scale_log2e, ctx_c - tc * kTokens, quad);
+        } else {
+            compute_tile(st, t.k, t.v, qb, p.scale_log2e, ctx_c - tc * kTokens, quad);
+        }
         ++tc;
         if (tc == rc.tiles && more) {  // row finished and the worker has more tiles
             finalize();
@@ -671,7 +718,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
             ctx_c = uniform(s_ctx[rc.n]);
             st.reset();
 #pragma unroll
-            for (int j = 0; j < 4; ++j) qb[j] = qb_next[j];
+            for (int j = 0; j < TS::kQ; ++j) qb[j] = qb_next[j];
             load_q(qb_next, next_row(rc));
         }
     };
@@ -681,30 +728,30 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     // consumed.  The last 1 to 3 tiles are peeled; the worker announces its arrival at its cut
     // rows right after the loads of its last tile have been issued, so that the counter's
     // answer travels while the last tiles are consumed.
-    uint4 kA[4], vA[4], kB[4], vB[4];
-    issue_next(kA, vA);
+    typename TS::Tile tA, tB;
+    issue_next(tA);
     int it = 0;
     for (; it + 3 < NT; it += 2) {
-        issue_next(kB, vB);
-        compute_next(kA, vA, true);
-        issue_next(kA, vA);
-        compute_next(kB, vB, true);
+        issue_next(tB);
+        compute_next(tA, true);
+        issue_next(tA);
+        compute_next(tB, true);
     }
     if (it + 3 == NT) {
-        issue_next(kB, vB);
-        compute_next(kA, vA, true);
-        issue_next(kA, vA);
+        issue_next(tB);
+        compute_next(tA, true);
+        issue_next(tA);
         arrive();
-        compute_next(kB, vB, true);
-        compute_next(kA, vA, false);
+        compute_next(tB, true);
+        compute_next(tA, false);
     } else if (it + 2 == NT) {
-        issue_next(kB, vB);
+        issue_next(tB);
         arrive();
-        compute_next(kA, vA, true);
-        compute_next(kB, vB, false);
+        compute_next(tA, true);
+        compute_next(tB, false);
     } else {
         arrive();
-        compute_next(kA, vA, false);
+        compute_next(tA, false);
     }
     finalize();
 
@@ -740,9 +787,10 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // the fetches stay behind the poll
             };
             float *lds = reinterpret_cast<float *>(&s_tile[wave][0]);  // the tile addresses are no longer needed
-            if (G <= 4) merge_cut_rows<2>(acc_buf, ml_buf, out, G, p.num_q_heads, lane, lds, rows, st, hp, await_row);
-            else if (G <= 8) merge_cut_rows<4>(acc_buf, ml_buf, out, G, p.num_q_heads, lane, lds, rows, st, hp, await_row);
-            else merge_cut_rows<8>(acc_buf, ml_buf, out, G, p.num_q_heads, lane, lds, rows, st, hp, await_row);
+            constexpr int NV = TS::kVecs;
+            if (G <= 4) merge_cut_rows<HD, NV / 4>(acc_buf, ml_buf, out, G, p.num_q_heads, lane, lds, rows, st, hp, await_row);
+            else if (G <= 8) merge_cut_rows<HD, NV / 2>(acc_buf, ml_buf, out, G, p.num_q_heads, lane, lds, rows, st, hp, await_row);
+            else merge_cut_rows<HD, NV>(acc_buf, ml_buf, out, G, p.num_q_heads, lane, lds, rows, st, hp, await_row);
             // every arrival and publication of these rows has happened: leave their counters at 0
             if (lane == 0) {
                 if (last_t) __hip_atomic_store(ws.cnt + t_j0, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -756,30 +804,29 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
 
 hipError_t launch_partial_mfma_stream(const void *q, const void *k_cache, const void *v_cache,
                                       const int32_t *block_tables, const int32_t *context_lens,
-                                      void *out, Workspace ws, const AttnParams &p, int grid,
+                                      void *out, Workspace ws, const AttnParams &p, int head_dim, int grid,
                                       int mode, Schedule sched, hipStream_t stream) {
-    // unit = min(block_size, 16) tokens; blocks hold block_size / unit units
-    int unit_log2 = 4, upb_log2 = 0;
-    if (p.block_size < 16) {
-        unit_log2 = p.block_size_log2;
-    } else {
-        while ((16 << upb_log2) < p.block_size) ++upb_log2;
-    }
+    // unit = min(block_size, tokens of a tile); blocks hold block_size / unit units
+    const int tile_log2 = head_dim == 128 ? Shape<128>::kTokensLog2 : Shape<64>::kTokensLog2;
+    const int unit_log2 = p.block_size_log2 < tile_log2 ? p.block_size_log2 : tile_log2;
+    const int upb_log2 = p.block_size_log2 - unit_log2;
     const auto *q_ = static_cast<const uint16_t *>(q), *k_ = static_cast<const uint16_t *>(k_cache),
                *v_ = static_cast<const uint16_t *>(v_cache);
     auto *o_ = static_cast<uint16_t *>(out);
     const dim3 g(grid), b(kThreads);
     constexpr int kBig = kMaxStreamSeqs / kThreads;
     const bool small = p.num_seqs <= 4 * kThreads;
-#define KVC_LAUNCH_STREAM(SPT, MODE) \
-    pa_stream_mfma_kernel<SPT, MODE><<<g, b, 0, stream>>>(q_, k_, v_, block_tables, context_lens, o_, ws, p, \
-                                                          unit_log2, upb_log2, sched)
-    if (mode == kDirect) {
-        if (small) KVC_LAUNCH_STREAM(4, kDirect); else KVC_LAUNCH_STREAM(kBig, kDirect);
+#define KVC_LAUNCH_STREAM(HD, SPT, MODE) \
+    pa_stream_mfma_kernel<HD, SPT, MODE><<<g, b, 0, stream>>>(q_, k_, v_, block_tables, context_lens, o_, ws, p, \
+                                                              unit_log2, upb_log2, sched)
+    if (head_dim == 64) {  // stateless calls only
+        if (small) KVC_LAUNCH_STREAM(64, 4, kDirect); else KVC_LAUNCH_STREAM(64, kBig, kDirect);
+    } else if (mode == kDirect) {
+        if (small) KVC_LAUNCH_STREAM(128, 4, kDirect); else KVC_LAUNCH_STREAM(128, kBig, kDirect);
     } else if (mode == kBuild) {
-        if (small) KVC_LAUNCH_STREAM(4, kBuild); else KVC_LAUNCH_STREAM(kBig, kBuild);
+        if (small) KVC_LAUNCH_STREAM(128, 4, kBuild); else KVC_LAUNCH_STREAM(128, kBig, kBuild);
     } else {
-        if (small) KVC_LAUNCH_STREAM(4, kScheduled); else KVC_LAUNCH_STREAM(kBig, kScheduled);
+        if (small) KVC_LAUNCH_STREAM(128, 4, kScheduled); else KVC_LAUNCH_STREAM(128, kBig, kScheduled);
     }
 #undef KVC_LAUNCH_STREAM
     return hipGetLastError();
