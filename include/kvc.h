@@ -71,7 +71,10 @@ typedef enum {
     KVC_KERNEL_MFMA_BALANCED = 4 /* matrix-core tiles, persistent grid: the batch's (sequence, kv head,
                             16-token tile) work is flattened and cut into equal per-wavefront ranges;
                             bf16, head_dim 128, block_size >= 4, group <= 16, num_seqs <= 4096.  AUTO
-                            also takes it for large bf16 batches at head_dim 64 (32-token tiles) */
+                            also takes it for bf16 at head_dim 64 (32-token tiles), large batches and
+                            few rows.  Without a partition_tokens of the caller's, few rows (up to 64
+                            sequences and 128 (sequence, kv head) rows of moderate length) are cut into
+                            pieces of rows, one per workgroup, instead of ranges */
 } kvc_kernel;
 
 typedef struct {
@@ -133,7 +136,7 @@ KVC_API size_t kvc_paged_attention_decode_workspace_bytes(const kvc_attn_desc *d
  *   - Accumulation is fp32; bf16 output is rounded to nearest even.
  *   - Split-K: a long context is cut into pieces whose (max, sum, accumulator) partials go
  *     through the workspace.  The balanced kernel (KVC_KERNEL_MFMA_BALANCED, what AUTO picks for
- *     bf16 / head_dim 128 and for large batches at head_dim 64) is ONE launch: the last wavefront to finish a piece of a cut context
+ *     bf16 / head_dim 128 and often at head_dim 64) is ONE launch: the last wavefront to finish a piece of a cut context
  *     merges its partials and writes the row.  The other kernels are followed by a merge launch.
  *   - `workspace`: device memory, 256-byte aligned, at least
  *     kvc_paged_attention_decode_workspace_bytes(desc); may be NULL when that is 0.  Its first

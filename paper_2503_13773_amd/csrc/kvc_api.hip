@@ -65,6 +65,7 @@ struct Plan {
     uint64_t workspace_bytes;
     int min_chunk_tiles;
     int max_context_len;
+    bool few_rows;        // balanced: a workgroup per piece of a row instead of a wavefront per flat range
 };
 
 bool mfma_ok(const kvc_attn_desc &d) {
@@ -80,16 +81,29 @@ bool balanced_ok(const kvc_attn_desc &d, int max_ctx) {
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 16) < (int64_t(1) << 31);
 }
 
-// At head_dim 64 the balanced kernel serves the calls that KVC_KERNEL_AUTO brings with a context bound
-// above 256 tokens and no split of the caller's own.  Up to 256 tokens the vector-ALU kernel is one launch
-// without a workspace as well, and a caller may rely on that.  Small batches stay on the vector ALUs too: the
-// line lies where the two meet in back-to-back launches (kv heads x tokens of the bound; vector ALUs / balanced
-// in us: 16 k 8.1 / 9.8, 51 k 10.9 / 14.2, 102 k 9.7 / 11.9, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
+// Few rows (sequence, KV head): a workgroup takes a piece of a row and pieces meet once, instead of a wavefront
+// taking a range of flat tiles.  The grid holds 256 pieces and the last piece of a row is half empty on average,
+// so what many rows of long contexts lose in streaming outgrows what the shorter chain saves.  The line, in
+// us with the ranges / with the pieces (head_dim 128, 32 / 8 heads unless said; rows x tokens of the bound):
+//   8 x 3217 15.0 / 11.9, 8 x 32000 68 / 28.6, 32 x 32000 76.7 / 68.1, 64 x 8192 38.6 / 37.1, 64 x 16000 63.6 / 64.5,
+//   64 x 32000 116 / 121, 128 x 400 11.5 / 10.6, 128 x 3000 25.2 / 25.7, 128 x 8192 60.6 / 69.4;
+//   head_dim 64: 8 x 32000 40.2 / 19.1, 64 x 8192 25.0 / 23.1, 128 x 400 11.3 / 7.0, 128 x 1500 12.6 / 13.1.
+constexpr int kFewRowsMinTiles = 8;  // smallest piece of a cut row: a tile for each wavefront
+bool few_rows_ok(const kvc_attn_desc &d, int max_ctx) {
+    const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
+    return d.partition_tokens == 0 && d.num_seqs >= 1 && d.num_seqs <= 64 && rows <= kvc::kMaxFewRows &&
+           rows * rows * rows * max_ctx <= (int64_t(1) << 31);
+}
+
+// At head_dim 64 the balanced kernel serves calls that KVC_KERNEL_AUTO brings without a split of the caller's
+// own: few rows, and large batches.  The batches between them stay on the vector ALUs; the line lies where
+// the two meet in back-to-back launches (KV heads x tokens of the bound; vector ALUs / balanced in us: 102 k
+// 9.7 / 11.9, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
 bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
     return d.kernel == KVC_KERNEL_AUTO && d.dtype == KVC_BF16 && d.head_dim == 64 && d.block_size >= 4 &&
-           d.partition_tokens == 0 && max_ctx > 256 && d.num_q_heads / d.num_kv_heads <= 16 &&
-           d.num_seqs <= kvc::kMaxStreamSeqs &&
-           int64_t(d.num_seqs) * d.num_kv_heads * max_ctx >= (1 << 17) &&
+           d.partition_tokens == 0 && d.num_q_heads / d.num_kv_heads <= 16 && d.num_seqs <= kvc::kMaxStreamSeqs &&
+           (few_rows_ok(d, max_ctx) ||
+            (max_ctx > 256 && int64_t(d.num_seqs) * d.num_kv_heads * max_ctx >= (1 << 17))) &&
            int64_t(d.num_seqs) * d.num_kv_heads * (ceil_div(max_ctx, 32) + 1) < (int64_t(1) << 30) &&
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
 }
@@ -129,8 +143,10 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         // fewer than min_chunk tiles; the workspace is two partial slots per wavefront.
         const int tile_tokens = d->head_dim == 64 ? 32 : 16;  // 8 KiB of K and V
         const int64_t max_tiles = ceil_div(max_ctx, tile_tokens);
-        const int min_chunk = d->partition_tokens ? d->partition_tokens / tile_tokens
-                                                  : int(std::max<int64_t>(4, ceil_div(max_tiles, 32)));
+        pl->few_rows = few_rows_ok(*d, max_ctx);
+        const int min_chunk = pl->few_rows         ? kFewRowsMinTiles
+                              : d->partition_tokens ? d->partition_tokens / tile_tokens
+                                                    : int(std::max<int64_t>(4, ceil_div(max_tiles, 32)));
         const int group = d->num_q_heads / d->num_kv_heads;
         const uint64_t slots = uint64_t(kvc::kNumCUs) * kvc::kWaves * 2;
         pl->kernel = kernel;
@@ -144,6 +160,9 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         pl->acc_offset = kHeader;
         pl->ml_offset = (kHeader + acc + 255) & ~uint64_t(255);
         pl->workspace_bytes = pl->ml_offset + slots * group * 2 * sizeof(float);
+        // head_dim 64 up to 256 tokens: every row is one piece, and no workspace was asked for before there
+        // was a matrix-core kernel for it
+        if (d->head_dim == 64 && pl->few_rows && max_ctx <= 256) pl->workspace_bytes = 0;
         return KVC_OK;
     }
 
@@ -172,6 +191,7 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
     pl->merge_grid = parts > 1 ? ceil_div(rows, kvc::kWaves) : 0;
     pl->max_context_len = max_ctx;
     pl->min_chunk_tiles = 0;
+    pl->few_rows = false;
     pl->acc_offset = kHeader;
     if (parts > 1) {
         const uint64_t acc = uint64_t(rows) * parts * d->head_dim * sizeof(float);
@@ -226,7 +246,7 @@ int run_partial(const void *q, const void *k_cache, const void *v_cache, const i
         e = kvc::launch_partial_valu(q, k_cache, v_cache, block_tables, context_lens, out, ws, p,
                                      desc->dtype, desc->head_dim, int(pl.partial_grid), stream);
     else if (pl.kernel == KVC_KERNEL_MFMA_BALANCED)
-        e = kvc::launch_partial_mfma_stream(q, k_cache, v_cache, block_tables, context_lens, out,
+        e = (pl.few_rows ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream)(q, k_cache, v_cache, block_tables, context_lens, out,
                                             ws, p, desc->head_dim, int(pl.partial_grid), 0, kvc::Schedule{}, stream);
     else
         e = kvc::launch_partial_mfma(q, k_cache, v_cache, block_tables, context_lens, out, ws, p,
@@ -251,11 +271,16 @@ struct ScheduleLayout {
 
 bool schedule_layout(const kvc_attn_desc &d, const Plan &pl, ScheduleLayout *L) {
     if (pl.kernel != KVC_KERNEL_MFMA_BALANCED || d.head_dim != 128) return false;
-    const int64_t workers = int64_t(kvc::kNumCUs) * kvc::kWaves;
+    const int64_t workers = pl.few_rows ? kvc::kNumCUs : int64_t(kvc::kNumCUs) * kvc::kWaves;  // workgroups / wavefronts
     const int64_t units_per_tile = d.block_size >= 16 ? 1 : 16 / d.block_size;
+    const int64_t max_tiles = ceil_div(pl.max_context_len, 16);
     // no worker takes more flat units than this, whatever the context lengths turn out to be
-    const int64_t max_units = int64_t(d.num_seqs) * d.num_kv_heads * (ceil_div(pl.max_context_len, 16) + 1);
-    const int64_t chunk = std::max<int64_t>(pl.min_chunk_tiles, ceil_div(max_units, workers));
+    const int64_t max_units = int64_t(d.num_seqs) * d.num_kv_heads * (max_tiles + 1);
+    int64_t chunk = std::max<int64_t>(pl.min_chunk_tiles, ceil_div(max_units, workers));
+    if (pl.few_rows)  // nor a workgroup more tiles than this
+        chunk = std::max({int64_t(pl.min_chunk_tiles), std::min<int64_t>(max_tiles, kvc::kRowWholeTiles),
+                          ceil_div(max_tiles, kvc::kMaxRowPieces),
+                          ceil_div(d.num_seqs * max_tiles, kvc::kNumCUs / d.num_kv_heads - d.num_seqs)});
     const int64_t stride = chunk * units_per_tile;
     if (stride > (int64_t(1) << 28)) return false;
     auto up = [](uint64_t x) { return (x + 255) & ~uint64_t(255); };
@@ -459,7 +484,7 @@ int kvc_attn_schedule_build(const int32_t *block_tables, const int32_t *context_
     if (desc->num_seqs == 0) return KVC_OK;
     if (!block_tables || !context_lens) return KVC_ERR_NULL;
     const kvc::AttnParams p = make_params(*desc, pl, 1.0f);
-    const hipError_t e = kvc::launch_partial_mfma_stream(nullptr, nullptr, nullptr, block_tables, context_lens,
+    const hipError_t e = (pl.few_rows ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream)(nullptr, nullptr, nullptr, block_tables, context_lens,
                                                          nullptr, kvc::Workspace{}, p, desc->head_dim, int(pl.partial_grid), 1,
                                                          schedule_view(schedule, L),
                                                          static_cast<hipStream_t>(hip_stream));
@@ -485,7 +510,7 @@ int kvc_paged_attention_decode_scheduled(const void *q, const void *k_cache, con
     rc = check_workspace(pl, workspace, workspace_bytes, &ws);
     if (rc != KVC_OK) return rc;
     const kvc::AttnParams p = make_params(*desc, pl, scale);
-    const hipError_t e = kvc::launch_partial_mfma_stream(q, k_cache, v_cache, nullptr, nullptr, out, ws, p,
+    const hipError_t e = (pl.few_rows ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream)(q, k_cache, v_cache, nullptr, nullptr, out, ws, p,
                                                          desc->head_dim, int(pl.partial_grid), 2,
                                                          schedule_view(const_cast<void *>(schedule), L),
                                                          static_cast<hipStream_t>(hip_stream));

@@ -20,7 +20,7 @@ struct AttnParams {
     int partition_tokens;   // split-K partition length, multiple of 16
     int max_partitions;     // partitions per sequence the grid and workspace provide for
     int k_via_lds;          // MFMA kernel: stage K tiles through LDS (1) or load them in operand layout (0)
-    int min_chunk_tiles;    // balanced kernel: smallest number of tiles (16 tokens, 32 at head_dim 64) a worker takes
+    int min_chunk_tiles;    // balanced kernel: smallest number of tiles (16 tokens, 32 at head_dim 64) a worker (few rows: a workgroup) takes
     int max_context_len;    // context lengths are clamped to this (the bound every size is derived from)
     float scale;            // as given by the caller
     float scale_log2e;      // scale * log2(e), for the base-2 softmax of the MFMA kernel
@@ -85,6 +85,15 @@ hipError_t launch_partial_mfma_stream(const void *q, const void *k_cache, const 
                                       const int32_t *block_tables, const int32_t *context_lens,
                                       void *out, Workspace ws, const AttnParams &p, int head_dim, int grid,
                                       int mode, Schedule sched, hipStream_t stream);
+// Few rows (num_seqs <= 64, rows = num_seqs * num_kv_heads <= kMaxFewRows): a workgroup takes one piece of a row.
+// Arguments as above.
+hipError_t launch_rows_mfma(const void *q, const void *k_cache, const void *v_cache,
+                            const int32_t *block_tables, const int32_t *context_lens,
+                            void *out, Workspace ws, const AttnParams &p, int head_dim, int grid,
+                            int mode, Schedule sched, hipStream_t stream);
+constexpr int kMaxFewRows = kNumCUs / 2;
+constexpr int kMaxRowPieces = 64;  // pieces a row is cut into at most
+constexpr int kRowWholeTiles = 20;  // few rows: up to this length a row is one piece when the grid allows
 // base2: partials are in base-2 units.
 hipError_t launch_merge(const int32_t *context_lens, void *out, Workspace ws, const AttnParams &p,
                         int dtype, int head_dim, bool base2, int grid, hipStream_t stream);

@@ -66,6 +66,7 @@
 
 #include "kvc_internal.h"
 #include "pa_mfma_tile.h"
+#include "pa_partials.h"
 
 namespace kvc {
 
@@ -73,57 +74,10 @@ namespace {
 
 using namespace mfma;
 
-__device__ inline int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// Partials cross from one wavefront to another inside a launch, between XCDs whose L2 caches
-// are not coherent with each other.  They are therefore written and read with device-scope
-// accesses (the sc1 cache policy: each access goes to the point of coherence of the whole
-// device by itself), 16 bytes per lane, through raw buffer instructions, instead of ordinary
-// stores followed by a write-back of the whole L2: that write-back, issued by 1024 wavefronts,
-// doubled the kernel time when it was measured.
-constexpr int kDeviceScope = 16;  // cache-policy operand of the buffer builtins: sc1
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-__device__ inline __amdgpu_buffer_rsrc_t raw_buffer(const void *base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
-}
-__device__ inline void store4_device_scope(__amdgpu_buffer_rsrc_t b, uint32_t byte_off, float x, float y, float z, float w) {
-    const u32x4 v = {__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), __float_as_uint(w)};
-    __builtin_amdgcn_raw_buffer_store_b128(v, b, byte_off, 0, kDeviceScope);
-}
-__device__ inline float4 load4_device_scope(__amdgpu_buffer_rsrc_t b, uint32_t byte_off) {
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(b, byte_off, 0, kDeviceScope);
-    return float4{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-}
-__device__ inline void store2_device_scope(__amdgpu_buffer_rsrc_t b, uint32_t byte_off, float x, float y) {
-    const u32x2 v = {__float_as_uint(x), __float_as_uint(y)};
-    __builtin_amdgcn_raw_buffer_store_b64(v, b, byte_off, 0, kDeviceScope);
-}
-__device__ inline float2 load2_device_scope(__amdgpu_buffer_rsrc_t b, uint32_t byte_off) {
-    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, byte_off, 0, kDeviceScope);
-    return float2{__uint_as_float(v.x), __uint_as_float(v.y)};
-}
-
 constexpr int kStageTiles = 256;  // tiles whose addresses are staged in LDS per wavefront at a time
 constexpr int kRowCost = 1;       // flat units charged for leaving a row
 static_assert(size_t(kNumCUs) * kWaves * sizeof(int32_t) <= kWorkspaceHeaderBytes,
               "one arrival counter per worker must fit the workspace header");
-
-// What depends on the head dimension: tokens of a tile (8 KiB of K and V either way), the registers a
-// tile is loaded into, Q operands, softmax state, dims a lane holds of its head.
-template <int HD>
-struct Shape;
-template <>
-struct Shape<128> {
-    static constexpr int kTokens = kTileTokens, kTokensLog2 = 4, kQ = 4, kVecs = 8;
-    using State = HeadStateN<8>;
-    struct Tile { uint4 k[4], v[4]; };
-};
-template <>
-struct Shape<64> {
-    static constexpr int kTokens = kTileTokens64, kTokensLog2 = 5, kQ = 2, kVecs = 4;
-    using State = HeadStateN<4>;
-    struct Tile { uint4 k[4]; uint2 v[8]; };
-};
 
 // ---- finishing cut rows --------------------------------------------------------------------
 // A cut row as seen by the worker that arrived last at it.
@@ -135,24 +89,7 @@ struct CutRow {
 };
 
 
-// Partial slot layout (fp32): [HD / 16 vectors][quad][head][4]; vector v of (quad, head) = dims
-// HD/4 * quad + 4v .. +3 of the head's accumulator; (max, sum) per head in a second array.  One
-// store or load instruction of a wavefront then covers whole 128-byte lines.  Offsets in bytes.
-template <int HD>
-__device__ inline uint32_t slot_vec(int slot, int G, int v, int quad, int head) {
-    return (uint32_t(slot) * uint32_t(G * HD) + uint32_t(((v * 4 + quad) * G + head) * 4)) * 4u;
-}
-__device__ inline uint32_t slot_ml(int slot, int G, int head) { return uint32_t(slot * G + head) * 8u; }
 __device__ inline int slot_of_partial(int j0, int i) { return i == 0 ? 2 * j0 + 1 : 2 * (j0 + i); }
-// vector v of a lane's accumulator registers: dims 4v .. 4v+3 of its slice of HD / 4 dims
-__device__ inline float4 acc_vec(const mfma::HeadStateN<8> &x, int v) {
-    const int e = 4 * (v & 1), i = v >> 1;
-    return float4{x.acc[e][i], x.acc[e + 1][i], x.acc[e + 2][i], x.acc[e + 3][i]};
-}
-__device__ inline float4 acc_vec(const mfma::HeadStateN<4> &x, int v) {
-    return float4{x.acc[0][v], x.acc[1][v], x.acc[2][v], x.acc[3][v]};
-}
-
 // Log-sum-exp merge of the partials of up to two cut rows, in slot order, and the write of the
 // rows.  The loads of both rows are issued before anything is consumed (device-scope loads
 // are slow, ~40 ns each per wavefront when measured, so only partials that exist and are not
@@ -296,16 +233,6 @@ struct RowCursor {
     int pref;    // flat units (per KV head) of all sequences before n
     int tiles;   // t_n (the row spans t_n + kRowCost flat units)
 };
-
-// What a launch does with the placement of the workers (the start-up work that depends only on
-// block_tables and context_lens, which all layers of one decode step share):
-//   kDirect     computes it and streams (the stateless call);
-//   kBuild      computes it and writes it to a schedule buffer, nothing else;
-//   kScheduled  reads it from a schedule buffer and streams: the prefix table, the worker's plan
-//               and its first tile addresses arrive in one memory round trip instead of the
-//               three dependent ones (context lengths, block table, first tile) of kDirect.
-enum : int { kDirect = 0, kBuild = 1, kScheduled = 2 };
-constexpr int kPlanInts = 16;  // a worker's plan in the schedule buffer
 
 // MAXSPT: sequences per thread in the start-up prefix sum (batches up to MAXSPT * 256 sequences);
 // the small instance keeps the start-up of ordinary batches short.

@@ -1,0 +1,81 @@
+"""Decode attention of few rows (a workgroup per piece of a row) against the fp64 oracle: lengths around the tile, the
+eight wavefronts, the uncut length of 20 tiles and the pieces; every merge layout; schedules; the counters."""
+import numpy as np
+import pytest
+import torch
+
+import kvc_workloads as W
+from gpu_util import BF16_TOL, out_bits, out_to_f64, to_device
+from test_gpu_attention import _scheduled_equals_direct, custom
+from test_gpu_prefill_d64 import bound, poison
+
+pytestmark = pytest.mark.gpu
+
+
+def check(w, oracle_mod, label, max_context_len=0):
+    import paper_2503_13773_amd as K
+    print(f"[case] rows {label} D={w.head_dim} nseq={w.num_seqs} max={w.max_context_len}", flush=True)
+    rows = w.num_seqs * w.num_kv_heads
+    tokens = max_context_len or max(1, w.max_context_len)
+    assert rows <= 128 and w.num_seqs <= 64 and rows ** 3 * tokens <= 1 << 31   # the line of the dispatch
+    d = to_device(w)
+    desc = K.attn_desc(d["q"], d["k"], d["tables"], max_context_len=tokens)
+    ws = K.new_workspace(desc)
+    outs = [K.paged_attention_decode(d["q"], d["k"], d["v"], d["tables"], d["lens"], w.scale, desc=desc, workspace=ws)
+            for _ in range(4)]
+    torch.cuda.synchronize()
+    assert ws is None or int(ws[:4096].max()) == 0
+    assert all(np.array_equal(out_bits(o), out_bits(outs[0])) for o in outs)
+    got, ref = out_to_f64(outs[0]), oracle_mod.attention_of_workload(w, num_threads=8)
+    assert np.isfinite(got).all()
+    if w.head_dim == 64:
+        assert (np.abs(got - ref) <= bound(ref)).all(), label
+    else:
+        assert np.abs(got - ref).max() <= BF16_TOL, label
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hq,hkv,bs", [(8, 2, 16), (7, 1, 8), (16, 1, 32), (9, 1, 4), (12, 12, 16), (1, 1, 64), (6, 3, 256)])
+def test_lengths_around_tiles_waves_and_pieces(oracle_mod, d, hq, hkv, bs):
+    t = 32 if d == 64 else 16
+    for lens in ([1, 0, t - 1, t, t + 1, 7 * t, 8 * t, 8 * t + 1], [20 * t, 0, 3], [20 * t + 1, 40, 0, 0], [16 * t, 17 * t + 5, 33 * t]):
+        w = custom(900 + hq + bs + d, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=d, bs=bs)
+        poison(w)
+        check(w, oracle_mod, f"{hq}/{hkv} bs={bs} {lens}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens,hq,hkv", [([3217], 32, 8), ([40000], 4, 1), ([40000, 9], 2, 1), ([12000, 100, 0, 7000], 8, 4),
+                                         ([900] * 8, 32, 16), ([300] * 64, 4, 2), ([0] * 5, 4, 2), ([250000], 1, 1)])
+def test_many_pieces_and_full_grids(oracle_mod, d, lens, hq, hkv):
+    """Up to 64 pieces per row, pieces longer than the 64 tiles staged per wavefront, 128 rows, no row at all."""
+    check(custom(920 + len(lens) + d, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=d, bs=16), oracle_mod, f"{lens[:4]}")
+
+
+def test_bound_far_above_the_lengths(oracle_mod):
+    w = custom(940, dtype=W.BF16, lens=[70, 300, 5], hq=8, hkv=2, d=128, bs=16, lmax=4096)
+    check(w, oracle_mod, "loose", max_context_len=65536)
+
+
+def test_schedules(oracle_mod):
+    for lens, hq, hkv, bs in [([3217], 32, 8, 16), ([0, 300, 0, 320, 321, 17], 8, 2, 8), ([20000, 37, 9000], 2, 1, 16),
+                              ([0, 0], 4, 2, 16), ([500] * 16, 32, 8, 32), ([100, 250], 16, 1, 4)]:
+        w = custom(950 + len(lens) + bs, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=128, bs=bs)
+        _scheduled_equals_direct(w, oracle_mod, f"rows {lens[:4]} bs={bs}")
+
+
+def test_one_workspace_for_few_rows_and_many(oracle_mod):
+    """Calls of both kinds in turn on one workspace: each leaves the counters at 0 for the next."""
+    import paper_2503_13773_amd as K
+    few = custom(960, dtype=W.BF16, lens=[3000, 70], hq=32, hkv=8, d=128, bs=16)
+    many = W.make_config("cfg3", num_seqs=40, ctx_scale=0.3)
+    ws, seen = None, {}
+    for turn in range(6):
+        for w in (few, many):
+            d = seen.setdefault(id(w), (to_device(w), oracle_mod.attention_of_workload(w, num_threads=8)))
+            desc = K.attn_desc(d[0]["q"], d[0]["k"], d[0]["tables"], max_context_len=w.max_context_len)
+            ws = ws if ws is not None else K.new_workspace(desc)
+            out = K.paged_attention_decode(d[0]["q"], d[0]["k"], d[0]["v"], d[0]["tables"], d[0]["lens"], w.scale,
+                                           desc=desc, workspace=ws)
+            assert np.abs(out_to_f64(out) - d[1]).max() <= BF16_TOL
+    assert int(ws[:4096].max()) == 0

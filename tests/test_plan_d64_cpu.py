@@ -15,7 +15,7 @@ def test_auto_takes_the_balanced_kernel_for_large_batches(K):  # noqa: F811
 
 @pytest.mark.parametrize("kw", [
     dict(max_context_len=256),            # one launch without a workspace before and after
-    dict(num_seqs=4, max_context_len=4095),   # 2^17 tokens x KV heads and more take the balanced kernel
+    dict(num_seqs=20, max_context_len=800),   # more than 128 rows, less than 2^17 tokens x KV heads
     dict(partition_tokens=512),           # the caller's own split
     dict(dtype=0), dict(block_size=2), dict(num_q_heads=136), dict(num_seqs=4097), dict(kernel=1),
 ])
@@ -24,6 +24,13 @@ def test_the_others_stay_on_the_vector_alus(K, kw):  # noqa: F811
     assert rc == 0 and p.kernel == K.KERNEL_VALU
     if kw.get("max_context_len") == 256:
         assert p.workspace_bytes == 0
+
+
+def test_few_rows_take_the_matrix_cores_and_short_ones_no_workspace(K):  # noqa: F811
+    for kw, need in [(dict(num_seqs=4, max_context_len=4000), True), (dict(num_seqs=16, max_context_len=257), True),
+                     (dict(num_seqs=16, max_context_len=256), False), (dict(num_seqs=1, max_context_len=7), False)]:
+        rc, p = plan_status(K, desc(K, head_dim=64, **kw))
+        assert rc == 0 and p.kernel == K.KERNEL_MFMA_BALANCED and (p.workspace_bytes > 0) == need
 
 
 def test_explicit_kernels_and_schedules_stay_refused(K):  # noqa: F811
