@@ -360,6 +360,7 @@ __device__ inline void pipeline_turn(ColumnState &st, float (&x)[16], bf16x8 (&k
 // groups); HEADS = 1: 32 query rows of one head.  GROUPS = 1: workgroups of four wavefronts, two
 // per compute unit.  GROUPS = 2: workgroups of two groups of four wavefronts, one per compute
 // unit; the groups run half a turn apart (see below).  Either way a SIMD holds two wavefronts.
+// SMALL: block_size < 8.
 template <bool SMALL, int GROUPS, int HEADS>
 __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
@@ -435,15 +436,19 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     const int my_tile = wave / kWavesPerTile;       // tile of the step this wavefront loads from
     const int lrow = 4 * kLoads * (wave % kWavesPerTile) + (lane >> 4);  // row inside the tile of load 0 (load 1: + 4)
     const int lchunk = lane & 15;
-    const uint32_t k_off = lrow * 256 + ((lchunk ^ lrow) << 4);
-    const uint32_t k_off1 = (lrow + 4) * 256 + ((lchunk ^ (lrow + 4)) << 4);
-    const uint32_t v_off = lrow * 256 + ((4 * (((lchunk >> 2) - lrow) & 3) + (lchunk & 3)) << 4);  // load 1: + 1024
+    const int brow = lrow & (p.block_size - 1);  // in its block, where that holds 8 tokens (16 or more: lrow)
+    const uint32_t k_off = brow * 256 + ((lchunk ^ lrow) << 4);
+    const uint32_t k_off1 = (brow + 4) * 256 + ((lchunk ^ (lrow + 4)) << 4);
+    const uint32_t v_off = brow * 256 + ((4 * (((lchunk >> 2) - lrow) & 3) + (lchunk & 3)) << 4);  // load 1: + 1024
     const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(&s_k[0][0])) + 1024 * kLoads * wave;
     const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(&s_v[0][0])) + 1024 * kLoads * wave;
 
-    // Large blocks: the block id of the wavefront's tile is uniform, it comes through the scalar
-    // cache one turn before the loads that use it.  Tiles past the last one repeat it (never
-    // used unmasked).  Small blocks: a / b are the blocks of this lane's row in loads 0 / 1.
+    // Blocks of 8 tokens and more: the block id of the wavefront's rows (8 or 4 consecutive ones, inside one
+    // block) is uniform, it comes through the scalar cache one turn before the loads that use it.  Rows past the
+    // last visible token repeat its block (never used unmasked).  Smaller blocks: a / b are the blocks of
+    // this lane's row in loads 0 / 1.  (Four chunks of 512 rows on 8-token blocks, contexts up to 4000, 32 / 8
+    // heads: 112 us; with a table load per lane, which drains the wavefront's loads in flight, 126 us.)
+    const int share_row = 4 * kLoads * (wave % kWavesPerTile);
     struct Ids { int a, b; };
     auto ids_of = [&](int step) __attribute__((always_inline)) -> Ids {
         Ids id;
@@ -452,9 +457,9 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
             id.a = table[tok >> p.block_size_log2];
             id.b = kLoads == 2 ? table[min(tok + 4, last_pos) >> p.block_size_log2] : 0;
         } else {
-            const int t = min(2 * step + my_tile, wg_tiles - 1);
-            id.a = __builtin_amdgcn_readfirstlane(table[t >> p.tiles_per_block_log2]);
-            id.b = t & sub_mask;
+            const int tok = min((2 * step + my_tile) * kTileTokens + share_row, last_pos);
+            id.a = __builtin_amdgcn_readfirstlane(table[tok >> p.block_size_log2]);
+            id.b = (tok >> 4) & sub_mask;
         }
         return id;
     };
@@ -655,7 +660,7 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
     const auto tiles_of = [&](int groups) { return (p.max_query_tiles + rows64 * groups - 1) / (rows64 * groups); };
     const int64_t wide_grid = int64_t(p.num_q_heads / heads) * p.num_seqs * tiles_of(2);
     const bool wide = wide_grid >= 2 * 256 && p.max_query_tiles >= 48;
-    const bool small = p.block_size < kTileTokens;
+    const bool small = p.block_size < 8;
     const int query_tiles = tiles_of(wide ? 2 : 1);  // max_query_tiles counts 64-row tiles
     // A grid that fits the device at once (two workgroups of four wavefronts per compute unit)
     // gets the second half of its query tiles in rising order (a few percent on one short request).
