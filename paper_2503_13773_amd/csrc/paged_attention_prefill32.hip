@@ -51,6 +51,7 @@
 // every query row and steps are walked in order, so every column has a finite reference point
 // after the first step.  Workgroups with the most steps (the last query rows) are dispatched
 // first.
+#include <float.h>
 #include <math.h>
 
 #include "kvc_internal.h"
@@ -70,6 +71,9 @@ constexpr int kStageBytes = kStepTokens * D * 2;  // K (or V) rows of a step: 32
 constexpr float kLazyLog2 = 8.0f;
 constexpr int kKStages = 4;   // K rows of steps s+1 .. s+4 during turn s
 constexpr int kVStages = 4;   // V rows of steps s .. s+3
+// Steps from which a split workgroup's second group takes a share (800 tokens whole 19.7, split 19.5 us; 1000 tokens
+// 23.1 / 22.4 us; 600 tokens 16.7 / 17.2 us).
+constexpr int kMinSplitSteps = 24;
 
 // Online-softmax state of one column (query row x head); lane (half, c) holds
 // O[column c][32*b + 8*(v/4) + 4*half + v%4] in acc[b][v].
@@ -78,13 +82,13 @@ struct ColumnState {
     float lsum;  // sum of the rounded weights of this lane's tokens (the other half's lane holds the rest)
     float m;     // reference point of the weights (base-2 units): within 2^kLazyLog2 of the column's running max
 
-    __device__ inline void reset() {
+    __device__ inline void reset(float lowest) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
         lsum = 0.f;
-        m = -INFINITY;
+        m = lowest;
     }
 };
 
@@ -360,19 +364,30 @@ __device__ inline void pipeline_turn(ColumnState &st, float (&x)[16], bf16x8 (&k
 // groups); HEADS = 1: 32 query rows of one head.  GROUPS = 1: workgroups of four wavefronts, two
 // per compute unit.  GROUPS = 2: workgroups of two groups of four wavefronts, one per compute
 // unit; the groups run half a turn apart (see below).  Either way a SIMD holds two wavefronts.
+// SPLIT (with GROUPS = 2): the two groups hold the same query rows, those of a four-wavefront workgroup, and
+// share the steps of long contexts: group 0 walks the first `cut` of them, group 1 the rest, each with a ring
+// of stages of its own, and the parts meet in LDS at the end (log-sum-exp rule).  Of short contexts group 1
+// ends at once.  For launches with too few workgroups to fill the device, where a four-wavefront workgroup would
+// run one wavefront per SIMD: 256 rows at the end of 12000 tokens, 32 / 8 heads, 172 -> 138 us, 64 rows of 4000
+// tokens 63.6 -> 53.7 us, 300 rows of 1000 tokens twice 24 -> 22.4 us.  The groups run in
+// step: half a turn apart the first case took 131 us, but the barrier in the middle of a turn cost short contexts,
+// which only group 0 walks, 25 ns per step, and a branch around it (154 us) or a second copy of the loop
+// (spills, 217 us) costs more.
 // SMALL: block_size < 8.
-template <bool SMALL, int GROUPS, int HEADS>
+template <bool SMALL, int GROUPS, int HEADS, bool SPLIT>
 __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
     uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at) {
-    __shared__ __attribute__((aligned(1024))) unsigned char s_k[kKStages][kStageBytes];
-    __shared__ __attribute__((aligned(1024))) unsigned char s_v[kVStages][kStageBytes];
+    static_assert(!SPLIT || GROUPS == 2, "the context is split between two groups");
+    constexpr int kParts = SPLIT ? 2 : 1;
+    constexpr int kShared = GROUPS / kParts;        // groups that share a ring of stages
+    __shared__ __attribute__((aligned(1024))) unsigned char s_kv[kParts][kKStages + kVStages][kStageBytes];
     constexpr int kWaveRows = 32 / HEADS;           // query rows of a wavefront: column c = kWaveRows * head + row
-    constexpr int kTileRows = 4 * kWaveRows * GROUPS;  // query rows of a workgroup
-    constexpr int kLoads = 2 / GROUPS;              // 1 KiB loads of K (and of V) per wavefront and step
-    constexpr int kWavesPerTile = 2 * GROUPS;       // wavefronts that share a 16-row tile of a step
+    constexpr int kTileRows = 4 * kWaveRows * kShared;  // query rows of a workgroup
+    constexpr int kLoads = 2 / kShared;             // 1 KiB loads of K (and of V) per wavefront and step
+    constexpr int kWavesPerTile = 2 * kShared;      // wavefronts that share a 16-row tile of a step
 
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order); the longest query tiles come
     // first, and from `fold_at` on the shortest: when every workgroup is resident at once, the two
@@ -392,16 +407,22 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
 
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int group = wave >> 2;  // GROUPS = 2: wavefronts w and w + 4 share a SIMD; group 1 runs half a turn behind group 0
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int group = wave_id >> 2;  // GROUPS = 2: wavefronts w and w + 4 share a SIMD; group 1 runs half a turn behind group 0
+    const int wave = SPLIT ? wave_id & 3 : wave_id;  // among the wavefronts that share a ring
+    unsigned char *const s_k = &s_kv[SPLIT ? group : 0][0][0], *const s_v = s_k + kKStages * kStageBytes;
     const int half = lane >> 5, c = lane & 31;
     const int r = c % kWaveRows;  // query row of the column inside the wavefront's rows
     const int my_head = head0 + c / kWaveRows;
 
     // tiles and steps this workgroup walks (up to the position of its last query row)
     const int last_pos = S - Qn + min(Qn, qtile * kTileRows + kTileRows) - 1;
-    const int wg_tiles = (last_pos >> 4) + 1;
-    const int wg_steps = (wg_tiles + 1) / 2;
+    const int all_steps = last_pos / kStepTokens + 1;
+    const int cut = SPLIT && all_steps >= kMinSplitSteps ? (all_steps + 1) / 2 : all_steps;  // group 0's share
+    const int s0 = SPLIT && group == 1 ? cut : 0;              // first step of this wavefront's part
+    const int wg_steps = SPLIT && group == 1 ? all_steps - cut : cut;  // and its number of steps
+    if (SPLIT && wg_steps == 0) return;  // group 1 of a short context; ended wavefronts do not count at barriers
+    constexpr bool phased = GROUPS == 2 && !SPLIT;  // the groups run half a turn apart
     const int32_t *table = block_tables + size_t(n) * p.max_blocks_per_seq;
 
     // wavefronts past the last query row still load and synchronise, they just never compute
@@ -412,7 +433,7 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     const int p0 = S - Qn + (active ? i0 : 0);  // position of row 0
     const int my_pos = p0 + row;
     const int wave_vis = p0 + nrows;        // tokens visible to some column of this wavefront
-    const int free_steps = (p0 + 1) / kStepTokens;  // steps whose every token every column sees
+    const int free_steps = (p0 + 1) / kStepTokens - s0;  // steps of the part whose every token every column sees
 
     bf16x8 qb[8];
     {
@@ -421,8 +442,10 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
         for (int j = 0; j < 8; ++j) qb[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qrow + 16 * j));
     }
 
+    // Token 0 is in the first step, so every column starts with a finite score there.  Group 1's first step may
+    // hide all its tokens from a column: its reference point starts at the lowest finite value, the weights are 0.
     ColumnState st;
-    st.reset();
+    st.reset(SPLIT ? -FLT_MAX : -INFINITY);
 
     // ---- this wavefront's share of a step's rows: 4 * kLoads consecutive rows of the 32 (inside
     // one 16-row tile of the step), kLoads loads of 4 rows for K and as many for V.  Lane l of
@@ -440,8 +463,8 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     const uint32_t k_off = brow * 256 + ((lchunk ^ lrow) << 4);
     const uint32_t k_off1 = (brow + 4) * 256 + ((lchunk ^ (lrow + 4)) << 4);
     const uint32_t v_off = brow * 256 + ((4 * (((lchunk >> 2) - lrow) & 3) + (lchunk & 3)) << 4);  // load 1: + 1024
-    const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(&s_k[0][0])) + 1024 * kLoads * wave;
-    const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(&s_v[0][0])) + 1024 * kLoads * wave;
+    const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(s_k)) + 1024 * kLoads * wave;
+    const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(s_v)) + 1024 * kLoads * wave;
 
     // Blocks of 8 tokens and more: the block id of the wavefront's rows (8 or 4 consecutive ones, inside one
     // block) is uniform, it comes through the scalar cache one turn before the loads that use it.  Rows past the
@@ -453,11 +476,11 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     auto ids_of = [&](int step) __attribute__((always_inline)) -> Ids {
         Ids id;
         if (SMALL) {
-            const int tok = min((2 * step + my_tile) * kTileTokens + lrow, last_pos);
+            const int tok = min((2 * (s0 + step) + my_tile) * kTileTokens + lrow, last_pos);
             id.a = table[tok >> p.block_size_log2];
             id.b = kLoads == 2 ? table[min(tok + 4, last_pos) >> p.block_size_log2] : 0;
         } else {
-            const int tok = min((2 * step + my_tile) * kTileTokens + share_row, last_pos);
+            const int tok = min((2 * (s0 + step) + my_tile) * kTileTokens + share_row, last_pos);
             id.a = __builtin_amdgcn_readfirstlane(table[tok >> p.block_size_log2]);
             id.b = (tok >> 4) & sub_mask;
         }
@@ -467,7 +490,7 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     auto issue_rows = [&](const unsigned char *head, uint32_t dst, uint32_t off, uint32_t off1, int src, const Ids &id)
                           __attribute__((always_inline)) {
         if (SMALL) {
-            const int tok = min((2 * src + my_tile) * kTileTokens + lrow, last_pos);
+            const int tok = min((2 * (s0 + src) + my_tile) * kTileTokens + lrow, last_pos);
             load_lane_to_lds(head + size_t(id.a) * block_bytes + size_t(tok & (p.block_size - 1)) * 256 + (off & 255), dst);
             if (kLoads == 2) {
                 const int tok1 = min(tok + 4, last_pos);
@@ -535,26 +558,37 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     wait_loads_but<2 * kLoads>();   \
     turn_barrier()
 
+    // Group 0's share may be a step longer than group 1's.
+    auto even_out = [&]() __attribute__((always_inline)) {
+        if (group == 1)
+            for (int i = wg_steps; i < cut; ++i) phase_barrier();
+    };
+
     // Every wavefront of the workgroup passes one more barrier here, two per turn, and one to
     // set group 1 back by half a turn (group 0 passes its counterpart after its last turn).  A
     // wavefront without query rows only loads and synchronises.
     if (!active) {
         __syncthreads();
-        if (GROUPS == 2 && group == 1) phase_barrier();
+        if (phased && group == 1) phase_barrier();
         for (; s < wg_steps; ++s) {
             KVC_TURN_BEGIN(s & 3);
-            if (GROUPS == 2) phase_barrier();
+            if (phased) phase_barrier();
             turn_lookup();
             turn_k();
             turn_v();
             KVC_TURN_END();
         }
-        if (GROUPS == 2 && group == 0) phase_barrier();
+        if (phased && group == 0) phase_barrier();
         wait_loads_but<0>();
+        if (SPLIT && cut < all_steps) {  // as the others below
+            even_out();
+            __syncthreads();
+            __syncthreads();
+        }
         return;
     }
 
-    const unsigned char *k_lane = &s_k[0][0] + c * 256;  // this lane's K row inside a stage
+    const unsigned char *k_lane = s_k + c * 256;  // this lane's K row inside a stage
     int voff[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) voff[b] = v_lane_offset(b, half, c);
@@ -572,21 +606,21 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
         ka[6] = read_k_operand<6>(k_lane, half, c); ka[7] = read_k_operand<7>(k_lane, half, c);
 #pragma unroll
         for (int j = 0; j < 8; ++j) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[j], qb[j], sc, 0, 0, 0);
-        rebase(st, take_scores<true>(x, sc, my_pos + 1, half), p.scale_log2e);
+        rebase(st, take_scores<true>(x, sc, my_pos + 1 - s0 * kStepTokens, half), p.scale_log2e);
         const unsigned char *krow = k_lane + kStageBytes;
         ka_lo[0] = read_k_operand<0>(krow, half, c); ka_lo[1] = read_k_operand<1>(krow, half, c);
         ka_lo[2] = read_k_operand<2>(krow, half, c); ka_lo[3] = read_k_operand<3>(krow, half, c);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) read_v_operand<0>(va0[b], &s_v[0][0] + voff[b]);
+        for (int b = 0; b < 4; ++b) read_v_operand<0>(va0[b], s_v + voff[b]);
     }
     __syncthreads();  // K stage 0 has been read: turn 0 may load step 4 over it
-    if (GROUPS == 2 && group == 1) phase_barrier();
+    if (phased && group == 1) phase_barrier();
 
     // The turns below the diagonal first (no mask), unrolled by the four phases of the stage
     // rings, then the one to three turns that the causal mask touches.
-    const unsigned char *v_base = &s_v[0][0];
+    const unsigned char *v_base = s_v;
     auto mid = []() __attribute__((always_inline)) {
-        if (GROUPS == 2) phase_barrier();
+        if (phased) phase_barrier();
     };
 #define KVC_TURN(MASKED, PH, VLIM, LIMIT)                                                                      \
     {                                                                                                          \
@@ -608,11 +642,12 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     while (s < plain_turns) KVC_TURN(false, s & 3, kStepTokens, kStepTokens)
     // steps past the last token that any row of this wavefront sees carry no weight for it: it
     // only loads and synchronises during the workgroup's remaining turns
-    const int live_turns = min(wg_steps, (wave_vis + kStepTokens - 1) / kStepTokens);
-    while (s < live_turns) KVC_TURN(true, s & 3, wave_vis - s * kStepTokens, my_pos + 1 - (s + 1) * kStepTokens)
+    const int live_turns = min(wg_steps, (wave_vis + kStepTokens - 1) / kStepTokens - s0);
+    while (s < live_turns)
+        KVC_TURN(true, s & 3, wave_vis - (s0 + s) * kStepTokens, my_pos + 1 - (s0 + s + 1) * kStepTokens)
     for (; s < wg_steps; ++s) {
         KVC_TURN_BEGIN(s & 3);
-        if (GROUPS == 2) phase_barrier();
+        mid();
         turn_lookup();
         turn_k();
         turn_v();
@@ -621,13 +656,48 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 #undef KVC_TURN
 #undef KVC_TURN_BEGIN
 #undef KVC_TURN_END
-    if (GROUPS == 2 && group == 0) phase_barrier();
+    if (phased && group == 0) phase_barrier();
     wait_loads_but<0>();  // nothing may still be landing in LDS when the workgroup's LDS is handed on
 
     // lane (half, c) holds O[query row i0 + r][my_head][32*b + 8*a + 4*half .. +3] in acc[b][4a .. 4a+3]
-    const float inv = 1.0f / sum_over_halves(st.lsum);
+    uint16_t *const dst = out + (size_t(qs + i0 + r) * p.num_q_heads + my_head) * D + 4 * half;
+    const float lsum = sum_over_halves(st.lsum);
+    if (SPLIT && cut < all_steps) {
+        // the parts meet: each group hands over two dim blocks and finishes the other two
+        even_out();
+        __syncthreads();  // every wavefront is past its last load and LDS read
+        float *const hand = reinterpret_cast<float *>(&s_kv[0][0][0]) + wave * (2 * 34 * 64) + lane;  // [wave][group][32 + 2][64]
+        float *const mine = hand + group * (34 * 64);
+        const float *const theirs = hand + (1 - group) * (34 * 64);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mine[(16 * b + v) * 64] = group == 0 ? st.acc[2 + b][v] : st.acc[b][v];
+        mine[32 * 64] = st.m;
+        mine[33 * 64] = lsum;
+        __syncthreads();
+        const float m_o = theirs[32 * 64], l_o = theirs[33 * 64];
+        const float M = fmaxf(st.m, m_o);
+        const float w_m = __builtin_amdgcn_exp2f(st.m - M), w_o = __builtin_amdgcn_exp2f(m_o - M);
+        const float inv = 1.0f / (w_m * lsum + w_o * l_o);
+        if (r < nrows) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    float o[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int v = 4 * a + i;
+                        o[i] = (w_m * (group == 0 ? st.acc[b][v] : st.acc[2 + b][v]) + w_o * theirs[(16 * b + v) * 64]) * inv;
+                    }
+                    *reinterpret_cast<uint2 *>(dst + 32 * (2 * group + b) + 8 * a) = uint2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+                }
+        }
+        return;
+    }
+    const float inv = 1.0f / lsum;
     if (r < nrows) {
-        uint16_t *dst = out + (size_t(qs + i0 + r) * p.num_q_heads + my_head) * D + 4 * half;
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -662,24 +732,30 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
     const bool wide = wide_grid >= 2 * 256 && p.max_query_tiles >= 48;
     const bool small = p.block_size < 8;
     const int query_tiles = tiles_of(wide ? 2 : 1);  // max_query_tiles counts 64-row tiles
+    const int64_t grid = int64_t(p.num_q_heads / heads) * p.num_seqs * query_tiles;
+    // at most one workgroup per compute unit (up to two the finer grain of plain ones wins: 2048 tokens 45.6 us
+    // plain, 46.2 us split; four chunks of 512 rows 112 / 118 us), and only where the block table reaches far enough
+    // for a share: the second group's start costs a short request up to 0.3 us (642 tokens, MHA: 17.3 / 17.6 us)
+    const bool split = !wide && !small && grid <= kNumCUs &&
+                       int64_t(p.max_blocks_per_seq) * p.block_size > (kMinSplitSteps - 1) * kStepTokens;
     // A grid that fits the device at once (two workgroups of four wavefronts per compute unit)
     // gets the second half of its query tiles in rising order (a few percent on one short request).
-    const int64_t grid = int64_t(p.num_q_heads / heads) * p.num_seqs * query_tiles;
     const int fold_at = (!wide && grid <= 2 * 256) ? (query_tiles + 1) / 2 : query_tiles;
-    const dim3 g(unsigned(int64_t(p.num_q_heads / heads) * p.num_seqs * query_tiles)), b(wide ? 512 : 256);
-#define KVC_LAUNCH(SMALL, GROUPS, HEADS)                                                                        \
-    pa_prefill_mfma32_kernel<SMALL, GROUPS, HEADS><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
-                                                                         q_start, oo, p, query_tiles, fold_at)
-#define KVC_LAUNCH_HEADS(SMALL, GROUPS)           \
-    do {                                          \
-        if (heads == 2) KVC_LAUNCH(SMALL, GROUPS, 2); \
-        else KVC_LAUNCH(SMALL, GROUPS, 1);        \
+    const dim3 g{unsigned(grid)}, b(wide || split ? 512 : 256);
+#define KVC_LAUNCH(SMALL, GROUPS, HEADS, SPLIT)                                                                        \
+    pa_prefill_mfma32_kernel<SMALL, GROUPS, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
+                                                                                q_start, oo, p, query_tiles, fold_at)
+#define KVC_LAUNCH_SHAPE(SMALL, HEADS)                       \
+    do {                                                     \
+        if (wide) KVC_LAUNCH(SMALL, 2, HEADS, false);        \
+        else if (split) KVC_LAUNCH(false, 2, HEADS, true);   \
+        else KVC_LAUNCH(SMALL, 1, HEADS, false);             \
     } while (0)
-    if (wide && small) KVC_LAUNCH_HEADS(true, 2);
-    else if (wide) KVC_LAUNCH_HEADS(false, 2);
-    else if (small) KVC_LAUNCH_HEADS(true, 1);
-    else KVC_LAUNCH_HEADS(false, 1);
-#undef KVC_LAUNCH_HEADS
+    if (small && heads == 2) KVC_LAUNCH_SHAPE(true, 2);
+    else if (small) KVC_LAUNCH_SHAPE(true, 1);
+    else if (heads == 2) KVC_LAUNCH_SHAPE(false, 2);
+    else KVC_LAUNCH_SHAPE(false, 1);
+#undef KVC_LAUNCH_SHAPE
 #undef KVC_LAUNCH
     return hipGetLastError();
 }

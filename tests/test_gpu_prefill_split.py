@@ -1,0 +1,44 @@
+"""Prefill launches of at most one workgroup per compute unit: from 768 tokens (24 steps of 32) on, the two groups of a
+workgroup share its context.  Lengths around that line and around odd and even numbers of steps, row counts that leave
+wavefronts without rows, every head layout, blocks of 8 tokens and more, against the oracle."""
+import numpy as np
+import pytest
+
+import kvc_workloads as W  # noqa: F401
+from test_gpu_prefill import check, make
+from test_gpu_prefill_d64 import poison
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,bs", [(8, 2, 16), (3, 1, 16), (4, 4, 8), (2, 1, 32), (16, 1, 64)])
+def test_contexts_around_the_line_and_odd_shares(oracle_mod, hq, hkv, bs):
+    lens = [735, 736, 737, 767, 768, 769, 800, 801, 833, 1000]
+    qlens = [64, 1, 17, 33, 64, 65, 128, 5, 63, 130]
+    for i in range(0, len(lens), 5):      # five at a time: the launch stays within 256 workgroups
+        w, q, qs = make(1100 + hq + bs + i, lens[i:i + 5], qlens[i:i + 5], hq, hkv, bs=bs)
+        poison(w)
+        assert len(lens[i:i + 5]) * 3 * hq <= 256
+        check(oracle_mod, w, q, qs, f"split {hq}/{hkv} bs={bs}")
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (5, 1)])
+def test_recompute_crosses_the_line_inside_one_launch(oracle_mod, hq, hkv):
+    """The first query tiles of a request walk too few steps to share, the last ones share."""
+    w, q, qs = make(1150 + hq, [1300, 40], [1300, 40], hq, hkv)
+    check(oracle_mod, w, q, qs, f"recompute {hq}/{hkv}")
+
+
+def test_long_context_short_chunk(oracle_mod):
+    w, q, qs = make(1160, [20000, 3001], [37, 1], 4, 2)
+    check(oracle_mod, w, q, qs, "long")
+
+
+def test_scores_that_keep_growing_reach_both_parts(oracle_mod):
+    """Rising scores keep the reference points of the two parts far apart."""
+    w, q, qs = make(1170, [1500], [64], 4, 2)
+    ramp = np.linspace(-40.0, 40.0, 1500).astype(np.float32)
+    q[:, :, 1] = 0x3F80                                   # q[1] = 1
+    for t in range(1500):
+        w.k_cache[w.block_tables[0, t // 16], :, t % 16, 1] = W.f32_to_bf16_bits(ramp[t:t + 1] * 8)[0]
+    check(oracle_mod, w, q, qs, "ramp")
