@@ -14,6 +14,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 # KVC_HIP_LIBRARY points at another build of the same library (A/B comparisons of kernels)
 _LIB_PATH = os.environ.get("KVC_HIP_LIBRARY") or os.path.join(_PKG, "libkvc_hip.so")
 _lib = None
+_native = None   # kvc_call: the calls of a serving loop, checked and marshalled in native code
 
 
 class KvcError(RuntimeError):
@@ -96,6 +97,35 @@ def lib():
     L.kvc_validate_block_mapping.argtypes = [pp, pp, vp, ctypes.c_int64, vp]
     _lib = L
     return L
+
+
+def _calls():
+    """The native call path (paper_2503_13773_amd.build makes it), bound to the loaded library."""
+    global _native
+    if _native is None:
+        L = lib()
+        try:
+            from . import kvc_call
+        except ImportError as e:
+            raise RuntimeError("kvc_call.so is missing or does not load: run "
+                               f"`python -m paper_2503_13773_amd.build` ({e})") from e
+        kvc_call.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
+            "kvc_paged_attention_decode", "kvc_paged_attention_decode_workspace_bytes",
+            "kvc_paged_attention_decode_scheduled", "kvc_attn_schedule_build", "kvc_paged_attention_prefill",
+            "kvc_kv_cache_append", "kvc_kv_block_copy")))
+        _native = kvc_call
+    return _native
+
+
+def _on_device(t) -> bool:
+    return isinstance(t, torch.Tensor) and t.is_cuda
+
+
+def _raw_stream(stream) -> int:
+    """Handle of `stream`, or of the current stream without building a Stream object for it."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream)
 
 
 def version() -> int:
@@ -197,6 +227,12 @@ def paged_attention_decode(q, k_cache, v_cache, block_tables, context_lens, scal
     if desc is None:
         desc = attn_desc(q, k_cache, block_tables, max_context_len=max_context_len,
                          partition_tokens=partition_tokens, kernel=kernel)
+    if out is not None and _on_device(q):
+        rc = _calls().decode(q, k_cache, v_cache, block_tables, context_lens, scale, out, desc, workspace,
+                             _raw_stream(stream))
+        if rc is not None:
+            _check(rc, "kvc_paged_attention_decode")
+            return out
     out, workspace, ws_ptr, ws_len = _attn_args(q, k_cache, v_cache, block_tables, context_lens,
                                                 out, desc, workspace)
     _check(lib().kvc_paged_attention_decode(
@@ -213,6 +249,11 @@ def schedule_bytes(desc: AttnDesc) -> int:
 def attn_schedule_build(block_tables, context_lens, desc: AttnDesc, schedule=None, stream=None):
     """Placement of the balanced kernel's workers for (block_tables, context_lens): built once per
     iteration, reused by every layer's paged_attention_decode_scheduled.  Returns the schedule tensor."""
+    if schedule is not None and _on_device(block_tables):
+        rc = _calls().schedule_build(block_tables, context_lens, desc, schedule, _raw_stream(stream))
+        if rc is not None:
+            _check(rc, "kvc_attn_schedule_build")
+            return schedule
     need = schedule_bytes(desc)
     if schedule is None:
         schedule = torch.empty(max(need, 256), dtype=torch.uint8, device=block_tables.device)
@@ -226,6 +267,11 @@ def paged_attention_decode_scheduled(q, k_cache, v_cache, schedule, scale: float
                                      workspace, stream=None):
     if out is None:
         out = torch.empty_like(q)
+    if _on_device(q):
+        rc = _calls().scheduled(q, k_cache, v_cache, schedule, scale, out, desc, workspace, _raw_stream(stream))
+        if rc is not None:
+            _check(rc, "kvc_paged_attention_decode_scheduled")
+            return out
     _check(lib().kvc_paged_attention_decode_scheduled(
         q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), schedule.data_ptr(), schedule.numel(), float(scale),
         out.data_ptr(), ctypes.byref(desc), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
@@ -281,6 +327,12 @@ def paged_attention_prefill(q, k_cache, v_cache, block_tables, context_lens, q_s
     """Causal attention of the last Qn = q_start[n+1]-q_start[n] positions of every sequence
     (q is [total_q][Hq][D], rows of all sequences back to back) over its block list.
     kernel=KERNEL_MFMA asks for the 16x16-tile matrix-core kernel where AUTO would take 32x32 tiles."""
+    if out is not None and _on_device(q):
+        rc = _calls().prefill(q, k_cache, v_cache, block_tables, context_lens, q_start, scale, max_query_len, out,
+                              kernel, _raw_stream(stream))
+        if rc is not None:
+            _check(rc, "kvc_paged_attention_prefill")
+            return out
     for t in (q, k_cache, v_cache, block_tables, context_lens, q_start):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError("tensors must be contiguous device tensors")
@@ -309,6 +361,11 @@ def paged_attention_prefill(q, k_cache, v_cache, block_tables, context_lens, q_s
 
 def kv_cache_append(k_new, v_new, k_cache, v_cache, block_tables, positions, stream=None) -> None:
     """Write token positions[n] of every sequence: cache[table[n][pos // Bs]][h][pos % Bs] = new[n][h]."""
+    if _on_device(k_new):
+        rc = _calls().append(k_new, v_new, k_cache, v_cache, block_tables, positions, _raw_stream(stream))
+        if rc is not None:
+            _check(rc, "kvc_kv_cache_append")
+            return
     for t in (k_new, v_new, k_cache, v_cache, block_tables, positions):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError("tensors must be contiguous device tensors")
@@ -366,6 +423,11 @@ def kv_block_copy(src_pool, dst_pool, block_mapping, stream=None) -> None:
 
     Pools are Pool structs or tensors shaped [num_planes][num_blocks][...].
     """
+    if _on_device(src_pool):
+        rc = _calls().block_copy(src_pool, dst_pool, block_mapping, _raw_stream(stream))
+        if rc is not None:
+            _check(rc, "kvc_kv_block_copy")
+            return
     src = src_pool if isinstance(src_pool, Pool) else pool_of(src_pool)
     dst = dst_pool if isinstance(dst_pool, Pool) else pool_of(dst_pool)
     if block_mapping.dtype != torch.int64 or not block_mapping.is_cuda or not block_mapping.is_contiguous():

@@ -74,6 +74,30 @@ def build_policy_library(verbose: bool = False, out: str = "", extra_flags=()) -
     return target
 
 
+CALL_LIB = os.path.join(PKG, "kvc_call.so")
+
+
+def build_call_module(verbose: bool = False) -> str:
+    """The native call path of binding.py (a CPython extension over torch's tensor type; no GPU code)."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-I", os.path.join(ROOT, "include")]
+    for d in cpp_extension.include_paths():
+        cmd += ["-isystem", d]
+    cmd += ["-isystem", sysconfig.get_path("include"), os.path.join(CSRC, "kvc_call.cpp"), "-o", CALL_LIB]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L", d]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on kvc_call.cpp:\n{r.stdout}\n{r.stderr}")
+    if verbose:
+        print("built", CALL_LIB)
+    return CALL_LIB
+
+
 if __name__ == "__main__":
     build_library(sys.argv[1:], verbose=True)
     build_policy_library(verbose=True)
+    build_call_module(verbose=True)
