@@ -58,6 +58,7 @@ struct Plan {
     int kernel;
     int partition_tokens;
     int max_partitions;
+    int head_chunk;       // vector-ALU kernel
     int64_t partial_grid;
     int64_t merge_grid;
     uint64_t acc_offset;  // offset of the accumulator array inside the workspace (after the counter header)
@@ -108,6 +109,8 @@ bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
 }
 
+constexpr int64_t kFewRowParts = 384;  // (query head, partition) pairs
+
 int make_plan(const kvc_attn_desc *d, Plan *pl) {
     if (!d) return KVC_ERR_NULL;
     if (d->num_seqs < 0 || d->num_q_heads <= 0 || d->num_kv_heads <= 0 || d->head_dim <= 0 ||
@@ -150,6 +153,7 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         const int group = d->num_q_heads / d->num_kv_heads;
         const uint64_t slots = uint64_t(kvc::kNumCUs) * kvc::kWaves * 2;
         pl->kernel = kernel;
+        pl->head_chunk = 0;
         pl->partition_tokens = min_chunk * tile_tokens;
         pl->min_chunk_tiles = min_chunk;
         pl->max_partitions = 2;           // partial slots per worker
@@ -167,9 +171,8 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
     }
 
     const int group = d->num_q_heads / d->num_kv_heads;
-    const int64_t base_items = kernel == KVC_KERNEL_VALU
-                                   ? int64_t(d->num_seqs) * (d->num_q_heads / kvc::valu_head_chunk(group))
-                                   : int64_t(d->num_seqs) * d->num_kv_heads;
+    pl->head_chunk = kvc::valu_head_chunk(group);
+    int64_t base_items = kernel == KVC_KERNEL_VALU ? rows / pl->head_chunk : int64_t(d->num_seqs) * d->num_kv_heads;
     int pt = d->partition_tokens;
     if (pt == 0) {
         // Short partitions spread a skewed length mix over the 256 CUs; longer ones keep the
@@ -182,6 +185,14 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         }
     }
     const int64_t parts = ceil_div(max_ctx, pt);
+    // A workgroup of the vector-ALU kernel takes as many heads of a KV head as its registers hold, which reads K and V
+    // once for all of them; a launch of few workgroups spends its time on the chain of one of them, which is
+    // shorter with a head each (fp32, 16 / 4 heads, with the heads together / one each: 4 x 256 tokens, 64 pairs, of 64
+    // 9.0 / 5.1 us, of 128 12.9 / 7.0 us; 4 x 1000, 256 pairs, 18.1 / 14.1 us; 4 x 2000, 512 pairs, 19.6 / 21.7 us).
+    if (kernel == KVC_KERNEL_VALU && rows * parts <= kFewRowParts) {
+        pl->head_chunk = 1;
+        base_items = rows;
+    }
     if (base_items * parts > kMaxGrid || rows * parts > kMaxGrid) return KVC_ERR_BAD_SHAPE;
 
     pl->kernel = kernel;
@@ -215,6 +226,7 @@ kvc::AttnParams make_params(const kvc_attn_desc &d, const Plan &pl, float scale)
     p.max_blocks_per_seq = d.max_blocks_per_seq;
     p.partition_tokens = pl.partition_tokens;
     p.max_partitions = pl.max_partitions;
+    p.head_chunk = pl.head_chunk;
     p.k_via_lds = pl.kernel == KVC_KERNEL_MFMA_LDS;
     p.min_chunk_tiles = pl.min_chunk_tiles;
     p.max_context_len = pl.max_context_len;
@@ -587,6 +599,7 @@ int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *
         vp.num_seqs = total_q;
         vp.partition_tokens = 1 << 30;
         vp.max_partitions = 1;
+        vp.head_chunk = kvc::valu_head_chunk(vp.group);
         vp.max_context_len = desc->max_blocks_per_seq * desc->block_size;
         const int64_t grid = int64_t(total_q) * (desc->num_q_heads / kvc::valu_head_chunk(vp.group));
         if (grid > kMaxGrid) return KVC_ERR_BAD_SHAPE;

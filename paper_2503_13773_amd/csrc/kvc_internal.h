@@ -19,6 +19,7 @@ struct AttnParams {
     int max_blocks_per_seq;
     int partition_tokens;   // split-K partition length, multiple of 16
     int max_partitions;     // partitions per sequence the grid and workspace provide for
+    int head_chunk;         // vector-ALU kernel: query heads a workgroup processes (divides group)
     int k_via_lds;          // MFMA kernel: stage K tiles through LDS (1) or load them in operand layout (0)
     int min_chunk_tiles;    // balanced kernel: smallest number of tiles (16 tokens, 32 at head_dim 64) a worker (few rows: a workgroup) takes
     int max_context_len;    // context lengths are clamped to this (the bound every size is derived from)

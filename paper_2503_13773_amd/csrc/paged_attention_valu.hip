@@ -61,10 +61,35 @@ struct Elem<uint16_t> {  // bfloat16 bit patterns
     }
 };
 
+// x + (x of lane l ^ OFF), for sums over aligned groups of lanes taken in the order OFF = 1, 2, 4, ...: before step
+// OFF all lanes of an aligned group of OFF hold the same value, so any lane of the neighbouring group will do
+// and the step is a lane permutation inside the vector ALU: a mirror of 8 or 16 lanes, or a swap of 16-lane rows.
+// The sums are the same bits as with shuffles through the LDS pipe, whose latency a decode call of few
+// workgroups waits for in every step (one sequence of 256 tokens, fp32, 16 / 4 heads of 128: 14.6 -> 10.4 us).
+// Prefill has wavefronts enough to hide it and keeps the shuffles, which leave the vector ALU free (fp32, 1000 rows,
+// 32 / 8 heads of 128: 503 us with shuffles, 566 us with permutations).
+template <int CTRL>
+__device__ inline float permuted(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int LR>
+__device__ inline float sum_over_row(float x) {  // LR = 8, 16 or 32 lanes of a token row
+    x += permuted<0xb1>(x);   // quad_perm [1, 0, 3, 2]
+    x += permuted<0x4e>(x);   // quad_perm [2, 3, 0, 1]
+    x += permuted<0x141>(x);  // row_half_mirror
+    if constexpr (LR > 8) x += permuted<0x140>(x);  // row_mirror
+    if constexpr (LR > 16) {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    }
+    return x;
+}
+
 constexpr int kUnroll = 4;  // tokens per lane group per loop trip (8 x 16-byte loads in flight)
 
-template <typename T, int D, int GC, bool PREFILL>
-__global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
+template <typename T, int D, int GC, bool PREFILL, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const T *__restrict__ q, const T *__restrict__ k_cache, const T *__restrict__ v_cache,
     const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens,
     const int32_t *__restrict__ q_start, int num_tables, int max_query_len,
@@ -73,7 +98,7 @@ __global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
     constexpr int EPL = E::kPerLane;
     constexpr int LR = D / EPL;    // lanes per token row
     constexpr int TPL = 64 / LR;   // tokens per wavefront load
-    static_assert(LR >= 1 && LR <= 64 && (LR & (LR - 1)) == 0, "row must be 16..1024 bytes");
+    static_assert(LR == 8 || LR == 16 || LR == 32, "a row is 128, 256 or 512 bytes");
 
     // blockIdx.x = head_chunk + chunks * (seq + num_seqs * partition): the partition index
     // varies slowest, so the (always busy) first partitions are dispatched first.
@@ -103,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
 
     if (ctx <= 0) {  // empty context: a row of zeros, written by partition 0
         if (part == 0)
-            for (int i = tid; i < GC * D; i += kThreads)
+            for (int i = tid; i < GC * D; i += 64 * WAVES)
                 out[(size_t(seq) * p.num_q_heads + head0) * D + i] = E::to_out(0.f);
         return;
     }
@@ -133,7 +158,7 @@ __global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
     const size_t block_stride = head_stride * p.num_kv_heads;
     constexpr int CH = TPL * kUnroll;                                   // tokens per wavefront per trip
 
-    for (int base = tok0 + wave * CH; base < tok1; base += kWaves * CH) {
+    for (int base = tok0 + wave * CH; base < tok1; base += WAVES * CH) {
         float kf[kUnroll][EPL], vf[kUnroll][EPL];
         bool valid[kUnroll];
 #pragma unroll
@@ -156,8 +181,12 @@ __global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
                 float d = 0.f;
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) d = fmaf(qf[g][e], kf[u][e], d);
+                if constexpr (PREFILL) {
 #pragma unroll
-                for (int off = 1; off < LR; off <<= 1) d += __shfl_xor(d, off);
+                    for (int off = 1; off < LR; off <<= 1) d += __shfl_xor(d, off);
+                } else {
+                    d = sum_over_row<LR>(d);
+                }
                 s[u] = valid[u] ? d * p.scale : -INFINITY;
                 mx = fmaxf(mx, s[u]);
             }
@@ -201,9 +230,9 @@ __global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
         }
     }
 
-    // merge the four wavefronts through LDS
-    __shared__ float sm_m[kWaves][GC], sm_l[kWaves][GC];
-    __shared__ float sm_acc[kWaves][GC][D];
+    // merge the wavefronts through LDS
+    __shared__ float sm_m[WAVES][GC], sm_l[WAVES][GC];
+    __shared__ float sm_acc[WAVES][GC][D];
     if (tg == 0) {
 #pragma unroll
         for (int g = 0; g < GC; ++g) {
@@ -221,14 +250,14 @@ __global__ __launch_bounds__(kThreads) void pa_partial_valu_kernel(
     __syncthreads();
 
     const bool single = ctx <= p.partition_tokens;  // the whole context sat in this partition
-    for (int i = tid; i < GC * D; i += kThreads) {
+    for (int i = tid; i < GC * D; i += 64 * WAVES) {
         const int g = i / D, d = i % D;
         float M = sm_m[0][g];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm_m[w][g]);
+        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][g]);
         float L = 0.f, A = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             const float wgt = E::exp_(sm_m[w][g] - M);  // M is finite: wavefront 0 always has a token
             L = fmaf(wgt, sm_l[w][g], L);
             A = fmaf(wgt, sm_acc[w][g][d], A);
@@ -251,10 +280,19 @@ template <typename T, int D, bool PREFILL>
 hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v, const int32_t *bt,
                             const int32_t *cl, const int32_t *qs, int num_tables, int max_query_len,
                             void *out, Workspace ws, const AttnParams &p, int grid, hipStream_t stream) {
-#define KVC_LAUNCH_VALU(GC)                                                                       \
-    pa_partial_valu_kernel<T, D, GC, PREFILL><<<dim3(grid), dim3(kThreads), 0, stream>>>(         \
+#define KVC_LAUNCH_WAVES(GC, WAVES)                                                               \
+    pa_partial_valu_kernel<T, D, GC, PREFILL, WAVES><<<dim3(grid), dim3(64 * WAVES), 0, stream>>>(\
         static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v), bt, cl, \
         qs, num_tables, max_query_len, static_cast<T *>(out), ws, p)
+    // Up to one workgroup per compute unit: sixteen wavefronts instead of four where the registers allow it and the
+    // merge in LDS is small (fp32, 24 x 256 tokens: 8 heads of 64 7.2 -> 6.4 us, 8 of 128 10.8 -> 8.7 us; four
+    // heads of 64 per workgroup 9.3 -> 9.7 us, so those stay at four).
+    constexpr bool kWide = !PREFILL && sizeof(T) == 4;
+#define KVC_LAUNCH_VALU(GC)                                                                       \
+    do {                                                                                          \
+        constexpr int kMany = kWide && (GC == 1 || (D == 128 && GC <= 4)) ? 16 : kWaves;          \
+        if (grid <= kNumCUs) KVC_LAUNCH_WAVES(GC, kMany); else KVC_LAUNCH_WAVES(GC, kWaves);      \
+    } while (0)
     switch (gc) {
         case 8: KVC_LAUNCH_VALU(8); break;
         case 4: KVC_LAUNCH_VALU(4); break;
@@ -262,6 +300,7 @@ hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v,
         default: KVC_LAUNCH_VALU(1); break;
     }
 #undef KVC_LAUNCH_VALU
+#undef KVC_LAUNCH_WAVES
     return hipGetLastError();
 }
 
@@ -271,7 +310,7 @@ hipError_t launch_for_type(const void *q, const void *k_cache, const void *v_cac
                            const int32_t *q_start, int num_tables, int max_query_len, void *out,
                            Workspace ws, const AttnParams &p, int dtype, int head_dim, int grid,
                            hipStream_t stream) {
-    const int gc = valu_head_chunk(p.group);
+    const int gc = p.head_chunk;
     if (dtype == KVC_F32) {
         if (head_dim == 64)
             return launch_for_chunk<float, 64, PREFILL>(gc, q, k_cache, v_cache, block_tables, context_lens, q_start,
