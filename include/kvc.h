@@ -71,10 +71,11 @@ typedef enum {
     KVC_KERNEL_MFMA_BALANCED = 4 /* matrix-core tiles, persistent grid: the batch's (sequence, kv head,
                             16-token tile) work is flattened and cut into equal per-wavefront ranges;
                             bf16, head_dim 128, block_size >= 4, group <= 16, num_seqs <= 4096.  AUTO
-                            also takes it for bf16 at head_dim 64 (32-token tiles), large batches and
-                            few rows.  Without a partition_tokens of the caller's, few rows (up to 64
-                            sequences and 128 (sequence, kv head) rows of moderate length) are cut into
-                            pieces of rows, one per workgroup, instead of ranges */
+                            also takes it for bf16 at head_dim 64 (32-token tiles).  Without a
+                            partition_tokens of the caller's, short contexts (bound of at most 512
+                            tokens; 640 to 1024 at head_dim 64) are dealt out by rows, one per workgroup, and few
+                            rows (up to 64 sequences and 128 (sequence, kv head) rows of moderate
+                            length) by pieces of rows, instead of ranges */
 } kvc_kernel;
 
 typedef struct {

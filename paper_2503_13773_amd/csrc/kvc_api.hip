@@ -66,8 +66,18 @@ struct Plan {
     uint64_t workspace_bytes;
     int min_chunk_tiles;
     int max_context_len;
-    bool few_rows;        // balanced: a workgroup per piece of a row instead of a wavefront per flat range
+    int layout;           // balanced: how the rows are dealt out (kRanges, kPieces, kWhole)
 };
+
+enum : int {
+    kRanges = 0,  // a wavefront per range of the batch's flat tiles
+    kPieces = 1,  // few rows: a workgroup per piece of a row
+    kWhole = 2    // short contexts: a workgroup per row
+};
+using BalancedLauncher = decltype(&kvc::launch_partial_mfma_stream);
+BalancedLauncher balanced_launcher(const Plan &pl) {
+    return pl.layout == kWhole ? kvc::launch_whole_mfma : pl.layout == kPieces ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream;
+}
 
 bool mfma_ok(const kvc_attn_desc &d) {
     return d.dtype == KVC_BF16 && d.head_dim == 128 && d.block_size >= 16 &&
@@ -96,14 +106,28 @@ bool few_rows_ok(const kvc_attn_desc &d, int max_ctx) {
            rows * rows * rows * max_ctx <= (int64_t(1) << 31);
 }
 
+// Short contexts: a workgroup per row, two memory round trips to the first K and V bytes and no exchange.  In us, the
+// best of the other layouts / whole rows (32 / 8 heads unless said, lengths at or below the bound):
+//   head_dim 128: 1 x 300 7.4 / 5.7, 1 x 500 8.9 / 8.1, 20 x 100 9.4 / 4.9, 64 x 300 19.8 / 14.5, 32 x 600 20.2 / 15.2,
+//     128 x 500 45.0 / 41.0; 14 / 2 heads 64 x 700 15.3 / 13.5, 20 x 1000 11.0 / 15.4; 64 x 1000 34.5 / 35.4; with more than
+//     about 1000 rows of up to 200 tokens the ranges win: 128 x 100 13.1 / 13.6, 1000 x 80 56 / 70 (128 x 300 31.8 / 26.9);
+//   head_dim 64: 1 x 500 7.0 / 5.5, 64 x 500 17.9 / 12.4, 20 x 1000 12.8 / 10.7; 14 / 2 heads on the vector ALUs before:
+//     128 x 500 36.2 / 8.2; but one head per KV head and 1000 rows of up to 200 tokens: 128 x 100 12.2 / 15.2.
+bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
+    const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
+    if (d.partition_tokens != 0 || d.num_seqs < 1 || d.num_seqs > kvc::kMaxStreamSeqs) return false;
+    const bool many_short = rows > 1000 && max_ctx <= 200;
+    if (d.head_dim == 128) return max_ctx <= 512 && !many_short;
+    return max_ctx <= (rows > kvc::kMaxFewRows ? 1024 : 640) && !(many_short && d.num_q_heads == d.num_kv_heads);
+}
+
 // At head_dim 64 the balanced kernel serves calls that KVC_KERNEL_AUTO brings without a split of the caller's
-// own: few rows, and large batches.  The batches between them stay on the vector ALUs; the line lies where
-// the two meet in back-to-back launches (KV heads x tokens of the bound; vector ALUs / balanced in us: 102 k
-// 9.7 / 11.9, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
+// own: whole rows, few rows, and ranges from 2^17 tokens x KV heads on (below that the vector ALUs are as good:
+// 102 k 9.7 / 11.9 us, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
 bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
     return d.kernel == KVC_KERNEL_AUTO && d.dtype == KVC_BF16 && d.head_dim == 64 && d.block_size >= 4 &&
            d.partition_tokens == 0 && d.num_q_heads / d.num_kv_heads <= 16 && d.num_seqs <= kvc::kMaxStreamSeqs &&
-           (few_rows_ok(d, max_ctx) ||
+           (whole_ok(d, max_ctx) || few_rows_ok(d, max_ctx) ||
             (max_ctx > 256 && int64_t(d.num_seqs) * d.num_kv_heads * max_ctx >= (1 << 17))) &&
            int64_t(d.num_seqs) * d.num_kv_heads * (ceil_div(max_ctx, 32) + 1) < (int64_t(1) << 30) &&
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
@@ -146,8 +170,9 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         // fewer than min_chunk tiles; the workspace is two partial slots per wavefront.
         const int tile_tokens = d->head_dim == 64 ? 32 : 16;  // 8 KiB of K and V
         const int64_t max_tiles = ceil_div(max_ctx, tile_tokens);
-        pl->few_rows = few_rows_ok(*d, max_ctx);
-        const int min_chunk = pl->few_rows         ? kFewRowsMinTiles
+        pl->layout = whole_ok(*d, max_ctx) ? kWhole : few_rows_ok(*d, max_ctx) ? kPieces : kRanges;
+        const int min_chunk = pl->layout == kWhole    ? int(max_tiles)
+                              : pl->layout == kPieces ? kFewRowsMinTiles
                               : d->partition_tokens ? d->partition_tokens / tile_tokens
                                                     : int(std::max<int64_t>(4, ceil_div(max_tiles, 32)));
         const int group = d->num_q_heads / d->num_kv_heads;
@@ -157,16 +182,16 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         pl->partition_tokens = min_chunk * tile_tokens;
         pl->min_chunk_tiles = min_chunk;
         pl->max_partitions = 2;           // partial slots per worker
-        pl->partial_grid = kvc::kNumCUs;  // 4 wavefronts per CU: one worker per SIMD
+        // 4 wavefronts per CU: one worker per SIMD; whole rows: a workgroup each
+        pl->partial_grid = pl->layout == kWhole ? int64_t(d->num_seqs) * d->num_kv_heads : kvc::kNumCUs;
         pl->merge_grid = 0;
         pl->max_context_len = max_ctx;
         const uint64_t acc = slots * group * d->head_dim * sizeof(float);
         pl->acc_offset = kHeader;
         pl->ml_offset = (kHeader + acc + 255) & ~uint64_t(255);
         pl->workspace_bytes = pl->ml_offset + slots * group * 2 * sizeof(float);
-        // head_dim 64 up to 256 tokens: every row is one piece, and no workspace was asked for before there
-        // was a matrix-core kernel for it
-        if (d->head_dim == 64 && pl->few_rows && max_ctx <= 256) pl->workspace_bytes = 0;
+        // whole rows need no workspace; head_dim 128 keeps asking for one (its size never depended on the lengths)
+        if (d->head_dim == 64 && pl->layout == kWhole) pl->workspace_bytes = 0;
         return KVC_OK;
     }
 
@@ -202,7 +227,7 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
     pl->merge_grid = parts > 1 ? ceil_div(rows, kvc::kWaves) : 0;
     pl->max_context_len = max_ctx;
     pl->min_chunk_tiles = 0;
-    pl->few_rows = false;
+    pl->layout = kRanges;
     pl->acc_offset = kHeader;
     if (parts > 1) {
         const uint64_t acc = uint64_t(rows) * parts * d->head_dim * sizeof(float);
@@ -258,7 +283,7 @@ int run_partial(const void *q, const void *k_cache, const void *v_cache, const i
         e = kvc::launch_partial_valu(q, k_cache, v_cache, block_tables, context_lens, out, ws, p,
                                      desc->dtype, desc->head_dim, int(pl.partial_grid), stream);
     else if (pl.kernel == KVC_KERNEL_MFMA_BALANCED)
-        e = (pl.few_rows ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream)(q, k_cache, v_cache, block_tables, context_lens, out,
+        e = balanced_launcher(pl)(q, k_cache, v_cache, block_tables, context_lens, out,
                                             ws, p, desc->head_dim, int(pl.partial_grid), 0, kvc::Schedule{}, stream);
     else
         e = kvc::launch_partial_mfma(q, k_cache, v_cache, block_tables, context_lens, out, ws, p,
@@ -283,13 +308,15 @@ struct ScheduleLayout {
 
 bool schedule_layout(const kvc_attn_desc &d, const Plan &pl, ScheduleLayout *L) {
     if (pl.kernel != KVC_KERNEL_MFMA_BALANCED || d.head_dim != 128) return false;
-    const int64_t workers = pl.few_rows ? kvc::kNumCUs : int64_t(kvc::kNumCUs) * kvc::kWaves;  // workgroups / wavefronts
+    // wavefronts, or workgroups
+    const int64_t workers = pl.layout == kRanges ? int64_t(kvc::kNumCUs) * kvc::kWaves : pl.partial_grid;
     const int64_t units_per_tile = d.block_size >= 16 ? 1 : 16 / d.block_size;
     const int64_t max_tiles = ceil_div(pl.max_context_len, 16);
     // no worker takes more flat units than this, whatever the context lengths turn out to be
     const int64_t max_units = int64_t(d.num_seqs) * d.num_kv_heads * (max_tiles + 1);
     int64_t chunk = std::max<int64_t>(pl.min_chunk_tiles, ceil_div(max_units, workers));
-    if (pl.few_rows)  // nor a workgroup more tiles than this
+    if (pl.layout == kWhole) chunk = max_tiles;
+    if (pl.layout == kPieces)  // nor a workgroup more tiles than this
         chunk = std::max({int64_t(pl.min_chunk_tiles), std::min<int64_t>(max_tiles, kvc::kRowWholeTiles),
                           ceil_div(max_tiles, kvc::kMaxRowPieces),
                           ceil_div(d.num_seqs * max_tiles, kvc::kNumCUs / d.num_kv_heads - d.num_seqs)});
@@ -496,7 +523,7 @@ int kvc_attn_schedule_build(const int32_t *block_tables, const int32_t *context_
     if (desc->num_seqs == 0) return KVC_OK;
     if (!block_tables || !context_lens) return KVC_ERR_NULL;
     const kvc::AttnParams p = make_params(*desc, pl, 1.0f);
-    const hipError_t e = (pl.few_rows ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream)(nullptr, nullptr, nullptr, block_tables, context_lens,
+    const hipError_t e = balanced_launcher(pl)(nullptr, nullptr, nullptr, block_tables, context_lens,
                                                          nullptr, kvc::Workspace{}, p, desc->head_dim, int(pl.partial_grid), 1,
                                                          schedule_view(schedule, L),
                                                          static_cast<hipStream_t>(hip_stream));
@@ -522,7 +549,7 @@ int kvc_paged_attention_decode_scheduled(const void *q, const void *k_cache, con
     rc = check_workspace(pl, workspace, workspace_bytes, &ws);
     if (rc != KVC_OK) return rc;
     const kvc::AttnParams p = make_params(*desc, pl, scale);
-    const hipError_t e = (pl.few_rows ? kvc::launch_rows_mfma : kvc::launch_partial_mfma_stream)(q, k_cache, v_cache, nullptr, nullptr, out, ws, p,
+    const hipError_t e = balanced_launcher(pl)(q, k_cache, v_cache, nullptr, nullptr, out, ws, p,
                                                          desc->head_dim, int(pl.partial_grid), 2,
                                                          schedule_view(const_cast<void *>(schedule), L),
                                                          static_cast<hipStream_t>(hip_stream));

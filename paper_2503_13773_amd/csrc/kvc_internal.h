@@ -92,6 +92,12 @@ hipError_t launch_rows_mfma(const void *q, const void *k_cache, const void *v_ca
                             const int32_t *block_tables, const int32_t *context_lens,
                             void *out, Workspace ws, const AttnParams &p, int head_dim, int grid,
                             int mode, Schedule sched, hipStream_t stream);
+// Short contexts: a workgroup takes a whole row.  At most 64 units (parts of a tile inside one block) for each of its
+// four wavefronts.  Arguments as above (workspace and grid unused).
+hipError_t launch_whole_mfma(const void *q, const void *k_cache, const void *v_cache,
+                             const int32_t *block_tables, const int32_t *context_lens,
+                             void *out, Workspace ws, const AttnParams &p, int head_dim, int grid,
+                             int mode, Schedule sched, hipStream_t stream);
 constexpr int kMaxFewRows = kNumCUs / 2;
 constexpr int kMaxRowPieces = 64;  // pieces a row is cut into at most
 constexpr int kRowWholeTiles = 20;  // few rows: up to this length a row is one piece when the grid allows

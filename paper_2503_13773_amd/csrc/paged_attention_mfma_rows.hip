@@ -53,6 +53,79 @@ __device__ inline int wave_max(int x) {
     return uniform(x);
 }
 
+// Loads of one tile: entry(u) = pool index of its unit u (a tile is 1 << (kTokensLog2 - unit_log2) of them).  k_off / v_off:
+// this lane's place inside a unit, in elements.  UNIFORM: units of 16 tokens and more, so that all lanes of a
+// wavefront ask for the same unit and entry() returns a scalar: base addresses stay in scalar registers.
+template <int HD, bool UNIFORM, class Entry>
+__device__ inline void load_tile(typename Shape<HD>::Tile &t, Entry entry, const uint16_t *k_cache, const uint16_t *v_cache, int k_off,
+                                 int v_off, size_t unit_elems, int unit_log2, int quad, int r) {
+    constexpr int kSubs = Shape<HD>::kTokens / 16;
+#pragma unroll
+    for (int h = 0; h < kSubs; ++h) {
+        const int in_unit = kSubs == 2 && unit_log2 == 5 ? 16 * h * HD : 0;  // second half of a 32-token unit
+        const uint16_t *kp, *vp;
+        if constexpr (UNIFORM) {
+            const size_t base = size_t(entry((16 * h) >> unit_log2)) * unit_elems + in_unit;
+            kp = k_cache + base + k_off;
+            vp = v_cache + base + v_off;
+        } else {
+            kp = k_cache + size_t(entry((16 * h + r) >> unit_log2)) * unit_elems + in_unit + k_off;
+            vp = v_cache + size_t(entry((16 * h + 4 * quad) >> unit_log2)) * unit_elems + in_unit + v_off;
+        }
+        if constexpr (HD == 128) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t.k[j] = load16_stream(kp + 32 * j);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t.v[i] = load16_stream(vp + i * HD);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) t.k[2 * h + j] = load16_stream(kp + 32 * j);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t.v[4 * h + i] = load8_stream(vp + i * HD);
+        }
+    }
+}
+
+template <int HD>
+__device__ inline void consume_tile(typename Shape<HD>::State &st, typename Shape<HD>::Tile &t, const bf16x8 (&qb)[Shape<HD>::kQ],
+                                    float scale_log2e, int left, int quad) {
+    if constexpr (HD == 128) {
+        bf16x8 ka[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ka[j] = __builtin_bit_cast(bf16x8, t.k[j]);
+        compute_tile(st, ka, t.v, qb, scale_log2e, left, quad);
+    } else {
+        compute_tile(st, t.k, t.v, qb, scale_log2e, left, quad);
+    }
+}
+
+// `count` tiles in two register sets, no branch around the loads of the steady loop (see the balanced kernel)
+template <class Tile, class Issue, class Compute>
+__device__ inline void stream_tiles(int count, Issue issue, Compute compute) {
+    Tile tA, tB;
+    issue(tA);
+    int it = 0;
+    for (; it + 3 < count; it += 2) {
+        issue(tB);
+        compute(tA);
+        issue(tA);
+        compute(tB);
+    }
+    if (it + 3 == count) {
+        issue(tB);
+        compute(tA);
+        issue(tA);
+        compute(tB);
+        compute(tA);
+    } else if (it + 2 == count) {
+        issue(tB);
+        compute(tA);
+        compute(tB);
+    } else {
+        compute(tA);
+    }
+}
+
 // One workgroup's share: a piece of a row.
 struct Piece {
     int n, kvh;         // sequence, KV head
@@ -189,9 +262,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
         }
 
         const size_t unit_elems = size_t(unit_tokens) * HD;
-        constexpr int kSubs = kTokens / 16;
-        const uint16_t *k_lane = k_cache + (r & (unit_tokens - 1)) * HD + 8 * quad;
-        const uint16_t *v_lane = v_cache + ((4 * quad) & (unit_tokens - 1)) * HD + HD / 16 * r;
+        const int k_off = (r & (unit_tokens - 1)) * HD + 8 * quad, v_off = ((4 * quad) & (unit_tokens - 1)) * HD + HD / 16 * r;
         int ki = 0, staged = 0;
         auto issue = [&](typename TS::Tile &t) __attribute__((always_inline)) {
             if (ki - staged == kStage) {  // long pieces only
@@ -199,60 +270,15 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
                 staged = ki;
             }
             const int *e = s_tile + ((ki - staged) << U_log2);
-#pragma unroll
-            for (int h = 0; h < kSubs; ++h) {
-                const int in_unit = kSubs == 2 && unit_log2 == 5 ? 16 * h * HD : 0;
-                const uint16_t *kp = k_lane + size_t(e[(16 * h + r) >> unit_log2]) * unit_elems + in_unit;
-                const uint16_t *vp = v_lane + size_t(e[(16 * h + 4 * quad) >> unit_log2]) * unit_elems + in_unit;
-                if constexpr (HD == 128) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) t.k[j] = load16_stream(kp + 32 * j);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) t.v[i] = load16_stream(vp + i * HD);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) t.k[2 * h + j] = load16_stream(kp + 32 * j);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) t.v[4 * h + i] = load8_stream(vp + i * HD);
-                }
-            }
+            load_tile<HD, false>(t, [&](int u) { return e[u]; }, k_cache, v_cache, k_off, v_off, unit_elems, unit_log2, quad, r);
             ++ki;
         };
         int left = pc.ctx - (pc.tile0 + wave) * kTokens;  // tokens of the context from the next tile on
         auto compute = [&](typename TS::Tile &t) __attribute__((always_inline)) {
-            if constexpr (HD == 128) {
-                bf16x8 ka[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) ka[j] = __builtin_bit_cast(bf16x8, t.k[j]);
-                compute_tile(st, ka, t.v, qb, p.scale_log2e, left, quad);
-            } else {
-                compute_tile(st, t.k, t.v, qb, p.scale_log2e, left, quad);
-            }
+            consume_tile<HD>(st, t, qb, p.scale_log2e, left, quad);
             left -= kRowWaves * kTokens;
         };
-        // two register sets, no branch around the loads of the steady loop (see the balanced kernel)
-        typename TS::Tile tA, tB;
-        issue(tA);
-        int it = 0;
-        for (; it + 3 < count; it += 2) {
-            issue(tB);
-            compute(tA);
-            issue(tA);
-            compute(tB);
-        }
-        if (it + 3 == count) {
-            issue(tB);
-            compute(tA);
-            issue(tA);
-            compute(tB);
-            compute(tA);
-        } else if (it + 2 == count) {
-            issue(tB);
-            compute(tA);
-            compute(tB);
-        } else {
-            compute(tA);
-        }
+        stream_tiles<typename TS::Tile>(count, issue, compute);
         st.finish();
     }
 
@@ -372,6 +398,118 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
     if (tid < nv4) write_out(a, s_ml[0][head].y);
 }
 
+// Short contexts, any number of rows: a workgroup of four wavefronts takes a whole row, no placement, no exchange.
+// Block-table entries and Q are requested together with the context length (entries past the context are read
+// but never used), so the first K and V bytes are two memory round trips away.  20 sequences of 100 tokens, 32 / 8
+// heads of 128: 4.9 us (9.4 us in ranges); 64 of 300: 14.5 us = 5.4 TB/s (19.8 us).  Two wavefronts per SIMD at
+// head_dim 128: with three the registers spill (16.3 us), at head_dim 64 three fit.
+constexpr int kWholeWaves = 4;
+
+template <int HD, int MODE, bool UNIFORM>
+__global__ __launch_bounds__(64 * kWholeWaves, HD == 128 ? 2 : 3) void pa_whole_mfma_kernel(
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
+    const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
+    const int32_t *__restrict__ context_lens, uint16_t *__restrict__ out, AttnParams p, int unit_log2,
+    int units_per_block_log2, Schedule sched) {
+    using TS = Shape<HD>;
+    constexpr int kTokens = TS::kTokens, NV = TS::kVecs;
+    __shared__ __attribute__((aligned(16))) float s_acc[kWholeWaves * 16 * HD];
+    __shared__ float2 s_ml[kWholeWaves][16];
+    __shared__ int s_tiles[kWholeWaves][64];  // pool indices of the units of a wavefront's tiles: at most 64 (checked by the host)
+
+    const int tid = threadIdx.x;
+    const int wave = uniform(tid >> 6), lane = tid & 63;
+    const int quad = lane >> 4, r = lane & 15;
+    const int kvh = blockIdx.x, n = blockIdx.y;
+    const int Hkv = p.num_kv_heads, G = p.group;
+    const int U_log2 = TS::kTokensLog2 - unit_log2;
+    const size_t row = size_t(n) * Hkv + kvh;
+
+    // unit of this lane's entry: the wavefront takes tiles wave, wave + 4, ... of the row
+    const int unit = ((wave + kWholeWaves * (lane >> U_log2)) << U_log2) + (lane & ((1 << U_log2) - 1));
+    int ctx, entry;
+    if constexpr (MODE == kScheduled) {
+        ctx = sched.ctx[n];
+        entry = sched.tiles[row * sched.stride + min(unit, sched.stride - 1)];
+    } else {
+        ctx = min(max(context_lens[n], 0), p.max_context_len);
+        const int blk = block_tables[size_t(n) * p.max_blocks_per_seq + min(unit >> units_per_block_log2, p.max_blocks_per_seq - 1)];
+        entry = int(((unsigned(blk) * unsigned(Hkv) + unsigned(kvh)) << units_per_block_log2) +
+                    unsigned(unit & ((1 << units_per_block_log2) - 1)));
+    }
+    const int tiles = (ctx + kTokens - 1) >> TS::kTokensLog2;
+    if constexpr (MODE == kBuild) {
+        if (tid == 0 && kvh == 0) sched.ctx[n] = ctx;
+        if (unit < sched.stride) sched.tiles[row * sched.stride + unit] = entry;
+        return;
+    }
+    bf16x8 qb[TS::kQ];
+    load_q_operand(qb, q + (size_t(n) * p.num_q_heads + kvh * G + (r < G ? r : 0)) * HD, quad, r < G);
+    uint16_t *const dst_row = out + (size_t(n) * p.num_q_heads + kvh * G) * HD;
+    if (tiles == 0) {
+        for (int i = tid; i < G * (HD / 8); i += 64 * kWholeWaves) reinterpret_cast<uint4 *>(dst_row)[i] = uint4{0u, 0u, 0u, 0u};
+        return;
+    }
+    if constexpr (!UNIFORM) s_tiles[wave][lane] = entry;
+
+    typename TS::State st;
+    st.reset();
+    const int count = tiles > wave ? (tiles - wave + kWholeWaves - 1) / kWholeWaves : 0;
+    if (count > 0) {
+        const int unit_tokens = 1 << unit_log2;
+        const int last_unit = ((ctx + unit_tokens - 1) >> unit_log2) - 1;
+        const size_t unit_elems = size_t(unit_tokens) * HD;
+        const int k_off = (r & (unit_tokens - 1)) * HD + 8 * quad, v_off = ((4 * quad) & (unit_tokens - 1)) * HD + HD / 16 * r;
+        int ki = 0;
+        auto issue = [&](typename TS::Tile &t) __attribute__((always_inline)) {
+            const int last = last_unit - ((wave + kWholeWaves * ki) << U_log2);  // units of the tile past it repeat it
+            const int first = ki << U_log2;
+            load_tile<HD, UNIFORM>(t, [&](int u) __attribute__((always_inline)) {
+                if constexpr (UNIFORM) return __builtin_amdgcn_readlane(entry, first + min(u, last));
+                else return s_tiles[wave][first + min(u, last)];
+            }, k_cache, v_cache, k_off, v_off, unit_elems, unit_log2, quad, r);
+            ++ki;
+        };
+        int left = ctx - wave * kTokens;
+        auto compute = [&](typename TS::Tile &t) __attribute__((always_inline)) {
+            consume_tile<HD>(st, t, qb, p.scale_log2e, left, quad);
+            left -= kWholeWaves * kTokens;
+        };
+        stream_tiles<typename TS::Tile>(count, issue, compute);
+        st.finish();
+    }
+    if (r < G) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            *reinterpret_cast<float4 *>(s_acc + wave * G * HD + slot_vec<HD>(0, G, v, quad, r) / 4) = acc_vec(st, v);
+        if (quad == 0) s_ml[wave][r] = float2{st.m, st.l};
+    }
+    __syncthreads();
+    const int nv4 = G * HD / 4;
+    for (int f = tid; f < nv4; f += 64 * kWholeWaves) {
+        const int head = f % G, vq = f / G;  // as in the kernel above
+        float M = -INFINITY, L = 0.f;
+        float4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWholeWaves; ++w) M = fmaxf(M, s_ml[w][head].x);
+#pragma unroll
+        for (int w = 0; w < kWholeWaves; ++w) {
+            if (w >= tiles) break;
+            const float2 ml = s_ml[w][head];
+            const float wgt = __builtin_amdgcn_exp2f(ml.x - M);
+            const float4 x = *reinterpret_cast<const float4 *>(s_acc + w * G * HD + 4 * f);
+            L = fmaf(wgt, ml.y, L);
+            a.x = fmaf(wgt, x.x, a.x);
+            a.y = fmaf(wgt, x.y, a.y);
+            a.z = fmaf(wgt, x.z, a.z);
+            a.w = fmaf(wgt, x.w, a.w);
+        }
+        const float inv = 1.0f / L;
+        *reinterpret_cast<uint2 *>(dst_row + head * HD + HD / 4 * (vq & 3) + 4 * (vq >> 2)) =
+            uint2{pack_bf16(a.x * inv, a.y * inv), pack_bf16(a.z * inv, a.w * inv)};
+    }
+}
+
 }  // namespace
 
 hipError_t launch_rows_mfma(const void *q, const void *k_cache, const void *v_cache,
@@ -389,6 +527,28 @@ hipError_t launch_rows_mfma(const void *q, const void *k_cache, const void *v_ca
     else if (mode == kBuild) KVC_LAUNCH_ROWS(128, kBuild);
     else KVC_LAUNCH_ROWS(128, kScheduled);
 #undef KVC_LAUNCH_ROWS
+    return hipGetLastError();
+}
+
+hipError_t launch_whole_mfma(const void *q, const void *k_cache, const void *v_cache,
+                             const int32_t *block_tables, const int32_t *context_lens,
+                             void *out, Workspace, const AttnParams &p, int head_dim, int,
+                             int mode, Schedule sched, hipStream_t stream) {
+    const int tile_log2 = head_dim == 128 ? Shape<128>::kTokensLog2 : Shape<64>::kTokensLog2;
+    const int unit_log2 = p.block_size_log2 < tile_log2 ? p.block_size_log2 : tile_log2;
+#define KVC_LAUNCH_WHOLE(HD, MODE, UNIFORM)                                                                                \
+    pa_whole_mfma_kernel<HD, MODE, UNIFORM><<<dim3(p.num_kv_heads, p.num_seqs), dim3(64 * kWholeWaves), 0, stream>>>( \
+        static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache), \
+        block_tables, context_lens, static_cast<uint16_t *>(out), p, unit_log2, p.block_size_log2 - unit_log2, sched)
+    const bool uniform_units = p.block_size >= 16;
+    if (mode == kBuild) KVC_LAUNCH_WHOLE(128, kBuild, false);
+    else if (head_dim == 64 && uniform_units) KVC_LAUNCH_WHOLE(64, kDirect, true);  // stateless calls only
+    else if (head_dim == 64) KVC_LAUNCH_WHOLE(64, kDirect, false);
+    else if (mode == kDirect && uniform_units) KVC_LAUNCH_WHOLE(128, kDirect, true);
+    else if (mode == kDirect) KVC_LAUNCH_WHOLE(128, kDirect, false);
+    else if (uniform_units) KVC_LAUNCH_WHOLE(128, kScheduled, true);
+    else KVC_LAUNCH_WHOLE(128, kScheduled, false);
+#undef KVC_LAUNCH_WHOLE
     return hipGetLastError();
 }
 

@@ -20,7 +20,7 @@ def check(w, oracle_mod, label, max_context_len=0):
     import paper_2503_13773_amd as K
     print(f"[case] decode d64 {label} nseq={w.num_seqs} max={w.max_context_len}", flush=True)
     rows = w.num_seqs * w.num_kv_heads
-    bound_tokens = max_context_len or max(w.max_context_len, -(-(1 << 17) // rows), (1 << 31) // rows ** 3 + 1)
+    bound_tokens = max_context_len or max(w.max_context_len, 1025, -(-(1 << 17) // rows), (1 << 31) // rows ** 3 + 1)
     w.block_tables = np.pad(w.block_tables, ((0, 0), (0, max(0, -(-bound_tokens // w.block_size) - w.max_blocks_per_seq))),
                             constant_values=-1)
     d = to_device(w)
@@ -69,7 +69,7 @@ def test_long_ranges_per_wavefront(oracle_mod):
           max_context_len=320000)
 
 
-@pytest.mark.parametrize("bound_tokens", [700, 1 << 24])   # few rows / ranges of flat tiles
+@pytest.mark.parametrize("bound_tokens", [700, 1 << 24])   # pieces / ranges of flat tiles
 def test_non_finite_values(oracle_mod, bound_tokens):
     """Inf / NaN in V reach their dim of their sequence with the sign they have, scores of -inf weigh nothing."""
     w = custom(860, dtype=W.BF16, lens=[700, 300, 400], hq=4, hkv=2, d=64, bs=16, lmax=1 << 20)

@@ -16,7 +16,9 @@ def check(w, oracle_mod, label, max_context_len=0):
     import paper_2503_13773_amd as K
     print(f"[case] rows {label} D={w.head_dim} nseq={w.num_seqs} max={w.max_context_len}", flush=True)
     rows = w.num_seqs * w.num_kv_heads
-    tokens = max_context_len or max(1, w.max_context_len)
+    # above the bound of the whole-row layout; the table has room for it
+    tokens = max(max_context_len, w.max_context_len, 641 if w.head_dim == 64 else 513)
+    w.block_tables = np.pad(w.block_tables, ((0, 0), (0, max(0, -(-tokens // w.block_size) - w.max_blocks_per_seq))), constant_values=-1)
     assert rows <= 128 and w.num_seqs <= 64 and rows ** 3 * tokens <= 1 << 31   # the line of the dispatch
     d = to_device(w)
     desc = K.attn_desc(d["q"], d["k"], d["tables"], max_context_len=tokens)
@@ -61,6 +63,9 @@ def test_schedules(oracle_mod):
     for lens, hq, hkv, bs in [([3217], 32, 8, 16), ([0, 300, 0, 320, 321, 17], 8, 2, 8), ([20000, 37, 9000], 2, 1, 16),
                               ([0, 0], 4, 2, 16), ([500] * 16, 32, 8, 32), ([100, 250], 16, 1, 4)]:
         w = custom(950 + len(lens) + bs, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=128, bs=bs)
+        if max(lens) <= 512:
+            w.context_lens[-1] = 513      # out of the whole-row layout
+            w = custom(950 + len(lens) + bs, dtype=W.BF16, lens=w.context_lens, hq=hq, hkv=hkv, d=128, bs=bs)
         _scheduled_equals_direct(w, oracle_mod, f"rows {lens[:4]} bs={bs}")
 
 
