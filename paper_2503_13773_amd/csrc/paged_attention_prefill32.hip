@@ -54,6 +54,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "kvc_internal.h"
 #include "pa_mfma_tile.h"
 
@@ -379,7 +381,7 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
-    uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at) {
+    uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at, bool ranked) {
     static_assert(!SPLIT || GROUPS == 2, "the context is split between two groups");
     constexpr int kParts = SPLIT ? 2 : 1;
     constexpr int kShared = GROUPS / kParts;        // groups that share a ring of stages
@@ -391,20 +393,47 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order); the longest query tiles come
     // first, and from `fold_at` on the shortest: when every workgroup is resident at once, the two
-    // that share a compute unit are then a long and a short one
+    // that share a compute unit are then a long and a short one.  `ranked`: the same order over the tiles of
+    // all sequences by their steps, which only the device knows.
     const int chunks = p.num_q_heads / HEADS;
-    const int item = blockIdx.x;
-    const int chunk = item % chunks;
-    const int n = (item / chunks) % p.num_seqs;
-    const int order = item / (chunks * p.num_seqs);
-    const int qtile = order < fold_at ? query_tiles - 1 - order : order - fold_at;
+    const int chunk = blockIdx.x % chunks, index = blockIdx.x / chunks;
     const int head0 = chunk * HEADS;
     const int kvh = head0 / p.group;
 
-    const int S = context_lens[n];
-    const int qs = q_start[n];
-    const int Qn = q_start[n + 1] - qs;
-    if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
+    int n, qtile, S, qs, Qn;
+    if (ranked) {
+        // several sequences: every (sequence, query tile) sits in a lane and is ranked by the steps it walks
+        const int l = threadIdx.x & 63, items = p.num_seqs * query_tiles;
+        int S_l = 0, qs_l = 0, Qn_l = 0, steps = 0;
+        if (l < items) {
+            const int n_l = l % p.num_seqs, t_l = l / p.num_seqs;
+            S_l = context_lens[n_l];
+            qs_l = q_start[n_l];
+            Qn_l = q_start[n_l + 1] - qs_l;
+            if (t_l * kTileRows < Qn_l && Qn_l <= S_l) steps = (S_l - Qn_l + min(Qn_l, (t_l + 1) * kTileRows) - 1) / kStepTokens + 1;
+        }
+        int rank = 0;
+        for (int j = 0; j < items; ++j) {
+            const int o = __builtin_amdgcn_readlane(steps, j);
+            rank += o > steps || (o == steps && j < l);
+        }
+        const uint64_t mine = __ballot(steps > 0 && rank == (index < fold_at ? index : items - 1 - (index - fold_at)));
+        if (mine == 0) return;  // uniform over the workgroup
+        const int it = __builtin_ctzll(mine);
+        n = it % p.num_seqs;
+        qtile = it / p.num_seqs;
+        S = __builtin_amdgcn_readlane(S_l, it);
+        qs = __builtin_amdgcn_readlane(qs_l, it);
+        Qn = __builtin_amdgcn_readlane(Qn_l, it);
+    } else {
+        n = index % p.num_seqs;
+        const int order = index / p.num_seqs;
+        qtile = order < fold_at ? query_tiles - 1 - order : order - fold_at;
+        S = context_lens[n];
+        qs = q_start[n];
+        Qn = q_start[n + 1] - qs;
+        if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
+    }
 
     const int tid = threadIdx.x;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -740,11 +769,23 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
                        int64_t(p.max_blocks_per_seq) * p.block_size > (kMinSplitSteps - 1) * kStepTokens;
     // A grid that fits the device at once (two workgroups of four wavefronts per compute unit)
     // gets the second half of its query tiles in rising order (a few percent on one short request).
-    const int fold_at = (!wide && grid <= 2 * 256) ? (query_tiles + 1) / 2 : query_tiles;
+    // Chunks of several sequences: what a tile walks depends on its sequence's context, which only the device knows.
+    // Up to 64 tiles are ranked there; grids that fit at once then put the shortest ranks beside the longest.  Four
+    // chunks of 512 rows, contexts of 2000 to 4000, 32 / 8 heads: 106 -> 94 us; six of 600 rows, 8000: 371 -> 344 us;
+    // three of 400, 7000: 151 -> 139 us; some placements lose 2 to 3 % (five of 200, 6000: 99 / 102 us, 122 / 105 us
+    // with other lengths).  Ranking costs a workgroup up to 1 us, so recomputations, whose tiles are in order
+    // anyway (three of 1000 tokens 36 -> 40 us), and launches that fill no compute unit twice do without: chunks are
+    // told by a block table that reaches four times as far as the longest one.
+    const int64_t items = int64_t(p.num_seqs) * query_tiles;
+    const int chunks = p.num_q_heads / heads;
+    const bool ranked = p.num_seqs > 1 && items <= 64 && grid > kNumCUs &&
+                        int64_t(p.max_blocks_per_seq) * p.block_size >= 4 * 64 * int64_t(p.max_query_tiles);
+    int fold_at = (!wide && grid <= 2 * kNumCUs) ? (query_tiles + 1) / 2 : query_tiles;
+    if (ranked) fold_at = grid <= 2 * kNumCUs ? std::max(1, std::min(int(items), kNumCUs / chunks)) : int(items);
     const dim3 g{unsigned(grid)}, b(wide || split ? 512 : 256);
 #define KVC_LAUNCH(SMALL, GROUPS, HEADS, SPLIT)                                                                        \
     pa_prefill_mfma32_kernel<SMALL, GROUPS, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
-                                                                                q_start, oo, p, query_tiles, fold_at)
+                                                                                q_start, oo, p, query_tiles, fold_at, ranked)
 #define KVC_LAUNCH_SHAPE(SMALL, HEADS)                       \
     do {                                                     \
         if (wide) KVC_LAUNCH(SMALL, 2, HEADS, false);        \

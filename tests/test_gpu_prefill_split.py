@@ -42,3 +42,14 @@ def test_scores_that_keep_growing_reach_both_parts(oracle_mod):
     for t in range(1500):
         w.k_cache[w.block_tables[0, t // 16], :, t % 16, 1] = W.f32_to_bf16_bits(ramp[t:t + 1] * 8)[0]
     check(oracle_mod, w, q, qs, "ramp")
+
+
+@pytest.mark.parametrize("nseq,rows,longest", [(6, 130, 2500), (8, 260, 1300)])   # at most / more than 512 workgroups
+def test_chunks_of_several_sequences_are_ranked(oracle_mod, nseq, rows, longest):
+    """Tiles are handed out by the steps they walk; sequences without rows, with few, and of equal lengths among them."""
+    lens = [longest, 300, longest, 700, 64, 1200, 555, 40][:nseq]
+    qlens = [rows, 33, rows, 1, 0, 100, rows, 40][:nseq]
+    w, q, qs = make(1180 + nseq, lens, qlens, 32, 8)
+    items = nseq * -(-rows // 64)
+    assert items <= 64 and items * 16 > 256 and w.max_blocks_per_seq * 16 >= 4 * 64 * -(-rows // 64)
+    check(oracle_mod, w, q, qs, f"ranked {nseq}")
