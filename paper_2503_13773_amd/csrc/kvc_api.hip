@@ -99,11 +99,34 @@ bool balanced_ok(const kvc_attn_desc &d, int max_ctx) {
 //   8 x 3217 15.0 / 11.9, 8 x 32000 68 / 28.6, 32 x 32000 76.7 / 68.1, 64 x 8192 38.6 / 37.1, 64 x 16000 63.6 / 64.5,
 //   64 x 32000 116 / 121, 128 x 400 11.5 / 10.6, 128 x 3000 25.2 / 25.7, 128 x 8192 60.6 / 69.4;
 //   head_dim 64: 8 x 32000 40.2 / 19.1, 64 x 8192 25.0 / 23.1, 128 x 400 11.3 / 7.0, 128 x 1500 12.6 / 13.1.
+constexpr int kFewRowSeqs = 64;
 constexpr int kFewRowsMinTiles = 8;  // smallest piece of a cut row: a tile for each wavefront
 bool few_rows_ok(const kvc_attn_desc &d, int max_ctx) {
     const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
-    return d.partition_tokens == 0 && d.num_seqs >= 1 && d.num_seqs <= 64 && rows <= kvc::kMaxFewRows &&
+    return d.partition_tokens == 0 && d.num_seqs >= 1 && d.num_seqs <= kFewRowSeqs && rows <= kvc::kMaxFewRows &&
            rows * rows * rows * max_ctx <= (int64_t(1) << 31);
+}
+
+// Workspace of the balanced kernel's ranges and pieces: the header and two partial slots per wavefront.
+struct BalancedWorkspace {
+    uint64_t ml_offset, bytes;
+    explicit BalancedWorkspace(const kvc_attn_desc &d) {
+        const uint64_t slots = uint64_t(kvc::kNumCUs) * kvc::kWaves * 2, group = d.num_q_heads / d.num_kv_heads;
+        ml_offset = (kvc::kWorkspaceHeaderBytes + slots * group * d.head_dim * sizeof(float) + 255) & ~uint64_t(255);
+        bytes = ml_offset + slots * group * 2 * sizeof(float);
+    }
+};
+
+bool balanced64_form(const kvc_attn_desc &d) {
+    return d.kernel == KVC_KERNEL_AUTO && d.dtype == KVC_BF16 && d.head_dim == 64 && d.block_size >= 4 &&
+           d.partition_tokens == 0 && d.num_q_heads / d.num_kv_heads <= 16;
+}
+
+// A workspace sized for a batch has to do for a smaller one or a lower bound, as it does in every other kernel.  Up to
+// 640 tokens a smaller batch at head_dim 64 is whole rows, which need none; above, it may be pieces.
+constexpr int kWhole64Tokens = 640, kWhole128Tokens = 512;
+bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
+    return balanced64_form(d) && d.num_seqs > 0 && max_ctx > kWhole64Tokens;
 }
 
 // Short contexts: a workgroup per row, two memory round trips to the first K and V bytes and no exchange.  In us, the
@@ -117,16 +140,15 @@ bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
     const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
     if (d.partition_tokens != 0 || d.num_seqs < 1 || d.num_seqs > kvc::kMaxStreamSeqs) return false;
     const bool many_short = rows > 1000 && max_ctx <= 200;
-    if (d.head_dim == 128) return max_ctx <= 512 && !many_short;
-    return max_ctx <= (rows > kvc::kMaxFewRows ? 1024 : 640) && !(many_short && d.num_q_heads == d.num_kv_heads);
+    if (d.head_dim == 128) return max_ctx <= kWhole128Tokens && !many_short;
+    return max_ctx <= (rows > kvc::kMaxFewRows ? 1024 : kWhole64Tokens) && !(many_short && d.num_q_heads == d.num_kv_heads);
 }
 
 // At head_dim 64 the balanced kernel serves calls that KVC_KERNEL_AUTO brings without a split of the caller's
 // own: whole rows, few rows, and ranges from 2^17 tokens x KV heads on (below that the vector ALUs are as good:
 // 102 k 9.7 / 11.9 us, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
 bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
-    return d.kernel == KVC_KERNEL_AUTO && d.dtype == KVC_BF16 && d.head_dim == 64 && d.block_size >= 4 &&
-           d.partition_tokens == 0 && d.num_q_heads / d.num_kv_heads <= 16 && d.num_seqs <= kvc::kMaxStreamSeqs &&
+    return balanced64_form(d) && d.num_seqs <= kvc::kMaxStreamSeqs &&
            (whole_ok(d, max_ctx) || few_rows_ok(d, max_ctx) ||
             (max_ctx > 256 && int64_t(d.num_seqs) * d.num_kv_heads * max_ctx >= (1 << 17))) &&
            int64_t(d.num_seqs) * d.num_kv_heads * (ceil_div(max_ctx, 32) + 1) < (int64_t(1) << 30) &&
@@ -175,8 +197,6 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
                               : pl->layout == kPieces ? kFewRowsMinTiles
                               : d->partition_tokens ? d->partition_tokens / tile_tokens
                                                     : int(std::max<int64_t>(4, ceil_div(max_tiles, 32)));
-        const int group = d->num_q_heads / d->num_kv_heads;
-        const uint64_t slots = uint64_t(kvc::kNumCUs) * kvc::kWaves * 2;
         pl->kernel = kernel;
         pl->head_chunk = 0;
         pl->partition_tokens = min_chunk * tile_tokens;
@@ -186,12 +206,12 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         pl->partial_grid = pl->layout == kWhole ? int64_t(d->num_seqs) * d->num_kv_heads : kvc::kNumCUs;
         pl->merge_grid = 0;
         pl->max_context_len = max_ctx;
-        const uint64_t acc = slots * group * d->head_dim * sizeof(float);
+        const BalancedWorkspace need(*d);
         pl->acc_offset = kHeader;
-        pl->ml_offset = (kHeader + acc + 255) & ~uint64_t(255);
-        pl->workspace_bytes = pl->ml_offset + slots * group * 2 * sizeof(float);
+        pl->ml_offset = need.ml_offset;
+        pl->workspace_bytes = need.bytes;
         // whole rows need no workspace; head_dim 128 keeps asking for one (its size never depended on the lengths)
-        if (d->head_dim == 64 && pl->layout == kWhole) pl->workspace_bytes = 0;
+        if (d->head_dim == 64 && pl->layout == kWhole && !smaller_calls_need_balanced(*d, max_ctx)) pl->workspace_bytes = 0;
         return KVC_OK;
     }
 
@@ -233,6 +253,8 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         const uint64_t acc = uint64_t(rows) * parts * d->head_dim * sizeof(float);
         pl->ml_offset = (kHeader + acc + 255) & ~uint64_t(255);
         pl->workspace_bytes = pl->ml_offset + uint64_t(rows) * parts * 2 * sizeof(float);
+        if (kernel == KVC_KERNEL_VALU && smaller_calls_need_balanced(*d, max_ctx))
+            pl->workspace_bytes = std::max(pl->workspace_bytes, BalancedWorkspace(*d).bytes);
     } else {
         pl->ml_offset = 0;
         pl->workspace_bytes = 0;
@@ -308,19 +330,21 @@ struct ScheduleLayout {
 
 bool schedule_layout(const kvc_attn_desc &d, const Plan &pl, ScheduleLayout *L) {
     if (pl.kernel != KVC_KERNEL_MFMA_BALANCED || d.head_dim != 128) return false;
-    // wavefronts, or workgroups
-    const int64_t workers = pl.layout == kRanges ? int64_t(kvc::kNumCUs) * kvc::kWaves : pl.partial_grid;
     const int64_t units_per_tile = d.block_size >= 16 ? 1 : 16 / d.block_size;
     const int64_t max_tiles = ceil_div(pl.max_context_len, 16);
-    // no worker takes more flat units than this, whatever the context lengths turn out to be
-    const int64_t max_units = int64_t(d.num_seqs) * d.num_kv_heads * (max_tiles + 1);
-    int64_t chunk = std::max<int64_t>(pl.min_chunk_tiles, ceil_div(max_units, workers));
-    if (pl.layout == kWhole) chunk = max_tiles;
-    if (pl.layout == kPieces)  // nor a workgroup more tiles than this
-        chunk = std::max({int64_t(pl.min_chunk_tiles), std::min<int64_t>(max_tiles, kvc::kRowWholeTiles),
-                          ceil_div(max_tiles, kvc::kMaxRowPieces),
-                          ceil_div(d.num_seqs * max_tiles, kvc::kNumCUs / d.num_kv_heads - d.num_seqs)});
-    const int64_t stride = chunk * units_per_tile;
+    const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
+    // Ranges: no wavefront takes more flat units than this, whatever the context lengths turn out to be.
+    const int64_t range_workers = int64_t(kvc::kNumCUs) * kvc::kWaves;
+    const int64_t min_chunk = d.partition_tokens ? d.partition_tokens / 16 : std::max<int64_t>(4, ceil_div(max_tiles, 32));
+    const int64_t range_chunk = std::max<int64_t>(min_chunk, ceil_div(rows * (max_tiles + 1), range_workers));
+    // Pieces: nor a workgroup more tiles than this with n sequences.
+    auto piece_chunk = [&](int64_t n) {
+        return std::max({int64_t(kFewRowsMinTiles), std::min<int64_t>(max_tiles, kvc::kRowWholeTiles),
+                         ceil_div(max_tiles, kvc::kMaxRowPieces),
+                         ceil_div(n * max_tiles, kvc::kNumCUs / d.num_kv_heads - n)});
+    };
+    const int64_t workers = pl.layout == kRanges ? range_workers : pl.partial_grid;  // wavefronts, or workgroups
+    const int64_t stride = units_per_tile * (pl.layout == kWhole ? max_tiles : pl.layout == kPieces ? piece_chunk(d.num_seqs) : range_chunk);
     if (stride > (int64_t(1) << 28)) return false;
     auto up = [](uint64_t x) { return (x + 255) & ~uint64_t(255); };
     L->stride = int(stride);
@@ -328,7 +352,18 @@ bool schedule_layout(const kvc_attn_desc &d, const Plan &pl, ScheduleLayout *L) 
     L->ctx_off = up(uint64_t(d.num_seqs + 2) * 4);
     L->plans_off = L->ctx_off + up(uint64_t(d.num_seqs) * 4);
     L->tiles_off = L->plans_off + up(uint64_t(workers) * 16 * 4);
-    L->bytes = L->tiles_off + up(uint64_t(workers) * uint64_t(stride) * 4);
+    // A buffer sized for a batch has to do for a smaller one or a lower bound, also where those have another
+    // layout: room for the largest of the layouts that they can have.
+    auto body = [&](int64_t n, int64_t chunk) {
+        return up(uint64_t(n) * 16 * 4) + up(uint64_t(n) * uint64_t(chunk * units_per_tile) * 4);
+    };
+    uint64_t most = body(range_workers, range_chunk);
+    if (d.partition_tokens == 0) {
+        most = std::max(most, body(rows, std::min<int64_t>(max_tiles, kWhole128Tokens / 16)));
+        const int64_t few = std::min<int64_t>({d.num_seqs, kFewRowSeqs, kvc::kMaxFewRows / d.num_kv_heads});
+        if (few > 0) most = std::max(most, body(kvc::kNumCUs, piece_chunk(few)));
+    }
+    L->bytes = L->plans_off + most;
     return true;
 }
 

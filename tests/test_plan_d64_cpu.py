@@ -27,11 +27,29 @@ def test_the_others_stay_on_the_vector_alus(K, kw):  # noqa: F811
 
 def test_whole_rows_need_no_workspace_and_pieces_do(K):  # noqa: F811
     for kw, need in [(dict(num_seqs=4, max_context_len=4000), True), (dict(num_seqs=16, max_context_len=641), True),
-                     (dict(num_seqs=16, max_context_len=640), False), (dict(num_seqs=17, max_context_len=1024), False),
+                     (dict(num_seqs=16, max_context_len=640), False), (dict(num_seqs=17, max_context_len=640), False),
                      (dict(num_seqs=17, max_context_len=1025), True), (dict(num_seqs=1, max_context_len=7), False)]:
         rc, p = plan_status(K, desc(K, head_dim=64, **kw))
         assert rc == 0 and p.kernel == K.KERNEL_MFMA_BALANCED and (p.workspace_bytes > 0) == need
         assert p.partial_grid == (256 if need else kw["num_seqs"] * 8)
+    rc, p = plan_status(K, desc(K, head_dim=64, num_seqs=17, max_context_len=1024))
+    assert rc == 0 and p.partial_grid == 17 * 8 and p.workspace_bytes > 0  # whole rows; 16 of them would be pieces
+
+
+@pytest.mark.parametrize("heads", [(32, 8), (16, 16), (14, 2), (12, 12), (1, 1), (2, 1), (64, 4), (256, 128)])
+@pytest.mark.parametrize("block_size", [4, 8, 16, 32])
+def test_buffers_do_for_smaller_batches_and_lower_bounds(K, heads, block_size):  # noqa: F811
+    """Workspaces and schedules: at every (batch, bound) the size is at least that of the next smaller batch and
+    of the next lower bound, whichever layouts these have."""
+    seqs = [0, 1, 2, 3, 8, 10, 11, 16, 17, 32, 33, 63, 64, 65, 66, 96, 125, 126, 127, 128, 129, 500, 1001, 4096]
+    bounds = [1, 16, 200, 201, 256, 257, 500, 512, 513, 560, 640, 641, 1000, 1024, 1025, 1100, 2000, 2049, 4096, 8192]
+    for size, dim in ((K.workspace_bytes, 64), (K.workspace_bytes, 128), (K.schedule_bytes, 128)):
+        table = [[size(desc(K, head_dim=dim, num_q_heads=heads[0], num_kv_heads=heads[1], num_seqs=n, block_size=block_size,
+                            max_blocks_per_seq=8192 // block_size, max_context_len=b)) for b in bounds] for n in seqs]
+        for i, n in enumerate(seqs):
+            for j, b in enumerate(bounds):
+                assert i < 2 or table[i][j] >= table[i - 1][j], (size.__name__, dim, n, b)
+                assert not j or table[i][j] >= table[i][j - 1], (size.__name__, dim, n, b)
 
 
 def test_layouts_of_head_dim_128(K):  # noqa: F811
