@@ -77,15 +77,16 @@ def build_policy_library(verbose: bool = False, out: str = "", extra_flags=()) -
 CALL_LIB = os.path.join(PKG, "kvc_call.so")
 
 
-def build_call_module(verbose: bool = False) -> str:
+def build_call_module(verbose: bool = False, source: str = "", out: str = "") -> str:
     """The native call path of binding.py (a CPython extension over torch's tensor type; no GPU code)."""
     import sysconfig
 
     from torch.utils import cpp_extension
+    source, target = source or os.path.join(CSRC, "kvc_call.cpp"), out or CALL_LIB
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-I", os.path.join(ROOT, "include")]
     for d in cpp_extension.include_paths():
         cmd += ["-isystem", d]
-    cmd += ["-isystem", sysconfig.get_path("include"), os.path.join(CSRC, "kvc_call.cpp"), "-o", CALL_LIB]
+    cmd += ["-isystem", sysconfig.get_path("include"), source, "-o", target]
     for d in cpp_extension.library_paths():
         cmd += ["-L", d]
     cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
@@ -93,8 +94,8 @@ def build_call_module(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed on kvc_call.cpp:\n{r.stdout}\n{r.stderr}")
     if verbose:
-        print("built", CALL_LIB)
-    return CALL_LIB
+        print("built", target)
+    return target
 
 
 if __name__ == "__main__":

@@ -3,9 +3,10 @@
 //
 // Every function takes the arguments of its counterpart in binding.py, with the stream as an integer handle, and
 // returns the status of the library call, or None when an argument is not what the common case looks like (not
-// exactly a torch.Tensor, another device, dtype or shape, not contiguous, nothing to write to): nothing has
-// been called then, and binding.py takes its general path, which says what is wrong.  The library's functions
-// are bound by address, so that the module works with whatever build of the library binding.py has loaded.
+// exactly a torch.Tensor, a nested one, another device, dtype or shape, not contiguous, nothing to write to) or
+// torch throws while it is looked at: nothing has been called then, and binding.py takes its general path, which
+// says what is wrong.  The library's functions are bound by address, so that the module works with whatever build
+// of the library binding.py has loaded.
 //
 // A decode call costs the host 10.8 us through ctypes and attribute look-ups, most of it Python; a call on a few
 // short sequences is over sooner than that on the device.
@@ -37,7 +38,8 @@ struct Args {
         PyObject *o = next();
         if (!ok || !THPVariable_CheckExact(o)) return ok = false, nullptr;
         const at::Tensor &t = THPVariable_Unpack(o);
-        if (!t.defined() || t.layout() != at::kStrided || !t.has_storage()) return ok = false, nullptr;
+        // a nested tensor calls itself strided and contiguous but has no sizes
+        if (!t.defined() || t.is_nested() || t.layout() != at::kStrided || !t.has_storage()) return ok = false, nullptr;
         return &t;
     }
     const at::Tensor *device_tensor() {
@@ -89,7 +91,7 @@ bool is_int32(const at::Tensor &t) { return t.scalar_type() == at::kInt; }
 size_t bytes_of(const at::Tensor &t) { return size_t(t.numel()) * t.element_size(); }
 bool fits(int64_t x) { return x == int32_t(x); }
 
-// Runs the library call (which does not throw) without the interpreter lock.
+// Runs the library call (which does not throw; nothing else may be in it) without the interpreter lock.
 template <class Call>
 PyObject *run(Call call) {
     PyThreadState *s = PyEval_SaveThread();
@@ -112,7 +114,7 @@ struct Data {
 };
 
 // q, k_cache, v_cache, block_tables, context_lens, scale, out, desc, workspace | None, stream
-PyObject *decode(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *decode(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
     const at::Tensor *q = a.device_tensor(), *k = a.device_tensor(), *v = a.device_tensor();
     const at::Tensor *bt = a.device_tensor(), *cl = a.device_tensor();
@@ -139,7 +141,7 @@ PyObject *decode(PyObject *, PyObject *const *args, Py_ssize_t n) {
 }
 
 // q, k_cache, v_cache, schedule, scale, out, desc, workspace, stream
-PyObject *scheduled(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *scheduled(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
     const at::Tensor *q = a.any_tensor(), *k = a.any_tensor(), *v = a.any_tensor(), *sched = a.any_tensor();
     const double scale = a.number();
@@ -151,13 +153,12 @@ PyObject *scheduled(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (!a.done()) Py_RETURN_NONE;
     const Data dq(q), dk(k), dv(v), ds(sched), dout(out), dw(ws);
     if (!(dq.ok && dk.ok && dv.ok && ds.ok && dout.ok && dw.ok)) Py_RETURN_NONE;
-    return run([&] {
-        return g_scheduled(dq.p, dk.p, dv.p, ds.p, size_t(sched->numel()), float(scale), dout.p, &d, dw.p, bytes_of(*ws), stream);
-    });
+    const size_t sched_bytes = size_t(sched->numel()), ws_bytes = bytes_of(*ws);
+    return run([&] { return g_scheduled(dq.p, dk.p, dv.p, ds.p, sched_bytes, float(scale), dout.p, &d, dw.p, ws_bytes, stream); });
 }
 
 // block_tables, context_lens, desc, schedule, stream
-PyObject *schedule_build(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *schedule_build(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
     const at::Tensor *bt = a.any_tensor(), *cl = a.any_tensor();
     kvc_attn_desc d;
@@ -167,13 +168,14 @@ PyObject *schedule_build(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (!a.done()) Py_RETURN_NONE;
     const Data db(bt), dc(cl), ds(sched);
     if (!(db.ok && dc.ok && ds.ok)) Py_RETURN_NONE;
+    const size_t sched_bytes = size_t(sched->numel());
     return run([&] {
-        return g_build(static_cast<const int32_t *>(db.p), static_cast<const int32_t *>(dc.p), &d, ds.p, size_t(sched->numel()), stream);
+        return g_build(static_cast<const int32_t *>(db.p), static_cast<const int32_t *>(dc.p), &d, ds.p, sched_bytes, stream);
     });
 }
 
 // q, k_cache, v_cache, block_tables, context_lens, q_start, scale, max_query_len, out, kernel, stream
-PyObject *prefill(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *prefill(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
     const at::Tensor *q = a.device_tensor(), *k = a.device_tensor(), *v = a.device_tensor();
     const at::Tensor *bt = a.device_tensor(), *cl = a.device_tensor(), *qs = a.device_tensor();
@@ -194,14 +196,15 @@ PyObject *prefill(PyObject *, PyObject *const *args, Py_ssize_t n) {
                              int32_t(bt->size(1)), int32_t(k->size(0)), dtype_code(*q), 0, 0, kernel, 0};
     const Data dq(q), dk(k), dv(v), db(bt), dc(cl), ds(qs), dout(out);
     if (!(dq.ok && dk.ok && dv.ok && db.ok && dc.ok && ds.ok && dout.ok)) Py_RETURN_NONE;
+    const int32_t total_q = int32_t(q->size(0));
     return run([&] {
         return g_prefill(dq.p, dk.p, dv.p, static_cast<const int32_t *>(db.p), static_cast<const int32_t *>(dc.p),
-                         static_cast<const int32_t *>(ds.p), float(scale), dout.p, &d, int32_t(q->size(0)), max_query_len, stream);
+                         static_cast<const int32_t *>(ds.p), float(scale), dout.p, &d, total_q, max_query_len, stream);
     });
 }
 
 // k_new, v_new, k_cache, v_cache, block_tables, positions, stream
-PyObject *append(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *append(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
     const at::Tensor *kn = a.device_tensor(), *vn = a.device_tensor(), *k = a.device_tensor(), *v = a.device_tensor();
     const at::Tensor *bt = a.device_tensor(), *pos = a.device_tensor();
@@ -233,7 +236,7 @@ bool pool_of(const at::Tensor &t, kvc_pool *p) {
 }
 
 // src, dst ([planes][blocks][...] on the device), block_mapping, stream
-PyObject *block_copy(PyObject *, PyObject *const *args, Py_ssize_t n) {
+PyObject *block_copy(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
     const at::Tensor *src = a.device_tensor(), *dst = a.device_tensor(), *map = a.device_tensor();
     void *stream = a.stream();
@@ -241,7 +244,8 @@ PyObject *block_copy(PyObject *, PyObject *const *args, Py_ssize_t n) {
     kvc_pool s, d;
     const Data dm(map);
     if (!pool_of(*src, &s) || !pool_of(*dst, &d) || !dm.ok) Py_RETURN_NONE;
-    return run([&] { return g_copy(&s, &d, static_cast<const int64_t *>(dm.p), map->numel() / 2, stream); });
+    const int64_t pairs = map->numel() / 2;
+    return run([&] { return g_copy(&s, &d, static_cast<const int64_t *>(dm.p), pairs, stream); });
 }
 
 // addresses of the library's functions, in the order of the assignments
@@ -268,9 +272,25 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-#define KVC_METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
-PyMethodDef g_methods[] = {KVC_METHOD(bind),    KVC_METHOD(decode), KVC_METHOD(scheduled),  KVC_METHOD(schedule_build),
-                           KVC_METHOD(prefill), KVC_METHOD(append), KVC_METHOD(block_copy), {nullptr, nullptr, 0, nullptr}};
+// The interpreter's frames are C: what torch throws (sizes() or data_ptr() of a tensor of an unusual kind) ends here.
+template <PyObject *(*Call)(PyObject *const *, Py_ssize_t)>
+PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
+    try {
+        return Call(args, n);
+    } catch (...) {
+        Py_RETURN_NONE;
+    }
+}
+
+#define KVC_METHOD(name, function) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(function)), METH_FASTCALL, nullptr}
+PyMethodDef g_methods[] = {KVC_METHOD("bind", bind),
+                           KVC_METHOD("decode", entry<decode>),
+                           KVC_METHOD("scheduled", entry<scheduled>),
+                           KVC_METHOD("schedule_build", entry<schedule_build>),
+                           KVC_METHOD("prefill", entry<prefill>),
+                           KVC_METHOD("append", entry<append>),
+                           KVC_METHOD("block_copy", entry<block_copy>),
+                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "kvc_call", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
