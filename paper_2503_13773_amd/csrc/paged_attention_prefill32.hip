@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
-    uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at, bool ranked) {
+    uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at, int fold_ranked, int rank_from) {
     static_assert(!SPLIT || GROUPS == 2, "the context is split between two groups");
     constexpr int kParts = SPLIT ? 2 : 1;
     constexpr int kShared = GROUPS / kParts;        // groups that share a ring of stages
@@ -393,47 +393,50 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order); the longest query tiles come
     // first, and from `fold_at` on the shortest: when every workgroup is resident at once, the two
-    // that share a compute unit are then a long and a short one.  `ranked`: the same order over the tiles of
-    // all sequences by their steps, which only the device knows.
+    // that share a compute unit are then a long and a short one.  With a context of `rank_from` tokens or more in
+    // the batch (0: never) the same order is taken over the tiles of all sequences by the steps they walk,
+    // which only the device knows.
     const int chunks = p.num_q_heads / HEADS;
     const int chunk = blockIdx.x % chunks, index = blockIdx.x / chunks;
     const int head0 = chunk * HEADS;
     const int kvh = head0 / p.group;
 
-    int n, qtile, S, qs, Qn;
-    if (ranked) {
-        // several sequences: every (sequence, query tile) sits in a lane and is ranked by the steps it walks
-        const int l = threadIdx.x & 63, items = p.num_seqs * query_tiles;
-        int S_l = 0, qs_l = 0, Qn_l = 0, steps = 0;
-        if (l < items) {
-            const int n_l = l % p.num_seqs, t_l = l / p.num_seqs;
-            S_l = context_lens[n_l];
-            qs_l = q_start[n_l];
-            Qn_l = q_start[n_l + 1] - qs_l;
-            if (t_l * kTileRows < Qn_l && Qn_l <= S_l) steps = (S_l - Qn_l + min(Qn_l, (t_l + 1) * kTileRows) - 1) / kStepTokens + 1;
+    int n = index % p.num_seqs;
+    const int order = index / p.num_seqs;
+    int qtile = order < fold_at ? query_tiles - 1 - order : order - fold_at;
+    int S = context_lens[n], qs = q_start[n], Qn = q_start[n + 1] - qs;
+    if (rank_from > 0) {
+        const int l = threadIdx.x & 63;
+        bool rank_all = false;  // what every workgroup asks in the same way
+        if (p.num_seqs <= 8) {  // scalar loads that travel with those above
+            for (int i = 0; i < p.num_seqs; i += 4)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) rank_all |= context_lens[min(i + u, p.num_seqs - 1)] >= rank_from;
+        } else {
+            rank_all = __ballot(context_lens[l % p.num_seqs] >= rank_from) != 0;
         }
-        int rank = 0;
-        for (int j = 0; j < items; ++j) {
-            const int o = __builtin_amdgcn_readlane(steps, j);
-            rank += o > steps || (o == steps && j < l);
+        if (rank_all) {  // every (sequence, query tile) sits in a lane
+            const int items = p.num_seqs * query_tiles, n_l = l % p.num_seqs, t_l = l / p.num_seqs;
+            const int S_l = context_lens[n_l], qs_l = q_start[n_l], Qn_l = q_start[n_l + 1] - qs_l;
+            int steps = 0;
+            if (l < items && t_l * kTileRows < Qn_l && Qn_l <= S_l)
+                steps = (S_l - Qn_l + min(Qn_l, (t_l + 1) * kTileRows) - 1) / kStepTokens + 1;
+            int rank = 0;
+            for (int j = 0; j < items; ++j) {
+                const int o = __builtin_amdgcn_readlane(steps, j);
+                rank += o > steps || (o == steps && j < l);
+            }
+            const uint64_t mine = __ballot(steps > 0 && rank == (index < fold_ranked ? index : items - 1 - (index - fold_ranked)));
+            if (mine == 0) return;  // uniform over the workgroup
+            const int it = __builtin_ctzll(mine);
+            n = it % p.num_seqs;
+            qtile = it / p.num_seqs;
+            S = __builtin_amdgcn_readlane(S_l, it);
+            qs = __builtin_amdgcn_readlane(qs_l, it);
+            Qn = __builtin_amdgcn_readlane(Qn_l, it);
         }
-        const uint64_t mine = __ballot(steps > 0 && rank == (index < fold_at ? index : items - 1 - (index - fold_at)));
-        if (mine == 0) return;  // uniform over the workgroup
-        const int it = __builtin_ctzll(mine);
-        n = it % p.num_seqs;
-        qtile = it / p.num_seqs;
-        S = __builtin_amdgcn_readlane(S_l, it);
-        qs = __builtin_amdgcn_readlane(qs_l, it);
-        Qn = __builtin_amdgcn_readlane(Qn_l, it);
-    } else {
-        n = index % p.num_seqs;
-        const int order = index / p.num_seqs;
-        qtile = order < fold_at ? query_tiles - 1 - order : order - fold_at;
-        S = context_lens[n];
-        qs = q_start[n];
-        Qn = q_start[n + 1] - qs;
-        if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
     }
+    if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
 
     const int tid = threadIdx.x;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -770,22 +773,24 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
     // A grid that fits the device at once (two workgroups of four wavefronts per compute unit)
     // gets the second half of its query tiles in rising order (a few percent on one short request).
     // Chunks of several sequences: what a tile walks depends on its sequence's context, which only the device knows.
-    // Up to 64 tiles are ranked there; grids that fit at once then put the shortest ranks beside the longest.  Four
-    // chunks of 512 rows, contexts of 2000 to 4000, 32 / 8 heads: 106 -> 94 us; six of 600 rows, 8000: 371 -> 344 us;
-    // three of 400, 7000: 151 -> 139 us; some placements lose 2 to 3 % (five of 200, 6000: 99 / 102 us, 122 / 105 us
-    // with other lengths).  Ranking costs a workgroup up to 1 us, so recomputations, whose tiles are in order
-    // anyway (three of 1000 tokens 36 -> 40 us), and launches that fill no compute unit twice do without: chunks are
-    // told by a block table that reaches four times as far as the longest one.
+    // Up to 64 tiles are ranked there; grids that fit at once then put the shortest ranks beside the longest.  32 / 8
+    // heads, 16-token blocks, in given order / ranked: four chunks of 512 rows, contexts of 2000 to 4000, 104 to 112 / 92 to
+    // 107 us; six of 600 rows, 8000: 393 to 411 / 365 to 391 us; three of 400, 7000: 138 to 154 / 124 to 147 us; five of 200,
+    // 6000: 111 to 127 / 102 to 109 us.  Recomputations, whose tiles are in order anyway, lose by it (three of 1000
+    // tokens 39.0 / 44.2 us, sixteen of 220 27.2 / 34.1 us), so the workgroups rank only if some context of the batch is
+    // four times as long as the longest chunk may be: under a 4096-token table these take 39.5 and 27.8 us.  A table
+    // that reaches less far says so before the launch, and launches that fill no compute unit twice do without.
     const int64_t items = int64_t(p.num_seqs) * query_tiles;
     const int chunks = p.num_q_heads / heads;
-    const bool ranked = p.num_seqs > 1 && items <= 64 && grid > kNumCUs &&
-                        int64_t(p.max_blocks_per_seq) * p.block_size >= 4 * 64 * int64_t(p.max_query_tiles);
-    int fold_at = (!wide && grid <= 2 * kNumCUs) ? (query_tiles + 1) / 2 : query_tiles;
-    if (ranked) fold_at = grid <= 2 * kNumCUs ? std::max(1, std::min(int(items), kNumCUs / chunks)) : int(items);
+    const int64_t chunk_reach = 4 * 64 * int64_t(p.max_query_tiles);
+    const int rank_from = p.num_seqs > 1 && items <= 64 && grid > kNumCUs &&
+                          int64_t(p.max_blocks_per_seq) * p.block_size >= chunk_reach ? int(chunk_reach) : 0;
+    const int fold_at = (!wide && grid <= 2 * kNumCUs) ? (query_tiles + 1) / 2 : query_tiles;
+    const int fold_ranked = grid <= 2 * kNumCUs ? std::max(1, std::min(int(items), kNumCUs / chunks)) : int(items);
     const dim3 g{unsigned(grid)}, b(wide || split ? 512 : 256);
 #define KVC_LAUNCH(SMALL, GROUPS, HEADS, SPLIT)                                                                        \
     pa_prefill_mfma32_kernel<SMALL, GROUPS, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
-                                                                                q_start, oo, p, query_tiles, fold_at, ranked)
+                                                                                q_start, oo, p, query_tiles, fold_at, fold_ranked, rank_from)
 #define KVC_LAUNCH_SHAPE(SMALL, HEADS)                       \
     do {                                                     \
         if (wide) KVC_LAUNCH(SMALL, 2, HEADS, false);        \
