@@ -112,7 +112,7 @@ def _calls():
         kvc_call.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
             "kvc_paged_attention_decode", "kvc_paged_attention_decode_workspace_bytes",
             "kvc_paged_attention_decode_scheduled", "kvc_attn_schedule_build", "kvc_paged_attention_prefill",
-            "kvc_kv_cache_append", "kvc_kv_block_copy")))
+            "kvc_kv_cache_append", "kvc_kv_block_copy")), AttnDesc)
         _native = kvc_call
     return _native
 

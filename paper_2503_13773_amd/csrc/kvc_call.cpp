@@ -25,6 +25,7 @@ decltype(&kvc_attn_schedule_build) g_build;
 decltype(&kvc_paged_attention_prefill) g_prefill;
 decltype(&kvc_kv_cache_append) g_append;
 decltype(&kvc_kv_block_copy) g_copy;
+PyTypeObject *g_desc_type;  // binding.AttnDesc, the ctypes structure of kvc_attn_desc
 
 // Arguments of one call; `ok` turns false at the first one that is not of the common kind.
 struct Args {
@@ -73,10 +74,10 @@ struct Args {
         if (PyErr_Occurred()) { PyErr_Clear(); ok = false; }
         return p;
     }
-    bool descriptor(kvc_attn_desc *d) {  // a ctypes structure of that layout
+    bool descriptor(kvc_attn_desc *d) {
         PyObject *o = next();
         Py_buffer b;
-        if (!ok || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); return ok = false; }
+        if (!ok || !PyObject_TypeCheck(o, g_desc_type) || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); return ok = false; }
         if (b.len == Py_ssize_t(sizeof *d)) memcpy(d, b.buf, sizeof *d); else ok = false;
         PyBuffer_Release(&b);
         return ok;
@@ -248,10 +249,10 @@ PyObject *block_copy(PyObject *const *args, Py_ssize_t n) {
     return run([&] { return g_copy(&s, &d, static_cast<const int64_t *>(dm.p), pairs, stream); });
 }
 
-// addresses of the library's functions, in the order of the assignments
+// addresses of the library's functions, in the order of the assignments, and the descriptor's type
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
-    if (n != 7) {
-        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of seven functions");
+    if (n != 8 || !PyType_Check(args[7])) {
+        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of seven functions and the descriptor's type");
         return nullptr;
     }
     void *f[7];
@@ -269,6 +270,9 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
     g_prefill = reinterpret_cast<decltype(g_prefill)>(f[4]);
     g_append = reinterpret_cast<decltype(g_append)>(f[5]);
     g_copy = reinterpret_cast<decltype(g_copy)>(f[6]);
+    Py_INCREF(args[7]);
+    Py_XDECREF(reinterpret_cast<PyObject *>(g_desc_type));
+    g_desc_type = reinterpret_cast<PyTypeObject *>(args[7]);
     Py_RETURN_NONE;
 }
 

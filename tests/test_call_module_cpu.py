@@ -28,7 +28,7 @@ stubs = [stub("decode", i32, *[vp] * 5, f, vp, vp, vp, sz, vp), stub("bytes", sz
          stub("scheduled", i32, *[vp] * 4, sz, f, vp, vp, vp, sz, vp), stub("build", i32, vp, vp, vp, vp, sz, vp),
          stub("prefill", i32, *[vp] * 6, f, vp, vp, i32, i32, vp), stub("append", i32, *[vp] * 8),
          stub("copy", i32, vp, vp, vp, i64, vp)]
-C.bind(*(ctypes.cast(s, vp).value for s in stubs))
+C.bind(*(ctypes.cast(s, vp).value for s in stubs), AttnDesc)
 bf = torch.bfloat16
 q, k = torch.zeros(3, 8, 64, dtype=bf), torch.zeros(5, 2, 16, 64, dtype=bf)
 bt, cl, qs = torch.zeros(3, 4, dtype=torch.int32), torch.zeros(3, dtype=torch.int32), torch.arange(4, dtype=torch.int32)
@@ -82,4 +82,19 @@ def test_a_nested_tensor_is_left_to_the_general_path(module):
             for i, a in enumerate(args):
                 if isinstance(a, torch.Tensor):
                     assert not call(name, **{f"a{i}": nested[a.dtype]}), (name, i)
+    """)
+
+
+def test_only_a_descriptor_is_read_as_one(module):
+    # 48 bytes of anything else: the general path's ctypes call refuses them
+    run(module, """
+        class Other(ctypes.Structure):
+            _fields_ = AttnDesc._fields_
+        class Derived(AttnDesc):
+            pass
+        words = [getattr(desc, f) for f, _ in AttnDesc._fields_]
+        for name, at in (("decode", "a7"), ("scheduled", "a6"), ("schedule_build", "a2")):
+            for what in (bytes(desc), bytearray(bytes(desc)), Other(*words)):
+                assert not call(name, **{at: what}), (name, type(what))
+            assert call(name, **{at: Derived(*words)})
     """)
