@@ -195,10 +195,14 @@ def new_workspace(desc: AttnDesc, device="cuda", stream=None):
     return ws
 
 
-def _attn_args(q, k_cache, v_cache, block_tables, context_lens, out, desc, workspace):
-    for t in (q, k_cache, v_cache, block_tables, context_lens):
+def _require_device(*tensors) -> None:
+    for t in tensors:
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError("tensors must be contiguous device tensors")
+
+
+def _attn_args(q, k_cache, v_cache, block_tables, context_lens, out, desc, workspace):
+    _require_device(q, k_cache, v_cache, block_tables, context_lens)
     if v_cache.shape != k_cache.shape or v_cache.dtype != q.dtype or k_cache.dtype != q.dtype:
         raise ValueError("k_cache / v_cache must match each other and q's dtype")
     if block_tables.dtype != torch.int32 or context_lens.dtype != torch.int32:
@@ -214,6 +218,8 @@ def _attn_args(q, k_cache, v_cache, block_tables, context_lens, out, desc, works
     need = workspace_bytes(desc)
     if workspace is None and need:
         workspace = new_workspace(desc, q.device)
+    if workspace is not None:
+        _require_device(workspace)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     return out, workspace, ws_ptr, ws_len
@@ -257,6 +263,11 @@ def attn_schedule_build(block_tables, context_lens, desc: AttnDesc, schedule=Non
     need = schedule_bytes(desc)
     if schedule is None:
         schedule = torch.empty(max(need, 256), dtype=torch.uint8, device=block_tables.device)
+    _require_device(block_tables, context_lens, schedule)
+    if block_tables.dtype != torch.int32 or context_lens.dtype != torch.int32:
+        raise TypeError("block_tables and context_lens must be int32")
+    if block_tables.numel() < desc.num_seqs * desc.max_blocks_per_seq or context_lens.numel() < desc.num_seqs:
+        raise ValueError("block_tables / context_lens are smaller than the descriptor says")
     _check(lib().kvc_attn_schedule_build(block_tables.data_ptr(), context_lens.data_ptr(), ctypes.byref(desc),
                                          schedule.data_ptr(), schedule.numel(), _stream_handle(stream)),
            "kvc_attn_schedule_build")
@@ -272,6 +283,11 @@ def paged_attention_decode_scheduled(q, k_cache, v_cache, schedule, scale: float
         if rc is not None:
             _check(rc, "kvc_paged_attention_decode_scheduled")
             return out
+    _require_device(q, k_cache, v_cache, schedule, out, workspace)
+    if v_cache.shape != k_cache.shape or v_cache.dtype != q.dtype or k_cache.dtype != q.dtype:
+        raise ValueError("k_cache / v_cache must match each other and q's dtype")
+    if out.dtype != q.dtype or min(q.numel(), out.numel()) < desc.num_seqs * desc.num_q_heads * desc.head_dim:
+        raise ValueError("q and out must be of one type and hold the descriptor's rows")
     _check(lib().kvc_paged_attention_decode_scheduled(
         q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), schedule.data_ptr(), schedule.numel(), float(scale),
         out.data_ptr(), ctypes.byref(desc), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
@@ -333,9 +349,7 @@ def paged_attention_prefill(q, k_cache, v_cache, block_tables, context_lens, q_s
         if rc is not None:
             _check(rc, "kvc_paged_attention_prefill")
             return out
-    for t in (q, k_cache, v_cache, block_tables, context_lens, q_start):
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError("tensors must be contiguous device tensors")
+    _require_device(q, k_cache, v_cache, block_tables, context_lens, q_start)
     if q_start.dtype != torch.int32 or q_start.shape != (context_lens.shape[0] + 1,):
         raise TypeError("q_start must be int32 [num_seqs + 1]")
     if block_tables.dtype != torch.int32 or context_lens.dtype != torch.int32:
@@ -348,6 +362,8 @@ def paged_attention_prefill(q, k_cache, v_cache, block_tables, context_lens, q_s
         raise ValueError("shapes do not match")
     if out is None:
         out = torch.empty_like(q)
+    elif not out.is_cuda or not out.is_contiguous() or out.dtype != q.dtype or out.numel() < q.numel():
+        raise ValueError("out must be a contiguous device tensor of q's type and at least its size")
     desc = AttnDesc(num_seqs=context_lens.shape[0], num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
                     block_size=bs, max_blocks_per_seq=block_tables.shape[1], num_pool_blocks=nb,
                     dtype=_dtype_code(q), max_context_len=0, partition_tokens=0, kernel=int(kernel),
@@ -366,9 +382,7 @@ def kv_cache_append(k_new, v_new, k_cache, v_cache, block_tables, positions, str
         if rc is not None:
             _check(rc, "kvc_kv_cache_append")
             return
-    for t in (k_new, v_new, k_cache, v_cache, block_tables, positions):
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError("tensors must be contiguous device tensors")
+    _require_device(k_new, v_new, k_cache, v_cache, block_tables, positions)
     nseq, hkv, d = k_new.shape
     if v_new.shape != k_new.shape or k_cache.shape != v_cache.shape or k_cache.shape[1] != hkv \
             or k_cache.shape[3] != d or not (k_new.dtype == v_new.dtype == k_cache.dtype == v_cache.dtype):

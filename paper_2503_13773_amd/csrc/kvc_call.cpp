@@ -91,6 +91,10 @@ int dtype_code(const at::Tensor &t) {
 bool is_int32(const at::Tensor &t) { return t.scalar_type() == at::kInt; }
 size_t bytes_of(const at::Tensor &t) { return size_t(t.numel()) * t.element_size(); }
 bool fits(int64_t x) { return x == int32_t(x); }
+// at least the rows of q that the descriptor speaks of
+bool holds_rows(const at::Tensor &t, const kvc_attn_desc &d) {
+    return t.numel() >= int64_t(d.num_seqs) * d.num_q_heads * d.head_dim;
+}
 
 // Runs the library call (which does not throw; nothing else may be in it) without the interpreter lock.
 template <class Call>
@@ -124,7 +128,7 @@ PyObject *decode(PyObject *const *args, Py_ssize_t n) {
     kvc_attn_desc d;
     if (!a.ok || !a.descriptor(&d)) Py_RETURN_NONE;
     const at::Tensor *ws = nullptr;
-    if (a.at < n && args[a.at] == Py_None) a.at++; else ws = a.any_tensor();
+    if (a.at < n && args[a.at] == Py_None) a.at++; else ws = a.device_tensor();
     void *stream = a.stream();
     if (!a.done()) Py_RETURN_NONE;
     if (v->sizes() != k->sizes() || v->scalar_type() != q->scalar_type() || k->scalar_type() != q->scalar_type() ||
@@ -144,14 +148,17 @@ PyObject *decode(PyObject *const *args, Py_ssize_t n) {
 // q, k_cache, v_cache, schedule, scale, out, desc, workspace, stream
 PyObject *scheduled(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
-    const at::Tensor *q = a.any_tensor(), *k = a.any_tensor(), *v = a.any_tensor(), *sched = a.any_tensor();
+    const at::Tensor *q = a.device_tensor(), *k = a.device_tensor(), *v = a.device_tensor(), *sched = a.device_tensor();
     const double scale = a.number();
-    const at::Tensor *out = a.any_tensor();
+    const at::Tensor *out = a.device_tensor();
     kvc_attn_desc d;
     if (!a.ok || !a.descriptor(&d)) Py_RETURN_NONE;
-    const at::Tensor *ws = a.any_tensor();
+    const at::Tensor *ws = a.device_tensor();
     void *stream = a.stream();
     if (!a.done()) Py_RETURN_NONE;
+    if (v->sizes() != k->sizes() || k->scalar_type() != q->scalar_type() || v->scalar_type() != q->scalar_type() ||
+        out->scalar_type() != q->scalar_type() || !holds_rows(*q, d) || !holds_rows(*out, d))
+        Py_RETURN_NONE;
     const Data dq(q), dk(k), dv(v), ds(sched), dout(out), dw(ws);
     if (!(dq.ok && dk.ok && dv.ok && ds.ok && dout.ok && dw.ok)) Py_RETURN_NONE;
     const size_t sched_bytes = size_t(sched->numel()), ws_bytes = bytes_of(*ws);
@@ -161,12 +168,14 @@ PyObject *scheduled(PyObject *const *args, Py_ssize_t n) {
 // block_tables, context_lens, desc, schedule, stream
 PyObject *schedule_build(PyObject *const *args, Py_ssize_t n) {
     Args a{args, n};
-    const at::Tensor *bt = a.any_tensor(), *cl = a.any_tensor();
+    const at::Tensor *bt = a.device_tensor(), *cl = a.device_tensor();
     kvc_attn_desc d;
     if (!a.ok || !a.descriptor(&d)) Py_RETURN_NONE;
-    const at::Tensor *sched = a.any_tensor();
+    const at::Tensor *sched = a.device_tensor();
     void *stream = a.stream();
     if (!a.done()) Py_RETURN_NONE;
+    if (!is_int32(*bt) || !is_int32(*cl) || bt->numel() < int64_t(d.num_seqs) * d.max_blocks_per_seq || cl->numel() < d.num_seqs)
+        Py_RETURN_NONE;
     const Data db(bt), dc(cl), ds(sched);
     if (!(db.ok && dc.ok && ds.ok)) Py_RETURN_NONE;
     const size_t sched_bytes = size_t(sched->numel());
@@ -182,14 +191,14 @@ PyObject *prefill(PyObject *const *args, Py_ssize_t n) {
     const at::Tensor *bt = a.device_tensor(), *cl = a.device_tensor(), *qs = a.device_tensor();
     const double scale = a.number();
     const int32_t max_query_len = a.int32();
-    const at::Tensor *out = a.any_tensor();
+    const at::Tensor *out = a.device_tensor();
     const int32_t kernel = a.int32();
     void *stream = a.stream();
     if (!a.done()) Py_RETURN_NONE;
     if (!is_int32(*qs) || !is_int32(*bt) || !is_int32(*cl) || cl->dim() != 1 || qs->dim() != 1 || qs->size(0) != cl->size(0) + 1 ||
         v->sizes() != k->sizes() || k->scalar_type() != q->scalar_type() || v->scalar_type() != q->scalar_type() ||
         q->dim() != 3 || k->dim() != 4 || bt->dim() != 2 || k->size(3) != q->size(2) || bt->size(0) != cl->size(0) ||
-        dtype_code(*q) < 0)
+        dtype_code(*q) < 0 || out->scalar_type() != q->scalar_type() || out->numel() < q->numel())
         Py_RETURN_NONE;
     for (int64_t x : {cl->size(0), q->size(0), q->size(1), q->size(2), k->size(0), k->size(1), k->size(2), bt->size(1)})
         if (!fits(x)) Py_RETURN_NONE;

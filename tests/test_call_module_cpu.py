@@ -98,3 +98,21 @@ def test_only_a_descriptor_is_read_as_one(module):
                 assert not call(name, **{at: what}), (name, type(what))
             assert call(name, **{at: Derived(*words)})
     """)
+
+
+def test_what_the_kernel_would_write_or_read_out_of_range_is_not_taken(module):
+    run(module, """
+        small, wide, strided = q[:2], q.float(), torch.zeros(3, 8, 128, dtype=bf)[..., ::2]
+        meta = torch.zeros(3, 8, 64, dtype=bf, device="meta")
+        for out in (small, wide, strided, meta, q.half()):
+            for name, at in (("prefill", "a8"), ("scheduled", "a5"), ("decode", "a5")):
+                assert not call(name, **{at: out}), (name, out.shape, out.dtype)
+        for flat in (torch.zeros(3 * 8 * 64, dtype=bf), torch.zeros(4, 8, 64, dtype=bf)):   # as large as q or larger
+            assert call("prefill", a8=flat) and call("scheduled", a5=flat)
+        assert not call("scheduled", a0=small) and not call("scheduled", a0=strided)
+        assert not call("scheduled", a1=k[:4]) and not call("scheduled", a2=k.float())
+        for at, what in (("a0", bt.long()), ("a1", cl.long()), ("a0", bt[:2]), ("a1", cl[:2]), ("a0", bt.t())):
+            assert not call("schedule_build", **{at: what}), (at, what.shape, what.dtype)
+        for name, at in (("decode", "a8"), ("scheduled", "a7"), ("scheduled", "a3"), ("schedule_build", "a3")):
+            assert not call(name, **{at: torch.zeros(4096, dtype=torch.uint8, device="meta")}), (name, at)
+    """)

@@ -125,3 +125,30 @@ def test_subclasses_and_functional_transforms_take_the_general_path(K):
         torch.vmap(lambda q: K.paged_attention_decode(q, d["k"], d["v"], d["tables"], d["lens"], w.scale, out, desc=desc,
                                                       workspace=ws))(torch.stack([d["q"], d["q"]]))
     assert K.counted["native"] == 1
+
+
+def test_unfit_outputs_and_arrays_are_refused_before_anything_is_launched(K):
+    """Prefill, schedule and the scheduled call, on both paths: what the kernel would write past or read as something else."""
+    w = W.make_config("cfg3", num_seqs=3, ctx_scale=0.2)
+    d = to_device(w)
+    desc = K.attn_desc(d["q"], d["k"], d["tables"], max_context_len=w.max_context_len)
+    ws, sched = K.new_workspace(desc), torch.empty(K.schedule_bytes(desc), dtype=torch.uint8, device="cuda")
+    qs = torch.arange(4, dtype=torch.int32, device="cuda")
+    q, out = d["q"], torch.empty_like(d["q"])
+    prefill = dict(q=q, k_cache=d["k"], v_cache=d["v"], block_tables=d["tables"], context_lens=d["lens"], q_start=qs, scale=w.scale,
+                   max_query_len=1, out=out)
+    scheduled = dict(q=q, k_cache=d["k"], v_cache=d["v"], schedule=sched, scale=w.scale, out=out, desc=desc, workspace=ws)
+    build = dict(block_tables=d["tables"], context_lens=d["lens"], desc=desc, schedule=sched)
+    outs = [dict(out=x) for x in (out[:2], out[:, ::2], out.float(), out.half(), out.cpu())]
+    cases = [(K.paged_attention_prefill, prefill, outs),
+             (K.paged_attention_decode_scheduled, scheduled, outs + [dict(q=q[:2]), dict(v_cache=d["v"].float()), dict(workspace=ws.cpu())]),
+             (K.attn_schedule_build, build, [dict(block_tables=d["tables"].long()), dict(context_lens=d["lens"].long()),
+                                             dict(block_tables=d["tables"][:2]), dict(context_lens=d["lens"][:2]), dict(schedule=sched.cpu())])]
+    for general in (False, True):
+        if general:
+            K.general()
+        for call, ok, bad in cases:
+            for b in bad:
+                with pytest.raises((ValueError, TypeError)):
+                    call(**{**ok, **b})
+    assert K.counted["native"] == 0
