@@ -155,6 +155,14 @@ bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
 }
 
+// head_dim 64 has a matrix-core prefill kernel of its own, for every group size and scale; the vector ALUs keep the calls
+// that ask one row of every sequence, and what the launch could not hold: HIP refuses 2^32 threads and more.
+bool prefill_d64_ok(const kvc::PrefillParams &p, int total_q, int max_query_len) {
+    const int tile_rows = 128 / p.heads_per_chunk;
+    const int64_t tiles = int64_t(p.num_q_heads / p.heads_per_chunk) * p.num_seqs * ceil_div(std::min(max_query_len, total_q), tile_rows);
+    return max_query_len > 1 && tiles < (int64_t(1) << 32) / kvc::kPrefill64Threads;
+}
+
 constexpr int64_t kFewRowParts = 384;  // (query head, partition) pairs
 
 int make_plan(const kvc_attn_desc *d, Plan *pl) {
@@ -646,13 +654,10 @@ int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *
     p.scale_log2e = float(double(scale) * 1.4426950408889634);
     const int64_t tile_grid = int64_t(p.num_q_heads / p.heads_per_chunk) * p.num_seqs * p.max_query_tiles;
     const bool on_mfma = desc->dtype == KVC_BF16 && desc->head_dim == 128 && p.group <= 16;
-    // head_dim 64 has a matrix-core kernel of its own, for every group size and scale.  Calls of one query row per
-    // sequence stay on the vector ALUs, which take 4 or 8 heads per workgroup and read K and V less often (64
-    // sequences of 500 to 1000 tokens, 32 / 8 heads: 27 us against 40 us; with two rows 43 us against 40 us), and so
-    // does a grid beyond the launch limit (very many sequences with a loose max_query_len; that one counts rows).
-    if (desc->dtype == KVC_BF16 && desc->head_dim == 64 && max_query_len > 1 && tile_grid <= kMaxGrid) {
+    if (desc->dtype == KVC_BF16 && desc->head_dim == 64 && prefill_d64_ok(p, total_q, max_query_len)) {
+        // no sequence has more rows than there are
         const hipError_t e = kvc::launch_prefill_d64(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p,
-                                                     max_query_len, static_cast<hipStream_t>(hip_stream));
+                                                     std::min(max_query_len, total_q), static_cast<hipStream_t>(hip_stream));
         return e == hipSuccess ? KVC_OK : hip_failed(e);
     }
     if (!on_mfma) {

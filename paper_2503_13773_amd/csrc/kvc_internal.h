@@ -115,6 +115,7 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
                                  const int32_t *q_start, void *out, const PrefillParams &p,
                                  hipStream_t stream);
 // head_dim 64, any group size and scale; rows past max_query_len of a sequence are not computed.
+constexpr int kPrefill64Threads = 512;  // of a workgroup
 hipError_t launch_prefill_d64(const void *q, const void *k_cache, const void *v_cache,
                               const int32_t *block_tables, const int32_t *context_lens,
                               const int32_t *q_start, void *out, const PrefillParams &p, int max_query_len,

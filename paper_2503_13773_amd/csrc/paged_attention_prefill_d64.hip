@@ -50,7 +50,7 @@ constexpr int kRowBytes = kDim * 2;
 constexpr int kStep = 64;                         // tokens of a step: 32 for each of the two wavefronts of a column set
 constexpr int kStageBytes = kStep * kRowBytes;    // K (or V) rows of a step
 constexpr int kStages = 4;
-constexpr int kBlockThreads = 512;
+constexpr int kBlockThreads = kPrefill64Threads;
 constexpr float kLazyLog2 = 8.0f;
 constexpr float kHugeScore = 1048576.f;  // 2^20: up to here the rounding of m is at most 2^-5
 
