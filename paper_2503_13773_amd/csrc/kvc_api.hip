@@ -155,12 +155,29 @@ bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
 }
 
-// head_dim 64 has a matrix-core prefill kernel of its own, for every group size and scale; the vector ALUs keep the calls
-// that ask one row of every sequence, and what the launch could not hold: HIP refuses 2^32 threads and more.
+// head_dim 64 has a matrix-core prefill kernel of its own, for every group size and scale.  A workgroup of it takes up to 64
+// or 128 rows of a sequence, two workgroups a compute unit; one on the vector ALUs takes one row for as many heads as
+// it holds (valu_head_chunk: 1 for odd groups, else 2, 4 or 8).  The vector ALUs keep (us there / on the matrix cores)
+//   launches of at most two workgroups a compute unit with one head each, or one with two: 14 / 2 heads, one sequence of
+//     400 tokens, 2 rows 5.9 / 8.2, 32 rows 7.2 / 8.6, 64 rows 9.3 / 8.9; of 1500, 2 rows 12.0 / 17.2, 32 rows 16.2 / 17.6; 16 / 8 heads
+//     of 1500, 2 rows 15.8 / 17.4, four sequences of 16 rows 20.1 / 17.2 (with four heads each, 32 / 8, 1 to 8 x 2 rows
+//     17 to 19 / 12 to 13);
+//   batches that are mostly decode steps, one row each, and a few longer ones, where K and V of a sequence are read
+//     once per head chunk by either: 32 / 8 heads, 128 sequences of 800, one of 64 rows and the rest of one 46.7 / 60.6, half of
+//     them of two 48.8 / 57.0; 24 / 8 heads of 200 28.1 / 41.2 and 28.4 / 40.1; at 1.75 rows on average 26.5 / 26.5, at 3 35 / 28.  Two heads per
+//     workgroup lose their lead earlier: 16 / 8 heads of 800, 1.0 rows 30.4 / 33.6, 1.2 rows 14.4 / 13.6.  Eight heads are too
+//     few workgroups: 16 / 1 heads, 128 of 800 at 1.5 rows 50.0 / 38.8;
+//   tiles most of which would be empty: a workgroup without rows still costs 1.2 ns (4096 sequences of 2 rows with a bound of
+//     8000 575 / 11000);
+//   and what a launch cannot hold: HIP refuses 2^32 threads and more.
 bool prefill_d64_ok(const kvc::PrefillParams &p, int total_q, int max_query_len) {
-    const int tile_rows = 128 / p.heads_per_chunk;
+    const int tile_rows = 128 / p.heads_per_chunk, valu_heads = kvc::valu_head_chunk(p.group);
     const int64_t tiles = int64_t(p.num_q_heads / p.heads_per_chunk) * p.num_seqs * ceil_div(std::min(max_query_len, total_q), tile_rows);
-    return max_query_len > 1 && tiles < (int64_t(1) << 32) / kvc::kPrefill64Threads;
+    const int64_t valu_grid = int64_t(total_q) * (p.num_q_heads / valu_heads);
+    if (max_query_len <= 1 || tiles >= (int64_t(1) << 32) / kvc::kPrefill64Threads || tiles > 8 * valu_grid) return false;
+    if (valu_heads <= 2 && valu_grid * valu_heads <= 2 * kvc::kNumCUs) return false;
+    const double rows = double(total_q) / p.num_seqs;
+    return valu_heads == 8 || rows >= (valu_heads == 2 ? 1.1 : 1.75);
 }
 
 constexpr int64_t kFewRowParts = 384;  // (query head, partition) pairs
