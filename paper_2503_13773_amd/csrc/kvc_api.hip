@@ -180,7 +180,20 @@ bool prefill_d64_ok(const kvc::PrefillParams &p, int total_q, int max_query_len)
     return valu_heads == 8 || rows >= (valu_heads == 2 ? 1.1 : 1.75);
 }
 
-constexpr int64_t kFewRowParts = 384;  // (query head, partition) pairs
+// A workgroup of the vector-ALU kernel takes as many heads of a KV head as its registers hold, which reads K and V
+// once for all of them; a launch of few workgroups spends its time on the chain of one of them, which is
+// shorter with a head each.  The line, in (query head, partition) pairs, and both sides, us with the heads together / one each:
+//   four or eight heads: fp32, 16 / 4 heads, 4 x 256 tokens, 64 pairs, of 64 9.0 / 5.1, of 128 12.9 / 7.0; 4 x 1000, 256 pairs,
+//     18.1 / 14.1; 4 x 2000, 512 pairs, 19.6 / 21.7; bf16 of 128, 40 / 2 heads, 1 x 2300, 360 pairs, 15.0 / 10.4, but with four heads per KV
+//     head, whose reads meet less often in the caches, 32 / 8, 1 x 2560, 320 pairs, 14.9 / 14.5, 1 x 3000, 384 pairs, 15.0 / 16.1
+//     (one partition, 12 x 100, 384 pairs, 8.1 / 5.0);
+//   two heads lose less together: rows of 256 bytes and more, 16 / 8 heads, 16 x 256, 256 pairs, 7.6 / 5.9 (fp32 of 64), 7.9 / 7.3
+//     (bf16 of 128), 20 x 256, 320 pairs, 7.7 / 10.5 and 7.9 / 10.6; rows of 128 bytes (bf16 of 64) 8 x 700, 384 pairs, 9.3 / 8.6.
+int64_t few_row_parts(const kvc_attn_desc &d, int heads, int64_t parts) {
+    const bool wide_rows = d.head_dim * (d.dtype == KVC_F32 ? 4 : 2) >= 256;
+    if (heads == 2 && wide_rows) return 256;
+    return d.dtype == KVC_BF16 && wide_rows && d.num_q_heads == 4 * d.num_kv_heads && parts > 1 ? 320 : 384;
+}
 
 int make_plan(const kvc_attn_desc *d, Plan *pl) {
     if (!d) return KVC_ERR_NULL;
@@ -255,11 +268,7 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         }
     }
     const int64_t parts = ceil_div(max_ctx, pt);
-    // A workgroup of the vector-ALU kernel takes as many heads of a KV head as its registers hold, which reads K and V
-    // once for all of them; a launch of few workgroups spends its time on the chain of one of them, which is
-    // shorter with a head each (fp32, 16 / 4 heads, with the heads together / one each: 4 x 256 tokens, 64 pairs, of 64
-    // 9.0 / 5.1 us, of 128 12.9 / 7.0 us; 4 x 1000, 256 pairs, 18.1 / 14.1 us; 4 x 2000, 512 pairs, 19.6 / 21.7 us).
-    if (kernel == KVC_KERNEL_VALU && rows * parts <= kFewRowParts) {
+    if (kernel == KVC_KERNEL_VALU && rows * parts <= few_row_parts(*d, pl->head_chunk, parts)) {
         pl->head_chunk = 1;
         base_items = rows;
     }

@@ -22,3 +22,21 @@ def test_launch_shapes(oracle_mod, dtype, d, hq, hkv, nseq, cap):
     got = out_to_f64(run_gpu(w, kernel=1, max_context_len=cap))
     assert np.isfinite(got).all()
     assert np.abs(got - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
+
+
+# two heads per KV head: 256 pairs where a row is 256 bytes or more, 384 below; four of bf16 and 128 in several partitions: 320
+@pytest.mark.parametrize("dtype,d,hq,hkv,nseq,cap,limit", [
+    (W.F32, 64, 16, 8, 16, 256, 256), (W.F32, 64, 16, 8, 17, 256, 256), (W.BF16, 128, 16, 8, 16, 256, 256), (W.BF16, 128, 16, 8, 17, 256, 256),
+    (W.BF16, 64, 16, 8, 24, 256, 384), (W.BF16, 64, 16, 8, 25, 256, 384), (W.BF16, 128, 16, 4, 24, 256, 384), (W.BF16, 128, 16, 4, 10, 512, 320),
+    (W.BF16, 128, 16, 4, 11, 512, 320), (W.BF16, 128, 12, 1, 16, 512, 384), (W.F32, 128, 16, 4, 12, 512, 384)])
+def test_where_heads_part(oracle_mod, dtype, d, hq, hkv, nseq, cap, limit):
+    import paper_2503_13773_amd as K
+    lens = np.random.default_rng(1350 + nseq).integers(0, cap, nseq)
+    w = custom(1350 + nseq + d, dtype=dtype, lens=lens, hq=hq, hkv=hkv, d=d, bs=16, lmax=512)
+    code, parts = K.KVC_F32 if dtype == W.F32 else K.KVC_BF16, cap // 256
+    plan = K.attn_plan(K.AttnDesc(nseq, hq, hkv, d, 16, 32, 64, code, cap, 0, 1, 0))
+    chunk = {2: 2, 4: 4, 12: 4}[hq // hkv]
+    assert plan.partial_grid == nseq * parts * (hq if nseq * hq * parts <= limit else hq // chunk)   # a head each, or several together
+    print(f"[case] valu {dtype} D={d} {hq}/{hkv} nseq={nseq} cap={cap} of {limit} pairs", flush=True)
+    got = out_to_f64(run_gpu(w, kernel=1, max_context_len=cap))
+    assert np.abs(got - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
