@@ -20,6 +20,8 @@
 // writes its normalised output directly.
 #include <math.h>
 
+#include <type_traits>
+
 #include "kvc_internal.h"
 
 namespace kvc {
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     if (tok0 >= ctx) return;
     const int tok1 = min(ctx, tok0 + p.partition_tokens);
 
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int tg = lane / LR, c = lane % LR;
 
     float qf[GC][EPL];
@@ -158,19 +160,30 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const size_t block_stride = head_stride * p.num_kv_heads;
     constexpr int CH = TPL * kUnroll;                                   // tokens per wavefront per trip
 
-    for (int base = tok0 + wave * CH; base < tok1; base += WAVES * CH) {
+    // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load the last one again, whose V
+    // must not meet the weight 0, where it is an infinity.  One head per workgroup: every trip asks, which is shortest (fp32
+    // of 64, 4 x 256 tokens 5.06 us, with the last trip apart 5.18); several: the last trip is code of its own (fp32 of
+    // 128, four heads, 24 x 256 15.6 us, asked in every trip 16.7).
+    auto trip = [&](auto may_end, int base) __attribute__((always_inline)) {
+        constexpr bool MAY_END = decltype(may_end)::value;
         float kf[kUnroll][EPL], vf[kUnroll][EPL];
         bool valid[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int t = base + u * TPL + tg;
-            valid[u] = t < tok1;
+            valid[u] = !MAY_END || t < tok1;
             const int tc = valid[u] ? t : tok1 - 1;  // clamp: never touch a table entry or slot past the context
             const int blk = table[tc >> p.block_size_log2];
             const int slot = tc & (p.block_size - 1);
             const size_t off = size_t(blk) * block_stride + kvh * head_stride + size_t(slot) * D + c * EPL;
             E::load16(k_cache + off, kf[u]);
             E::load16(v_cache + off, vf[u]);
+        }
+        if (MAY_END && base + CH > tok1) {
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) vf[u][e] = valid[u] ? vf[u][e] : 0.f;
         }
 #pragma unroll
         for (int g = 0; g < GC; ++g) {
@@ -208,6 +221,13 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
             for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(acc[g][e], alpha, pv[e]);
             m[g] = m_new;
         }
+    };
+    int base = tok0 + wave * CH;
+    if constexpr (GC == 1) {
+        for (; base < tok1; base += WAVES * CH) trip(std::true_type{}, base);
+    } else {
+        for (; base + CH <= tok1; base += WAVES * CH) trip(std::false_type{}, base);
+        if (base < tok1) trip(std::true_type{}, base);
     }
 
     // merge the TPL lane groups of this wavefront (log-sum-exp rule)
