@@ -76,6 +76,10 @@ using namespace mfma;
 
 constexpr int kStageTiles = 256;  // tiles whose addresses are staged in LDS per wavefront at a time
 constexpr int kRowCost = 1;       // flat units charged for leaving a row
+// head_dim 64: where no row is longer than this (256 tokens) and there is a worker for every row, each takes one, and nothing
+// is cut or merged.  The bound by which the host chose ranges was loose then: 32 / 8 heads under a bound of 4096 tokens, 16
+// sequences of up to 100 tokens 10.8 -> 7.2 us, 64 of them 11.1 -> 7.6 us, 16 of up to 250 12.0 -> 10.7 us.
+constexpr int kShortRow = 8;
 static_assert(size_t(kNumCUs) * kWaves * sizeof(int32_t) <= kWorkspaceHeaderBytes,
               "one arrival counter per worker must fit the workspace header");
 
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     constexpr int kSeqs = MAXSPT * kThreads;
     __shared__ int s_pref[kSeqs + 2];  // exclusive prefix of flat units (tiles + row cost) per sequence (+ guard)
     __shared__ int s_ctx[kSeqs];       // context length per sequence
-    __shared__ int s_wave_tot[kWaves];
+    __shared__ int s_wave_tot[kWaves], s_most;
     __shared__ int s_tile[kWaves][kStageTiles * kMaxUnits];  // per worker: pool index of each unit of its next tiles
 
     const int tid = threadIdx.x;
@@ -258,6 +262,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
 
     const int worker = blockIdx.x * kWaves + wave;
     const int U_log2 = TS::kTokensLog2 - unit_log2;                 // log2(units per tile)
+    bool row_each = false;                            // every worker takes a row (see below)
     int plan_word = 0;                                // kScheduled: lane i < kPlanInts holds word i of the plan
     if constexpr (MODE == kScheduled) {
         // one round trip: the worker's plan, its first tile addresses (as many as the staging
@@ -276,6 +281,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         constexpr int kMaxSpt = MAXSPT;
         const int spt = (nseq + kThreads - 1) / kThreads;  // <= kMaxSpt
         int local[kMaxSpt], sum = 0;
+        int longest = 0;
 #pragma unroll
         for (int i = 0; i < kMaxSpt; ++i) {
             const int n = tid * spt + i;
@@ -284,6 +290,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
                 const int c = min(max(context_lens[n], 0), p.max_context_len);
                 s_ctx[n] = c;
                 t = (c + kTokens - 1) >> TS::kTokensLog2;
+                longest = max(longest, t);
                 if (t > 0) t += kRowCost;
             }
             local[i] = sum;
@@ -296,9 +303,18 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
             if (lane >= off) inc += v;
         }
         if (lane == 63) s_wave_tot[wave] = inc;
+        if (HD == 64 && tid == 0) s_most = kShortRow;
         __syncthreads();
         int base = 0;
         for (int w = 0; w < wave; ++w) base += s_wave_tot[w];
+        if (HD == 64 && __ballot(longest > kShortRow) != 0) {
+            // a power of two that no row is longer than, from ballots (a maximum over the lanes takes longer)
+            int most = 128;
+            if (p.min_chunk_tiles > 4)
+#pragma unroll
+                for (int x = 128; x <= 512; x *= 2) most = __ballot(longest > x) != 0 ? 2 * x : most;
+            if (lane == 0) __hip_atomic_fetch_max(&s_most, most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
         const int excl = base + inc - sum;
 #pragma unroll
         for (int i = 0; i < kMaxSpt; ++i) {
@@ -333,10 +349,19 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     auto write_empty_plan = [&]() __attribute__((always_inline)) {
         if (MODE == kBuild && lane < kPlanInts) sched.plans[size_t(worker) * kPlanInts + lane] = 0;
     };
-    const int T = uniform(s_pref[nseq]) * Hkv;
+    const int seq_units = uniform(s_pref[nseq]), T = seq_units * Hkv;
     const int workers = gridDim.x * kWaves;
-    const int C = max(p.min_chunk_tiles, (T + workers - 1) / workers);
-    if (MODE != kScheduled && int64_t(worker) * C >= T) {
+    // The smallest range keeps the pieces of a row at about 32, whose lengths the host bounds; at head_dim 64 the lengths
+    // themselves put a loose bound right (no row is longer than all of them together): 16 / 16 heads, four sequences of up to
+    // 8000 tokens under a bound of 32000 39.9 -> 26.4 us.
+    int least = p.min_chunk_tiles;
+    if constexpr (HD == 64) {
+        const int most = uniform(s_most);
+        row_each = most == kShortRow && nseq * Hkv <= workers;
+        if (least > 4) least = min(least, max(4, min((seq_units + 31) / 32, most <= 512 ? most / 32 : least)));
+    }
+    const int C = max(least, (T + workers - 1) / workers);
+    if (MODE != kScheduled && !row_each && int64_t(worker) * C >= T) {
         write_empty_plan();
         return;
     }
@@ -381,6 +406,13 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         first_tile = word(5);
         h_n = word(6); h_kvh = word(7); h_j0 = word(8); h_cnt = word(9);
         t_n = word(10); t_kvh = word(11); t_j0 = word(12); t_cnt = word(13);
+    } else if (row_each) {  // worker n * Hkv + kvh takes that row, from its first tile to its last
+        first.n = min(worker / Hkv, nseq);
+        first.kvh = worker - first.n * Hkv;
+        first.pref = uniform(s_pref[first.n]);
+        first.tiles = uniform(s_pref[first.n + 1]) - first.pref - kRowCost;
+        first_tile = 0;
+        NT = first.n < nseq ? max(first.tiles, 0) : 0;
     } else {
         int lo = 0;
         if (nseq <= 4 * 64) {  // every lane tests one entry: the table is sorted, so the count is the position
@@ -410,7 +442,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
     }
     // tiles of this worker: the part of [f0, f1) that falls on tiles rather than cost units;
     // the walk also finds the last row it touches and where its piece of that row ends
-    if constexpr (MODE != kScheduled) {
+    if (MODE != kScheduled && !row_each) {
         RowCursor last = first;
         int last_t0 = first_tile, last_end = first_tile;
         RowCursor c = first;
