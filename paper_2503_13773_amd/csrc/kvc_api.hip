@@ -124,7 +124,7 @@ bool balanced64_form(const kvc_attn_desc &d) {
 
 // A workspace sized for a batch has to do for a smaller one or a lower bound, as it does in every other kernel.  Up to
 // 640 tokens a smaller batch at head_dim 64 is whole rows, which need none; above, it may be pieces.
-constexpr int kWhole64Tokens = 640, kWhole128Tokens = 512;
+constexpr int kWhole64Tokens = 640, kWhole128Tokens = 512, kWhole128Rows = 2048;
 bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
     return balanced64_form(d) && d.num_seqs > 0 && max_ctx > kWhole64Tokens;
 }
@@ -133,15 +133,18 @@ bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
 // best of the other layouts / whole rows (32 / 8 heads unless said, lengths at or below the bound):
 //   head_dim 128: 1 x 300 7.4 / 5.7, 1 x 500 8.9 / 8.1, 20 x 100 9.4 / 4.9, 64 x 300 19.8 / 14.5, 32 x 600 20.2 / 15.2,
 //     128 x 500 45.0 / 41.0; 14 / 2 heads 64 x 700 15.3 / 13.5, 20 x 1000 11.0 / 15.4; 64 x 1000 34.5 / 35.4; with more than
-//     about 1000 rows of up to 200 tokens the ranges win: 128 x 100 13.1 / 13.6, 1000 x 80 56 / 70 (128 x 300 31.8 / 26.9);
+//     about 1000 rows of up to 200 tokens the ranges win: 128 x 100 13.1 / 13.6, 1000 x 80 56 / 70 (128 x 300 31.8 / 26.9).
+//     The compute units hold 512 of these workgroups at a time, so a bound far above the lengths costs the more the more rows there
+//     are: bounds of 300 to 512, 256 x 250 39.3 / 35.8, 256 x 150 27.3 / 25.5, 256 x 16 7.6 / 11.6; 64 / 8 heads 512 x 150 54.1 / 54.2,
+//     512 x 16 13.9 / 23.9; 1024 x 150 97 / 99, 1024 x 16 23 / 42: no more than 2048 rows;
 //   head_dim 64: 1 x 500 7.0 / 5.5, 64 x 500 17.9 / 12.4, 20 x 1000 12.8 / 10.7; 14 / 2 heads on the vector ALUs before:
 //     128 x 500 36.2 / 8.2; but one head per KV head and 1000 rows of up to 200 tokens: 128 x 100 12.2 / 15.2.
 bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
     const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
     if (d.partition_tokens != 0 || d.num_seqs < 1 || d.num_seqs > kvc::kMaxStreamSeqs) return false;
-    const bool many_short = rows > 1000 && max_ctx <= 200;
-    if (d.head_dim == 128) return max_ctx <= kWhole128Tokens && !many_short;
-    return max_ctx <= (rows > kvc::kMaxFewRows ? 1024 : kWhole64Tokens) && !(many_short && d.num_q_heads == d.num_kv_heads);
+    if (d.head_dim == 128) return max_ctx <= kWhole128Tokens && rows <= kWhole128Rows && !(rows > 1000 && max_ctx <= 200);
+    return max_ctx <= (rows > kvc::kMaxFewRows ? 1024 : kWhole64Tokens) &&
+           !(rows > 1000 && max_ctx <= 200 && d.num_q_heads == d.num_kv_heads);
 }
 
 // At head_dim 64 the balanced kernel serves calls that KVC_KERNEL_AUTO brings without a split of the caller's
@@ -393,7 +396,7 @@ bool schedule_layout(const kvc_attn_desc &d, const Plan &pl, ScheduleLayout *L) 
     };
     uint64_t most = body(range_workers, range_chunk);
     if (d.partition_tokens == 0) {
-        most = std::max(most, body(rows, std::min<int64_t>(max_tiles, kWhole128Tokens / 16)));
+        most = std::max(most, body(std::min<int64_t>(rows, kWhole128Rows), std::min<int64_t>(max_tiles, kWhole128Tokens / 16)));
         const int64_t few = std::min<int64_t>({d.num_seqs, kFewRowSeqs, kvc::kMaxFewRows / d.num_kv_heads});
         if (few > 0) most = std::max(most, body(kvc::kNumCUs, piece_chunk(few)));
     }

@@ -65,3 +65,10 @@ def test_explicit_kernels_and_schedules_stay_refused(K):  # noqa: F811
     for kernel in (2, 3, 4):
         assert plan_status(K, desc(K, head_dim=64, kernel=kernel))[0] == -4
     assert K.schedule_bytes(desc(K, head_dim=64)) == 0
+
+
+def test_whole_rows_of_head_dim_128_end_at_2048_rows(K):  # noqa: F811
+    for n, heads, grid in [(256, 8, 2048), (257, 8, 256), (64, 32, 2048), (65, 32, 256), (2048, 1, 2048), (2049, 1, 256)]:
+        d = desc(K, num_seqs=n, num_q_heads=heads, num_kv_heads=heads, max_context_len=300)
+        rc, p = plan_status(K, d)
+        assert rc == 0 and p.kernel == K.KERNEL_MFMA_BALANCED and p.partial_grid == grid
