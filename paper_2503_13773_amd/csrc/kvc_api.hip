@@ -138,23 +138,32 @@ bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
 //     are: bounds of 300 to 512, 256 x 250 39.3 / 35.8, 256 x 150 27.3 / 25.5, 256 x 16 7.6 / 11.6; 64 / 8 heads 512 x 150 54.1 / 54.2,
 //     512 x 16 13.9 / 23.9; 1024 x 150 97 / 99, 1024 x 16 23 / 42: no more than 2048 rows;
 //   head_dim 64: 1 x 500 7.0 / 5.5, 64 x 500 17.9 / 12.4, 20 x 1000 12.8 / 10.7; 14 / 2 heads on the vector ALUs before:
-//     128 x 500 36.2 / 8.2; but one head per KV head and 1000 rows of up to 200 tokens: 128 x 100 12.2 / 15.2.
+//     128 x 500 36.2 / 8.2; but one head per KV head and many rows of one partition on the vector ALUs: 12 / 12 heads 42 x 100 4.25 /
+//     4.26, 64 x 100 4.5 / 5.1, 83 x 150 6.7 / 8.1.
 bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
     const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
     if (d.partition_tokens != 0 || d.num_seqs < 1 || d.num_seqs > kvc::kMaxStreamSeqs) return false;
     if (d.head_dim == 128) return max_ctx <= kWhole128Tokens && rows <= kWhole128Rows && !(rows > 1000 && max_ctx <= 200);
     return max_ctx <= (rows > kvc::kMaxFewRows ? 1024 : kWhole64Tokens) &&
-           !(rows > 1000 && max_ctx <= 200 && d.num_q_heads == d.num_kv_heads);
+           (max_ctx > 256 || rows <= 640 || d.num_q_heads > d.num_kv_heads);
 }
 
 // At head_dim 64 the balanced kernel serves calls that KVC_KERNEL_AUTO brings without a split of the caller's
-// own: whole rows, few rows, and ranges from 2^17 tokens x KV heads on (below that the vector ALUs are as good:
-// 102 k 9.7 / 11.9 us, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1).
+// own: whole rows, few rows, and ranges; the vector ALUs keep what they do as fast.  In us, there / here:
+//   few rows about as long as the launch takes a head per workgroup (few_row_parts): 14 / 2 heads 1 x 1000 8.0 / 8.5, 1 x 4000 7.4 /
+//     8.8, 4 x 2000, 448 pairs, 9.6 / 8.8; 16 / 8 heads 1 x 2000 7.1 / 9.0, 1 x 8000, 512 pairs, 9.2 / 11.7, 4 x 4000, 1024 pairs,
+//     11.4 / 11.7, but 4 x 250 under a bound of 4096 6.7 / 5.8; 32 / 8 heads 1 x 2000 7.4 / 8.9, 1 x 4000,
+//     512 pairs, 10.3 / 9.8; one head per KV head, where they read nothing twice, to 1024 pairs: 12 / 12 heads 1 x 4000 7.4 / 10.7,
+//     4 x 4000, 768 pairs, 12.3 / 14.2, 4 x 8000 20.1 / 20.6 (but 128 rows fill the device here: 16 / 16 heads 8 x 1500 15.0 / 13.9);
+//   more rows below 2^17 tokens x KV heads: 102 k 9.7 / 11.9, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1 (one head per KV head: 128 rows
+//     of 1500 15.5 / 14.2, 12 / 12 heads 16 x 2000 18.8 / 18.6, 64 x 2000 52.6 / 53.1, 64 x 4000 114 / 98).
 bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
+    const int group = d.num_q_heads / d.num_kv_heads;
+    const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads, pairs = rows * group * ceil_div(max_ctx, 256);
     return balanced64_form(d) && d.num_seqs <= kvc::kMaxStreamSeqs &&
-           (whole_ok(d, max_ctx) || few_rows_ok(d, max_ctx) ||
-            (max_ctx > 256 && int64_t(d.num_seqs) * d.num_kv_heads * max_ctx >= (1 << 17))) &&
-           int64_t(d.num_seqs) * d.num_kv_heads * (ceil_div(max_ctx, 32) + 1) < (int64_t(1) << 30) &&
+           (whole_ok(d, max_ctx) || (few_rows_ok(d, max_ctx) ? pairs > (group == 1 && rows < kvc::kMaxFewRows ? 1024 : group == 2 ? 512 : 384)
+                                                              : max_ctx > 256 && rows * max_ctx >= (1 << 17))) &&
+           rows * (ceil_div(max_ctx, 32) + 1) < (int64_t(1) << 30) &&
            int64_t(d.num_pool_blocks) * d.num_kv_heads * std::max(1, d.block_size / 32) < (int64_t(1) << 31);
 }
 

@@ -84,3 +84,43 @@ def test_one_workspace_for_few_rows_and_many(oracle_mod):
                                            desc=desc, workspace=ws)
             assert np.abs(out_to_f64(out) - d[1]).max() <= BF16_TOL
     assert int(ws[:4096].max()) == 0
+
+
+# small calls at head_dim 64 are the vector ALUs' under a tight bound; this one makes them pieces
+LOOSE64 = 65536
+
+
+def check_pieces64(w, oracle_mod, label):
+    import paper_2503_13773_amd as K
+    d = K.AttnDesc(w.num_seqs, w.num_q_heads, w.num_kv_heads, 64, w.block_size, -(-LOOSE64 // w.block_size), w.num_pool_blocks, K.KVC_BF16,
+                   LOOSE64, 0, 0, 0)
+    plan = K.attn_plan(d)
+    assert plan.kernel == K.KERNEL_MFMA_BALANCED and plan.partial_grid == 256 and plan.partition_tokens == 8 * 32   # pieces
+    check(w, oracle_mod, label, max_context_len=LOOSE64)
+
+
+@pytest.mark.parametrize("hq,hkv,bs", [(8, 2, 16), (7, 1, 8), (16, 1, 32), (9, 1, 4), (4, 4, 16), (2, 1, 64), (6, 3, 256)])
+def test_pieces_at_head_dim_64(oracle_mod, hq, hkv, bs):
+    t = 32
+    for lens in ([1, 0, t - 1, t, t + 1, 7 * t, 8 * t, 8 * t + 1], [20 * t, 0, 3], [20 * t + 1, 40, 0, 0], [16 * t, 17 * t + 5, 33 * t], [300] * 7,
+                 [9000, 5]):
+        w = custom(980 + hq + bs, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=64, bs=bs)
+        poison(w)
+        check_pieces64(w, oracle_mod, f"{hq}/{hkv} bs={bs} {lens}")
+
+
+def test_non_finite_values_in_pieces_at_head_dim_64(oracle_mod):
+    w = custom(990, dtype=W.BF16, lens=[700, 300, 400], hq=4, hkv=2, d=64, bs=16, lmax=LOOSE64 // 16)
+    for n, t, h, dim, what in [(0, 50, 0, 3, 0x7F80), (0, 650, 1, 40, 0x7FC0), (1, 299, 0, 63, 0xFF80)]:
+        w.v_cache[w.block_tables[n, t // 16], h, t % 16, dim] = what
+    w.q[:, :, 0] = 0x3F80                                       # q[0] = 1
+    w.k_cache[w.block_tables[2, :4], :, :, 0] = 0xFF80          # scores of -inf for the first 64 tokens of sequence 2
+    print("[case] pieces d64 non-finite values", flush=True)
+    import paper_2503_13773_amd as K
+    d = to_device(w)
+    with np.errstate(all="ignore"):
+        ref = oracle_mod.attention_of_workload(w, num_threads=8)
+        got = out_to_f64(K.paged_attention_decode(d["q"], d["k"], d["v"], d["tables"], d["lens"], w.scale, max_context_len=LOOSE64))
+        fine = np.isfinite(ref)
+        assert np.array_equal(np.isfinite(got), fine) and (np.abs(got - ref)[fine] <= bound(ref)[fine]).all()
+        assert np.array_equal(got[~fine], ref[~fine], equal_nan=True)

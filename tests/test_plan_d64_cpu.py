@@ -72,3 +72,19 @@ def test_whole_rows_of_head_dim_128_end_at_2048_rows(K):  # noqa: F811
         d = desc(K, num_seqs=n, num_q_heads=heads, num_kv_heads=heads, max_context_len=300)
         rc, p = plan_status(K, d)
         assert rc == 0 and p.kernel == K.KERNEL_MFMA_BALANCED and p.partial_grid == grid
+
+
+def test_few_rows_of_head_dim_64(K):  # noqa: F811
+    """The vector ALUs keep up to 384 (query head, 256-token partition) pairs, 512 with two heads per KV head, 1024
+    with one and less than 128 rows."""
+    for n, hq, hkv, ctx, balanced in [(1, 14, 2, 6912, False), (1, 14, 2, 6913, True), (3, 32, 8, 1024, False), (4, 32, 8, 1024, True),
+                                      (1, 16, 8, 8192, False), (1, 16, 8, 8193, True), (4, 16, 16, 4096, False), (5, 16, 16, 4096, True), (8, 16, 16, 768, False), (8, 16, 16, 769, True),
+                                      (1, 1, 1, 65536, False), (64, 1, 1, 8192, True)]:
+        rc, p = plan_status(K, desc(K, head_dim=64, num_seqs=n, num_q_heads=hq, num_kv_heads=hkv, max_blocks_per_seq=8192, max_context_len=ctx))
+        assert rc == 0 and (p.kernel == K.KERNEL_MFMA_BALANCED) == balanced, (n, hq, hkv, ctx)
+
+
+def test_one_head_per_kv_head_and_many_short_rows(K):  # noqa: F811
+    for n, ctx, kernel in [(40, 256, 4), (41, 256, 1), (41, 257, 4)]:
+        rc, p = plan_status(K, desc(K, head_dim=64, num_seqs=n, num_q_heads=16, num_kv_heads=16, max_context_len=ctx))
+        assert rc == 0 and p.kernel == kernel and (kernel == 1 or p.partial_grid == n * 16)
