@@ -63,7 +63,8 @@ struct Plan {
     int64_t merge_grid;
     uint64_t acc_offset;  // offset of the accumulator array inside the workspace (after the counter header)
     uint64_t ml_offset;   // offset of the (max, sum) array
-    uint64_t workspace_bytes;
+    uint64_t workspace_bytes;  // asked for: does for smaller calls too (below)
+    uint64_t workspace_need;   // this call's own
     int min_chunk_tiles;
     int max_context_len;
     int layout;           // balanced: how the rows are dealt out (kRanges, kPieces, kWhole)
@@ -122,8 +123,11 @@ bool balanced64_form(const kvc_attn_desc &d) {
            d.partition_tokens == 0 && d.num_q_heads / d.num_kv_heads <= 16;
 }
 
-// A workspace sized for a batch has to do for a smaller one or a lower bound, as it does in every other kernel.  Up to
-// 640 tokens a smaller batch at head_dim 64 is whole rows, which need none; above, it may be pieces.
+// A workspace sized for a batch has to do for a smaller one or a lower bound that the balanced kernel serves, also where the
+// batch itself is the vector ALUs': too many sequences, or few rows.  Up to 640 tokens a smaller batch at head_dim 64 is
+// whole rows, which need none; above, it may be pieces or ranges.  (Among calls of the vector-ALU kernel alone sizes can fall
+// with the batch, whose partitions get longer then: fp32 of 64, 32 / 8 heads, 1000 tokens, 17305600 bytes for 512
+// sequences and 8671744 for 513.)
 constexpr int kWhole64Tokens = 640, kWhole128Tokens = 512, kWhole128Rows = 2048;
 bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
     return balanced64_form(d) && d.num_seqs > 0 && max_ctx > kWhole64Tokens;
@@ -262,6 +266,7 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
         pl->workspace_bytes = need.bytes;
         // whole rows need no workspace; head_dim 128 keeps asking for one (its size never depended on the lengths)
         if (d->head_dim == 64 && pl->layout == kWhole && !smaller_calls_need_balanced(*d, max_ctx)) pl->workspace_bytes = 0;
+        pl->workspace_need = pl->workspace_bytes;
         return KVC_OK;
     }
 
@@ -298,13 +303,14 @@ int make_plan(const kvc_attn_desc *d, Plan *pl) {
     if (parts > 1) {
         const uint64_t acc = uint64_t(rows) * parts * d->head_dim * sizeof(float);
         pl->ml_offset = (kHeader + acc + 255) & ~uint64_t(255);
-        pl->workspace_bytes = pl->ml_offset + uint64_t(rows) * parts * 2 * sizeof(float);
-        if (kernel == KVC_KERNEL_VALU && smaller_calls_need_balanced(*d, max_ctx))
-            pl->workspace_bytes = std::max(pl->workspace_bytes, BalancedWorkspace(*d).bytes);
+        pl->workspace_need = pl->ml_offset + uint64_t(rows) * parts * 2 * sizeof(float);
     } else {
         pl->ml_offset = 0;
-        pl->workspace_bytes = 0;
+        pl->workspace_need = 0;
     }
+    pl->workspace_bytes = pl->workspace_need;
+    if (kernel == KVC_KERNEL_VALU && smaller_calls_need_balanced(*d, max_ctx))
+        pl->workspace_bytes = std::max(pl->workspace_bytes, BalancedWorkspace(*d).bytes);
     return KVC_OK;
 }
 
@@ -332,8 +338,8 @@ int check_workspace(const Plan &pl, void *workspace, size_t workspace_bytes, kvc
     ws->acc = nullptr;
     ws->ml = nullptr;
     ws->cnt = nullptr;
-    if (pl.workspace_bytes == 0) return KVC_OK;
-    if (!workspace || workspace_bytes < pl.workspace_bytes) return KVC_ERR_WORKSPACE;
+    if (pl.workspace_need == 0) return KVC_OK;
+    if (!workspace || workspace_bytes < pl.workspace_need) return KVC_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return KVC_ERR_ALIGN;
     unsigned char *base = static_cast<unsigned char *>(workspace);
     ws->cnt = reinterpret_cast<int32_t *>(base);
@@ -568,7 +574,7 @@ int kvc_paged_attention_decode_noalloc(const void *q, const void *k_cache, const
     Plan pl;
     int rc = make_plan(desc, &pl);
     if (rc != KVC_OK) return rc;
-    if (pl.workspace_bytes > kScratchBytes) return KVC_ERR_WORKSPACE;
+    if (pl.workspace_need > kScratchBytes) return KVC_ERR_WORKSPACE;
     if (desc->num_seqs == 0) return KVC_OK;
     rc = check_attn_args(q, k_cache, v_cache, block_tables, context_lens, scale, out);
     if (rc != KVC_OK) return rc;

@@ -88,3 +88,30 @@ def test_one_head_per_kv_head_and_many_short_rows(K):  # noqa: F811
     for n, ctx, kernel in [(40, 256, 4), (41, 256, 1), (41, 257, 4)]:
         rc, p = plan_status(K, desc(K, head_dim=64, num_seqs=n, num_q_heads=16, num_kv_heads=16, max_context_len=ctx))
         assert rc == 0 and p.kernel == kernel and (kernel == 1 or p.partial_grid == n * 16)
+
+
+@pytest.mark.parametrize("heads", [(32, 8), (16, 16), (14, 2), (1, 1), (64, 4)])
+def test_workspaces_of_batches_beyond_the_balanced_kernel_do_for_smaller_ones(K, heads):  # noqa: F811
+    """4097 and more sequences are the vector ALUs', often without a workspace of their own: what the query answers for them
+    is enough for the batches below, bound by bound, and the call itself still runs with what it needs."""
+    import ctypes
+    kw = dict(head_dim=64, num_q_heads=heads[0], num_kv_heads=heads[1], max_blocks_per_seq=512, num_pool_blocks=64)
+    for bound in (600, 640, 641, 1000, 1024, 1025, 4096, 8192):
+        below = max(K.workspace_bytes(desc(K, num_seqs=n, max_context_len=b, **kw)) for n in (1, 3, 20, 65, 129, 2000, 4096)
+                    for b in (600, 640, 641, 1000, bound) if b <= bound)
+        for n in (4097, 5000, 8192, 20000):
+            d = desc(K, num_seqs=n, max_context_len=bound, **kw)
+            rc, p = plan_status(K, d)
+            assert rc == 0 and p.kernel == K.KERNEL_VALU and p.workspace_bytes >= below, (n, bound)
+            if p.merge_grid == 0:   # one partition: no workspace is needed, and none is missed
+                a = ctypes.c_void_p(4096)
+                assert K.lib().kvc_paged_attention_decode_merge(a, a, ctypes.byref(d), None, 0, None) == 0, (n, bound)
+
+
+def test_sizes_of_the_vector_alu_kernel_are_its_own(K):  # noqa: F811
+    """fp32 is never the balanced kernel's: what the query answers is what the call needs."""
+    for n in (1, 512, 513, 4097):
+        rc, p = plan_status(K, desc(K, dtype=0, head_dim=64, num_seqs=n, max_context_len=1000))
+        parts = p.max_partitions
+        want = 0 if parts == 1 else (4096 + n * 32 * parts * 64 * 4 + 255) // 256 * 256 + n * 32 * parts * 8
+        assert rc == 0 and p.workspace_bytes == want
