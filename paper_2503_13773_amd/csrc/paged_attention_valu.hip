@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         float L = 0.f, A = 0.f;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
-            const float wgt = E::exp_(sm_m[w][g] - M);  // M is finite: wavefront 0 always has a token
+            const float wgt = E::exp_(sm_m[w][g] - (M == -INFINITY ? 0.f : M));  // -inf: every score of the partition is
             L = fmaf(wgt, sm_l[w][g], L);
             A = fmaf(wgt, sm_acc[w][g][d], A);
         }
