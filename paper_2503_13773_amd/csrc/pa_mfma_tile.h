@@ -65,7 +65,7 @@ struct HeadStateN {
     __device__ inline void reset() {
 #pragma unroll
         for (int e = 0; e < N; ++e) acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
-        m = N == 8 ? -INFINITY : -FLT_MAX;  // head_dim 64: scores may be -inf (see below)
+        m = -FLT_MAX;  // not -inf: a first tile of -inf scores weighs nothing then, instead of -inf - -inf
         l = 0.f;
     }
     // sum l over the 4 quads (the max is already common to them)
@@ -174,8 +174,7 @@ __device__ inline void compute_tile(HeadState &st, const bf16x8 (&ka)[4], uint4 
 // The weights keep fp32 accuracy: a weight enters the product as the sum of two bf16 values (its
 // upper bits and the rounded rest, 2^-16 relative) and the normaliser sums the fp32 weights.  The upper part
 // is cut off and the rest made positive by 2^-23 of the weight (a factor all weights share), so that
-// an infinity in V keeps its sign, which a rest of 0 or of the other sign would turn into NaN.  A score of
-// -inf weighs nothing: the running max starts at the lowest finite value.
+// an infinity in V keeps its sign, which a rest of 0 or of the other sign would turn into NaN.
 constexpr int kTileTokens64 = 32;
 
 __device__ inline uint2 load8_stream(const uint16_t *p) {

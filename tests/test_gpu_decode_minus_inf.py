@@ -10,7 +10,8 @@ from test_gpu_attention import custom
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("opts", [dict(kernel=1)], ids=["valu"])
+@pytest.mark.parametrize("opts", [dict(), dict(max_context_len=4096), dict(partition_tokens=64), dict(partition_tokens=16), dict(kernel=2),
+                                  dict(kernel=1)], ids=["whole", "pieces", "ranges", "cut", "fixed", "valu"])
 def test_tiles_of_minus_infinity(oracle_mod, opts):
     w = custom(1700, dtype=W.BF16, lens=[200, 500, 64, 333], hq=8, hkv=2, d=128, bs=16, lmax=256)
     w.q[:, :, 5] = 0x3F80                                                # q[5] = 1
