@@ -66,12 +66,21 @@ hipError_t launch_cache_append(const void *k_new, const void *v_new, void *k_cac
     // of 128 2.01 and 2.06, 1000 of four 2.24 and 2.31, 4000 of eight 6.66 and 6.87.
     const bool packed = words <= 32 && num_seqs > 1024;
     const int64_t per_group = packed ? kThreads / words : 1;
-    const int64_t grid = packed ? (num_seqs + per_group - 1) / per_group : num_seqs * chunks;
-    (packed ? kv_cache_append_kernel<true> : kv_cache_append_kernel<false>)<<<dim3(unsigned(grid)), dim3(kThreads), 0, stream>>>(
-        static_cast<const uint4 *>(k_new), static_cast<const uint4 *>(v_new),
-        static_cast<uint4 *>(k_cache), static_cast<uint4 *>(v_cache), block_tables, positions, num_seqs,
-        int(chunks), num_kv_heads, words_log2, block_size_log2, max_blocks_per_seq);
-    return hipGetLastError();
+    // a launch holds fewer than 2^32 threads: more sequences than fit go in several
+    constexpr int64_t kMostGroups = (int64_t(1) << 32) / kThreads - 1;
+    const int64_t most = packed ? kMostGroups * per_group : kMostGroups / chunks;
+    if (most == 0) return hipErrorInvalidValue;  // the words of one sequence alone
+    for (int64_t n = 0; n < num_seqs; n += most) {
+        const int64_t seqs = num_seqs - n < most ? num_seqs - n : most;
+        const int64_t grid = packed ? (seqs + per_group - 1) / per_group : seqs * chunks;
+        (packed ? kv_cache_append_kernel<true> : kv_cache_append_kernel<false>)<<<dim3(unsigned(grid)), dim3(kThreads), 0, stream>>>(
+            static_cast<const uint4 *>(k_new) + n * words, static_cast<const uint4 *>(v_new) + n * words,
+            static_cast<uint4 *>(k_cache), static_cast<uint4 *>(v_cache), block_tables + n * max_blocks_per_seq,
+            positions + n, int(seqs), int(chunks), num_kv_heads, words_log2, block_size_log2, max_blocks_per_seq);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace kvc
