@@ -1,4 +1,4 @@
-"""What the compiler made of the balanced decode kernel's publication protocol (no GPU needed).
+"""What the compiler made of the balanced decode kernels' publication protocols (no GPU needed).
 
 A cut row's partial travels from one wavefront to another inside a launch: the writer stores
 it with device-scope accesses, waits until those stores have completed and only then adds to
@@ -20,13 +20,13 @@ from paper_2503_13773_amd import build as B
 SRC = os.path.join(B.CSRC, "paged_attention_mfma_stream.hip")
 
 
-def _assembly(tmp_path):
+def _assembly(tmp_path, src=SRC):
     hipcc = B._hipcc()
     if not (shutil.which(hipcc) or os.path.exists(hipcc)):
         pytest.skip("hipcc not available")
     out = tmp_path / "stream.s"
     flags = [f for f in B.FLAGS if f != "-fPIC"]
-    r = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", SRC, "-o", str(out)], capture_output=True, text=True)
+    r = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", src, "-o", str(out)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     return out.read_text().splitlines()
 
@@ -61,3 +61,33 @@ def test_partial_stores_complete_before_the_publication(tmp_path):
                 f"{name}: no wait for the partial's stores before `{body[i]}`"
             checked += 1
     assert checked >= 4
+
+
+def test_pieces_are_published_before_they_are_counted(tmp_path):
+    """The kernel of few rows: every wavefront of a workgroup waits for its own stores of the piece, then all meet at a
+    barrier, then one lane counts the piece at the row's counter (an add whose result it reads)."""
+    kernels, name = {}, None
+    for ln in _assembly(tmp_path, os.path.join(B.CSRC, "paged_attention_mfma_rows.hip")):
+        m = re.match(r"^(_ZN\S*pa_rows_mfma_kernel\S*):", ln)
+        if m:
+            name = m.group(1)
+            kernels[name] = []
+        elif ln.startswith(".Lfunc_end"):
+            name = None
+        elif name is not None:
+            kernels[name].append(ln.strip())
+    checked = 0
+    for name, body in kernels.items():
+        adds = [i for i, ln in enumerate(body) if ln.startswith("global_atomic_add")]
+        stores = [i for i, ln in enumerate(body) if ln.startswith("buffer_store_dword") and "sc1" in ln]
+        assert bool(adds) == bool(stores), name             # the schedule-building instance has neither
+        for i in adds:
+            before = [j for j in stores if j < i]
+            assert before and not [j for j in stores if j > i], (name, body[i])
+            between = body[before[-1] + 1:i]
+            waits = [j for j, ln in enumerate(between) if re.match(r"s_waitcnt\b.*vmcnt\(0\)", ln)]
+            assert waits, f"{name}: no wait for the piece's stores before `{body[i]}`"
+            assert any(ln.startswith("s_barrier") for ln in between[waits[0]:]), \
+                f"{name}: no barrier between the wait for the piece's stores and `{body[i]}`"
+            checked += 1
+    assert checked >= 3, sorted(kernels)
