@@ -71,11 +71,15 @@ typedef enum {
     KVC_KERNEL_MFMA_BALANCED = 4 /* matrix-core tiles, persistent grid: the batch's (sequence, kv head,
                             16-token tile) work is flattened and cut into equal per-wavefront ranges;
                             bf16, head_dim 128, block_size >= 4, group <= 16, num_seqs <= 4096.  AUTO
-                            also takes it for bf16 at head_dim 64 (32-token tiles).  Without a
+                            also takes it for bf16 at head_dim 64 (32-token tiles) where there is enough
+                            work for it (small calls, and those with a partition_tokens of the
+                            caller's, stay on kernel 1); kvc_attn_plan reports 4 for these, but 4
+                            asked for explicitly is refused at head_dim 64: pass AUTO.  Without a
                             partition_tokens of the caller's, short contexts (bound of at most 512
-                            tokens; 640 to 1024 at head_dim 64) are dealt out by rows, one per workgroup, and few
-                            rows (up to 64 sequences and 128 (sequence, kv head) rows of moderate
-                            length) by pieces of rows, instead of ranges */
+                            tokens and up to 2048 (sequence, kv head) rows; 640 to 1024 tokens at
+                            head_dim 64) are dealt out by rows, one per workgroup, and few rows (up to
+                            64 sequences and 128 rows of moderate length) by pieces of rows, instead
+                            of ranges */
 } kvc_kernel;
 
 typedef struct {
@@ -100,7 +104,8 @@ typedef struct {
 
 /* What the library will do for a descriptor (filled by kvc_attn_plan). */
 typedef struct {
-    int32_t kernel;            /* the kvc_kernel that will run (never AUTO) */
+    int32_t kernel;            /* the kvc_kernel that will run (never AUTO).  At head_dim 64 a 4 is AUTO's
+                                  own choice and is not accepted back in desc->kernel */
     int32_t partition_tokens;
     int32_t max_partitions;    /* partitions per sequence the grid provides for (balanced kernel:
                                   partial slots per wavefront) */
@@ -119,8 +124,13 @@ KVC_API int kvc_last_hip_error(void);
 KVC_API int kvc_attn_plan(const kvc_attn_desc *desc, kvc_attn_plan_info *plan);
 
 /* Bytes of device workspace kvc_paged_attention_decode needs for `desc`
- * (0 when no sequence can span more than one partition, or on a bad desc).  For the balanced
- * kernel it depends on the group size only, not on the batch or the context lengths. */
+ * (0 when no sequence can span more than one partition, or on a bad desc).  At head_dim 128 the
+ * balanced kernel's workspace depends on the group size only, not on the batch or the context
+ * lengths.  At head_dim 64 (bf16, AUTO) a descriptor asks for at least what the balanced kernel
+ * needs for any smaller batch or bound of the same heads, also where its own call needs nothing; the
+ * vector-ALU and fixed-partition kernels promise no such order: their partitions grow with the batch,
+ * so a smaller one can need more.  A call is refused only for what it needs itself, which can be less
+ * than what is reported here. */
 KVC_API size_t kvc_paged_attention_decode_workspace_bytes(const kvc_attn_desc *desc);
 
 /*
@@ -137,8 +147,9 @@ KVC_API size_t kvc_paged_attention_decode_workspace_bytes(const kvc_attn_desc *d
  *   - Accumulation is fp32; bf16 output is rounded to nearest even.
  *   - Split-K: a long context is cut into pieces whose (max, sum, accumulator) partials go
  *     through the workspace.  The balanced kernel (KVC_KERNEL_MFMA_BALANCED, what AUTO picks for
- *     bf16 / head_dim 128 and often at head_dim 64) is ONE launch: the last wavefront to finish a piece of a cut context
- *     merges its partials and writes the row.  The other kernels are followed by a merge launch.
+ *     bf16 / head_dim 128 and for larger calls at head_dim 64) is ONE launch: the last wavefront or
+ *     workgroup to finish a piece of a cut context merges its partials and writes the row.  The other
+ *     kernels are followed by a merge launch where a context can span more than one partition.
  *   - `workspace`: device memory, 256-byte aligned, at least
  *     kvc_paged_attention_decode_workspace_bytes(desc); may be NULL when that is 0.  Its first
  *     4096 bytes hold arrival counters that must be 0 when a call starts:
@@ -208,8 +219,8 @@ KVC_API int kvc_paged_attention_decode_scheduled(const void *q, const void *k_ca
  * the split-K workspace is a fixed region of KVC_NOALLOC_WORKSPACE_BYTES that the library
  * holds on every GPU it is loaded on (placed with the code object, kept until the process
  * ends).  The call allocates and frees nothing.
- *   - A descriptor whose kvc_paged_attention_decode_workspace_bytes exceeds
- *     KVC_NOALLOC_WORKSPACE_BYTES is refused with KVC_ERR_WORKSPACE (nothing is launched);
+ *   - A call that needs more workspace than KVC_NOALLOC_WORKSPACE_BYTES (never more than
+ *     kvc_paged_attention_decode_workspace_bytes) is refused with KVC_ERR_WORKSPACE (nothing is launched);
  *     every descriptor the balanced kernel serves fits.
  *   - The device that owns `hip_stream` must be the current device.  The first call on a
  *     device looks up the region's address (a HIP symbol query); make that call outside a
@@ -247,9 +258,10 @@ KVC_API int kvc_validate_attention_inputs(const int32_t *block_tables, const int
  * the matrix cores (any block size): on 32x32 tiles when the scale is positive (two heads of a KV
  * head per wavefront for even group sizes, one head otherwise), on 16x16 tiles for other scales or
  * when desc->kernel is KVC_KERNEL_MFMA; bf16 with head_dim 64 runs on 32x32 tiles with the softmax
- * weights kept at fp32 accuracy (any group size, any scale; calls with max_query_len 1 excepted);
- * everything else (fp32, larger groups at head_dim 128) on the vector ALUs, one workgroup per query row
- * and head chunk.  No workspace.  desc->max_context_len and partition_tokens are ignored; desc->kernel must
+ * weights kept to 16 bits (any group size, any scale), except one query row per sequence, launches of a
+ * few rows, batches that are mostly decode steps and bounds far above the rows there are; these and
+ * everything else (fp32, larger groups at head_dim 128) run on the vector ALUs, one workgroup per query
+ * row and head chunk.  No workspace.  desc->max_context_len and partition_tokens are ignored; desc->kernel must
  * be valid for the shape and is otherwise ignored.
  */
 KVC_API int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *v_cache,

@@ -1,5 +1,5 @@
-// One 16-token tile of decode attention on the gfx950 matrix cores, shared by the MFMA
-// partial kernels (bf16, head_dim 128).  Lane = 16*quad + r throughout.
+// One 16-token tile of decode attention on the gfx950 matrix cores (bf16, head_dim 128), shared by the decode
+// kernels; the 32-token tile of head_dim 64 is further down.  Lane = 16*quad + r throughout.
 //
 //   S[token][head]  = K[16 x 128] . Q^T[128 x 16]       4 x v_mfma_f32_16x16x32_bf16
 //       A operand: lane holds K[token r][32j + 8*quad .. +7]; B operand: the same dims of
@@ -171,10 +171,11 @@ __device__ inline void compute_tile(HeadState &st, const bf16x8 (&ka)[4], uint4 
 //                    row-wise, 8 bytes (dims 4r .. 4r+3) of a token per lane, 16 lanes read one 128-byte
 //                    row; MFMA number e yields dims {4*row + e}.
 //
-// The weights keep fp32 accuracy: a weight enters the product as the sum of two bf16 values (its
+// The weights keep 16 bits: a weight enters the product as the sum of two bf16 values (its
 // upper bits and the rounded rest, 2^-16 relative) and the normaliser sums the fp32 weights.  The upper part
 // is cut off and the rest made positive by 2^-23 of the weight (a factor all weights share), so that
-// an infinity in V keeps its sign, which a rest of 0 or of the other sign would turn into NaN.
+// an infinity in V keeps its sign, which a rest of 0 or of the other sign would turn into NaN (a weight below
+// about 2^-110 of the largest leaves no rest, and makes one of it).
 constexpr int kTileTokens64 = 32;
 
 __device__ inline uint2 load8_stream(const uint16_t *p) {

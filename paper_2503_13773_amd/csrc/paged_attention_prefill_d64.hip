@@ -1,9 +1,9 @@
 // Causal attention of many query positions per sequence over the block-allocated KV cache for
-// head_dim 64 (gfx950, bf16) on 32x32x16 matrix-core tiles, with softmax weights at fp32 accuracy.
+// head_dim 64 (gfx950, bf16) on 32x32x16 matrix-core tiles, with softmax weights kept to 16 bits.
 //
 // Bound: the vector issue port.  Per 32 tokens x 32 score columns a wavefront needs 12 matrix
 // instructions (4 for K.Q, 8 for V.P) and about 105 plain vector instructions plus 16 exponentials.
-// The weights stay in fp32 up to the product with V: a weight goes into the matrix core as the sum
+// The weights stay in fp32 up to the product with V, where a weight goes into the matrix core as the sum
 // of two bf16 values (its upper bits and the rounded rest, 2^-16 relative), the normaliser
 // sums the fp32 weights.  A recomputation of 1999 tokens (32 / 8 heads) takes 35 to 39 us = 420 to 470 TFLOP/s; on the
 // vector ALUs, with one workgroup per query row, it took 503 us (every K and V row read once per query row

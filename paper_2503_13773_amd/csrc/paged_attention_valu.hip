@@ -3,18 +3,19 @@
 // Computes, for one (sequence, chunk of query heads sharing a KV head, partition of the
 // context), the un-normalised softmax-weighted sum of V rows together with the running
 // max and sum, reading K and V through the block table (block-allocated KV cache:
-// paper Section 1 and 3.3.1).  It serves fp32 tensors, head_dim 64 and any
-// power-of-two block size; bf16 / head_dim 128 shapes normally take the MFMA kernel.
+// paper Section 1 and 3.3.1).  It serves any supported shape: fp32 tensors, blocks of 1 or 2
+// tokens, groups above 16, and at head_dim 64 the calls too small for the matrix-core kernels; other bf16
+// shapes normally take those.
 //
 // Mapping: a token row of K or V is D*sizeof(T) bytes = LR lanes x 16 bytes, so one
 // wavefront load covers TPL = 64/LR tokens, fully coalesced.  Each group of LR lanes
 // keeps its own online-softmax state over the tokens it sees (no cross-lane traffic in
 // the loop beyond the LR-lane dot-product reduction); the TPL groups, then the four
-// wavefronts, are merged with the log-sum-exp rule at the end.  Scores and softmax are
+// (or, in launches of at most a workgroup per compute unit, sixteen) wavefronts, are merged with the log-sum-exp rule at the end.  Scores and softmax are
 // in natural-log units, accumulation in fp32.
 //
 // PREFILL variant (causal attention of several query positions per sequence, the recompute
-// path of Section 2.5 / 3.5, for the shapes the MFMA prefill kernel does not take): a
+// path of Section 2.5 / 3.5, for the calls the matrix-core prefill kernels do not take): a
 // "sequence" of the grid is one query row; the row finds its sequence n by a search over
 // q_start, attends to the first S_n - Qn + i + 1 tokens of n's block list in one partition and
 // writes its normalised output directly.

@@ -1,4 +1,4 @@
-"""Decode attention at head_dim 64 on the balanced matrix-core kernel (32-token tiles, weights at fp32 accuracy) against
+"""Decode attention at head_dim 64 on the balanced matrix-core kernel (32-token tiles, weights kept to 16 bits) against
 the fp64 oracle.  Tolerance as in test_gpu_prefill_d64: one rounding of the output to bf16 plus weights that enter the
 product as two bf16 values (2^-16 relative each)."""
 import numpy as np

@@ -1,4 +1,4 @@
-"""Causal multi-query attention at head_dim 64 (32x32 matrix-core tiles, weights at fp32 accuracy) against the
+"""Causal multi-query attention at head_dim 64 (32x32 matrix-core tiles, weights kept to 16 bits) against the
 fp64 oracle.
 
 Tolerance: the output is one rounding to bf16 (2^-9 relative) of a value whose own error is that of fp32 sums and of
