@@ -11,8 +11,9 @@
 // wavefront load covers TPL = 64/LR tokens, fully coalesced.  Each group of LR lanes
 // keeps its own online-softmax state over the tokens it sees (no cross-lane traffic in
 // the loop beyond the LR-lane dot-product reduction); the TPL groups, then the four
-// (or, in launches of at most a workgroup per compute unit, sixteen) wavefronts, are merged with the log-sum-exp rule at the end.  Scores and softmax are
-// in natural-log units, accumulation in fp32.
+// wavefronts (sixteen in launches of at most a workgroup per compute unit, where the registers
+// allow it), are merged with the log-sum-exp rule at the end.  Scores and softmax are in
+// natural-log units, accumulation in fp32.
 //
 // PREFILL variant (causal attention of several query positions per sequence, the recompute
 // path of Section 2.5 / 3.5, for the calls the matrix-core prefill kernels do not take): a
