@@ -724,7 +724,7 @@ int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *
     // for the 16x16-tile kernel whatever the shape
     const bool tiles32 = p.scale_log2e > 0.0f && desc->kernel != KVC_KERNEL_MFMA;
     const hipError_t e = tiles32 ? kvc::launch_prefill_mfma32(q, k_cache, v_cache, block_tables, context_lens, q_start,
-                                                              out, p, static_cast<hipStream_t>(hip_stream))
+                                                              out, p, total_q, static_cast<hipStream_t>(hip_stream))
                                  : kvc::launch_prefill_mfma(q, k_cache, v_cache, block_tables, context_lens, q_start,
                                                             out, p, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? KVC_OK : hip_failed(e);

@@ -110,10 +110,17 @@ hipError_t launch_prefill_mfma(const void *q, const void *k_cache, const void *v
                                const int32_t *block_tables, const int32_t *context_lens,
                                const int32_t *q_start, void *out, const PrefillParams &p,
                                hipStream_t stream);
+// total_q: query rows of all sequences.
 hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void *v_cache,
                                  const int32_t *block_tables, const int32_t *context_lens,
-                                 const int32_t *q_start, void *out, const PrefillParams &p,
+                                 const int32_t *q_start, void *out, const PrefillParams &p, int total_q,
                                  hipStream_t stream);
+// Long requests: HEADS (1, 2 or 4, a divisor of the group) query heads and 256 / HEADS query rows per workgroup.
+template <int HEADS>
+hipError_t launch_prefill_wide(const void *q, const void *k_cache, const void *v_cache,
+                               const int32_t *block_tables, const int32_t *context_lens,
+                               const int32_t *q_start, void *out, const PrefillParams &p,
+                               hipStream_t stream);
 // head_dim 64, any group size and scale; rows past max_query_len of a sequence are not computed.
 constexpr int kPrefill64Threads = 512;  // of a workgroup
 hipError_t launch_prefill_d64(const void *q, const void *k_cache, const void *v_cache,

@@ -1,0 +1,567 @@
+// Causal attention of many query positions over the block-allocated KV cache, long requests (gfx950, bf16, head_dim
+// 128, positive scale): wavefronts of 64 score columns on 32x32x16 matrix-core tiles.  Included by one source per
+// HEADS, so that they compile side by side.
+//
+// What bounds it.  Wavefronts of 32 columns, two per SIMD (paged_attention_prefill32.hip), read 16 KiB of K and V
+// operands from LDS per 32 x 32 scores: 128 KiB per step of a compute unit, 1024 cycles of LDS bandwidth against 1024
+// matrix cycles; a step takes about 1500 cycles.  Here a wavefront owns two groups of 32 columns that share every
+// operand read, which halves the LDS reads, the address arithmetic and the scalar work per score.  128 accumulator and
+// 64 Q registers (AGPRs, which only matrix instructions touch) leave room for one wavefront per SIMD, so everything
+// that hides latency is in the order of the instructions: a step of 64 columns takes 1390 cycles for 1024 matrix cycles.
+// The issue of one wavefront is what is left: about 220 instructions per step of 4 to 5 cycles each, 8 for an
+// exponential (without loads, LDS reads and barriers a step still takes 1160 cycles).  Long launches run at the power
+// limit (1.75 to 1.9 of 2.4 GHz), where the LDS reads saved count as well.  32 / 8 heads, one request, kernel of 32
+// columns / this one: 3000 tokens 82.4 / 77.9 us, 4096 132.6 / 120.8, 8192 480 / 444, 16384 1850 / 1711 (1285
+// TFLOP/s); three of 3000 181 / 168, six of 4900 774 / 702.
+//
+// Workgroup = (sequence, HEADS query heads of one KV head, 256 / HEADS consecutive query rows), four wavefronts, one
+// workgroup per compute unit.  Column C = kWaveRows * head + row of a wavefront is column c = C % 32 of group C / 32.
+// Layouts of the tiles, of the weights and of the LDS stages are those of paged_attention_prefill32.hip: lane = 32 *
+// half + c holds the 16 scores of column c against tokens 8 (v / 4) + 4 half + v % 4; K rows with 16-byte chunks
+// XOR-permuted by the row, V rows with 64-byte granules rotated by the row, both written by direct loads.
+//
+// Turn s of the pipeline: S(s + 1) = K . Q (matrix instructions 0 .. 15), the weights of step s, and O += V . P of step
+// s - 1 (16 .. 31).  Three steps are in flight, so the softmax arithmetic spreads over the whole turn.
+//
+// The reference point of a column is set kBias above its largest score, and moves when some weight reaches 2: that
+// shows in the exponent bits of the rounded weights, which are collected by OR (10 instructions instead of the 20 of a
+// running maximum).  The weights of the step are then made again from its scores, which stay in registers; weights are
+// below 2 as they reach O and the sum, and below 2^kBias of the largest at the last move.
+//
+// The score products are inline asm: the compiler would put their results into AGPRs and copy each score.  It inserts
+// no wait states for them, so nothing near them needs any: scores are read two and more matrix instructions after the
+// last one that writes them, operands come from LDS and from Q (checked in the compiled form by a test).
+#pragma once
+
+#include <float.h>
+#include <math.h>
+
+#include <type_traits>
+
+#include "kvc_internal.h"
+#include "pa_mfma_tile.h"
+
+namespace kvc {
+
+namespace {
+
+using namespace mfma;
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kStepTokens = 32;
+constexpr int kStageBytes = kStepTokens * D * 2;  // K (or V) rows of a step: 32 rows x 256 bytes
+constexpr int kRing = 4;                          // stages of K and of V
+constexpr int kLoads = 2;                         // 1 KiB loads of K (and of V) per wavefront and step
+constexpr float kBias = 7.0f;                     // powers of two that the reference point is set above the largest score
+
+template <int I, int N, class F>
+__device__ inline void static_for(const F &f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// The value lane l ^ 32 holds, next to this lane's: one swap of the two 32-lane halves.
+__device__ inline float max_over_halves(float x) {
+    const unsigned u = __float_as_uint(x);
+    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ inline float sum_over_halves(float x) {
+    const unsigned u = __float_as_uint(x);
+    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Byte offset inside a V stage of what this lane reads for dim block b (the transposing read hands lane i of a 16-lane
+// block the i-th element of the four 16-element groups that lanes 4 k .. 4 k + 3 point at).
+__device__ inline int v_lane_offset(int b, int half, int c) {
+    const int i16 = c & 15, k = i16 >> 2;
+    return (4 * half + k) * 256 + ((b + k) & 3) * 64 + 32 * (c >> 4) + 8 * (i16 & 3);
+}
+// Half H of the V operand of slice N: tokens 16 N + 8 H + 4 * half .. +3 of the lane's dim.
+template <int N, int H>
+__device__ inline uint2 read_v_half(const unsigned char *vlane) {
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef v4i16 __attribute__((address_space(3))) * lds_v4i16_ptr;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vlane + (16 * N + 8 * H) * 256)));
+}
+// V rows at or past `vlim` have weights of 0 and may hold NaN.
+template <int N>
+__device__ inline void mask_v_operand(uint2 (&va)[2], int vlim, int half) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const int tok = 16 * N + 8 * g + 4 * half;
+        va[g].x &= (tok < vlim ? 0xffffu : 0u) | (tok + 1 < vlim ? 0xffff0000u : 0u);
+        va[g].y &= (tok + 2 < vlim ? 0xffffu : 0u) | (tok + 3 < vlim ? 0xffff0000u : 0u);
+    }
+}
+__device__ inline bf16x8 v_operand(const uint2 (&va)[2]) {
+    const uint4 aw = {va[0].x, va[0].y, va[1].x, va[1].y};
+    return __builtin_bit_cast(bf16x8, aw);
+}
+__device__ inline bf16x8 four_words(const uint32_t (&w)[8], int n) {
+    const uint4 v = {w[4 * n], w[4 * n + 1], w[4 * n + 2], w[4 * n + 3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+// Dims 16 J + 8 * half .. +7 of a row with XOR-permuted chunks; c: the row.
+template <int J>
+__device__ inline bf16x8 read_k_operand(const unsigned char *krow, int half, int c) {
+    return *reinterpret_cast<const bf16x8 *>(krow + (((2 * J + half) ^ (c & 15)) << 4));
+}
+
+// 16 bytes per lane from global memory straight into LDS, to lds_addr + IMM + 16 * lane (lds_addr uniform).  The compiler
+// does not see these accesses: barriers order them against LDS reads, wait_for() counts them.
+template <int IMM>
+__device__ inline void load_rows(const void *base, uint32_t off, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" :: "s"(lds_addr), "v"(off), "s"(base), "n"(IMM) : "memory");
+}
+__device__ inline void load_lane_to_lds(const void *addr, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(addr) : "memory");
+}
+// Waits until at most LOADS of the wavefront's loads (and stores) and LDS of its LDS reads are under way.
+template <int LOADS, int LDS>
+__device__ inline void wait_for() {
+    static_assert(LOADS < 64 && LDS < 16, "fields of the wait instruction");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((LOADS & 15) | (LOADS >> 4) << 14 | 7 << 4 | LDS << 8);
+    asm volatile("" ::: "memory");
+}
+__device__ inline void barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Nothing moves across this point when the compiler orders the instructions of a turn.
+#define KVC_PIN() __builtin_amdgcn_sched_barrier(0)
+
+// Chunk of the turn (one matrix instruction each) in which the arithmetic of score e starts: argument, exponential,
+// rounding and pair sum, sum, one chunk after the other.  Score e: register 2 (e / 4) + e % 2 of group (e / 2) % 2.
+constexpr int arg_chunk(int e) { return e * 3 / 4; }
+// Chunk of load i of the turn, K rows first.  Behind the LDS reads, one in two chunks: 1402 cycles a turn; all four in
+// two chunks 1391, but between the LDS reads 1426 to 1470.
+constexpr int load_chunk(int i) { return 24 + 2 * i; }
+
+// One turn: S of step `next`, the weights of step cur (raw scores in x), O += V . P of the step before (weights in w).
+//     chunks  0 .. 15   S += K operand j . Q, both groups; reads K operands 4 .. 7, then the V operands
+//     chunks 16 .. 31   O block += V operand . weights, both groups; reads K operands 0 .. 3 of the step after next,
+//                       requests the K rows of the step four ahead of cur and the V rows of the step two ahead
+// The turn starts with ka[0 .. 3] = K operands of step next.  On return x holds the raw scores of step next, w the
+// weights of step cur.  MASKED: `vlim_prev` = tokens of the step before that some column sees, `limit_next` = tokens of
+// step next that this lane's columns see.
+template <bool MASKED, class Issue, class Lookup, class Math>
+__device__ inline void pipeline_turn(floatx16 (&acc)[2][4], float (&x)[2][16], uint32_t (&w)[2][8], float (&lsum)[2], float (&m)[2],
+                                     bf16x8 (&ka)[8], const unsigned char *krow1, const unsigned char *krow2, const unsigned char *sv_prev,
+                                     const int (&voff)[4], const bf16x8 (&qb)[2][8], float scale_log2e, int vlim_prev,
+                                     const int (&limit_next)[2], int half, int c, const Issue &issue,
+                                     const Lookup &lookup, const Math &math) {
+    float arg[32], pf[32], pair[16];
+    uint2 va[8][2];
+    uint32_t wn[2][8], any[4];
+    floatx16 s[2];
+    const float neg_m[2] = {-m[0], -m[1]}, lsum_before[2] = {lsum[0], lsum[1]};
+    static_for<0, 32>([&](auto chunk) __attribute__((always_inline)) {
+        constexpr int T = decltype(chunk)::value;
+        KVC_PIN();
+        if constexpr (T < 16) {
+            constexpr int J = T >> 1, G = T & 1;
+            if constexpr (J == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s[G]) : "v"(ka[J]), "a"(qb[G][J]));
+            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s[G]) : "v"(ka[J]), "a"(qb[G][J]));
+        } else {
+            constexpr int U = (T - 16) >> 1, G = T & 1, N = U >> 2, B = U & 3;
+            if constexpr (G == 0 && MASKED) mask_v_operand<N>(va[U], vlim_prev, half);
+            acc[G][B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va[U]), four_words(w[G], N), acc[G][B], 0, 0, 0);
+        }
+        if constexpr (T < 4) ka[4 + T] = read_k_operand<4 + T>(krow1, half, c);
+        if constexpr (T >= 4 && T < 20) {
+            constexpr int U = (T - 4) >> 1, H = T & 1;
+            va[U][H] = read_v_half<(U >> 2), H>(sv_prev + voff[U & 3]);
+        }
+        if constexpr (T >= 20 && T < 24) ka[T - 20] = read_k_operand<T - 20>(krow2, half, c);
+        static_for<0, 32>([&](auto score) __attribute__((always_inline)) {
+            constexpr int E = decltype(score)::value, P = E >> 1;
+            constexpr int G = P & 1, V = 2 * (P >> 1) + (E & 1);
+            if constexpr (arg_chunk(E) == T) arg[E] = __builtin_fmaf(x[G][V], scale_log2e, neg_m[G]);
+            if constexpr (arg_chunk(E) + 1 == T) pf[E] = __builtin_amdgcn_exp2f(arg[E]);
+            if constexpr ((E & 1) && arg_chunk(E) + 2 == T) {
+                wn[G][P >> 1] = pack_bf16(pf[E - 1], pf[E]);
+                asm volatile("" : "+v"(wn[G][P >> 1]));
+                pair[P] = pf[E - 1] + pf[E];
+            }
+            if constexpr ((E & 1) && arg_chunk(E) + 3 == T) {
+                lsum[G] += pair[P];
+                asm volatile("" : "+v"(lsum[G]));
+            }
+            if constexpr ((E & 7) == 7 && arg_chunk(E) + 3 == T) {   // words of pairs P - 3 .. P
+                constexpr int I = P >> 1;
+                uint32_t o = wn[0][I - 1] | wn[1][I - 1] | wn[0][I];
+                if constexpr (P >= 4) o = o | wn[1][I] | any[(P >> 2) - 1];
+                else o = o | wn[1][I];
+                asm volatile("" : "+v"(o));
+                any[P >> 2] = o;
+            }
+        });
+        if constexpr (T == 0) lookup();
+        if constexpr (T == 31) math();
+        static_for<0, 2 * kLoads>([&](auto load) __attribute__((always_inline)) {
+            if constexpr (T == load_chunk(decltype(load)::value)) issue(load);
+        });
+        if constexpr (MASKED && T == 18) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[g][v] = 8 * (v >> 2) + 4 * half + (v & 3) >= limit_next[g] ? -INFINITY : s[g][v];
+        }
+    });
+    KVC_PIN();
+    // Both ways to the join below have the accumulators in AGPRs: otherwise they are copied there and back in each turn.
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) asm volatile("" : "+a"(acc[g][b]));
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64((any[3] & 0x40004000u) != 0) != 0, 0)) {
+        // some weight is 2 or more (or NaN): a new reference point, and the weights by it
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            float top = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) top = fmaxf(top, x[g][v]);
+            const float m_new = fmaxf(m[g], max_over_halves(top) * scale_log2e + kBias);
+            const float alpha = __builtin_amdgcn_exp2f(m[g] - m_new);
+            m[g] = m_new;
+            lsum[g] = lsum_before[g] * alpha;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                acc[g][b] *= alpha;
+                asm volatile("" : "+a"(acc[g][b]));
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(x[g][2 * i], scale_log2e, -m_new));
+                const float b = __builtin_amdgcn_exp2f(__builtin_fmaf(x[g][2 * i + 1], scale_log2e, -m_new));
+                wn[g][i] = pack_bf16(a, b);
+                lsum[g] += a + b;
+            }
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[g][v] = s[g][v];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[g][i] = wn[g][i];
+    }
+}
+
+// SMALL: block_size < 8, rows gathered by a table look-up per lane.
+template <int HEADS, bool SMALL>
+__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void pa_prefill_wide_kernel(
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
+    const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
+    uint16_t *__restrict__ out, PrefillParams p, int query_tiles) {
+    constexpr int kWaveRows = 64 / HEADS;          // query rows of a wavefront
+    constexpr int kTileRows = 4 * kWaveRows;       // and of the workgroup
+    constexpr int kQBytes = 64 * D * 2;            // Q rows of a wavefront's columns
+    __shared__ __attribute__((aligned(1024))) unsigned char s_k[kRing * kStageBytes], s_v[kRing * kStageBytes], s_q4[4 * kQBytes];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int half = lane >> 5, c = lane & 31;
+    unsigned char *const s_q = s_q4 + wave * kQBytes;
+
+    const int chunks = p.num_q_heads / HEADS;
+    // blockIdx.x = head chunk + chunks * (seq + num_seqs * order), the longest query tiles first
+    const int chunk = blockIdx.x % chunks, index = blockIdx.x / chunks;
+    const int head0 = chunk * HEADS;
+    const int kvh = head0 / p.group;
+    const int n = index % p.num_seqs, qtile = query_tiles - 1 - index / p.num_seqs;
+    const int S = context_lens[n], qs = q_start[n], Qn = q_start[n + 1] - qs;
+    if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
+    const int last_pos = S - Qn + min(Qn, (qtile + 1) * kTileRows) - 1;  // position of the workgroup's last query row
+    const int steps = last_pos / kStepTokens + 1;
+    const int32_t *const table = block_tables + size_t(n) * p.max_blocks_per_seq;
+    // a wavefront past the last query row shadows that row
+    const int first_row = qtile * kTileRows + kWaveRows * wave;
+    const bool active = first_row < Qn;
+    const int i0 = min(first_row, Qn - 1);
+    const int nrows = min(kWaveRows, Qn - i0);
+    const int p0 = S - Qn + i0;         // position of row 0
+    const int wave_vis = p0 + nrows;    // tokens visible to some column
+
+    // This wavefront's share of a step's rows: 8 consecutive ones, inside one 16-row tile and one block (SMALL apart).
+    const size_t head_bytes = size_t(p.block_size) * D * 2;
+    const size_t block_bytes = head_bytes * p.num_kv_heads;
+    const unsigned char *const k_head = reinterpret_cast<const unsigned char *>(k_cache) + size_t(kvh) * head_bytes;
+    const unsigned char *const v_head = reinterpret_cast<const unsigned char *>(v_cache) + size_t(kvh) * head_bytes;
+    const int sub_mask = (1 << p.tiles_per_block_log2) - 1;
+    const int share_row = 8 * wave;
+    const int lchunk = lane & 15;
+    const int lrow = (share_row & 15) + (lane >> 4);  // row of load 0 in its tile; load 1: + 4
+    const int brow = lrow & (p.block_size - 1);       // in its block, where that holds 8 tokens (16 or more: lrow)
+    // offsets of load 1 are 1024 bytes on through its immediate, on both sides
+    const uint32_t k_off[kLoads] = {uint32_t(brow * 256 + ((lchunk ^ lrow) << 4)), uint32_t(brow * 256 + ((lchunk ^ (lrow + 4)) << 4))};
+    const uint32_t v_off = brow * 256 + ((4 * (((lchunk >> 2) - lrow) & 3) + (lchunk & 3)) << 4);
+    const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(s_k)) + 256 * share_row;
+    const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(s_v)) + 256 * share_row;
+    const uint32_t lds_q0 = uint32_t(reinterpret_cast<uintptr_t>(s_q));
+    const unsigned char *const k_lane = s_k + c * 256;
+    int voff[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) voff[b] = v_lane_offset(b, half, c);
+
+    // Block ids of the wavefront's rows, through the scalar cache a turn before the loads (SMALL: of this lane's rows in
+    // loads 0 and 1), then their byte offsets.  Rows past the last visible token repeat it (never used unmasked).
+    struct Ids { uint32_t a, b; };
+    int tok_next = share_row;
+    auto next_ids = [&]() __attribute__((always_inline)) -> Ids {
+        Ids id;
+        if constexpr (SMALL) {
+            const int tok = tok_next - (share_row & 15) + lrow;
+            id.a = table[min(tok, last_pos) >> p.block_size_log2];
+            id.b = table[min(tok + 4, last_pos) >> p.block_size_log2];
+        } else {
+            const unsigned tok = unsigned(min(tok_next, last_pos));
+            id.a = __builtin_amdgcn_readfirstlane(table[tok >> p.block_size_log2]);
+            id.b = ((tok >> 4) & sub_mask) * (kTileTokens * 256);
+        }
+        tok_next += kStepTokens;
+        return id;
+    };
+    using At = std::conditional_t<SMALL, Ids, uint64_t>;
+    auto offset_of = [&](const Ids &id) __attribute__((always_inline)) -> At {
+        if constexpr (SMALL) return id;
+        else return uint64_t(id.a) * block_bytes + id.b;
+    };
+    auto issue = [&](const unsigned char *head, uint32_t off, uint32_t lds, const At &at, auto load) __attribute__((always_inline)) {
+        constexpr int I = decltype(load)::value;
+        if constexpr (SMALL)
+            load_lane_to_lds(head + size_t(I ? at.b : at.a) * block_bytes + ((lrow + 4 * I) & (p.block_size - 1)) * 256 + (off & 255),
+                             __builtin_amdgcn_readfirstlane(lds + 1024 * I));
+        else
+            load_rows<1024 * I>(head + at, off, __builtin_amdgcn_readfirstlane(lds));
+    };
+    auto issue_k = [&](int stage, const At &at, auto load) __attribute__((always_inline)) {
+        issue(k_head, k_off[decltype(load)::value], lds_k0 + stage * kStageBytes, at, load);
+    };
+    auto issue_v = [&](int stage, const At &at, auto load) __attribute__((always_inline)) {
+        issue(v_head, v_off, lds_v0 + stage * kStageBytes, at, load);
+    };
+    // Q rows go through LDS as well: their loads are then waited for together with those of the first K and V rows.
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int C = 4 * i + (lane >> 4), row = min(C % kWaveRows, nrows - 1);
+        load_lane_to_lds(reinterpret_cast<const unsigned char *>(q) +
+                             (size_t(qs + i0 + row) * p.num_q_heads + head0 + C / kWaveRows) * (D * 2) + ((lchunk ^ (C & 15)) << 4),
+                         __builtin_amdgcn_readfirstlane(lds_q0 + 1024 * i));
+    }
+    // Rows of step j live in stages j % 4.  Turn s requests the K rows of step s + 4 (over those of step s) and the V rows
+    // of step s + 2 (over those of step s - 2), and reads K rows of steps s + 1 and s + 2 and V rows of step s - 1.  Before
+    // the barrier that ends it a wavefront waits for its LDS reads and for its loads up to the K rows of turn s - 1.
+    At at_v[2], at_k;
+    static_for<0, kRing>([&](auto i) __attribute__((always_inline)) {
+        constexpr int I = decltype(i)::value;
+        const At at = offset_of(next_ids());
+        static_for<0, kLoads>([&](auto load) __attribute__((always_inline)) {
+            issue_k(I, at, load);
+            if constexpr (I < kRing - 2) issue_v(I, at, load);
+        });
+        if constexpr (I >= kRing - 2) at_v[I - (kRing - 2)] = at;
+    });
+    at_k = offset_of(next_ids());
+    Ids ids;
+    // V rows of the step before the first: turn 0, or the last step if it is the first, multiplies them by weights of 0
+#pragma unroll
+    for (int i = 0; i < kStageBytes / 4096; ++i)
+        *reinterpret_cast<uint4 *>(s_v + (kRing - 1) * kStageBytes + (4 * i + wave) * 1024 + lane * 16) = uint4{0, 0, 0, 0};
+    wait_for<0, 0>();
+    barrier();
+
+    bf16x8 qb[2][8];
+    static_for<0, 8>([&](auto j) __attribute__((always_inline)) {
+        constexpr int J = decltype(j)::value;
+        qb[0][J] = read_k_operand<J>(s_q + c * 256, half, c);
+        qb[1][J] = read_k_operand<J>(s_q + (32 + c) * 256, half, c);
+    });
+    floatx16 acc[2][4];
+    float x[2][16], m[2], lsum[2];
+    uint32_t w[2][8];
+    bf16x8 ka[8];
+    int seen[2];  // tokens that a column sees
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[g][b][v] = 0.f;
+        lsum[g] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[g][i] = 0;
+        seen[g] = p0 + min((32 * g + c) % kWaveRows, nrows - 1) + 1;
+    }
+    {  // scores of step 0
+        floatx16 sc[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sc[0][v] = sc[1][v] = 0.f;
+        static_for<0, 8>([&](auto j) __attribute__((always_inline)) {
+            constexpr int J = decltype(j)::value;
+            const bf16x8 a = read_k_operand<J>(k_lane, half, c);
+            sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb[0][J], sc[0], 0, 0, 0);
+            sc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb[1][J], sc[1], 0, 0, 0);
+        });
+        static_for<0, 4>([&](auto j) __attribute__((always_inline)) {
+            constexpr int J = decltype(j)::value;
+            ka[J] = read_k_operand<J>(k_lane + kStageBytes, half, c);
+        });
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            float top = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                x[g][v] = 8 * (v >> 2) + 4 * half + (v & 3) >= seen[g] ? -INFINITY : sc[g][v];
+                top = fmaxf(top, x[g][v]);
+            }
+            // not below the lowest finite value: a first step of -inf scores weighs nothing then, instead of -inf - -inf
+            m[g] = fmaxf(max_over_halves(top) * p.scale_log2e + kBias, -FLT_MAX);
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) asm volatile("" : "+a"(qb[g][j]));
+    wait_for<0, 0>();
+    barrier();  // the first K stage has been read, and Q: turn 0 may load step 4 over it
+
+    int s = 0;
+#define KVC_TURN(MASKED, PHASE, VLIM, LIMIT0, LIMIT1)                                                                 \
+    {                                                                                                                 \
+        const int ph = (PHASE);                                                                                       \
+        auto turn_math = [&]() __attribute__((always_inline)) {                                                       \
+            at_v[0] = at_v[1];                                                                                        \
+            at_v[1] = at_k;                                                                                           \
+            at_k = offset_of(ids);                                                                                    \
+        };                                                                                                            \
+        auto turn_issue = [&](auto load) __attribute__((always_inline)) {                                             \
+            constexpr int I = decltype(load)::value;                                                                  \
+            if constexpr (I < kLoads) issue_k(ph, at_k, load);                                                        \
+            else issue_v((ph + kRing - 2) % kRing, at_v[0], std::integral_constant<int, I - kLoads>{});               \
+        };                                                                                                            \
+        auto turn_lookup = [&]() __attribute__((always_inline)) { ids = next_ids(); };                                \
+        const int lim[2] = {LIMIT0, LIMIT1};                                                                          \
+        pipeline_turn<MASKED>(acc, x, w, lsum, m, ka, k_lane + ((ph + 1) % kRing) * kStageBytes,                      \
+                              k_lane + ((ph + 2) % kRing) * kStageBytes, s_v + ((ph + kRing - 1) % kRing) * kStageBytes,\
+                              voff, qb, p.scale_log2e, VLIM, lim, half, c, turn_issue, turn_lookup, turn_math);       \
+        wait_for<((kRing - 3) * 2 + 1) * kLoads, 0>();                                                                \
+        barrier();                                                                                                    \
+        ++s;                                                                                                          \
+    }
+    const int plain = min((p0 + 1) / kStepTokens - 1, steps - 1);  // turns whose next step every column sees whole
+    // One after the other and not as paths of one loop: the compiler would keep a copy of the accumulators for each.
+    while (s + kRing <= plain) {
+        KVC_TURN(false, 0, 0, 0, 0)
+        KVC_TURN(false, 1, 0, 0, 0)
+        KVC_TURN(false, 2, 0, 0, 0)
+        KVC_TURN(false, 3, 0, 0, 0)
+    }
+    while (s < plain) KVC_TURN(false, s % kRing, 0, 0, 0)
+    while (s < steps - 1)
+        KVC_TURN(true, s % kRing, wave_vis - (s - 1) * kStepTokens, seen[0] - (s + 1) * kStepTokens, seen[1] - (s + 1) * kStepTokens)
+#undef KVC_TURN
+    // the last step, a turn without scores of a next one
+    {
+        float top[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            top[g] = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) top[g] = fmaxf(top[g], x[g][v]);
+            top[g] = fmaxf(m[g], max_over_halves(top[g]) * p.scale_log2e - 1.0f);
+        }
+        auto pv = [&](const unsigned char *sv, int vlim, const uint32_t (&ww)[2][8]) __attribute__((always_inline)) {
+            static_for<0, 8>([&](auto u) __attribute__((always_inline)) {
+                constexpr int U = decltype(u)::value, N = U >> 2, B = U & 3;
+                uint2 va[2] = {read_v_half<N, 0>(sv + voff[B]), read_v_half<N, 1>(sv + voff[B])};
+                mask_v_operand<N>(va, vlim, half);
+                acc[0][B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va), four_words(ww[0], N), acc[0][B], 0, 0, 0);
+                acc[1][B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va), four_words(ww[1], N), acc[1][B], 0, 0, 0);
+            });
+        };
+        pv(s_v + ((s + kRing - 1) % kRing) * kStageBytes, wave_vis - (s - 1) * kStepTokens, w);
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) asm volatile("" : "+a"(acc[g][b]));
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(top[0] > m[0] || top[1] > m[1]) != 0, 0)) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const float alpha = __builtin_amdgcn_exp2f(m[g] - top[g]);
+                lsum[g] *= alpha;
+                m[g] = top[g];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    acc[g][b] *= alpha;
+                    asm volatile("" : "+a"(acc[g][b]));
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(x[g][2 * i], p.scale_log2e, -m[g]));
+                const float b = __builtin_amdgcn_exp2f(__builtin_fmaf(x[g][2 * i + 1], p.scale_log2e, -m[g]));
+                w[g][i] = pack_bf16(a, b);
+                lsum[g] += a + b;
+            }
+        pv(s_v + (s % kRing) * kStageBytes, wave_vis - s * kStepTokens, w);
+    }
+    wait_for<0, 0>();  // nothing may still be landing in LDS when the workgroup's LDS is handed on
+    // lane (half, c) holds O[column 32 g + c][32 b + 8 a + 4 half .. +3] in acc[g][b][4 a .. 4 a + 3]
+    auto store = [&](int g, int b, const float (&o)[16], float inv) __attribute__((always_inline)) {
+        const int C = 32 * g + c, row = C % kWaveRows;
+        if (active && row < nrows) {
+            uint16_t *const dst = out + (size_t(qs + i0 + row) * p.num_q_heads + head0 + C / kWaveRows) * D + 32 * b + 8 * half;
+#pragma unroll
+            for (int a = 0; a < 4; a += 2) {
+                // halves swap four dims, so that each lane stores eight
+                const u32x2 lo = __builtin_amdgcn_permlane32_swap(pack_bf16(o[4 * a] * inv, o[4 * a + 1] * inv),
+                                                                  pack_bf16(o[4 * a + 4] * inv, o[4 * a + 5] * inv), false, false);
+                const u32x2 hi = __builtin_amdgcn_permlane32_swap(pack_bf16(o[4 * a + 2] * inv, o[4 * a + 3] * inv),
+                                                                  pack_bf16(o[4 * a + 6] * inv, o[4 * a + 7] * inv), false, false);
+                *reinterpret_cast<uint4 *>(dst + 8 * a) = uint4{lo[0], hi[0], lo[1], hi[1]};
+            }
+        }
+    };
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const float inv = 1.0f / sum_over_halves(lsum[g]);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            float o[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[v] = acc[g][b][v];
+            store(g, b, o, inv);
+        }
+    }
+}
+
+}  // namespace
+
+template <int HEADS>
+hipError_t launch_prefill_wide(const void *q, const void *k_cache, const void *v_cache, const int32_t *block_tables,
+                               const int32_t *context_lens, const int32_t *q_start, void *out, const PrefillParams &p,
+                               hipStream_t stream) {
+    constexpr int kRows64 = 4 / HEADS;  // 64-row units of a workgroup's query rows; max_query_tiles counts these
+    const int query_tiles = (p.max_query_tiles + kRows64 - 1) / kRows64;
+    const int64_t grid = int64_t(p.num_q_heads / HEADS) * p.num_seqs * query_tiles;
+    const auto kernel = p.block_size < 8 ? pa_prefill_wide_kernel<HEADS, true> : pa_prefill_wide_kernel<HEADS, false>;
+    kernel<<<dim3(unsigned(grid)), dim3(256), 0, stream>>>(static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
+                                                           static_cast<const uint16_t *>(v_cache), block_tables, context_lens,
+                                                           q_start, static_cast<uint16_t *>(out), p, query_tiles);
+    return hipGetLastError();
+}
+
+}  // namespace kvc

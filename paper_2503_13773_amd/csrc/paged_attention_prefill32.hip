@@ -742,14 +742,37 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     }
 }
 
+// Calls that the kernel of 64-column wavefronts takes (pa_prefill_wide.h), by heads per workgroup; 0: none.  One workgroup
+// of it fills a compute unit, so that a launch needs about 360 of them before the longest tiles no longer stand alone.
+// 32 columns / 64 columns, us, one request and 32 / 8 heads: 2500 tokens (320 workgroups) 58.7 / 64.3, 3000 (376) 81.7 /
+// 78.0, 4096 130 / 119; 64 / 8 heads: 1000 tokens (256) 27.6 / 31.8, 1500 (384) 50.0 / 44.4; 8 / 2 heads: 4096 (128) 56 / 88,
+// four of 4096 120 / 117.  Short requests pay for the start and end of a tile, 15000 cycles against 1400 per 32 tokens: four of
+// 1500 tokens, 32 / 8 heads, 77.8 / 80.1, of 2048 131 / 129, of 3000 260 / 251; with two workgroups per KV head, which share
+// its rows in L2, four of 1000 81.1 / 80.7 and of 1500 156 / 151 (64 / 8 heads).  Two heads per workgroup (16 / 8 heads): four
+// of 2500 96.6 / 99.9, 4096 240 / 228; one request of 8000 244 / 219.  One head: one request of 4096 132 / 129 (32 / 32), 125 /
+// 118 (28 / 4), but four of 4096 490 / 488 and 415 / 422.  Batches with a few long requests among short ones stay here.
+int wide_heads(const PrefillParams &p, int total_q) {
+    const int heads = p.group % 4 == 0 ? 4 : p.group % 2 == 0 ? 2 : 1;
+    const int64_t tile_rows = 256 / heads;
+    if (p.num_q_heads / heads * ((total_q + tile_rows - 1) / tile_rows) < 360) return 0;
+    if (total_q < int64_t(p.num_seqs) * p.max_query_tiles * 32) return 0;  // on average half the longest
+    const int least = heads == 4 ? (p.group % 8 == 0 ? 16 : 32) : heads == 2 ? 48 : 40;  // 64-row tiles of the longest
+    return p.max_query_tiles >= least && (heads > 1 || p.num_seqs == 1) ? heads : 0;
+}
+
 }  // namespace
 
 // Needs a positive scale (the max is taken over raw scores).  heads_per_chunk = 2: two heads of a
 // KV head per wavefront (even group sizes); 1: one head, twice the query rows.
 hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void *v_cache,
                                  const int32_t *block_tables, const int32_t *context_lens,
-                                 const int32_t *q_start, void *out, const PrefillParams &p,
+                                 const int32_t *q_start, void *out, const PrefillParams &p, int total_q,
                                  hipStream_t stream) {
+    switch (wide_heads(p, total_q)) {
+        case 4: return launch_prefill_wide<4>(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
+        case 2: return launch_prefill_wide<2>(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
+        case 1: return launch_prefill_wide<1>(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
+    }
     const auto *qq = static_cast<const uint16_t *>(q);
     const auto *kk = static_cast<const uint16_t *>(k_cache);
     const auto *vv = static_cast<const uint16_t *>(v_cache);

@@ -1,0 +1,86 @@
+"""Long requests: the prefill kernel of 64-column wavefronts (four, two or one query heads and 64, 128 or 256 query rows per
+workgroup), against attention in float64 on the dense sequence.
+
+Sizes are just above the lines from which that kernel takes a call, with row counts that leave wavefronts with part of
+their rows or none, contexts longer than the rows, blocks of 4 to 256 tokens, and NaN wherever no context reaches.
+
+Tolerance: weights are rounded to bf16 (2^-9 relative, with |V| < 6 at most 0.012) and so is the output (2^-9 relative)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import kvc_workloads as W
+from gpu_util import BF16_TOL, dev_tensor, out_to_f64
+from test_gpu_prefill import make, run
+from test_gpu_prefill_d64 import poison
+
+pytestmark = pytest.mark.gpu
+
+
+def takes(heads, hq, qlens):
+    """The rule by which the library picks the kernel, restated."""
+    tiles = -(-max(qlens) // 64)
+    least = {4: 16 if hq[0] // hq[1] % 8 == 0 else 32, 2: 48, 1: 40}[heads]
+    return (hq[0] // heads * -(-sum(qlens) // (256 // heads)) >= 360 and sum(qlens) >= len(qlens) * tiles * 32
+            and tiles >= least and (heads > 1 or len(qlens) == 1))
+
+
+def exact(w, q, qs):
+    qd, k, v = (dev_tensor(x, w.dtype) for x in (q, w.k_cache, w.v_cache))
+    out = np.zeros(q.shape)
+    group = w.num_q_heads // w.num_kv_heads
+    for n, S in enumerate(w.context_lens.tolist()):
+        rows = int(qs[n + 1] - qs[n])
+        ids = torch.from_numpy(w.block_tables[n, :-(-S // w.block_size)].astype(np.int64)).cuda()
+        for h in range(w.num_kv_heads):
+            kd, vd = (x[ids, h].reshape(-1, x.shape[3])[:S].double() for x in (k, v))
+            hidden = torch.arange(S, device="cuda")[None] > torch.arange(S - rows, S, device="cuda")[:, None]
+            for g in range(group):
+                score = qd[int(qs[n]):int(qs[n + 1]), h * group + g].double() @ kd.t().contiguous() * w.scale
+                out[int(qs[n]):int(qs[n + 1]), h * group + g] = (
+                    torch.softmax(score.masked_fill(hidden, -math.inf), dim=1) @ vd).cpu().numpy()
+    return out
+
+
+def check(w, q, qs, qlens, what):
+    print(f"[case] prefill wide {what}", flush=True)
+    got = out_to_f64(run(w, q, qs, max(qlens)))
+    ref = exact(w, q, qs)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= BF16_TOL
+
+
+@pytest.mark.parametrize("heads,hq,lens,qlens,bs", [
+    (4, (128, 16), [1000], [1000], 16), (4, (128, 16), [1100], [961], 4), (4, (128, 8), [1025], [1025], 8),
+    (4, (128, 16), [1301, 700, 33], [1000, 700, 33], 64), (4, (64, 16), [1985], [1985], 16), (4, (64, 16), [2111, 1990], [1999, 1990], 256),
+    (2, (32, 16), [3009], [3009], 16), (2, (32, 16), [3200], [3041], 4), (2, (48, 8), [3137], [3137], 8),
+    (1, (40, 40), [2497], [2497], 16), (1, (39, 13), [2600], [2561], 2)])
+def test_matches_float64(heads, hq, lens, qlens, bs):
+    assert takes(heads, hq, qlens)
+    w, q, qs = make(1300 + heads + bs, lens, qlens, *hq, bs=bs)
+    poison(w)
+    check(w, q, qs, qlens, f"{hq} {lens} {qlens} bs={bs}")
+
+
+def test_scores_that_keep_growing_move_the_reference_point():
+    """Every few steps the largest score so far is passed by more than the reference point allows, in all columns."""
+    w, q, qs = make(1350, [1030], [1030], 128, 16)
+    q[:, :, 1] = 0x3F80                                   # q[1] = 1
+    ramp = np.linspace(-40.0, 40.0, 1030).astype(np.float32)
+    for t in range(1030):
+        w.k_cache[w.block_tables[0, t // 16], :, t % 16, 1] = W.f32_to_bf16_bits(ramp[t:t + 1] * 8)[0]
+    check(w, q, qs, [1030], "ramp")
+
+
+def test_scores_of_minus_infinity_weigh_nothing():
+    """The first two steps' scores are -inf in every column, and single ones later."""
+    w, q, qs = make(1360, [1000], [1000], 128, 16)
+    q[:, :, 0] = 0x3F80
+    for t in [*range(64), 100, 511, 999]:
+        w.k_cache[w.block_tables[0, t // 16], :, t % 16, 0] = 0xFF80
+    print("[case] prefill wide -inf", flush=True)
+    got, ref = out_to_f64(run(w, q, qs, 1000))[64:], exact(w, q, qs)[64:]  # earlier rows see nothing else
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= BF16_TOL

@@ -91,3 +91,44 @@ def test_pieces_are_published_before_they_are_counted(tmp_path):
                 f"{name}: no barrier between the wait for the piece's stores and `{body[i]}`"
             checked += 1
     assert checked >= 3, sorted(kernels)
+
+
+def test_score_products_of_the_wide_prefill_need_no_wait_states(tmp_path):
+    """The wide prefill kernel's score products are inline asm, for which the compiler inserts no wait states: operands
+    must not come from a vector instruction one or two before, and the scores of a product must not be touched by a
+    vector instruction until two more matrix instructions (8 passes each, 11 states are needed) have been issued."""
+    def registers(operand):
+        m = re.match(r"^([va])\[(\d+):(\d+)\]$", operand) or re.match(r"^([va])(\d+)$", operand)
+        if not m:
+            return set()
+        return {(m.group(1), i) for i in range(int(m.group(2)), int(m.group(m.lastindex)) + 1)}
+
+    products, kernel = 0, False
+    recent, pending = [], {}      # the last instructions' results; registers of scores -> matrix instructions since
+    for ln in _assembly(tmp_path, os.path.join(B.CSRC, "paged_attention_prefill_wide4.hip")):
+        if re.match(r"^_ZN\S*pa_prefill_wide_kernel\S*:", ln):
+            kernel, recent, pending = True, [], {}
+        t = ln.strip()
+        if not kernel or not t or t[0] in ".;_":
+            continue
+        if t.startswith("s_endpgm"):
+            kernel = False
+            continue
+        op, _, rest = t.partition(" ")
+        operands = [o.strip() for o in rest.split(";")[0].split(",")]
+        touched = set().union(*map(registers, operands)) if operands else set()
+        if op.startswith("v_mfma_f32_32x32x16"):
+            pending = {r: n + 1 for r, n in pending.items() if n < 2}
+            if operands[0].startswith("v"):
+                products += 1
+                sources = registers(operands[1]) | registers(operands[2])
+                assert not sources & set().union(*recent[-2:], set()), f"operand written just before `{t}`"
+                pending.update({r: 0 for r in registers(operands[0])})
+            recent.append(set())
+        elif op.startswith("v_"):
+            early = [r for r in touched if pending.get(r, 2) < 2]
+            assert not early, f"`{t}` touches a score right behind its product"
+            recent.append(registers(operands[0]))
+        elif op != "s_waitcnt":
+            recent.append(set())
+    assert products >= 2 * 6 * 16, products    # four unrolled turns and two loops of single ones, in two instances
