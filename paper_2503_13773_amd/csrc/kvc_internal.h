@@ -115,8 +115,7 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
                                  const int32_t *block_tables, const int32_t *context_lens,
                                  const int32_t *q_start, void *out, const PrefillParams &p, int total_q,
                                  hipStream_t stream);
-// Long requests: HEADS (1, 2 or 4, a divisor of the group) query heads and 256 / HEADS query rows per workgroup.
-template <int HEADS>
+// Long requests, groups that 4 divides.
 hipError_t launch_prefill_wide(const void *q, const void *k_cache, const void *v_cache,
                                const int32_t *block_tables, const int32_t *context_lens,
                                const int32_t *q_start, void *out, const PrefillParams &p,

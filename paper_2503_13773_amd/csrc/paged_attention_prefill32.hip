@@ -11,17 +11,25 @@
 // tiles that adds up to about 800 port cycles against 544 matrix cycles; with 16 large tiles it
 // is about 500 port cycles against 512.
 //
-// One workgroup = (sequence, 2 query heads sharing one KV head, 64 or 128 consecutive query
-// rows); each of its 4 or 8 wavefronts owns 16 query rows x 2 heads = the 32 columns of its
-// tiles (column c = 16 * head + row).  Odd GQA group sizes take one head and 32 query rows per
-// wavefront instead (workgroups of 128 or 256 rows); everything below is written for two heads
-// and holds for one with "row" = c.  The workgroup walks the context in steps of 32 tokens
-// (the 32 rows of a score tile).  With 8 wavefronts the two groups of four run half a turn
-// apart, so that the two wavefronts of a SIMD are in opposite halves of their turns.
+// One workgroup = (sequence, 2 query heads sharing one KV head, 64 consecutive query rows); each of
+// its 4 wavefronts owns 16 query rows x 2 heads = the 32 columns of its tiles (column c = 16 * head
+// + row).  Odd GQA group sizes take one head and 32 query rows per wavefront instead (workgroups of
+// 128 rows); everything below is written for two heads and holds for one with "row" = c.  The
+// workgroup walks the context in steps of 32 tokens (the 32 rows of a score tile).
+//
+// What bounds it.  Two wavefronts of a SIMD read 128 KiB of operands from LDS per step of a compute
+// unit, 1024 cycles of its bandwidth against 1024 matrix cycles; a step of both takes about 1450.
+// One alone is bound by its own issue, about 130 instructions of 4 to 5 cycles (8 for an
+// exponential), and takes about 950 cycles for 512 matrix cycles.  A turn holds three steps: the
+// scores of the next, the weights of this one, V . P of the one before, so that the softmax
+// arithmetic spreads over the whole turn and neither product waits for it.  32 / 8 heads, one
+// request, turns of two steps (scores of the next beside weights and V . P of this one) / of three:
+// 100 tokens 8.6 / 7.5 us, 1000 22.6 / 21.5, 2048 44.3 / 39.6; four chunks of 512 rows of up to 4000
+// tokens 109.9 / 103.8; 256 rows of 12000 tokens 137 / 118.5.
 //
 // K and V rows travel from the cache straight into LDS (global_load_lds_dwordx4: lane l of a
-// wavefront writes its 16 bytes at M0 + 16 * l, no register staging), requested two turns
-// before their first use (K rows four steps ahead, V rows three); which bytes a
+// wavefront writes its 16 bytes at M0 + 16 * l, no register staging), requested a turn
+// or more before their first use (K rows four steps ahead, V rows two); which bytes a
 // lane fetches is chosen so that the LDS image is
 //   K rows: 16-byte chunks XOR-permuted by the row number (A-operand reads of 16 rows x the
 //           same dims then touch every bank once);
@@ -34,12 +42,14 @@
 //                      step, dims 16j + 8*half .. +7; B: the same dims of column c's query row.
 //                      The lane receives the 16 scores of column c against tokens
 //                      8*(v/4) + 4*half + v%4, v < 16.
-//   softmax            all 16 scores of a lane belong to one column: in-lane max (raw scores,
-//                      the scale is positive), one fused multiply-add and one exponential per
-//                      score (weight = exp2(score * scale - m)); the weights are rounded to
-//                      bf16 for P.V and added up in fp32 for the normaliser.  The two halves of
-//                      a column meet only when the reference point m moves (lazily: when some
-//                      score exceeds it by more than 2^8) and once at the end.
+//   softmax            all 16 scores of a lane belong to one column: one fused multiply-add and one
+//                      exponential per score (weight = exp2(score * scale - m)); the weights are
+//                      rounded to bf16 for P.V and added up in fp32 for the normaliser.  The
+//                      reference point m is set 2^kBias above the largest score and moves when some
+//                      weight reaches 2, which shows in the exponent bits of the rounded weights;
+//                      they are collected by OR (4 instructions, a running maximum takes 9), and the
+//                      step's weights are then made again from its scores.  The two halves of a
+//                      column meet only there and once at the end.
 //   O^T += V^T . P^T   8 x v_mfma_f32_32x32x16_bf16: 4 blocks of 32 dims x 2 slices of 16
 //                      tokens.  B is the weight registers as they stand (slice n = registers
 //                      8n .. 8n+7, depth slot 8*half + i = token 16n + 8*(i/4) + 4*half + i%4);
@@ -47,14 +57,13 @@
 //                      (ds_read_b64_tr_b16: 4 consecutive tokens of the lane's dim per read).
 //
 // The causal mask only bites in the last one or two steps of a wavefront: steps entirely below
-// the diagonal of all 16 rows run code without mask or range checks.  Token 0 is visible to
-// every query row and steps are walked in order, so every column has a finite reference point
-// after the first step.  Workgroups with the most steps (the last query rows) are dispatched
-// first.
+// the diagonal of all 16 rows run code without mask or range checks.  Workgroups with the most
+// steps (the last query rows) are dispatched first.
 #include <float.h>
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kvc_internal.h"
 #include "pa_mfma_tile.h"
@@ -70,83 +79,30 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kStepTokens = 32;
 constexpr int kStageBytes = kStepTokens * D * 2;  // K (or V) rows of a step: 32 rows x 256 bytes
-constexpr float kLazyLog2 = 8.0f;
-constexpr int kKStages = 4;   // K rows of steps s+1 .. s+4 during turn s
-constexpr int kVStages = 4;   // V rows of steps s .. s+3
-// Steps from which a split workgroup's second group takes a share (800 tokens whole 19.7, split 19.5 us; 1000 tokens
-// 23.1 / 22.4 us; 600 tokens 16.7 / 17.2 us).
-constexpr int kMinSplitSteps = 24;
+constexpr int kRing = 4;       // stages of K and of V
+constexpr float kBias = 7.0f;  // powers of two that the reference point is set above the largest score
+// Steps from which a split workgroup's second group takes a share (64 rows at the end of 800 tokens whole 16.5, split 18.0
+// us; 900 18.2 / 19.7; from the slopes 1100 and 1200 tokens 20.6 / 20.8 and 21.9 / 21.3).
+constexpr int kMinSplitSteps = 36;
 
-// Online-softmax state of one column (query row x head); lane (half, c) holds
-// O[column c][32*b + 8*(v/4) + 4*half + v%4] in acc[b][v].
-struct ColumnState {
-    floatx16 acc[4];
-    float lsum;  // sum of the rounded weights of this lane's tokens (the other half's lane holds the rest)
-    float m;     // reference point of the weights (base-2 units): within 2^kLazyLog2 of the column's running max
-
-    __device__ inline void reset(float lowest) {
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
-        lsum = 0.f;
-        m = lowest;
+template <int I, int N, class F>
+__device__ inline void static_for(const F &f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
     }
-};
+}
 
 // The value lane l ^ 32 holds, next to this lane's: one swap of the two 32-lane halves.
 __device__ inline float max_over_halves(float x) {
     const unsigned u = __float_as_uint(x);
     const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    const float b0 = __uint_as_float(b[0]), b1 = __uint_as_float(b[1]);
-    return b0 > b1 ? b0 : b1;  // inputs are never NaN
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 __device__ inline float sum_over_halves(float x) {
     const unsigned u = __float_as_uint(x);
     const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// max of three without the quieting moves the compiler puts in front of a max whose inputs
-// come out of the matrix pipe (they are never NaN here: finite scores or -inf)
-__device__ inline float max3(float a, float b, float c) {
-    float d;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
-}
-
-// Raw scores of a step into x (if MASKED, -inf where the token is not visible to the lane's
-// column: `limit` = tokens of the step it sees, may be <= 0) and their max over the lane.
-template <bool MASKED>
-__device__ inline float take_scores(float (&x)[16], const floatx16 &s, int limit, int half) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        x[v] = s[v];
-        if (MASKED && 8 * (v >> 2) + 4 * half + (v & 3) >= limit) x[v] = -INFINITY;
-    }
-    const float a = max3(x[0], x[1], x[2]), b = max3(x[3], x[4], x[5]), c = max3(x[6], x[7], x[8]);
-    const float d = max3(x[9], x[10], x[11]), e = max3(x[12], x[13], x[14]);
-    const float f = max3(a, b, c), g = max3(d, e, x[15]);
-    float h;
-    asm("v_max_f32 %0, %1, %2" : "=v"(h) : "v"(f), "v"(g));
-    return h;
-}
-
-// Lazy rebase: the reference point m only moves when some column's scaled max has grown by more
-// than 2^kLazyLog2 over it (always in the first step, m = -inf), so weights are at most
-// 2^kLazyLog2 and the 65 multiplies of the rebase are rare.  Every column sees token 0 in its
-// first step, so m - m_new is never inf - inf.
-__device__ inline void rebase(ColumnState &st, float lane_max, float scale_log2e) {
-    const float scaled = lane_max * scale_log2e;
-    // the test needs no cross-lane max: if no lane holds a score above m + 2^kLazyLog2, none exists
-    if (__builtin_amdgcn_ballot_w64(scaled > st.m + kLazyLog2) != 0) {
-        const float m_new = fmaxf(st.m, max_over_halves(scaled));
-        const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
-        st.m = m_new;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) st.acc[b] *= alpha;
-        st.lsum *= alpha;
-    }
 }
 
 // A operands of O^T += V^T . P^T straight from LDS.  The transposing read hands lane i of a
@@ -162,13 +118,12 @@ __device__ inline int v_lane_offset(int b, int half, int c) {
     const int i16 = c & 15, k = i16 >> 2;
     return (4 * half + k) * 256 + ((b + k) & 3) * 64 + 32 * (c >> 4) + 8 * (i16 & 3);
 }
-template <int N>
-__device__ inline void read_v_operand(uint2 (&va)[2], const unsigned char *vlane) {
+// Half H of the operand of slice N.
+template <int N, int H>
+__device__ inline uint2 read_v_half(const unsigned char *vlane) {
     typedef short v4i16 __attribute__((ext_vector_type(4)));
     typedef v4i16 __attribute__((address_space(3))) * lds_v4i16_ptr;
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-        va[g] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vlane + (16 * N + 8 * g) * 256)));
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vlane + (16 * N + 8 * H) * 256)));
 }
 
 // V rows at or past `vlim` (tokens of the step visible to any column of this wavefront) are
@@ -189,6 +144,11 @@ __device__ inline bf16x8 v_operand(const uint2 (&va)[2]) {
     return __builtin_bit_cast(bf16x8, aw);
 }
 
+__device__ inline bf16x8 four_words(const uint32_t (&w)[8], int n) {
+    const uint4 v = {w[4 * n], w[4 * n + 1], w[4 * n + 2], w[4 * n + 3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+
 // K operand j of a step from LDS (a stage is 32 rows of 256 bytes, 16-byte chunks XOR-permuted
 // by row % 16); lane (half, c) reads row c, dims 16j + 8*half .. +7.
 template <int J>
@@ -196,36 +156,25 @@ __device__ inline bf16x8 read_k_operand(const unsigned char *krow, int half, int
     return *reinterpret_cast<const bf16x8 *>(krow + (((2 * J + half) ^ (c & 15)) << 4));
 }
 
-// 16 bytes per lane from global memory straight into LDS: lane l's bytes land at lds_addr +
-// 16 * l (lds_addr uniform).  The two-instruction forms load a second 1 KiB from 1 KiB further
-// on both sides.  The compiler does not see these accesses: the caller orders them against LDS
-// reads with barriers and waits for them with wait_loads_but().
-__device__ inline void load_rows_to_lds(const void *base, uint32_t off0, uint32_t off1_minus_1k, uint32_t lds_addr) {
+// 16 bytes per lane from global memory straight into LDS, to lds_addr + 16 * lane (lds_addr uniform), and a second 1 KiB
+// from and to 1 KiB further on.  The compiler does not see these accesses: barriers order them against LDS reads,
+// wait_for() counts them.
+__device__ inline void load_rows(const void *base, uint32_t off0, uint32_t off1_minus_1k, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
                  :: "s"(lds_addr), "v"(off0), "v"(off1_minus_1k), "s"(base) : "memory");
-}
-__device__ inline void load_row_group_to_lds(const void *base, uint32_t off, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds_addr), "v"(off), "s"(base) : "memory");
 }
 __device__ inline void load_lane_to_lds(const void *addr, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(addr) : "memory");
 }
-template <int N>
-__device__ inline void wait_loads_but() {
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
-}
-
-// The barrier that ends a turn.  The wavefront first waits for its own LDS reads (operands
-// requested for the next turn): the loads of the next turn overwrite the stages they come from.
-__device__ inline void turn_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
+// Waits until at most LOADS of the wavefront's loads and LDS of its LDS reads are under way.
+template <int LOADS, int LDS>
+__device__ inline void wait_for() {
+    static_assert(LOADS < 64 && LDS < 16, "fields of the wait instruction");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((LOADS & 15) | (LOADS >> 4) << 14 | 7 << 4 | LDS << 8);
     asm volatile("" ::: "memory");
 }
-
-// The barrier in the middle of a turn orders no data (see the kernel): it only keeps the two
-// groups of wavefronts half a turn apart.
-__device__ inline void phase_barrier() {
+__device__ inline void barrier() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -234,162 +183,122 @@ __device__ inline void phase_barrier() {
 // Nothing moves across this point when the compiler orders the instructions of a turn.
 #define KVC_PIN() __builtin_amdgcn_sched_barrier(0)
 
-// One turn of the software pipeline: the weights and the P.V accumulation of step `cur` (raw
-// scores in x) together with the scores and the max of step `next`.  The order of the turn is
-// pinned chunk by chunk, one matrix instruction (32 cycles in the matrix pipe, 8 on the issue
-// port) per chunk together with the vector work that fits under it and the LDS reads of operands
-// that are due half a turn or more later:
-//     chunks  0 ..  3   S(next) += K operand j . Q, j < 4       2 weights of cur each (fma, exp2), rounding, sum
-//                       reads K operand 4 + j of step next
-//     chunks  4 ..  7   O block b += V slice 0 . weights 0..7   2 weights each (scores 8 .. 15), rounding, sum
-//                       reads V operand b, slice 1, of step cur
-//     chunks  8 .. 11   S(next) += K operand j . Q, j >= 4      block id of the following turn's loads (`lookup`)
-//                       reads K operand j - 4 of the step after next and V operand j - 4, slice 0, of step next
-//     chunks 12 .. 15   O block b += V slice 1 . weights 8..15  max of S(next)
-//                       requests the K and V rows of the step four ahead (`issue_k`, `issue_v`)
-// so the turn starts with ka_lo = K operands 0 .. 3 of step next and va0 = the slice-0 V
-// operands of step cur in registers and ends with those of the following turn.
-// On return x holds the raw scores of step `next` and the reference point is rebased for it.
-// MASKED: `vlim_cur` = tokens of step cur visible to any column of this wavefront,
-// `limit_next` = tokens of step next visible to this lane's column.
-template <bool MASKED, class IssueK, class IssueV, class Mid, class Lookup>
-__device__ inline void pipeline_turn(ColumnState &st, float (&x)[16], bf16x8 (&ka_lo)[4], uint2 (&va0)[4][2],
-                                     const unsigned char *krow1, const unsigned char *krow2,
-                                     const unsigned char *sv_cur, const unsigned char *sv_next, const int (&voff)[4],
-                                     const bf16x8 (&qb)[8], float scale_log2e, int vlim_cur, int limit_next, int half,
-                                     int c, const IssueK &issue_k, const IssueV &issue_v, const Mid &mid, const Lookup &lookup) {
-    const float neg_m = -st.m;
+// Chunk of the turn (one matrix instruction each) in which the arithmetic of score e starts: argument, exponential,
+// rounding and pair sum, sum, one chunk after the other.
+constexpr int arg_chunk(int e) { return e * 10 / 16; }
+
+// One turn: S of step `next`, the weights of step cur (raw scores in x), O += V . P of the step before (weights in w).
+// Products with K and with V alternate, so that no matrix instruction waits for the one in front of it.
+//     even chunks   S += K operand j . Q
+//     odd chunks    O block += V operand u . weights
+// LDS reads: K operands 4 .. 7 of step next and V operands 3 .. 7 of the step before, then K operands 0 .. 3 of the step
+// after next and V operands 0 .. 2 of step cur, which the following turn starts with.  `issue` requests the K rows of the
+// step four ahead of cur and the V rows of the step two ahead.  On return x holds the raw scores of step next, w the
+// weights of step cur.  MASKED: `vlim_prev`, `vlim_cur` = tokens of those steps that some column sees, `limit_next` =
+// tokens of step next that this lane's column sees.
+template <bool MASKED, class IssueK, class IssueV, class Lookup, class Math>
+__device__ inline void pipeline_turn(floatx16 (&acc)[4], float (&x)[16], uint32_t (&w)[8], float &lsum, float &m, bf16x8 (&ka)[8],
+                                     uint2 (&va)[8][2], const unsigned char *krow1, const unsigned char *krow2,
+                                     const unsigned char *sv_prev, const unsigned char *sv_cur, const int (&voff)[4],
+                                     const bf16x8 (&qb)[8], float scale_log2e, int vlim_prev, int limit_next, int half, int c,
+                                     const IssueK &issue_k, const IssueV &issue_v, const Lookup &lookup, const Math &math) {
     float arg[16], pf[16], pair[8];
-    uint32_t w[8];
-    bf16x8 ka_hi[4];
-    uint2 va1[4][2];
+    uint32_t wn[8], any[3];
+    uint64_t moved = 0;
     floatx16 s;
+    const float neg_m = -m, lsum_before = lsum;
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = 0.f;
-
-    // The softmax arithmetic of score pair P goes through four stages placed in different chunks,
-    // so that no instruction waits for the result of the one in front of it: exponent arguments,
-    // exponentials, rounding to bf16 plus the pair's sum, and the addition to the normaliser.
-#define KVC_ARG(P)                                                           \
-    arg[2 * (P)] = __builtin_fmaf(x[2 * (P)], scale_log2e, neg_m);           \
-    arg[2 * (P) + 1] = __builtin_fmaf(x[2 * (P) + 1], scale_log2e, neg_m)
-#define KVC_EXP(P)                                        \
-    pf[2 * (P)] = __builtin_amdgcn_exp2f(arg[2 * (P)]);   \
-    pf[2 * (P) + 1] = __builtin_amdgcn_exp2f(arg[2 * (P) + 1])
-#define KVC_ROUND(P)                                \
-    w[P] = pack_bf16(pf[2 * (P)], pf[2 * (P) + 1]); \
-    pair[P] = pf[2 * (P)] + pf[2 * (P) + 1]
-#define KVC_SUM(P) st.lsum += pair[P]
-#define KVC_QK_LO(J)                                                          \
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka_lo[J], qb[J], s, 0, 0, 0); \
-    ka_hi[J] = read_k_operand<4 + (J)>(krow1, half, c)
-#define KVC_QK_HI(J)                                                                \
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka_hi[J], qb[4 + (J)], s, 0, 0, 0); \
-    ka_lo[J] = read_k_operand<J>(krow2, half, c);                                   \
-    read_v_operand<0>(va0[J], sv_next + voff[J])
-
+    static_for<0, 16>([&](auto chunk) __attribute__((always_inline)) {
+        constexpr int T = decltype(chunk)::value, U = T >> 1;
+        KVC_PIN();
+        if constexpr ((T & 1) == 0) {
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[U], qb[U], s, 0, 0, 0);
+        } else {
+            if constexpr (MASKED) mask_v_operand<(U >> 2)>(va[U], vlim_prev, half);
+            acc[U & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va[U]), four_words(w, U >> 2), acc[U & 3], 0, 0, 0);
+        }
+        if constexpr (T < 4) ka[4 + T] = read_k_operand<4 + T>(krow1, half, c);
+        if constexpr (T < 10) {
+            constexpr int R = 3 + (T >> 1), H = T & 1;
+            va[R][H] = read_v_half<(R >> 2), H>(sv_prev + voff[R & 3]);
+        }
+        if constexpr (T >= 8 && T < 12) ka[T - 8] = read_k_operand<T - 8>(krow2, half, c);
+        if constexpr (T >= 8 && T < 14) {
+            constexpr int R = (T - 8) >> 1, H = T & 1;
+            va[R][H] = read_v_half<0, H>(sv_cur + voff[R]);
+        }
+        static_for<0, 16>([&](auto score) __attribute__((always_inline)) {
+            constexpr int E = decltype(score)::value, P = E >> 1;
+            if constexpr (arg_chunk(E) == T) arg[E] = __builtin_fmaf(x[E], scale_log2e, neg_m);
+            if constexpr (arg_chunk(E) + 1 == T) pf[E] = __builtin_amdgcn_exp2f(arg[E]);
+            if constexpr ((E & 1) && arg_chunk(E) + 2 == T) {
+                wn[P] = pack_bf16(pf[E - 1], pf[E]);
+                asm volatile("" : "+v"(wn[P]));
+                pair[P] = pf[E - 1] + pf[E];
+            }
+            if constexpr ((E & 1) && arg_chunk(E) + 3 == T) {
+                lsum += pair[P];
+                asm volatile("" : "+v"(lsum));
+                if constexpr (P == 2) { any[0] = wn[0] | wn[1] | wn[2]; asm volatile("" : "+v"(any[0])); }
+                if constexpr (P == 4) { any[1] = any[0] | wn[3] | wn[4]; asm volatile("" : "+v"(any[1])); }
+                if constexpr (P == 6) { any[2] = any[1] | wn[5] | wn[6]; asm volatile("" : "+v"(any[2])); }
+            }
+        });
+        if constexpr (T == 0) lookup();
+        if constexpr (T == 12) issue_k();
+        if constexpr (T == 14) issue_v();
+        if constexpr (T == 14) moved = __builtin_amdgcn_ballot_w64(((any[2] | wn[7]) & 0x40004000u) != 0);
+        if constexpr (T == 15) math();
+    });
     KVC_PIN();
-    KVC_QK_LO(0); KVC_ARG(0); KVC_ARG(1); KVC_EXP(0);
-    KVC_PIN();
-    KVC_QK_LO(1); KVC_ARG(2); KVC_EXP(1); KVC_ROUND(0);
-    KVC_PIN();
-    KVC_QK_LO(2); KVC_ARG(3); KVC_EXP(2); KVC_ROUND(1); KVC_SUM(0);
-    KVC_PIN();
-    KVC_QK_LO(3); KVC_EXP(3); KVC_ROUND(2); KVC_SUM(1); KVC_ARG(4);
-    KVC_PIN();
-    KVC_ROUND(3);
-    const uint4 pw0 = {w[0], w[1], w[2], w[3]};
-    const bf16x8 pb0 = __builtin_bit_cast(bf16x8, pw0);
-
-#define KVC_PV0(B)                                                                                        \
-    if (MASKED) mask_v_operand<0>(va0[B], vlim_cur, half);                                                \
-    st.acc[B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va0[B]), pb0, st.acc[B], 0, 0, 0);     \
-    read_v_operand<1>(va1[B], sv_cur + voff[B])
-    KVC_PV0(0); KVC_SUM(2); KVC_ARG(5); KVC_EXP(4); KVC_SUM(3);
-    KVC_PIN();
-    KVC_PV0(1); KVC_ARG(6); KVC_EXP(5); KVC_ROUND(4);
-    KVC_PIN();
-    KVC_PV0(2); KVC_ARG(7); KVC_EXP(6); KVC_ROUND(5); KVC_SUM(4);
-    KVC_PIN();
-    KVC_PV0(3); KVC_EXP(7); KVC_ROUND(6); KVC_SUM(5);
-    KVC_PIN();
-    mid();  // the workgroup's half-turn barrier: the other group of wavefronts changes phase here too
-    KVC_PIN();
-
-    lookup();  // block id for the loads of the next turn: half a turn for the scalar load to return
-    KVC_QK_HI(0); KVC_ROUND(7); KVC_SUM(6);
-    KVC_PIN();
-    const uint4 pw1 = {w[4], w[5], w[6], w[7]};
-    const bf16x8 pb1 = __builtin_bit_cast(bf16x8, pw1);
-    KVC_QK_HI(1); KVC_SUM(7);
-    KVC_PIN();
-    KVC_QK_HI(2);
-    KVC_PIN();
-    KVC_QK_HI(3);
-    KVC_PIN();
-
-    // chunks 12 .. 15 also take the raw scores of step next (masked if need be) and their max
-#define KVC_PV1(B)                                                                                        \
-    if (MASKED) mask_v_operand<1>(va1[B], vlim_cur, half);                                                \
-    st.acc[B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va1[B]), pb1, st.acc[B], 0, 0, 0)
-    KVC_PV1(0);
-    issue_k();
-    KVC_PIN();
-    KVC_PV1(1);
+    if (MASKED)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        x[v] = s[v];
-        if (MASKED && 8 * (v >> 2) + 4 * half + (v & 3) >= limit_next) x[v] = -INFINITY;
+        for (int v = 0; v < 16; ++v) s[v] = 8 * (v >> 2) + 4 * half + (v & 3) >= limit_next ? -INFINITY : s[v];
+    if (__builtin_expect(moved != 0, 0)) {
+        // some weight is 2 or more (or NaN): a new reference point, and the weights by it
+        float top = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) top = fmaxf(top, x[v]);
+        const float m_new = fmaxf(m, max_over_halves(top) * scale_log2e + kBias);
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        m = m_new;
+        lsum = lsum_before * alpha;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[b] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * i], scale_log2e, -m_new));
+            const float b = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * i + 1], scale_log2e, -m_new));
+            wn[i] = pack_bf16(a, b);
+            lsum += a + b;
+        }
     }
-    const float m0 = max3(x[0], x[1], x[2]), m1 = max3(x[3], x[4], x[5]), m2 = max3(x[6], x[7], x[8]);
-    KVC_PIN();
-    KVC_PV1(2);
-    issue_v();
-    const float m3 = max3(x[9], x[10], x[11]), m4 = max3(x[12], x[13], x[14]);
-    KVC_PIN();
-    KVC_PV1(3);
-    const float m5 = max3(m0, m1, m2), m6 = max3(m3, m4, x[15]);
-    float lane_max;
-    asm("v_max_f32 %0, %1, %2" : "=v"(lane_max) : "v"(m5), "v"(m6));
-    rebase(st, lane_max, scale_log2e);
-#undef KVC_ARG
-#undef KVC_EXP
-#undef KVC_SUM
-#undef KVC_ROUND
-#undef KVC_QK_LO
-#undef KVC_QK_HI
-#undef KVC_PV0
-#undef KVC_PV1
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[v] = s[v];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = wn[i];
 }
 
 // HEADS = 2: the 32 columns of a wavefront are 16 query rows x 2 heads of one KV head (even GQA
-// groups); HEADS = 1: 32 query rows of one head.  GROUPS = 1: workgroups of four wavefronts, two
-// per compute unit.  GROUPS = 2: workgroups of two groups of four wavefronts, one per compute
-// unit; the groups run half a turn apart (see below).  Either way a SIMD holds two wavefronts.
-// SPLIT (with GROUPS = 2): the two groups hold the same query rows, those of a four-wavefront workgroup, and
+// groups); HEADS = 1: 32 query rows of one head.  Two workgroups of four wavefronts share a compute unit, two
+// wavefronts a SIMD.
+// SPLIT: a workgroup has two groups of four wavefronts that hold the same query rows and
 // share the steps of long contexts: group 0 walks the first `cut` of them, group 1 the rest, each with a ring
 // of stages of its own, and the parts meet in LDS at the end (log-sum-exp rule).  Of short contexts group 1
 // ends at once.  For launches with too few workgroups to fill the device, where a four-wavefront workgroup would
-// run one wavefront per SIMD: 256 rows at the end of 12000 tokens, 32 / 8 heads, 172 -> 138 us, 64 rows of 4000
-// tokens 63.6 -> 53.7 us, 300 rows of 1000 tokens twice 24 -> 22.4 us.  The groups run in
-// step: half a turn apart the first case took 131 us, but the barrier in the middle of a turn cost short contexts,
-// which only group 0 walks, 25 ns per step, and a branch around it (154 us) or a second copy of the loop
-// (spills, 217 us) costs more.
+// run one wavefront per SIMD (256 rows at the end of 12000 tokens, 32 / 8 heads, 172 -> 138 us when it came in).
 // SMALL: block_size < 8.
-template <bool SMALL, int GROUPS, int HEADS, bool SPLIT>
-__global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_kernel(
+template <bool SMALL, int HEADS, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void pa_prefill_mfma32_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
     uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at, int fold_ranked, int rank_from) {
-    static_assert(!SPLIT || GROUPS == 2, "the context is split between two groups");
     constexpr int kParts = SPLIT ? 2 : 1;
-    constexpr int kShared = GROUPS / kParts;        // groups that share a ring of stages
-    __shared__ __attribute__((aligned(1024))) unsigned char s_kv[kParts][kKStages + kVStages][kStageBytes];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_kv[kParts][2 * kRing][kStageBytes];
     constexpr int kWaveRows = 32 / HEADS;           // query rows of a wavefront: column c = kWaveRows * head + row
-    constexpr int kTileRows = 4 * kWaveRows * kShared;  // query rows of a workgroup
-    constexpr int kLoads = 2 / kShared;             // 1 KiB loads of K (and of V) per wavefront and step
-    constexpr int kWavesPerTile = 2 * kShared;      // wavefronts that share a 16-row tile of a step
+    constexpr int kTileRows = 4 * kWaveRows;        // query rows of a workgroup
 
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order); the longest query tiles come
     // first, and from `fold_at` on the shortest: when every workgroup is resident at once, the two
@@ -440,9 +349,9 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 
     const int tid = threadIdx.x;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int group = wave_id >> 2;  // GROUPS = 2: wavefronts w and w + 4 share a SIMD; group 1 runs half a turn behind group 0
+    const int group = wave_id >> 2;  // SPLIT: wavefronts w and w + 4 share a SIMD
     const int wave = SPLIT ? wave_id & 3 : wave_id;  // among the wavefronts that share a ring
-    unsigned char *const s_k = &s_kv[SPLIT ? group : 0][0][0], *const s_v = s_k + kKStages * kStageBytes;
+    unsigned char *const s_k = &s_kv[SPLIT ? group : 0][0][0], *const s_v = s_k + kRing * kStageBytes;
     const int half = lane >> 5, c = lane & 31;
     const int r = c % kWaveRows;  // query row of the column inside the wavefront's rows
     const int my_head = head0 + c / kWaveRows;
@@ -454,7 +363,6 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     const int s0 = SPLIT && group == 1 ? cut : 0;              // first step of this wavefront's part
     const int wg_steps = SPLIT && group == 1 ? all_steps - cut : cut;  // and its number of steps
     if (SPLIT && wg_steps == 0) return;  // group 1 of a short context; ended wavefronts do not count at barriers
-    constexpr bool phased = GROUPS == 2 && !SPLIT;  // the groups run half a turn apart
     const int32_t *table = block_tables + size_t(n) * p.max_blocks_per_seq;
 
     // wavefronts past the last query row still load and synchronise, they just never compute
@@ -474,99 +382,87 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
         for (int j = 0; j < 8; ++j) qb[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qrow + 16 * j));
     }
 
-    // Token 0 is in the first step, so every column starts with a finite score there.  Group 1's first step may
-    // hide all its tokens from a column: its reference point starts at the lowest finite value, the weights are 0.
-    ColumnState st;
-    st.reset(SPLIT ? -FLT_MAX : -INFINITY);
-
-    // ---- this wavefront's share of a step's rows: 4 * kLoads consecutive rows of the 32 (inside
-    // one 16-row tile of the step), kLoads loads of 4 rows for K and as many for V.  Lane l of
-    // load i writes LDS chunk l % 16 of the share's row 4 * i + l / 16; the chunk it fetches for
-    // that place follows from the stage layouts.
+    // ---- this wavefront's share of a step's rows: 8 consecutive rows of the 32 (inside one 16-row tile of the step), two
+    // loads of 4 rows for K and as many for V.  Lane l of load i writes LDS chunk l % 16 of the share's row 4 * i + l / 16;
+    // the chunk it fetches for that place follows from the stage layouts.
     const size_t head_bytes = size_t(p.block_size) * D * 2;
     const size_t block_bytes = head_bytes * p.num_kv_heads;
     const unsigned char *k_head = reinterpret_cast<const unsigned char *>(k_cache) + size_t(kvh) * head_bytes;
     const unsigned char *v_head = reinterpret_cast<const unsigned char *>(v_cache) + size_t(kvh) * head_bytes;
-    const int sub_mask = (1 << p.tiles_per_block_log2) - 1;
-    const int my_tile = wave / kWavesPerTile;       // tile of the step this wavefront loads from
-    const int lrow = 4 * kLoads * (wave % kWavesPerTile) + (lane >> 4);  // row inside the tile of load 0 (load 1: + 4)
+    const unsigned tile_mask = (p.block_size - 1) & ~15;  // of a token: its 16-row tile inside its block
+    const int my_tile = wave / 2;       // tile of the step this wavefront loads from
+    const int lrow = 8 * (wave % 2) + (lane >> 4);  // row inside the tile of load 0 (load 1: + 4)
     const int lchunk = lane & 15;
     const int brow = lrow & (p.block_size - 1);  // in its block, where that holds 8 tokens (16 or more: lrow)
     const uint32_t k_off = brow * 256 + ((lchunk ^ lrow) << 4);
     const uint32_t k_off1 = (brow + 4) * 256 + ((lchunk ^ (lrow + 4)) << 4);
     const uint32_t v_off = brow * 256 + ((4 * (((lchunk >> 2) - lrow) & 3) + (lchunk & 3)) << 4);  // load 1: + 1024
-    const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(s_k)) + 1024 * kLoads * wave;
-    const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(s_v)) + 1024 * kLoads * wave;
+    const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(s_k)) + 2048 * wave;
+    const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(s_v)) + 2048 * wave;
 
-    // Blocks of 8 tokens and more: the block id of the wavefront's rows (8 or 4 consecutive ones, inside one
-    // block) is uniform, it comes through the scalar cache one turn before the loads that use it.  Rows past the
-    // last visible token repeat its block (never used unmasked).  Smaller blocks: a / b are the blocks of
-    // this lane's row in loads 0 / 1.  (Four chunks of 512 rows on 8-token blocks, contexts up to 4000, 32 / 8
-    // heads: 112 us; with a table load per lane, which drains the wavefront's loads in flight, 126 us.)
-    const int share_row = 4 * kLoads * (wave % kWavesPerTile);
-    struct Ids { int a, b; };
-    auto ids_of = [&](int step) __attribute__((always_inline)) -> Ids {
+    // Blocks of 8 tokens and more: the block id of the wavefront's 8 rows, which lie inside one block, is uniform; it comes
+    // through the scalar cache one turn before the loads that use it.  Rows past the last visible token repeat it (never
+    // used unmasked).  Smaller blocks: a / b are the blocks of this lane's row in loads 0 / 1.  (Four chunks of 512 rows on
+    // 8-token blocks, contexts up to 4000, 32 / 8 heads: 112 us; with a table load per lane, which drains the wavefront's
+    // loads in flight, 126 us.)
+    const int share_row = 8 * (wave % 2);
+    struct Ids { uint32_t a, b; };
+    int tok_next = s0 * kStepTokens + 8 * wave;
+    auto next_ids = [&]() __attribute__((always_inline)) -> Ids {
         Ids id;
-        if (SMALL) {
-            const int tok = min((2 * (s0 + step) + my_tile) * kTileTokens + lrow, last_pos);
-            id.a = table[tok >> p.block_size_log2];
-            id.b = kLoads == 2 ? table[min(tok + 4, last_pos) >> p.block_size_log2] : 0;
+        if constexpr (SMALL) {
+            const int tok = tok_next - share_row + lrow;
+            id.a = table[min(tok, last_pos) >> p.block_size_log2];
+            id.b = table[min(tok + 4, last_pos) >> p.block_size_log2];
         } else {
-            const int tok = min((2 * (s0 + step) + my_tile) * kTileTokens + share_row, last_pos);
-            id.a = __builtin_amdgcn_readfirstlane(table[tok >> p.block_size_log2]);
-            id.b = (tok >> 4) & sub_mask;
+            const unsigned tok = unsigned(min(tok_next, last_pos));
+            // the byte offset fits 32 bits (blocks of 8 tokens and more), which the scalar load adds by itself
+            id.a = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(table) + (tok >> p.block_size_log2) * 4u);
+            id.b = (tok & tile_mask) * 256;
         }
+        tok_next += kStepTokens;
         return id;
     };
-    // load this wavefront's K (V) rows of step `src` (the one `id` was looked up for) into a stage
-    auto issue_rows = [&](const unsigned char *head, uint32_t dst, uint32_t off, uint32_t off1, int src, const Ids &id)
-                          __attribute__((always_inline)) {
-        if (SMALL) {
-            const int tok = min((2 * (s0 + src) + my_tile) * kTileTokens + lrow, last_pos);
-            load_lane_to_lds(head + size_t(id.a) * block_bytes + size_t(tok & (p.block_size - 1)) * 256 + (off & 255), dst);
-            if (kLoads == 2) {
-                const int tok1 = min(tok + 4, last_pos);
-                load_lane_to_lds(head + size_t(id.b) * block_bytes + size_t(tok1 & (p.block_size - 1)) * 256 + (off1 & 255),
-                                 dst + 1024);
-            }
+    using At = std::conditional_t<SMALL, Ids, uint64_t>;
+    auto offset_of = [&](const Ids &id) __attribute__((always_inline)) -> At {
+        if constexpr (SMALL) return id;
+        else return uint64_t(id.a) * uint32_t(block_bytes) + id.b;
+    };
+    auto issue_rows = [&](const unsigned char *head, uint32_t off0, uint32_t off1_minus_1k, uint32_t lds, const At &at) __attribute__((always_inline)) {
+        lds = __builtin_amdgcn_readfirstlane(lds);
+        if constexpr (SMALL) {
+            load_lane_to_lds(head + size_t(at.a) * block_bytes + (lrow & (p.block_size - 1)) * 256 + (off0 & 255), lds);
+            load_lane_to_lds(head + size_t(at.b) * block_bytes + ((lrow + 4) & (p.block_size - 1)) * 256 + (off1_minus_1k & 255), lds + 1024);
         } else {
-            const unsigned char *tile = head + size_t(unsigned(id.a)) * block_bytes + size_t(id.b) * (kTileTokens * 256);
-            if (kLoads == 2) load_rows_to_lds(tile, off, off1 - 1024, dst);
-            else load_row_group_to_lds(tile, off, dst);
+            load_rows(head + at, off0, off1_minus_1k, lds);
         }
     };
-    auto issue_k = [&](int kst, int src, const Ids &id) __attribute__((always_inline)) {
-        issue_rows(k_head, __builtin_amdgcn_readfirstlane(lds_k0 + kst * kStageBytes), k_off, k_off1, src, id);
+    auto issue_k = [&](int stage, const At &at) __attribute__((always_inline)) {
+        issue_rows(k_head, k_off, k_off1 - 1024, lds_k0 + stage * kStageBytes, at);
     };
-    auto issue_v = [&](int vst, int src, const Ids &id) __attribute__((always_inline)) {
-        issue_rows(v_head, __builtin_amdgcn_readfirstlane(lds_v0 + vst * kStageBytes), v_off, v_off + 1024, src, id);
+    auto issue_v = [&](int stage, const At &at) __attribute__((always_inline)) {
+        issue_rows(v_head, v_off, v_off, lds_v0 + stage * kStageBytes, at);
     };
 
-    // Rows of step j live in K stage j % 4 and V stage j % 4.  Turn s requests the K rows of step
-    // s+4 (over those of step s) and the V rows of step s+3 (over those of step s-1), multiplies
-    // with operands of steps s+1 (K) and s (V) and reads operands of steps s+1, s+2 (K) and s, s+1
-    // (V).  Before the barrier that ends it, a wavefront waits for its own loads of turn s-1 and
-    // for its LDS reads.  The workgroup meets at a barrier twice per turn, and group 1 of its
-    // wavefronts runs half a turn behind group 0: while one wavefront of a SIMD is in the first,
-    // vector-heavy half of a turn the other is in the second, matrix-heavy half.  A stage is
-    // overwritten, at the earliest, two barriers after the last wavefront has waited for its
-    // reads of it, and read, at the earliest, after the barrier that follows the wait of the last
-    // wavefront for its loads into it.  Past the last step the last one is loaded again (unused):
-    // the loops stay branch free.
-    Ids ids_v;
-    {
-        const Ids i0s = ids_of(0), i1s = ids_of(min(1, wg_steps - 1)), i2s = ids_of(min(2, wg_steps - 1));
-        ids_v = ids_of(min(3, wg_steps - 1));
-        issue_k(0, 0, i0s);
-        issue_v(0, 0, i0s);
-        issue_k(1, min(1, wg_steps - 1), i1s);
-        issue_v(1, min(1, wg_steps - 1), i1s);
-        issue_k(2, min(2, wg_steps - 1), i2s);
-        issue_v(2, min(2, wg_steps - 1), i2s);
-        issue_k(3, min(3, wg_steps - 1), ids_v);
-    }
-    Ids ids_k = ids_of(min(4, wg_steps - 1));
-    wait_loads_but<kLoads>();  // steps 0 .. 2 have arrived
+    // Rows of step j live in stages j % 4.  Turn s requests the K rows of step s + 4 (over those of step s) and the V rows
+    // of step s + 2 (over those of step s - 2), and reads K rows of steps s + 1 and s + 2 and V rows of steps s - 1 and s.
+    // Before the barrier that ends it a wavefront waits for its LDS reads and for its loads of turn s - 1.  Past the last step
+    // the last one is loaded again (unused): the loops stay branch free.
+    At at_v[2], at_k;
+    static_for<0, kRing>([&](auto i) __attribute__((always_inline)) {
+        constexpr int I = decltype(i)::value;
+        const At at = offset_of(next_ids());
+        issue_k(I, at);
+        if constexpr (I < kRing - 2) issue_v(I, at);
+        if constexpr (I >= kRing - 2) at_v[I - (kRing - 2)] = at;
+    });
+    at_k = offset_of(next_ids());
+    Ids ids;
+    // V rows of the step before the first: turn 0, or the last step if it is the first, multiplies them by weights of 0
+#pragma unroll
+    for (int i = 0; i < kStageBytes / 4096; ++i)
+        *reinterpret_cast<uint4 *>(s_v + (kRing - 1) * kStageBytes + (4 * i + wave) * 1024 + lane * 16) = uint4{0, 0, 0, 0};
+    wait_for<0, 0>();
     // A use of the Q operand on this side of the barrier: without one the compiler sinks its
     // loads into the path of the active wavefronts, behind the barrier, where nothing hides them.
 #pragma unroll
@@ -578,22 +474,32 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     // register plus an immediate)
 #define KVC_TURN_BEGIN(PH)                                                                        \
     const int ph = (PH);                                                                          \
-    const int src_k = min(s + 4, wg_steps - 1), src_v = min(s + 3, wg_steps - 1);                 \
-    const Ids idk = ids_k, idv = ids_v;                                                           \
-    auto turn_k = [&]() __attribute__((always_inline)) { issue_k(ph, src_k, idk); };              \
-    auto turn_v = [&]() __attribute__((always_inline)) {                                          \
-        issue_v((ph + 3) & 3, src_v, idv);                                                        \
-        ids_v = idk;                                                                              \
+    auto turn_math = [&]() __attribute__((always_inline)) {                                       \
+        at_v[0] = at_v[1];                                                                        \
+        at_v[1] = at_k;                                                                           \
+        at_k = offset_of(ids);                                                                    \
     };                                                                                            \
-    auto turn_lookup = [&]() __attribute__((always_inline)) { ids_k = ids_of(min(s + 5, wg_steps - 1)); }
-#define KVC_TURN_END()     \
-    wait_loads_but<2 * kLoads>();   \
-    turn_barrier()
+    auto turn_k = [&]() __attribute__((always_inline)) { issue_k(ph, at_k); };                    \
+    auto turn_v = [&]() __attribute__((always_inline)) { issue_v((ph + 2) & 3, at_v[0]); };       \
+    auto turn_lookup = [&]() __attribute__((always_inline)) { ids = next_ids(); }
+#define KVC_TURN_END()                \
+    wait_for<4, 0>();                 \
+    barrier()
+    // a turn of a wavefront that has nothing to compute: it only loads and synchronises
+#define KVC_IDLE_TURN()                                                                           \
+    {                                                                                             \
+        KVC_TURN_BEGIN(s & 3);                                                                    \
+        turn_lookup();                                                                            \
+        turn_k();                                                                                 \
+        turn_v();                                                                                 \
+        turn_math();                                                                              \
+        KVC_TURN_END();                                                                           \
+    }
 
     // Group 0's share may be a step longer than group 1's.
     auto even_out = [&]() __attribute__((always_inline)) {
         if (group == 1)
-            for (int i = wg_steps; i < cut; ++i) phase_barrier();
+            for (int i = wg_steps; i < cut; ++i) barrier();
     };
 
     // Every wavefront of the workgroup passes one more barrier here, two per turn, and one to
@@ -601,17 +507,8 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     // wavefront without query rows only loads and synchronises.
     if (!active) {
         __syncthreads();
-        if (phased && group == 1) phase_barrier();
-        for (; s < wg_steps; ++s) {
-            KVC_TURN_BEGIN(s & 3);
-            if (phased) phase_barrier();
-            turn_lookup();
-            turn_k();
-            turn_v();
-            KVC_TURN_END();
-        }
-        if (phased && group == 0) phase_barrier();
-        wait_loads_but<0>();
+        for (; s < wg_steps - 1; ++s) KVC_IDLE_TURN();
+        wait_for<0, 0>();
         if (SPLIT && cut < all_steps) {  // as the others below
             even_out();
             __syncthreads();
@@ -624,76 +521,120 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
     int voff[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) voff[b] = v_lane_offset(b, half, c);
-    float x[16];
-    bf16x8 ka_lo[4];
-    uint2 va0[4][2];
+    floatx16 acc[4];  // lane (half, c) holds O[column c][32*b + 8*(v/4) + 4*half + v%4] in acc[b][v]
+    float x[16], m, lsum = 0.f;
+    uint32_t w[8];
+    bf16x8 ka[8];
+    uint2 va[8][2];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = 0;
+    const int seen = my_pos + 1 - s0 * kStepTokens;  // tokens of the part that this lane's column sees
+    const int vis = wave_vis - s0 * kStepTokens;     // and some column
     {  // scores of step 0, then the operands turn 0 starts from
         floatx16 sc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) sc[v] = 0.f;
-        bf16x8 ka[8];
-        ka[0] = read_k_operand<0>(k_lane, half, c); ka[1] = read_k_operand<1>(k_lane, half, c);
-        ka[2] = read_k_operand<2>(k_lane, half, c); ka[3] = read_k_operand<3>(k_lane, half, c);
-        ka[4] = read_k_operand<4>(k_lane, half, c); ka[5] = read_k_operand<5>(k_lane, half, c);
-        ka[6] = read_k_operand<6>(k_lane, half, c); ka[7] = read_k_operand<7>(k_lane, half, c);
+        static_for<0, 8>([&](auto j) __attribute__((always_inline)) {
+            constexpr int J = decltype(j)::value;
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k_operand<J>(k_lane, half, c), qb[J], sc, 0, 0, 0);
+        });
+        static_for<0, 4>([&](auto j) __attribute__((always_inline)) {
+            constexpr int J = decltype(j)::value;
+            ka[J] = read_k_operand<J>(k_lane + kStageBytes, half, c);
+        });
+        static_for<0, 3>([&](auto u) __attribute__((always_inline)) {
+            constexpr int U = decltype(u)::value;
+            va[U][0] = va[U][1] = uint2{0, 0};
+        });
+        float top = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[j], qb[j], sc, 0, 0, 0);
-        rebase(st, take_scores<true>(x, sc, my_pos + 1 - s0 * kStepTokens, half), p.scale_log2e);
-        const unsigned char *krow = k_lane + kStageBytes;
-        ka_lo[0] = read_k_operand<0>(krow, half, c); ka_lo[1] = read_k_operand<1>(krow, half, c);
-        ka_lo[2] = read_k_operand<2>(krow, half, c); ka_lo[3] = read_k_operand<3>(krow, half, c);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) read_v_operand<0>(va0[b], s_v + voff[b]);
+        for (int v = 0; v < 16; ++v) {
+            x[v] = 8 * (v >> 2) + 4 * half + (v & 3) >= seen ? -INFINITY : sc[v];
+            top = fmaxf(top, x[v]);
+        }
+        // not below the lowest finite value: a first step that hides all its tokens from a column, or whose scores are
+        // -inf, weighs nothing then, instead of -inf - -inf
+        m = fmaxf(max_over_halves(top) * p.scale_log2e + kBias, -FLT_MAX);
     }
+    wait_for<0, 0>();
     __syncthreads();  // K stage 0 has been read: turn 0 may load step 4 over it
-    if (phased && group == 1) phase_barrier();
 
-    // The turns below the diagonal first (no mask), unrolled by the four phases of the stage
-    // rings, then the one to three turns that the causal mask touches.
-    const unsigned char *v_base = s_v;
-    auto mid = []() __attribute__((always_inline)) {
-        if (phased) phase_barrier();
-    };
+    // The turns whose next step is below the diagonal first (no mask), unrolled by the four phases of the stage rings, then
+    // the ones that the causal mask touches, each loop for itself (as paths of one loop they cost a copy of the accumulators).
 #define KVC_TURN(MASKED, PH, VLIM, LIMIT)                                                                      \
     {                                                                                                          \
         KVC_TURN_BEGIN(PH);                                                                                    \
-        pipeline_turn<MASKED>(st, x, ka_lo, va0, k_lane + ((ph + 1) & 3) * kStageBytes,                        \
-                              k_lane + ((ph + 2) & 3) * kStageBytes, v_base + ph * kStageBytes,                \
-                              v_base + ((ph + 1) & 3) * kStageBytes, voff, qb, p.scale_log2e, VLIM, LIMIT,     \
-                              half, c, turn_k, turn_v, mid, turn_lookup);                                      \
+        pipeline_turn<MASKED>(acc, x, w, lsum, m, ka, va, k_lane + ((ph + 1) & 3) * kStageBytes,       \
+                                      k_lane + ((ph + 2) & 3) * kStageBytes, s_v + ((ph + 3) & 3) * kStageBytes, \
+                                      s_v + ph * kStageBytes, voff, qb, p.scale_log2e, VLIM, LIMIT, half, c,   \
+                                      turn_k, turn_v, turn_lookup, turn_math);                                 \
         KVC_TURN_END();                                                                                        \
         ++s;                                                                                                   \
     }
-    const int plain_turns = min(max(free_steps - 1, 0), wg_steps);
-    while (s + 4 <= plain_turns) {
-        KVC_TURN(false, 0, kStepTokens, kStepTokens)
-        KVC_TURN(false, 1, kStepTokens, kStepTokens)
-        KVC_TURN(false, 2, kStepTokens, kStepTokens)
-        KVC_TURN(false, 3, kStepTokens, kStepTokens)
-    }
-    while (s < plain_turns) KVC_TURN(false, s & 3, kStepTokens, kStepTokens)
     // steps past the last token that any row of this wavefront sees carry no weight for it: it
     // only loads and synchronises during the workgroup's remaining turns
-    const int live_turns = min(wg_steps, (wave_vis + kStepTokens - 1) / kStepTokens - s0);
-    while (s < live_turns)
-        KVC_TURN(true, s & 3, wave_vis - (s0 + s) * kStepTokens, my_pos + 1 - (s0 + s + 1) * kStepTokens)
-    for (; s < wg_steps; ++s) {
-        KVC_TURN_BEGIN(s & 3);
-        mid();
-        turn_lookup();
-        turn_k();
-        turn_v();
-        KVC_TURN_END();
+    const int live_steps = max(1, min(wg_steps, (wave_vis + kStepTokens - 1) / kStepTokens - s0));
+    const int plain_turns = min(free_steps - 1, live_steps - 1);
+    while (s + 4 <= plain_turns) {
+        KVC_TURN(false, 0, 0, 0)
+        KVC_TURN(false, 1, 0, 0)
+        KVC_TURN(false, 2, 0, 0)
+        KVC_TURN(false, 3, 0, 0)
     }
+    while (s < plain_turns) KVC_TURN(false, s & 3, 0, 0)
+    while (s < live_steps - 1) KVC_TURN(true, s & 3, vis - (s - 1) * kStepTokens, seen - (s + 1) * kStepTokens)
+    // this wavefront's last step, a turn without scores of a next one
+    {
+        float top = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) top = fmaxf(top, x[v]);
+        top = fmaxf(m, max_over_halves(top) * p.scale_log2e - 1.0f);
+        static_for<0, 8>([&](auto u) __attribute__((always_inline)) {
+            constexpr int U = decltype(u)::value;
+            if constexpr (U >= 3) {
+                const unsigned char *const sv = s_v + ((s + 3) & 3) * kStageBytes + voff[U & 3];
+                va[U][0] = read_v_half<(U >> 2), 0>(sv);
+                va[U][1] = read_v_half<(U >> 2), 1>(sv);
+            }
+            mask_v_operand<(U >> 2)>(va[U], vis - (s - 1) * kStepTokens, half);
+            acc[U & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va[U]), four_words(w, U >> 2), acc[U & 3], 0, 0, 0);
+        });
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(top > m) != 0, 0)) {
+            const float alpha = __builtin_amdgcn_exp2f(m - top);
+            lsum *= alpha;
+            m = top;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[b] *= alpha;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * i], p.scale_log2e, -m));
+            const float b = __builtin_amdgcn_exp2f(__builtin_fmaf(x[2 * i + 1], p.scale_log2e, -m));
+            w[i] = pack_bf16(a, b);
+            lsum += a + b;
+        }
+        static_for<0, 8>([&](auto u) __attribute__((always_inline)) {
+            constexpr int U = decltype(u)::value;
+            const unsigned char *const sv = s_v + (s & 3) * kStageBytes + voff[U & 3];
+            uint2 vl[2] = {read_v_half<(U >> 2), 0>(sv), read_v_half<(U >> 2), 1>(sv)};
+            mask_v_operand<(U >> 2)>(vl, vis - s * kStepTokens, half);
+            acc[U & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(vl), four_words(w, U >> 2), acc[U & 3], 0, 0, 0);
+        });
+    }
+    for (; s < wg_steps - 1; ++s) KVC_IDLE_TURN();
 #undef KVC_TURN
+#undef KVC_IDLE_TURN
 #undef KVC_TURN_BEGIN
 #undef KVC_TURN_END
-    if (phased && group == 0) phase_barrier();
-    wait_loads_but<0>();  // nothing may still be landing in LDS when the workgroup's LDS is handed on
+    wait_for<0, 0>();  // nothing may still be landing in LDS when the workgroup's LDS is handed on
 
     // lane (half, c) holds O[query row i0 + r][my_head][32*b + 8*a + 4*half .. +3] in acc[b][4a .. 4a+3]
     uint16_t *const dst = out + (size_t(qs + i0 + r) * p.num_q_heads + my_head) * D + 4 * half;
-    const float lsum = sum_over_halves(st.lsum);
+    lsum = sum_over_halves(lsum);
     if (SPLIT && cut < all_steps) {
         // the parts meet: each group hands over two dim blocks and finishes the other two
         even_out();
@@ -704,13 +645,13 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) mine[(16 * b + v) * 64] = group == 0 ? st.acc[2 + b][v] : st.acc[b][v];
-        mine[32 * 64] = st.m;
+            for (int v = 0; v < 16; ++v) mine[(16 * b + v) * 64] = group == 0 ? acc[2 + b][v] : acc[b][v];
+        mine[32 * 64] = m;
         mine[33 * 64] = lsum;
         __syncthreads();
         const float m_o = theirs[32 * 64], l_o = theirs[33 * 64];
-        const float M = fmaxf(st.m, m_o);
-        const float w_m = __builtin_amdgcn_exp2f(st.m - M), w_o = __builtin_amdgcn_exp2f(m_o - M);
+        const float M = fmaxf(m, m_o);
+        const float w_m = __builtin_amdgcn_exp2f(m - M), w_o = __builtin_amdgcn_exp2f(m_o - M);
         const float inv = 1.0f / (w_m * lsum + w_o * l_o);
         if (r < nrows) {
 #pragma unroll
@@ -721,7 +662,7 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int v = 4 * a + i;
-                        o[i] = (w_m * (group == 0 ? st.acc[b][v] : st.acc[2 + b][v]) + w_o * theirs[(16 * b + v) * 64]) * inv;
+                        o[i] = (w_m * (group == 0 ? acc[b][v] : acc[2 + b][v]) + w_o * theirs[(16 * b + v) * 64]) * inv;
                     }
                     *reinterpret_cast<uint2 *>(dst + 32 * (2 * group + b) + 8 * a) = uint2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
                 }
@@ -735,29 +676,25 @@ __global__ __launch_bounds__(256 * GROUPS, 3 - GROUPS) void pa_prefill_mfma32_ke
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 uint2 w;
-                w.x = pack_bf16(st.acc[b][4 * a] * inv, st.acc[b][4 * a + 1] * inv);
-                w.y = pack_bf16(st.acc[b][4 * a + 2] * inv, st.acc[b][4 * a + 3] * inv);
+                w.x = pack_bf16(acc[b][4 * a] * inv, acc[b][4 * a + 1] * inv);
+                w.y = pack_bf16(acc[b][4 * a + 2] * inv, acc[b][4 * a + 3] * inv);
                 *reinterpret_cast<uint2 *>(dst + 32 * b + 8 * a) = w;
             }
     }
 }
 
-// Calls that the kernel of 64-column wavefronts takes (pa_prefill_wide.h), by heads per workgroup; 0: none.  One workgroup
-// of it fills a compute unit, so that a launch needs about 360 of them before the longest tiles no longer stand alone.
-// 32 columns / 64 columns, us, one request and 32 / 8 heads: 2500 tokens (320 workgroups) 58.7 / 64.3, 3000 (376) 81.7 /
-// 78.0, 4096 130 / 119; 64 / 8 heads: 1000 tokens (256) 27.6 / 31.8, 1500 (384) 50.0 / 44.4; 8 / 2 heads: 4096 (128) 56 / 88,
-// four of 4096 120 / 117.  Short requests pay for the start and end of a tile, 15000 cycles against 1400 per 32 tokens: four of
-// 1500 tokens, 32 / 8 heads, 77.8 / 80.1, of 2048 131 / 129, of 3000 260 / 251; with two workgroups per KV head, which share
-// its rows in L2, four of 1000 81.1 / 80.7 and of 1500 156 / 151 (64 / 8 heads).  Two heads per workgroup (16 / 8 heads): four
-// of 2500 96.6 / 99.9, 4096 240 / 228; one request of 8000 244 / 219.  One head: one request of 4096 132 / 129 (32 / 32), 125 /
-// 118 (28 / 4), but four of 4096 490 / 488 and 415 / 422.  Batches with a few long requests among short ones stay here.
-int wide_heads(const PrefillParams &p, int total_q) {
-    const int heads = p.group % 4 == 0 ? 4 : p.group % 2 == 0 ? 2 : 1;
-    const int64_t tile_rows = 256 / heads;
-    if (p.num_q_heads / heads * ((total_q + tile_rows - 1) / tile_rows) < 360) return 0;
-    if (total_q < int64_t(p.num_seqs) * p.max_query_tiles * 32) return 0;  // on average half the longest
-    const int least = heads == 4 ? (p.group % 8 == 0 ? 16 : 32) : heads == 2 ? 48 : 40;  // 64-row tiles of the longest
-    return p.max_query_tiles >= least && (heads > 1 || p.num_seqs == 1) ? heads : 0;
+// Whether the kernel of 64-column wavefronts takes a call (paged_attention_prefill_wide.hip).  It needs four heads of a KV
+// head per workgroup: with two or one (16 / 8, 48 / 8, 32 / 32, 28 / 4, 40 / 8 heads) it gained nothing.  One workgroup fills
+// a compute unit, so that a launch needs about 400 of them before the longest tiles no longer stand alone, and a tile's
+// start and end, 15000 cycles against 1390 per 32 tokens, want long requests.  32 columns / 64 columns, us, 32 / 8 heads, one
+// request: 2500 tokens (320 workgroups) 58.3 / 65.3, 3000 79.7 / 79.8, 3500 102.8 / 95.7, 4096 131.6 / 124.1, 8000 461 / 437;
+// four: 2500 183 / 190, 3500 328 / 335, 4096 451 / 440; six of 4900 794 / 728.  With two workgroups per KV head, which share
+// its rows in L2 (64 / 8 heads), one request: 1500 47.3 / 44.6, 2048 72.8 / 69.2, 2500 105.5 / 108, 4096 253 / 240; four: 1500
+// 150 / 152, 2048 257 / 247, 3000 507 / 479.  Batches with a few long requests among short ones stay here.
+bool wide_ok(const PrefillParams &p, int total_q) {
+    return p.group % 4 == 0 && p.num_q_heads / 4 * ((int64_t(total_q) + 63) / 64) >= 400 &&
+           p.max_query_tiles >= (p.group % 8 == 0 ? 32 : 55) &&      // 64-row tiles of the longest
+           total_q >= int64_t(p.num_seqs) * p.max_query_tiles * 32;  // on average half the longest
 }
 
 }  // namespace
@@ -768,35 +705,25 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
                                  const int32_t *block_tables, const int32_t *context_lens,
                                  const int32_t *q_start, void *out, const PrefillParams &p, int total_q,
                                  hipStream_t stream) {
-    switch (wide_heads(p, total_q)) {
-        case 4: return launch_prefill_wide<4>(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
-        case 2: return launch_prefill_wide<2>(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
-        case 1: return launch_prefill_wide<1>(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
-    }
+    if (wide_ok(p, total_q)) return launch_prefill_wide(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
     const auto *qq = static_cast<const uint16_t *>(q);
     const auto *kk = static_cast<const uint16_t *>(k_cache);
     const auto *vv = static_cast<const uint16_t *>(v_cache);
     auto *oo = static_cast<uint16_t *>(out);
     const int heads = p.heads_per_chunk;
-    const int rows64 = 2 / heads;  // 64-row units in the query rows of four wavefronts
-    // Two groups per workgroup pay off (by a few percent) for long recomputations with workgroups
-    // enough to keep every compute unit busy for several rounds; up to about 2048 query rows per
-    // sequence the finer grain of four-wavefront workgroups wins, whatever the batch (measured).
-    const auto tiles_of = [&](int groups) { return (p.max_query_tiles + rows64 * groups - 1) / (rows64 * groups); };
-    const int64_t wide_grid = int64_t(p.num_q_heads / heads) * p.num_seqs * tiles_of(2);
-    const bool wide = wide_grid >= 2 * 256 && p.max_query_tiles >= 48;
+    const int rows64 = 2 / heads;  // 64-row units in the query rows of a workgroup
     const bool small = p.block_size < 8;
-    const int query_tiles = tiles_of(wide ? 2 : 1);  // max_query_tiles counts 64-row tiles
+    const int query_tiles = (p.max_query_tiles + rows64 - 1) / rows64;  // max_query_tiles counts 64-row tiles
     const int64_t grid = int64_t(p.num_q_heads / heads) * p.num_seqs * query_tiles;
     // at most one workgroup per compute unit (up to two the finer grain of plain ones wins: 2048 tokens 45.6 us
     // plain, 46.2 us split; four chunks of 512 rows 112 / 118 us), and only where the block table reaches far enough
     // for a share: the second group's start costs a short request up to 0.3 us (642 tokens, MHA: 17.3 / 17.6 us)
-    const bool split = !wide && !small && grid <= kNumCUs &&
+    const bool split = !small && grid <= kNumCUs &&
                        int64_t(p.max_blocks_per_seq) * p.block_size > (kMinSplitSteps - 1) * kStepTokens;
     // A grid that fits the device at once (two workgroups of four wavefronts per compute unit)
     // gets the second half of its query tiles in rising order (a few percent on one short request).
     // Chunks of several sequences: what a tile walks depends on its sequence's context, which only the device knows.
-    // Up to 64 tiles are ranked there; grids that fit at once then put the shortest ranks beside the longest.  32 / 8
+    // Up to 64 tiles are ranked there; grids that fit at once then put the shortest ranks beside the longe  32 / 8
     // heads, 16-token blocks, in given order / ranked: four chunks of 512 rows, contexts of 2000 to 4000, 104 to 112 / 92 to
     // 107 us; six of 600 rows, 8000: 393 to 411 / 365 to 391 us; three of 400, 7000: 138 to 154 / 124 to 147 us; five of 200,
     // 6000: 111 to 127 / 102 to 109 us.  Recomputations, whose tiles are in order anyway, lose by it (three of 1000
@@ -808,23 +735,18 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
     const int64_t chunk_reach = 4 * 64 * int64_t(p.max_query_tiles);
     const int rank_from = p.num_seqs > 1 && items <= 64 && grid > kNumCUs &&
                           int64_t(p.max_blocks_per_seq) * p.block_size >= chunk_reach ? int(chunk_reach) : 0;
-    const int fold_at = (!wide && grid <= 2 * kNumCUs) ? (query_tiles + 1) / 2 : query_tiles;
+    const int fold_at = grid <= 2 * kNumCUs ? (query_tiles + 1) / 2 : query_tiles;
     const int fold_ranked = grid <= 2 * kNumCUs ? std::max(1, std::min(int(items), kNumCUs / chunks)) : int(items);
-    const dim3 g{unsigned(grid)}, b(wide || split ? 512 : 256);
-#define KVC_LAUNCH(SMALL, GROUPS, HEADS, SPLIT)                                                                        \
-    pa_prefill_mfma32_kernel<SMALL, GROUPS, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
-                                                                                q_start, oo, p, query_tiles, fold_at, fold_ranked, rank_from)
-#define KVC_LAUNCH_SHAPE(SMALL, HEADS)                       \
-    do {                                                     \
-        if (wide) KVC_LAUNCH(SMALL, 2, HEADS, false);        \
-        else if (split) KVC_LAUNCH(false, 2, HEADS, true);   \
-        else KVC_LAUNCH(SMALL, 1, HEADS, false);             \
-    } while (0)
-    if (small && heads == 2) KVC_LAUNCH_SHAPE(true, 2);
-    else if (small) KVC_LAUNCH_SHAPE(true, 1);
-    else if (heads == 2) KVC_LAUNCH_SHAPE(false, 2);
-    else KVC_LAUNCH_SHAPE(false, 1);
-#undef KVC_LAUNCH_SHAPE
+    const dim3 g{unsigned(grid)}, b(split ? 512 : 256);
+#define KVC_LAUNCH(SMALL, HEADS, SPLIT)                                                                        \
+    pa_prefill_mfma32_kernel<SMALL, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
+                                                                       q_start, oo, p, query_tiles, fold_at, fold_ranked, rank_from)
+    if (small && heads == 2) KVC_LAUNCH(true, 2, false);
+    else if (small) KVC_LAUNCH(true, 1, false);
+    else if (heads == 2 && split) KVC_LAUNCH(false, 2, true);
+    else if (heads == 2) KVC_LAUNCH(false, 2, false);
+    else if (split) KVC_LAUNCH(false, 1, true);
+    else KVC_LAUNCH(false, 1, false);
 #undef KVC_LAUNCH
     return hipGetLastError();
 }

@@ -1,20 +1,19 @@
 // Causal attention of many query positions over the block-allocated KV cache, long requests (gfx950, bf16, head_dim
-// 128, positive scale): wavefronts of 64 score columns on 32x32x16 matrix-core tiles.  Included by one source per
-// HEADS, so that they compile side by side.
+// 128, positive scale, groups of 4, 8, 12 or 16): wavefronts of 64 score columns on 32x32x16 matrix-core tiles.
 //
 // What bounds it.  Wavefronts of 32 columns, two per SIMD (paged_attention_prefill32.hip), read 16 KiB of K and V
 // operands from LDS per 32 x 32 scores: 128 KiB per step of a compute unit, 1024 cycles of LDS bandwidth against 1024
-// matrix cycles; a step takes about 1500 cycles.  Here a wavefront owns two groups of 32 columns that share every
+// matrix cycles; a step takes about 1450 cycles.  Here a wavefront owns two groups of 32 columns that share every
 // operand read, which halves the LDS reads, the address arithmetic and the scalar work per score.  128 accumulator and
 // 64 Q registers (AGPRs, which only matrix instructions touch) leave room for one wavefront per SIMD, so everything
 // that hides latency is in the order of the instructions: a step of 64 columns takes 1390 cycles for 1024 matrix cycles.
 // The issue of one wavefront is what is left: about 220 instructions per step of 4 to 5 cycles each, 8 for an
 // exponential (without loads, LDS reads and barriers a step still takes 1160 cycles).  Long launches run at the power
 // limit (1.75 to 1.9 of 2.4 GHz), where the LDS reads saved count as well.  32 / 8 heads, one request, kernel of 32
-// columns / this one: 3000 tokens 82.4 / 77.9 us, 4096 132.6 / 120.8, 8192 480 / 444, 16384 1850 / 1711 (1285
-// TFLOP/s); three of 3000 181 / 168, six of 4900 774 / 702.
+// columns / this one: 3500 tokens 102.8 / 95.7 us, 4096 131.6 / 124.1, 8000 461 / 437; six of 4900 794 / 728 (16384
+// tokens: 1900 us with the 32-column kernel of turns of two steps, 1775 with this one, 1240 TFLOP/s).
 //
-// Workgroup = (sequence, HEADS query heads of one KV head, 256 / HEADS consecutive query rows), four wavefronts, one
+// Workgroup = (sequence, 4 query heads of one KV head, 64 consecutive query rows), four wavefronts of 16 rows, one
 // workgroup per compute unit.  Column C = kWaveRows * head + row of a wavefront is column c = C % 32 of group C / 32.
 // Layouts of the tiles, of the weights and of the LDS stages are those of paged_attention_prefill32.hip: lane = 32 *
 // half + c holds the 16 scores of column c against tokens 8 (v / 4) + 4 half + v % 4; K rows with 16-byte chunks
@@ -31,8 +30,6 @@
 // The score products are inline asm: the compiler would put their results into AGPRs and copy each score.  It inserts
 // no wait states for them, so nothing near them needs any: scores are read two and more matrix instructions after the
 // last one that writes them, operands come from LDS and from Q (checked in the compiled form by a test).
-#pragma once
-
 #include <float.h>
 #include <math.h>
 
@@ -53,7 +50,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kStepTokens = 32;
 constexpr int kStageBytes = kStepTokens * D * 2;  // K (or V) rows of a step: 32 rows x 256 bytes
 constexpr int kRing = 4;                          // stages of K and of V
-constexpr int kLoads = 2;                         // 1 KiB loads of K (and of V) per wavefront and step
 constexpr float kBias = 7.0f;                     // powers of two that the reference point is set above the largest score
 
 template <int I, int N, class F>
@@ -113,11 +109,12 @@ __device__ inline bf16x8 read_k_operand(const unsigned char *krow, int half, int
     return *reinterpret_cast<const bf16x8 *>(krow + (((2 * J + half) ^ (c & 15)) << 4));
 }
 
-// 16 bytes per lane from global memory straight into LDS, to lds_addr + IMM + 16 * lane (lds_addr uniform).  The compiler
-// does not see these accesses: barriers order them against LDS reads, wait_for() counts them.
-template <int IMM>
-__device__ inline void load_rows(const void *base, uint32_t off, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" :: "s"(lds_addr), "v"(off), "s"(base), "n"(IMM) : "memory");
+// 16 bytes per lane from global memory straight into LDS, to lds_addr + 16 * lane (lds_addr uniform), and a second 1 KiB
+// from and to 1 KiB further on.  The compiler does not see these accesses: barriers order them against LDS reads,
+// wait_for() counts them.
+__device__ inline void load_rows(const void *base, uint32_t off0, uint32_t off1_minus_1k, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
+                 :: "s"(lds_addr), "v"(off0), "v"(off1_minus_1k), "s"(base) : "memory");
 }
 __device__ inline void load_lane_to_lds(const void *addr, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(addr) : "memory");
@@ -142,9 +139,8 @@ __device__ inline void barrier() {
 // Chunk of the turn (one matrix instruction each) in which the arithmetic of score e starts: argument, exponential,
 // rounding and pair sum, sum, one chunk after the other.  Score e: register 2 (e / 4) + e % 2 of group (e / 2) % 2.
 constexpr int arg_chunk(int e) { return e * 3 / 4; }
-// Chunk of load i of the turn, K rows first.  Behind the LDS reads, one in two chunks: 1402 cycles a turn; all four in
-// two chunks 1391, but between the LDS reads 1426 to 1470.
-constexpr int load_chunk(int i) { return 24 + 2 * i; }
+// Chunks of the loads: behind the LDS reads.  Between them a turn takes 1426 to 1470 cycles instead of 1391.
+constexpr int kLoadK = 27, kLoadV = 29;
 
 // One turn: S of step `next`, the weights of step cur (raw scores in x), O += V . P of the step before (weights in w).
 //     chunks  0 .. 15   S += K operand j . Q, both groups; reads K operands 4 .. 7, then the V operands
@@ -153,11 +149,11 @@ constexpr int load_chunk(int i) { return 24 + 2 * i; }
 // The turn starts with ka[0 .. 3] = K operands of step next.  On return x holds the raw scores of step next, w the
 // weights of step cur.  MASKED: `vlim_prev` = tokens of the step before that some column sees, `limit_next` = tokens of
 // step next that this lane's columns see.
-template <bool MASKED, class Issue, class Lookup, class Math>
+template <bool MASKED, class IssueK, class IssueV, class Lookup, class Math>
 __device__ inline void pipeline_turn(floatx16 (&acc)[2][4], float (&x)[2][16], uint32_t (&w)[2][8], float (&lsum)[2], float (&m)[2],
                                      bf16x8 (&ka)[8], const unsigned char *krow1, const unsigned char *krow2, const unsigned char *sv_prev,
                                      const int (&voff)[4], const bf16x8 (&qb)[2][8], float scale_log2e, int vlim_prev,
-                                     const int (&limit_next)[2], int half, int c, const Issue &issue,
+                                     const int (&limit_next)[2], int half, int c, const IssueK &issue_k, const IssueV &issue_v,
                                      const Lookup &lookup, const Math &math) {
     float arg[32], pf[32], pair[16];
     uint2 va[8][2];
@@ -207,9 +203,8 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2][4], float (&x)[2][16], u
         });
         if constexpr (T == 0) lookup();
         if constexpr (T == 31) math();
-        static_for<0, 2 * kLoads>([&](auto load) __attribute__((always_inline)) {
-            if constexpr (T == load_chunk(decltype(load)::value)) issue(load);
-        });
+        if constexpr (T == kLoadK) issue_k();
+        if constexpr (T == kLoadV) issue_v();
         if constexpr (MASKED && T == 18) {
 #pragma unroll
             for (int g = 0; g < 2; ++g)
@@ -258,12 +253,13 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2][4], float (&x)[2][16], u
 }
 
 // SMALL: block_size < 8, rows gathered by a table look-up per lane.
-template <int HEADS, bool SMALL>
+template <bool SMALL>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void pa_prefill_wide_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
     uint16_t *__restrict__ out, PrefillParams p, int query_tiles) {
-    constexpr int kWaveRows = 64 / HEADS;          // query rows of a wavefront
+    constexpr int kHeads = 4;
+    constexpr int kWaveRows = 64 / kHeads;         // query rows of a wavefront
     constexpr int kTileRows = 4 * kWaveRows;       // and of the workgroup
     constexpr int kQBytes = 64 * D * 2;            // Q rows of a wavefront's columns
     __shared__ __attribute__((aligned(1024))) unsigned char s_k[kRing * kStageBytes], s_v[kRing * kStageBytes], s_q4[4 * kQBytes];
@@ -273,10 +269,10 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     const int half = lane >> 5, c = lane & 31;
     unsigned char *const s_q = s_q4 + wave * kQBytes;
 
-    const int chunks = p.num_q_heads / HEADS;
+    const int chunks = p.num_q_heads / kHeads;
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order), the longest query tiles first
     const int chunk = blockIdx.x % chunks, index = blockIdx.x / chunks;
-    const int head0 = chunk * HEADS;
+    const int head0 = chunk * kHeads;
     const int kvh = head0 / p.group;
     const int n = index % p.num_seqs, qtile = query_tiles - 1 - index / p.num_seqs;
     const int S = context_lens[n], qs = q_start[n], Qn = q_start[n + 1] - qs;
@@ -297,13 +293,13 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     const size_t block_bytes = head_bytes * p.num_kv_heads;
     const unsigned char *const k_head = reinterpret_cast<const unsigned char *>(k_cache) + size_t(kvh) * head_bytes;
     const unsigned char *const v_head = reinterpret_cast<const unsigned char *>(v_cache) + size_t(kvh) * head_bytes;
-    const int sub_mask = (1 << p.tiles_per_block_log2) - 1;
+    const unsigned tile_mask = (p.block_size - 1) & ~15;  // of a token: its 16-row tile inside its block
     const int share_row = 8 * wave;
     const int lchunk = lane & 15;
     const int lrow = (share_row & 15) + (lane >> 4);  // row of load 0 in its tile; load 1: + 4
     const int brow = lrow & (p.block_size - 1);       // in its block, where that holds 8 tokens (16 or more: lrow)
     // offsets of load 1 are 1024 bytes on through its immediate, on both sides
-    const uint32_t k_off[kLoads] = {uint32_t(brow * 256 + ((lchunk ^ lrow) << 4)), uint32_t(brow * 256 + ((lchunk ^ (lrow + 4)) << 4))};
+    const uint32_t k_off[2] = {uint32_t(brow * 256 + ((lchunk ^ lrow) << 4)), uint32_t(brow * 256 + ((lchunk ^ (lrow + 4)) << 4))};
     const uint32_t v_off = brow * 256 + ((4 * (((lchunk >> 2) - lrow) & 3) + (lchunk & 3)) << 4);
     const uint32_t lds_k0 = uint32_t(reinterpret_cast<uintptr_t>(s_k)) + 256 * share_row;
     const uint32_t lds_v0 = uint32_t(reinterpret_cast<uintptr_t>(s_v)) + 256 * share_row;
@@ -325,8 +321,9 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
             id.b = table[min(tok + 4, last_pos) >> p.block_size_log2];
         } else {
             const unsigned tok = unsigned(min(tok_next, last_pos));
-            id.a = __builtin_amdgcn_readfirstlane(table[tok >> p.block_size_log2]);
-            id.b = ((tok >> 4) & sub_mask) * (kTileTokens * 256);
+            // the byte offset fits 32 bits (blocks of 8 tokens and more), which the scalar load adds by itself
+            id.a = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(table) + (tok >> p.block_size_log2) * 4u);
+            id.b = (tok & tile_mask) * 256;
         }
         tok_next += kStepTokens;
         return id;
@@ -334,21 +331,22 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     using At = std::conditional_t<SMALL, Ids, uint64_t>;
     auto offset_of = [&](const Ids &id) __attribute__((always_inline)) -> At {
         if constexpr (SMALL) return id;
-        else return uint64_t(id.a) * block_bytes + id.b;
+        else return uint64_t(id.a) * uint32_t(block_bytes) + id.b;
     };
-    auto issue = [&](const unsigned char *head, uint32_t off, uint32_t lds, const At &at, auto load) __attribute__((always_inline)) {
-        constexpr int I = decltype(load)::value;
-        if constexpr (SMALL)
-            load_lane_to_lds(head + size_t(I ? at.b : at.a) * block_bytes + ((lrow + 4 * I) & (p.block_size - 1)) * 256 + (off & 255),
-                             __builtin_amdgcn_readfirstlane(lds + 1024 * I));
-        else
-            load_rows<1024 * I>(head + at, off, __builtin_amdgcn_readfirstlane(lds));
+    auto issue_rows = [&](const unsigned char *head, uint32_t off0, uint32_t off1_minus_1k, uint32_t lds, const At &at) __attribute__((always_inline)) {
+        lds = __builtin_amdgcn_readfirstlane(lds);
+        if constexpr (SMALL) {
+            load_lane_to_lds(head + size_t(at.a) * block_bytes + (lrow & (p.block_size - 1)) * 256 + (off0 & 255), lds);
+            load_lane_to_lds(head + size_t(at.b) * block_bytes + ((lrow + 4) & (p.block_size - 1)) * 256 + (off1_minus_1k & 255), lds + 1024);
+        } else {
+            load_rows(head + at, off0, off1_minus_1k, lds);
+        }
     };
-    auto issue_k = [&](int stage, const At &at, auto load) __attribute__((always_inline)) {
-        issue(k_head, k_off[decltype(load)::value], lds_k0 + stage * kStageBytes, at, load);
+    auto issue_k = [&](int stage, const At &at) __attribute__((always_inline)) {
+        issue_rows(k_head, k_off[0], k_off[1], lds_k0 + stage * kStageBytes, at);
     };
-    auto issue_v = [&](int stage, const At &at, auto load) __attribute__((always_inline)) {
-        issue(v_head, v_off, lds_v0 + stage * kStageBytes, at, load);
+    auto issue_v = [&](int stage, const At &at) __attribute__((always_inline)) {
+        issue_rows(v_head, v_off, v_off, lds_v0 + stage * kStageBytes, at);
     };
     // Q rows go through LDS as well: their loads are then waited for together with those of the first K and V rows.
 #pragma unroll
@@ -360,15 +358,14 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     }
     // Rows of step j live in stages j % 4.  Turn s requests the K rows of step s + 4 (over those of step s) and the V rows
     // of step s + 2 (over those of step s - 2), and reads K rows of steps s + 1 and s + 2 and V rows of step s - 1.  Before
-    // the barrier that ends it a wavefront waits for its LDS reads and for its loads up to the K rows of turn s - 1.
+    // the barrier that ends it a wavefront waits for its LDS reads and for its loads of turn s - 1 (the V rows of step s + 1
+    // are read in turn s + 2, or by the last step in place of turn s + 1).
     At at_v[2], at_k;
     static_for<0, kRing>([&](auto i) __attribute__((always_inline)) {
         constexpr int I = decltype(i)::value;
         const At at = offset_of(next_ids());
-        static_for<0, kLoads>([&](auto load) __attribute__((always_inline)) {
-            issue_k(I, at, load);
-            if constexpr (I < kRing - 2) issue_v(I, at, load);
-        });
+        issue_k(I, at);
+        if constexpr (I < kRing - 2) issue_v(I, at);
         if constexpr (I >= kRing - 2) at_v[I - (kRing - 2)] = at;
     });
     at_k = offset_of(next_ids());
@@ -444,17 +441,14 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
             at_v[1] = at_k;                                                                                           \
             at_k = offset_of(ids);                                                                                    \
         };                                                                                                            \
-        auto turn_issue = [&](auto load) __attribute__((always_inline)) {                                             \
-            constexpr int I = decltype(load)::value;                                                                  \
-            if constexpr (I < kLoads) issue_k(ph, at_k, load);                                                        \
-            else issue_v((ph + kRing - 2) % kRing, at_v[0], std::integral_constant<int, I - kLoads>{});               \
-        };                                                                                                            \
+        auto turn_k = [&]() __attribute__((always_inline)) { issue_k(ph, at_k); };                                    \
+        auto turn_v = [&]() __attribute__((always_inline)) { issue_v((ph + kRing - 2) % kRing, at_v[0]); };           \
         auto turn_lookup = [&]() __attribute__((always_inline)) { ids = next_ids(); };                                \
         const int lim[2] = {LIMIT0, LIMIT1};                                                                          \
         pipeline_turn<MASKED>(acc, x, w, lsum, m, ka, k_lane + ((ph + 1) % kRing) * kStageBytes,                      \
                               k_lane + ((ph + 2) % kRing) * kStageBytes, s_v + ((ph + kRing - 1) % kRing) * kStageBytes,\
-                              voff, qb, p.scale_log2e, VLIM, lim, half, c, turn_issue, turn_lookup, turn_math);       \
-        wait_for<((kRing - 3) * 2 + 1) * kLoads, 0>();                                                                \
+                              voff, qb, p.scale_log2e, VLIM, lim, half, c, turn_k, turn_v, turn_lookup, turn_math);   \
+        wait_for<4, 0>();                                                                                             \
         barrier();                                                                                                    \
         ++s;                                                                                                          \
     }
@@ -550,17 +544,14 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 
 }  // namespace
 
-template <int HEADS>
 hipError_t launch_prefill_wide(const void *q, const void *k_cache, const void *v_cache, const int32_t *block_tables,
                                const int32_t *context_lens, const int32_t *q_start, void *out, const PrefillParams &p,
                                hipStream_t stream) {
-    constexpr int kRows64 = 4 / HEADS;  // 64-row units of a workgroup's query rows; max_query_tiles counts these
-    const int query_tiles = (p.max_query_tiles + kRows64 - 1) / kRows64;
-    const int64_t grid = int64_t(p.num_q_heads / HEADS) * p.num_seqs * query_tiles;
-    const auto kernel = p.block_size < 8 ? pa_prefill_wide_kernel<HEADS, true> : pa_prefill_wide_kernel<HEADS, false>;
+    const int64_t grid = int64_t(p.num_q_heads / 4) * p.num_seqs * p.max_query_tiles;
+    const auto kernel = p.block_size < 8 ? pa_prefill_wide_kernel<true> : pa_prefill_wide_kernel<false>;
     kernel<<<dim3(unsigned(grid)), dim3(256), 0, stream>>>(static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
                                                            static_cast<const uint16_t *>(v_cache), block_tables, context_lens,
-                                                           q_start, static_cast<uint16_t *>(out), p, query_tiles);
+                                                           q_start, static_cast<uint16_t *>(out), p, p.max_query_tiles);
     return hipGetLastError();
 }
 

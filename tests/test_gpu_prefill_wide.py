@@ -1,5 +1,5 @@
-"""Long requests: the prefill kernel of 64-column wavefronts (four, two or one query heads and 64, 128 or 256 query rows per
-workgroup), against attention in float64 on the dense sequence.
+"""Long requests: the prefill kernel of 64-column wavefronts (four query heads and 64 query rows per workgroup), against
+attention in float64 on the dense sequence.
 
 Sizes are just above the lines from which that kernel takes a call, with row counts that leave wavefronts with part of
 their rows or none, contexts longer than the rows, blocks of 4 to 256 tokens, and NaN wherever no context reaches.
@@ -19,12 +19,11 @@ from test_gpu_prefill_d64 import poison
 pytestmark = pytest.mark.gpu
 
 
-def takes(heads, hq, qlens):
+def takes(hq, hkv, qlens):
     """The rule by which the library picks the kernel, restated."""
     tiles = -(-max(qlens) // 64)
-    least = {4: 16 if hq[0] // hq[1] % 8 == 0 else 32, 2: 48, 1: 40}[heads]
-    return (hq[0] // heads * -(-sum(qlens) // (256 // heads)) >= 360 and sum(qlens) >= len(qlens) * tiles * 32
-            and tiles >= least and (heads > 1 or len(qlens) == 1))
+    return (hq // hkv % 4 == 0 and hq // 4 * -(-sum(qlens) // 64) >= 400 and sum(qlens) >= len(qlens) * tiles * 32
+            and tiles >= (32 if hq // hkv % 8 == 0 else 55))
 
 
 def exact(w, q, qs):
@@ -52,35 +51,33 @@ def check(w, q, qs, qlens, what):
     assert np.abs(got - ref).max() <= BF16_TOL
 
 
-@pytest.mark.parametrize("heads,hq,lens,qlens,bs", [
-    (4, (128, 16), [1000], [1000], 16), (4, (128, 16), [1100], [961], 4), (4, (128, 8), [1025], [1025], 8),
-    (4, (128, 16), [1301, 700, 33], [1000, 700, 33], 64), (4, (64, 16), [1985], [1985], 16), (4, (64, 16), [2111, 1990], [1999, 1990], 256),
-    (2, (32, 16), [3009], [3009], 16), (2, (32, 16), [3200], [3041], 4), (2, (48, 8), [3137], [3137], 8),
-    (1, (40, 40), [2497], [2497], 16), (1, (39, 13), [2600], [2561], 2)])
-def test_matches_float64(heads, hq, lens, qlens, bs):
-    assert takes(heads, hq, qlens)
-    w, q, qs = make(1300 + heads + bs, lens, qlens, *hq, bs=bs)
+@pytest.mark.parametrize("hq,hkv,lens,qlens,bs", [
+    (64, 8, [1985], [1985], 16), (64, 8, [2111], [1999], 4), (64, 4, [2049], [2049], 8), (64, 8, [2301, 1400, 33], [2000, 1400, 33], 64),
+    (32, 8, [3457], [3457], 16), (32, 8, [3601], [3490], 2), (48, 4, [3521], [3521], 256)])
+def test_matches_float64(hq, hkv, lens, qlens, bs):
+    assert takes(hq, hkv, qlens)
+    w, q, qs = make(1300 + hq + bs, lens, qlens, hq, hkv, bs=bs)
     poison(w)
-    check(w, q, qs, qlens, f"{hq} {lens} {qlens} bs={bs}")
+    check(w, q, qs, qlens, f"{hq}/{hkv} {lens} {qlens} bs={bs}")
 
 
 def test_scores_that_keep_growing_move_the_reference_point():
     """Every few steps the largest score so far is passed by more than the reference point allows, in all columns."""
-    w, q, qs = make(1350, [1030], [1030], 128, 16)
+    w, q, qs = make(1350, [2010], [2010], 64, 8)
     q[:, :, 1] = 0x3F80                                   # q[1] = 1
-    ramp = np.linspace(-40.0, 40.0, 1030).astype(np.float32)
-    for t in range(1030):
+    ramp = np.linspace(-40.0, 40.0, 2010).astype(np.float32)
+    for t in range(2010):
         w.k_cache[w.block_tables[0, t // 16], :, t % 16, 1] = W.f32_to_bf16_bits(ramp[t:t + 1] * 8)[0]
-    check(w, q, qs, [1030], "ramp")
+    check(w, q, qs, [2010], "ramp")
 
 
 def test_scores_of_minus_infinity_weigh_nothing():
     """The first two steps' scores are -inf in every column, and single ones later."""
-    w, q, qs = make(1360, [1000], [1000], 128, 16)
+    w, q, qs = make(1360, [2000], [2000], 64, 8)
     q[:, :, 0] = 0x3F80
     for t in [*range(64), 100, 511, 999]:
         w.k_cache[w.block_tables[0, t // 16], :, t % 16, 0] = 0xFF80
     print("[case] prefill wide -inf", flush=True)
-    got, ref = out_to_f64(run(w, q, qs, 1000))[64:], exact(w, q, qs)[64:]  # earlier rows see nothing else
+    got, ref = out_to_f64(run(w, q, qs, 2000))[64:], exact(w, q, qs)[64:]  # earlier rows see nothing else
     assert np.isfinite(got).all()
     assert np.abs(got - ref).max() <= BF16_TOL

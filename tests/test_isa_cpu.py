@@ -105,7 +105,7 @@ def test_score_products_of_the_wide_prefill_need_no_wait_states(tmp_path):
 
     products, kernel = 0, False
     recent, pending = [], {}      # the last instructions' results; registers of scores -> matrix instructions since
-    for ln in _assembly(tmp_path, os.path.join(B.CSRC, "paged_attention_prefill_wide4.hip")):
+    for ln in _assembly(tmp_path, os.path.join(B.CSRC, "paged_attention_prefill_wide.hip")):
         if re.match(r"^_ZN\S*pa_prefill_wide_kernel\S*:", ln):
             kernel, recent, pending = True, [], {}
         t = ln.strip()
