@@ -1,12 +1,13 @@
-"""Prefill launches of at most one workgroup per compute unit: from 768 tokens (24 steps of 32) on, the two groups of a
-workgroup share its context.  Lengths around that line and around odd and even numbers of steps, row counts that leave
+"""Prefill launches of at most one workgroup per compute unit: from 1121 tokens (36 steps of 32) on, the two groups of a
+workgroup share its context.  Lengths around that line, and below it, and around odd and even numbers of steps, row counts that leave
 wavefronts without rows, every head layout, blocks of 8 tokens and more, against the oracle."""
 import numpy as np
 import pytest
 
 import kvc_workloads as W  # noqa: F401
-from test_gpu_prefill import check, make
-from test_gpu_prefill_d64 import poison
+from gpu_util import BF16_TOL, out_to_f64
+from test_gpu_prefill import check, make, run
+from test_gpu_prefill_d64 import poison, reference
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,28 @@ def test_chunks_of_several_sequences_are_ranked(oracle_mod, nseq, rows, longest)
     items = nseq * -(-rows // 64)
     assert items <= 64 and items * 16 > 256 and w.max_blocks_per_seq * 16 >= 4 * 64 * -(-rows // 64)
     check(oracle_mod, w, q, qs, f"ranked {nseq}")
+
+
+@pytest.mark.parametrize("hq,hkv,bs", [(8, 2, 16), (3, 1, 32), (4, 4, 8)])
+def test_contexts_around_the_line_from_which_they_are_shared(oracle_mod, hq, hkv, bs):
+    lens = [1119, 1120, 1121, 1152, 1153, 1154, 1184, 1185, 1217, 1300]
+    qlens = [64, 1, 17, 33, 64, 65, 128, 5, 63, 130]
+    for i in range(0, len(lens), 5):      # five at a time: the launch stays within 256 workgroups
+        w, q, qs = make(1190 + hq + bs + i, lens[i:i + 5], qlens[i:i + 5], hq, hkv, bs=bs)
+        poison(w)
+        assert len(lens[i:i + 5]) * 3 * hq <= 256
+        check(oracle_mod, w, q, qs, f"split line {hq}/{hkv} bs={bs}")
+
+
+@pytest.mark.parametrize("hq,hkv,lens,qlens", [(32, 8, [300, 200], [300, 200]), (8, 2, [1400], [1400])])  # plain; shared
+def test_scores_of_minus_infinity_weigh_nothing(oracle_mod, hq, hkv, lens, qlens):
+    """The first two steps' scores are -inf in every column of the first sequence."""
+    w, q, qs = make(1195 + hq, lens, qlens, hq, hkv)
+    q[:, :, 0] = 0x3F80
+    for t in range(64):
+        w.k_cache[w.block_tables[0, t // 16], :, t % 16, 0] = 0xFF80
+    print(f"[case] prefill -inf {hq}/{hkv}", flush=True)
+    got = out_to_f64(run(w, q, qs, max(qlens)))
+    ref = reference(oracle_mod, w, q, qs)
+    assert np.isfinite(got[64:]).all()     # earlier rows see nothing else
+    assert np.abs(got[64:] - ref[64:]).max() <= BF16_TOL
