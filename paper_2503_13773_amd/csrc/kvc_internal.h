@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "kvc.h"
+#include "prefill_route.h"
 
 namespace kvc {
 
@@ -25,21 +26,6 @@ struct AttnParams {
     int max_context_len;    // context lengths are clamped to this (the bound every size is derived from)
     float scale;            // as given by the caller
     float scale_log2e;      // scale * log2(e), for the base-2 softmax of the MFMA kernel
-};
-
-// Causal multi-query (prefill / recompute) attention.
-struct PrefillParams {
-    int num_seqs;
-    int num_q_heads;
-    int num_kv_heads;
-    int group;                 // num_q_heads / num_kv_heads
-    int heads_per_chunk;       // query heads one wavefront carries (1 or 2; divides group)
-    int block_size;
-    int block_size_log2;
-    int tiles_per_block_log2;  // log2(block_size / 16); 0 for block sizes below 16
-    int max_blocks_per_seq;
-    int max_query_tiles;       // ceil(max_query_len / 64)
-    float scale_log2e;
 };
 
 // Workspace layout.  The first kWorkspaceHeaderBytes hold the arrival counters of the
@@ -68,7 +54,6 @@ struct Schedule {
 
 constexpr int kThreads = 256;       // 4 wavefronts per workgroup, every attention kernel
 constexpr int kWaves = kThreads / 64;
-constexpr int kNumCUs = 256;        // MI355X
 constexpr int kMaxStreamSeqs = 4096;  // batch limit of the balanced kernel (prefix sum lives in LDS)
 
 // Launchers (defined next to their kernels).  All enqueue on `stream` and return the
