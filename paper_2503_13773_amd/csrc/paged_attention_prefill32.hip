@@ -689,20 +689,6 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void pa_prefill_m
     }
 }
 
-// Whether the kernel of 64-column wavefronts takes a call (paged_attention_prefill_wide.hip).  It needs four heads of a KV
-// head per workgroup: with two or one (16 / 8, 48 / 8, 32 / 32, 28 / 4, 40 / 8 heads) it gained nothing.  One workgroup fills
-// a compute unit, so that a launch needs about 400 of them before the longest tiles no longer stand alone, and a tile's
-// start and end, 15000 cycles against 1390 per 32 tokens, want long requests.  32 columns / 64 columns, us, 32 / 8 heads, one
-// request: 2500 tokens (320 workgroups) 58.3 / 65.3, 3000 79.7 / 79.8, 3500 102.8 / 95.7, 4096 131.6 / 124.1, 8000 461 / 437;
-// four: 2500 183 / 190, 3500 328 / 335, 4096 451 / 440; six of 4900 794 / 728.  With two workgroups per KV head, which share
-// its rows in L2 (64 / 8 heads), one request: 1500 47.3 / 44.6, 2048 72.8 / 69.2, 2500 105.5 / 108, 4096 253 / 240; four: 1500
-// 150 / 152, 2048 257 / 247, 3000 507 / 479.  Batches with a few long requests among short ones stay here.
-bool wide_ok(const PrefillParams &p, int total_q) {
-    return p.group % 4 == 0 && p.num_q_heads / 4 * ((int64_t(total_q) + 63) / 64) >= 400 &&
-           p.max_query_tiles >= (p.group % 8 == 0 ? 32 : 55) &&      // 64-row tiles of the longest
-           total_q >= int64_t(p.num_seqs) * p.max_query_tiles * 32;  // on average half the longest
-}
-
 }  // namespace
 
 // Needs a positive scale (the max is taken over raw scores).  heads_per_chunk = 2: two heads of a
@@ -711,7 +697,7 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
                                  const int32_t *block_tables, const int32_t *context_lens,
                                  const int32_t *q_start, void *out, const PrefillParams &p, int total_q,
                                  hipStream_t stream) {
-    if (wide_ok(p, total_q)) return launch_prefill_wide(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
+    if (prefill_wide(p, total_q)) return launch_prefill_wide(q, k_cache, v_cache, block_tables, context_lens, q_start, out, p, stream);
     const auto *qq = static_cast<const uint16_t *>(q);
     const auto *kk = static_cast<const uint16_t *>(k_cache);
     const auto *vv = static_cast<const uint16_t *>(v_cache);

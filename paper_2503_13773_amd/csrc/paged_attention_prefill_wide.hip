@@ -10,8 +10,8 @@
 // The issue of one wavefront is what is left: about 220 instructions per step of 4 to 5 cycles each, 8 for an
 // exponential (without loads, LDS reads and barriers a step still takes 1160 cycles).  Long launches run at the power
 // limit (1.75 to 1.9 of 2.4 GHz), where the LDS reads saved count as well.  32 / 8 heads, one request, kernel of 32
-// columns / this one: 3500 tokens 102.8 / 95.7 us, 4096 131.6 / 124.1, 8000 461 / 437; six of 4900 794 / 728 (16384
-// tokens: 1900 us with the 32-column kernel of turns of two steps, 1775 with this one, 1240 TFLOP/s).
+// columns / this one, us: 3500 tokens 98.9 / 93.6, 4096 126.1 / 121.2, 8000 442 / 434, 16384 1803 / 1768 (1244 TFLOP/s);
+// six of 3600 437 / 417.  Which calls it takes: prefill_wide() in prefill_route.h.
 //
 // Workgroup = (sequence, 4 query heads of one KV head, 64 consecutive query rows), four wavefronts of 16 rows, one
 // workgroup per compute unit.  Column C = kWaveRows * head + row of a wavefront is column c = C % 32 of group C / 32.

@@ -17,6 +17,7 @@ static PrefillParams params(const int *v) {
     return p;
 }
 extern "C" {
+int wide(const int *v, long long total_q) { return prefill_wide(params(v), total_q); }
 int by_units(const int *v, long long grid) { return prefill_by_units(params(v), grid); }
 void places(int blocks, int group, int kv_heads, int *out) {
     for (int b = 0; b < blocks; ++b) {

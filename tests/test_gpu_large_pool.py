@@ -13,6 +13,9 @@ pytestmark = pytest.mark.gpu
 NB_BIG = 150_000            # x 8 heads x 16 tokens x 128 dims x 2 bytes = 4.9 GB per pool
 
 
+WIDE = (32, 8, [3500])      # a long request on the kernel of 64-column wavefronts
+
+
 def big_pools(w, rng):
     """Device pools of NB_BIG blocks holding w's blocks at ids spread over the whole range."""
     nb = w.k_cache.shape[0]
@@ -85,3 +88,19 @@ def test_decode_prefill_append_and_copy_beyond_4_gib(oracle_mod):
     torch.cuda.synchronize()
     assert torch.equal(pool[0, torch.from_numpy(far).cuda()], dst_small[0, :len(far)])
     assert torch.equal(pool[1, torch.from_numpy(far).cuda()], dst_small[1, :len(far)])
+
+
+def test_long_prefill_beyond_4_gib():
+    from test_gpu_prefill import make
+    from test_gpu_prefill_wide import exact
+    import paper_2503_13773_amd as K
+    if torch.cuda.get_device_properties(0).total_memory < 24e9:
+        pytest.skip("needs 24 GB of device memory")
+    hq, hkv, lens = WIDE
+    w, q, qs = make(4200, lens, lens, hq, hkv)
+    kb, vb, tables, _ = big_pools(w, np.random.default_rng(4201))
+    print("[case] long prefill, pool of 4.9 GB", flush=True)
+    out = K.paged_attention_prefill(dev_tensor(q, W.BF16), kb, vb, torch.from_numpy(tables).cuda(), torch.from_numpy(w.context_lens).cuda(),
+                                    torch.from_numpy(qs).cuda(), w.scale, lens[0])
+    torch.cuda.synchronize()
+    assert np.abs(out_to_f64(out) - exact(w, q, qs)).max() <= BF16_TOL

@@ -83,10 +83,9 @@ def test_blocks_of_several_tiles(oracle_mod, bs):
     check(oracle_mod, w, q, qs, f"bs={bs}")
 
 
-def test_long_ragged_recompute_in_128_row_workgroups(oracle_mod):
-    """From 3072 query rows per sequence on (and 512 workgroups or more) a workgroup is two groups of
-    four wavefronts and 128 query rows: 3100 and 3073 rows leave the last workgroup with 28 rows (two
-    wavefronts of the first group) and with 1 row; sampled rows against the oracle's decode over the
+def test_long_ragged_recompute_of_two_requests(oracle_mod):
+    """Long requests on 32-column wavefronts: 3100 and 3073 rows leave the last workgroup of 64 rows with 28
+    rows (two of its wavefronts) and with 1 row; sampled rows against the oracle's decode over the
     truncated context."""
     lens, qlens = [3100, 3300], [3100, 3073]
     w, q, qs = make(370, lens, qlens, 32, 8)

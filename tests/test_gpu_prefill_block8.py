@@ -29,10 +29,12 @@ def paged(dense, bs, seed):
     return tables, pool
 
 
-# 64-row and 128-row workgroups, two heads and one head per wavefront
-@pytest.mark.parametrize("hq,hkv,lens,qlens", [(8, 2, [1, 7, 8, 9, 25, 200, 333], [1, 7, 8, 9, 25, 100, 333]),
-                                               (7, 1, [1, 8, 15, 17, 130, 300], [1, 8, 15, 17, 130, 40]),
-                                               (32, 2, [3100, 3073], [3100, 3073]), (28, 4, [3333, 70], [3333, 70])])
+# two heads and one head per workgroup, launches that fit the device at once and long ones, 64 columns per wavefront (the last)
+SHAPES = [(8, 2, [1, 7, 8, 9, 25, 200, 333], [1, 7, 8, 9, 25, 100, 333]), (7, 1, [1, 8, 15, 17, 130, 300], [1, 8, 15, 17, 130, 40]),
+          (32, 2, [3100, 3073], [3100, 3073]), (28, 4, [3333, 70], [3333, 70]), (32, 2, [3600], [3577])]
+
+
+@pytest.mark.parametrize("hq,hkv,lens,qlens", SHAPES)
 def test_blocks_of_8_equal_blocks_of_16(hq, hkv, lens, qlens):
     import paper_2503_13773_amd as K
     gen = torch.Generator().manual_seed(11)

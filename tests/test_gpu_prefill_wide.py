@@ -1,7 +1,7 @@
 """Long requests: the prefill kernel of 64-column wavefronts (four query heads and 64 query rows per workgroup), against
 attention in float64 on the dense sequence.
 
-Sizes are just above the lines from which that kernel takes a call, with row counts that leave wavefronts with part of
+Sizes are near the lines between which that kernel takes a call, with row counts that leave wavefronts with part of
 their rows or none, contexts longer than the rows, blocks of 4 to 256 tokens, and NaN wherever no context reaches.
 
 Tolerance: weights are rounded to bf16 (2^-9 relative, with |V| < 6 at most 0.012) and so is the output (2^-9 relative)."""
@@ -19,11 +19,11 @@ from test_gpu_prefill_d64 import poison
 pytestmark = pytest.mark.gpu
 
 
-def takes(hq, hkv, qlens):
-    """The rule by which the library picks the kernel, restated."""
-    tiles = -(-max(qlens) // 64)
-    return (hq // hkv % 4 == 0 and hq // 4 * -(-sum(qlens) // 64) >= 400 and sum(qlens) >= len(qlens) * tiles * 32
-            and tiles >= (32 if hq // hkv % 8 == 0 else 55))
+# (query heads, KV heads, contexts, query rows, block size); a test on the host asks the library whether they take this kernel
+SHAPES = [(64, 8, [1985], [1985], 16), (64, 8, [2111], [1999], 4), (64, 4, [2049], [2040], 8),
+          (64, 8, [2301, 2000, 1990, 1500, 33], [2000, 2000, 1990, 1500, 33], 64),
+          (32, 8, [3457], [3457], 16), (32, 8, [3601], [3490], 2), (48, 4, [2321], [2321], 256)]
+SPECIAL = (64, 8, [2000])
 
 
 def exact(w, q, qs):
@@ -51,11 +51,8 @@ def check(w, q, qs, qlens, what):
     assert np.abs(got - ref).max() <= BF16_TOL
 
 
-@pytest.mark.parametrize("hq,hkv,lens,qlens,bs", [
-    (64, 8, [1985], [1985], 16), (64, 8, [2111], [1999], 4), (64, 4, [2049], [2049], 8), (64, 8, [2301, 1400, 33], [2000, 1400, 33], 64),
-    (32, 8, [3457], [3457], 16), (32, 8, [3601], [3490], 2), (48, 4, [3521], [3521], 256)])
+@pytest.mark.parametrize("hq,hkv,lens,qlens,bs", SHAPES)
 def test_matches_float64(hq, hkv, lens, qlens, bs):
-    assert takes(hq, hkv, qlens)
     w, q, qs = make(1300 + hq + bs, lens, qlens, hq, hkv, bs=bs)
     poison(w)
     check(w, q, qs, qlens, f"{hq}/{hkv} {lens} {qlens} bs={bs}")
@@ -63,21 +60,23 @@ def test_matches_float64(hq, hkv, lens, qlens, bs):
 
 def test_scores_that_keep_growing_move_the_reference_point():
     """Every few steps the largest score so far is passed by more than the reference point allows, in all columns."""
-    w, q, qs = make(1350, [2010], [2010], 64, 8)
+    hq, hkv, lens = SPECIAL
+    w, q, qs = make(1350, lens, lens, hq, hkv)
     q[:, :, 1] = 0x3F80                                   # q[1] = 1
-    ramp = np.linspace(-40.0, 40.0, 2010).astype(np.float32)
-    for t in range(2010):
+    ramp = np.linspace(-40.0, 40.0, lens[0]).astype(np.float32)
+    for t in range(lens[0]):
         w.k_cache[w.block_tables[0, t // 16], :, t % 16, 1] = W.f32_to_bf16_bits(ramp[t:t + 1] * 8)[0]
-    check(w, q, qs, [2010], "ramp")
+    check(w, q, qs, lens, "ramp")
 
 
 def test_scores_of_minus_infinity_weigh_nothing():
     """The first two steps' scores are -inf in every column, and single ones later."""
-    w, q, qs = make(1360, [2000], [2000], 64, 8)
+    hq, hkv, lens = SPECIAL
+    w, q, qs = make(1360, lens, lens, hq, hkv)
     q[:, :, 0] = 0x3F80
     for t in [*range(64), 100, 511, 999]:
         w.k_cache[w.block_tables[0, t // 16], :, t % 16, 0] = 0xFF80
     print("[case] prefill wide -inf", flush=True)
-    got, ref = out_to_f64(run(w, q, qs, 2000))[64:], exact(w, q, qs)[64:]  # earlier rows see nothing else
+    got, ref = out_to_f64(run(w, q, qs, lens[0]))[64:], exact(w, q, qs)[64:]  # earlier rows see nothing else
     assert np.isfinite(got).all()
     assert np.abs(got - ref).max() <= BF16_TOL

@@ -46,3 +46,36 @@ def test_odd_groups_place_long_launches_by_units(route, hq, hkv, qlens, units):
     heads = 2 if hq // hkv % 2 == 0 else 1
     grid = hq // heads * len(qlens) * -(-max(qlens) // (128 // heads))
     assert bool(route.by_units(v, ctypes.c_longlong(grid))) == units
+
+
+def wide(route, hq, hkv, qlens):
+    return bool(route.wide(prefill_route.values(hq, hkv, qlens, max(qlens)), ctypes.c_longlong(sum(qlens))))
+
+
+def test_shapes_of_the_device_tests_reach_the_kernel_of_64_columns(route):
+    import test_gpu_large_pool as P
+    import test_gpu_prefill_block8 as B
+    import test_gpu_prefill_wide as T
+    for hq, hkv, _, qlens, _ in T.SHAPES:
+        assert wide(route, hq, hkv, qlens), (hq, hkv, qlens)
+    assert wide(route, *T.SPECIAL[:2], T.SPECIAL[2])
+    assert [wide(route, hq, hkv, qlens) for hq, hkv, _, qlens in B.SHAPES].count(True) >= 1
+    assert wide(route, *P.WIDE)
+
+
+# both sides of every line of the rule, with the shapes that were slower on 64 columns
+@pytest.mark.parametrize("hq,hkv,qlens,yes", [
+    (32, 8, [54 * 64], True), (32, 8, [52 * 64], False),              # rounds of 1.65 (one request)
+    (32, 8, [65 * 64], True), (32, 8, [66 * 64], False), (32, 8, [5000], False), (32, 8, [6500], False),      # of 2
+    (32, 8, [109 * 64], True), (32, 8, [108 * 64], False), (32, 8, [16384], True),                            # of 3.4
+    (64, 8, [32 * 64], True), (96, 8, [31 * 64], False), (128, 16, [31 * 64], False), (128, 16, [32 * 64], True),  # 32 tiles
+    (64, 8, [2500], False), (16, 2, [6500], False), (16, 2, [7300], True),
+    (32, 8, [3500] * 4, False), (32, 8, [4900] * 4, False), (32, 8, [4096] * 5, True),                        # heads times requests
+    (64, 8, [4096] * 2, False), (64, 8, [4096] * 3, True), (16, 2, [6500] * 2, False), (24, 2, [5000] * 2, False),
+    (32, 8, [55 * 64] * 6, True), (32, 8, [54 * 64] * 6, False), (64, 8, [32 * 64] * 4, True), (64, 8, [31 * 64] * 4, False),  # tiles
+    (64, 8, [32 * 64] * 3 + [16 * 64], True), (64, 8, [32 * 64] * 3 + [15 * 64], False),                      # seven rounds
+    (8, 2, [8000] * 2, True), (8, 1, [5000] * 2, False), (8, 2, [54 * 64] * 2, False),                        # two of eight heads
+    (128, 8, [8000] * 3 + [10] * 4, False), (128, 8, [8000] * 4 + [10] * 3, True),                            # a mean of half
+    (24, 8, [8000], False), (40, 8, [8000], False), (48, 8, [8000], False)])                                  # groups
+def test_which_calls_take_64_columns(route, hq, hkv, qlens, yes):
+    assert wide(route, hq, hkv, qlens) == yes
