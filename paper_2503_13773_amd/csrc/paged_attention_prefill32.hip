@@ -81,9 +81,6 @@ constexpr int kStepTokens = 32;
 constexpr int kStageBytes = kStepTokens * D * 2;  // K (or V) rows of a step: 32 rows x 256 bytes
 constexpr int kRing = 4;       // stages of K and of V
 constexpr float kBias = 7.0f;  // powers of two that the reference point is set above the largest score
-// Steps from which a split workgroup's second group takes a share (64 rows at the end of 800 tokens whole 16.5, split 18.0
-// us; 900 18.2 / 19.7; from the slopes 1100 and 1200 tokens 20.6 / 20.8 and 21.9 / 21.3).
-constexpr int kMinSplitSteps = 36;
 
 template <int I, int N, class F>
 __device__ inline void static_for(const F &f) {
@@ -703,15 +700,10 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
     const auto *vv = static_cast<const uint16_t *>(v_cache);
     auto *oo = static_cast<uint16_t *>(out);
     const int heads = p.heads_per_chunk;
-    const int rows64 = 2 / heads;  // 64-row units in the query rows of a workgroup
     const bool small = p.block_size < 8;
-    const int query_tiles = (p.max_query_tiles + rows64 - 1) / rows64;  // max_query_tiles counts 64-row tiles
-    const int64_t grid = int64_t(p.num_q_heads / heads) * p.num_seqs * query_tiles;
-    // at most one workgroup per compute unit (up to two the finer grain of plain ones wins: 2048 tokens 45.6 us
-    // plain, 46.2 us split; four chunks of 512 rows 112 / 118 us), and only where the block table reaches far enough
-    // for a share: the second group's start costs a short request up to 0.3 us (642 tokens, MHA: 17.3 / 17.6 us)
-    const bool split = !small && grid <= kNumCUs &&
-                       int64_t(p.max_blocks_per_seq) * p.block_size > (kMinSplitSteps - 1) * kStepTokens;
+    const int query_tiles = prefill32_tiles(p);
+    const int64_t grid = prefill32_grid(p);
+    const bool split = prefill_split(p);
     // A grid that fits the device at once (two workgroups of four wavefronts per compute unit)
     // gets the second half of its query tiles in rising order (a few percent on one short request).
     // Chunks of several sequences: what a tile walks depends on its sequence's context, which only the device knows.
@@ -729,7 +721,7 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
                           int64_t(p.max_blocks_per_seq) * p.block_size >= chunk_reach ? int(chunk_reach) : 0;
     const int fold_at = grid <= 2 * kNumCUs ? (query_tiles + 1) / 2 : query_tiles;
     const int fold_ranked = grid <= 2 * kNumCUs ? std::max(1, std::min(int(items), kNumCUs / chunks)) : int(items);
-    const int by_units = prefill_by_units(p, grid) ? int(grid) : 0;
+    const int by_units = prefill_by_units(p) ? int(grid) : 0;
     const dim3 g{unsigned(grid)}, b(split ? 512 : 256);
 #define KVC_LAUNCH(SMALL, HEADS, SPLIT)                                                                        \
     pa_prefill_mfma32_kernel<SMALL, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \

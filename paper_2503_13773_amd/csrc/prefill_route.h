@@ -22,6 +22,30 @@ struct PrefillParams {
     float scale_log2e;
 };
 
+// Query tiles of the longest sequence and workgroups of a launch on 32-column wavefronts: 64 rows of two heads, or 128 of one.
+inline int prefill32_tiles(const PrefillParams &p) {
+    const int rows64 = 2 / p.heads_per_chunk;
+    return (p.max_query_tiles + rows64 - 1) / rows64;
+}
+inline int64_t prefill32_grid(const PrefillParams &p) {
+    return int64_t(p.num_q_heads / p.heads_per_chunk) * p.num_seqs * prefill32_tiles(p);
+}
+
+// Steps (32 tokens) from which the second group of a split workgroup takes a share.  The last 64 rows of one request, 32 / 8
+// heads, us, whole / split: 800 tokens 15.2 / 16.7, 1200 20.0 / 20.7, 1500 (47 steps) 23.2 / 23.8, 1600 (50 steps, equal
+// shares) 24.1 / 23.8, 1900 28.2 / 27.3, 2100 30.5 / 28.8; 200 rows of two 1500 23.8 / 24.2, 1600 24.7 / 24.4, 1700 25.6 / 25.8, 1800
+// 26.3 / 26.0; 4 / 4 heads, 64 rows 1500 20.6 / 21.1, 1600 21.1 / 21.0, 2100 26.3 / 25.7.
+constexpr int kMinSplitSteps = 50;
+
+// Whether workgroups are split: at most one per compute unit (up to two the finer grain of plain ones wins: one request of 2048
+// tokens 40.0 us plain, 49.2 split; four chunks of 512 rows at 4000 tokens 106.6 / 118.2), where the block table
+// reaches far enough for a share (the second group costs a short context nothing measurable then: 642 tokens 13.8 us
+// either way) and holds blocks of 8 tokens or more.
+inline bool prefill_split(const PrefillParams &p) {
+    return p.block_size >= 8 && prefill32_grid(p) <= kNumCUs &&
+           int64_t(p.max_blocks_per_seq) * p.block_size > (kMinSplitSteps - 1) * 32;
+}
+
 // Workgroups of odd groups, one query head each: where a launch has enough of them, the `group` workgroups of a unit
 // (KV head, sequence, query tile) are eight blocks apart, which the device hands to one XCD, so that one L2 fetches the
 // unit's K and V rows instead of up to `group` of them.  With fewer than eight KV heads the tiles of a sequence differ too much from
@@ -29,8 +53,8 @@ struct PrefillParams {
 // (50 / 10, one of 1200, 500 workgroups, 29.0 / 30.9; four of 500, 800 workgroups, 28.7 / 29.8).  us, plain order / by units:
 // 40 / 8 heads, two chunks of 3600 rows at 12000 tokens 1303 / 1111, four of 4096 620 / 540, one of 4096 165.7 / 165.3; 56 / 8,
 // four of 4096 915 / 757; 50 / 10, four of 4096 823 / 702; 48 / 16 775 / 679.  One head per KV head has nothing to share.
-inline bool prefill_by_units(const PrefillParams &p, int64_t grid) {
-    return p.heads_per_chunk == 1 && p.group > 1 && p.num_kv_heads >= 8 && grid > 4 * kNumCUs;
+inline bool prefill_by_units(const PrefillParams &p) {
+    return p.heads_per_chunk == 1 && p.group > 1 && p.num_kv_heads >= 8 && prefill32_grid(p) > 4 * kNumCUs;
 }
 
 // The place of workgroup `block` of `blocks` (a multiple of group * kv_heads) by units.  A unit's number rises with the KV

@@ -18,7 +18,9 @@ static PrefillParams params(const int *v) {
 }
 extern "C" {
 int wide(const int *v, long long total_q) { return prefill_wide(params(v), total_q); }
-int by_units(const int *v, long long grid) { return prefill_by_units(params(v), grid); }
+int by_units(const int *v) { return prefill_by_units(params(v)); }
+int split(const int *v) { return prefill_split(params(v)); }
+int split_steps() { return kMinSplitSteps; }
 void places(int blocks, int group, int kv_heads, int *out) {
     for (int b = 0; b < blocks; ++b) {
         const HeadPlace at = head_place(b, blocks, group, kv_heads);

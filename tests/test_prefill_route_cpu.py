@@ -42,10 +42,35 @@ def test_units_cover_every_workgroup_and_share_an_xcd(route, group, kv_heads, in
     (28, 4, [4096] * 4, False), (35, 5, [3600] * 2, False), (49, 7, [4096] * 4, False),   # fewer than eight KV heads
     (32, 32, [4096] * 4, False), (32, 8, [4096] * 4, False)])       # nothing to share; two heads per workgroup
 def test_odd_groups_place_long_launches_by_units(route, hq, hkv, qlens, units):
-    v = prefill_route.values(hq, hkv, qlens, max(qlens))
-    heads = 2 if hq // hkv % 2 == 0 else 1
-    grid = hq // heads * len(qlens) * -(-max(qlens) // (128 // heads))
-    assert bool(route.by_units(v, ctypes.c_longlong(grid))) == units
+    assert bool(route.by_units(prefill_route.values(hq, hkv, qlens, max(qlens)))) == units
+
+
+@pytest.mark.parametrize("hq,hkv,qlens,tokens,bs,yes", [
+    (32, 8, [64], 1568, 16, False), (32, 8, [64], 1569, 16, True), (32, 8, [64], 1200, 16, False),   # 49 and 50 steps
+    (32, 8, [16 * 64], 4000, 16, True), (32, 8, [16 * 64 + 1], 4000, 16, False),                     # workgroups
+    (28, 4, [9 * 128], 4000, 16, True), (28, 4, [9 * 128 + 1], 4000, 16, False),
+    (32, 8, [64], 4000, 8, True), (32, 8, [64], 4000, 4, False)])                                    # blocks
+def test_which_launches_are_split(route, hq, hkv, qlens, tokens, bs, yes):
+    assert bool(route.split(prefill_route.values(hq, hkv, qlens, tokens, bs))) == yes
+
+
+def test_device_tests_of_split_workgroups_reach_them(route):
+    import test_gpu_prefill_split as T
+
+    def split(hq, hkv, lens, qlens, bs=16):
+        blocks = -(-max(lens) // bs) + 1     # of their tables
+        return bool(route.split(prefill_route.values(hq, hkv, qlens, blocks * bs, bs)))
+
+    line = 32 * (route.split_steps() - 1)
+    for hq, hkv, bs in T.HEADS:
+        for lens, qlens in T.fives(T.AROUND):
+            assert split(hq, hkv, lens, qlens, bs) and min(lens) <= line + 200 and max(lens) > line
+        for lens, qlens in T.fives(T.BELOW):
+            assert max(lens) <= line and not split(hq, hkv, lens, qlens, bs)
+    assert min(T.AROUND) < line and {line, line + 1} <= set(T.AROUND)
+    for hq, hkv, lens, qlens in [*T.CROSSING, T.LONG, T.RAMP, T.MINUS_INF[1]]:
+        assert split(hq, hkv, lens, qlens) and max(lens) > line + 64
+    assert not split(*T.MINUS_INF[0])
 
 
 def wide(route, hq, hkv, qlens):
