@@ -99,14 +99,25 @@ constexpr HeadPlace head_place(int block, int blocks, int group, int kv_heads) {
 //     325 / 337; 64 / 8, two of 4096 [7] 413 / 434; 16 / 2, two of 6500 [2.8] 262 / 290, each on four XCDs of its own, the longer one
 //     last.  With two requests of eight heads it is the workgroups of 32 columns that place them so: 8 / 2, two of 8000 [1.7]
 //     231 / 201, of 13000 [2.8] 579 / 537.
+//   Blocks of fewer than 8 tokens cost the workgroups of 32 columns more (an address per row and load, registers that spill),
+//     and the lines lie lower: three rounds for one request, 2.8 and 45 tiles for several, except those whose requests
+//     get XCDs of their own and two of 64 heads and more.  Blocks of 4: 32 / 8, one of 5000 [2.5] 201.2 / 201.7, of 6500 [3.2]
+//     323.9 / 313.6, three of 4096 [5.3] 332 / 311, six of 3200 [7.3] 375 / 342, two of 3200 [2.75] 148.1 / 151.2, eight of 2600 (41
+//     tiles) [8.4] 378 / 394; 16 / 2, six of 3200 [3.7] 181.7 / 167.7, two of 6500 281 / 308; 64 / 8, two of 3600 [6.2] 361 / 370,
+//     three of 2600 [6.7] 299 / 273.
 // Batches with a few long requests among short ones (a mean below half the longest) stay on 32 columns.
 inline bool prefill_wide(const PrefillParams &p, int64_t total_q) {
     if (p.group % 4 != 0 || total_q < int64_t(p.num_seqs) * p.max_query_tiles * 32) return false;
     const int chunks = p.num_q_heads / 4;
     const int64_t rounds100 = 100 * chunks * ((total_q + 63) / 64) / kNumCUs;
-    if (p.num_seqs == 1) return p.max_query_tiles >= 32 && ((rounds100 >= 165 && rounds100 <= 205) || rounds100 >= 340);
+    const bool small = p.block_size < 8, many_heads = chunks >= 16;
+    if (p.num_seqs == 1)
+        return p.max_query_tiles >= 32 && ((rounds100 >= 165 && rounds100 <= 205) || rounds100 >= (small ? 300 : 340));
     if (p.num_seqs == 2 && chunks == 2) return p.max_query_tiles >= 55 && rounds100 >= 165;
-    return rounds100 >= 700 && int64_t(chunks) * p.num_seqs > 32 && p.max_query_tiles >= (chunks >= 16 ? 32 : 55);
+    const int64_t tile_row = int64_t(chunks) * p.num_seqs;  // workgroups of one query tile of all requests
+    if (small)
+        return rounds100 >= (p.num_seqs == 2 && many_heads ? 700 : 280) && tile_row > 8 && p.max_query_tiles >= (many_heads ? 32 : 45);
+    return rounds100 >= 700 && tile_row > 32 && p.max_query_tiles >= (many_heads ? 32 : 55);
 }
 
 }  // namespace kvc

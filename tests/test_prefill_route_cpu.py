@@ -73,16 +73,16 @@ def test_device_tests_of_split_workgroups_reach_them(route):
     assert not split(*T.MINUS_INF[0])
 
 
-def wide(route, hq, hkv, qlens):
-    return bool(route.wide(prefill_route.values(hq, hkv, qlens, max(qlens)), ctypes.c_longlong(sum(qlens))))
+def wide(route, hq, hkv, qlens, bs=16):
+    return bool(route.wide(prefill_route.values(hq, hkv, qlens, max(qlens), bs), ctypes.c_longlong(sum(qlens))))
 
 
 def test_shapes_of_the_device_tests_reach_the_kernel_of_64_columns(route):
     import test_gpu_large_pool as P
     import test_gpu_prefill_block8 as B
     import test_gpu_prefill_wide as T
-    for hq, hkv, _, qlens, _ in T.SHAPES:
-        assert wide(route, hq, hkv, qlens), (hq, hkv, qlens)
+    for hq, hkv, _, qlens, bs in T.SHAPES:
+        assert wide(route, hq, hkv, qlens, bs), (hq, hkv, qlens, bs)
     assert wide(route, *T.SPECIAL[:2], T.SPECIAL[2])
     assert [wide(route, hq, hkv, qlens) for hq, hkv, _, qlens in B.SHAPES].count(True) >= 1
     assert wide(route, *P.WIDE)
@@ -104,3 +104,20 @@ def test_shapes_of_the_device_tests_reach_the_kernel_of_64_columns(route):
     (24, 8, [8000], False), (40, 8, [8000], False), (48, 8, [8000], False)])                                  # groups
 def test_which_calls_take_64_columns(route, hq, hkv, qlens, yes):
     assert wide(route, hq, hkv, qlens) == yes
+
+
+@pytest.mark.parametrize("hq,hkv,qlens,yes", [
+    (32, 8, [5000], False), (32, 8, [95 * 64], False), (32, 8, [96 * 64], True), (32, 8, [65 * 64], True), (32, 8, [66 * 64], False),
+    (32, 8, [4096] * 3, True), (32, 8, [45 * 64] * 6, True), (32, 8, [44 * 64] * 6, False),
+    (32, 8, [45 * 64, 44 * 64], False), (32, 8, [45 * 64] * 2, True),                       # 2.8 rounds
+    (16, 2, [8000] * 2, False), (16, 2, [8000] * 3, True), (8, 2, [9000] * 4, False),       # XCDs of their own
+    (64, 8, [3600, 2700], False), (64, 8, [56 * 64] * 2, True), (64, 8, [2600] * 3, True), (64, 8, [31 * 64] * 3, False),
+    (24, 8, [8000], False)])
+@pytest.mark.parametrize("bs", [1, 4])
+def test_which_calls_take_64_columns_on_blocks_of_few_tokens(route, hq, hkv, qlens, yes, bs):
+    assert wide(route, hq, hkv, qlens, bs) == yes
+
+
+def test_blocks_of_8_tokens_and_more_are_judged_alike(route):
+    for shape in [(32, 8, [6500]), (32, 8, [4096] * 3), (64, 8, [2600] * 3), (64, 8, [2600] * 5)]:
+        assert len({wide(route, *shape, bs) for bs in (8, 16, 256)}) == 1
