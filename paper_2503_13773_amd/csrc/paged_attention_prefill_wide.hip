@@ -25,7 +25,7 @@
 // The reference point of a column is set kBias above its largest score, and moves when some weight reaches 2: that
 // shows in the exponent bits of the rounded weights, which are collected by OR (10 instructions instead of the 20 of a
 // running maximum).  The weights of the step are then made again from its scores, which stay in registers; weights are
-// below 2 as they reach O and the sum, and below 2^kBias of the largest at the last move.
+// below 2 as they reach O and the sum, and so below 2^(kBias + 1) times what the largest score of the last move weighs.
 //
 // The score products are inline asm: the compiler would put their results into AGPRs and copy each score.  It inserts
 // no wait states for them, so nothing near them needs any: scores are read two and more matrix instructions after the
@@ -36,105 +36,13 @@
 #include <type_traits>
 
 #include "kvc_internal.h"
-#include "pa_mfma_tile.h"
+#include "pa_prefill32_tile.h"
 
 namespace kvc {
 
 namespace {
 
-using namespace mfma;
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kStepTokens = 32;
-constexpr int kStageBytes = kStepTokens * D * 2;  // K (or V) rows of a step: 32 rows x 256 bytes
-constexpr int kRing = 4;                          // stages of K and of V
-constexpr float kBias = 7.0f;                     // powers of two that the reference point is set above the largest score
-
-template <int I, int N, class F>
-__device__ inline void static_for(const F &f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-// The value lane l ^ 32 holds, next to this lane's: one swap of the two 32-lane halves.
-__device__ inline float max_over_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ inline float sum_over_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// Byte offset inside a V stage of what this lane reads for dim block b (the transposing read hands lane i of a 16-lane
-// block the i-th element of the four 16-element groups that lanes 4 k .. 4 k + 3 point at).
-__device__ inline int v_lane_offset(int b, int half, int c) {
-    const int i16 = c & 15, k = i16 >> 2;
-    return (4 * half + k) * 256 + ((b + k) & 3) * 64 + 32 * (c >> 4) + 8 * (i16 & 3);
-}
-// Half H of the V operand of slice N: tokens 16 N + 8 H + 4 * half .. +3 of the lane's dim.
-template <int N, int H>
-__device__ inline uint2 read_v_half(const unsigned char *vlane) {
-    typedef short v4i16 __attribute__((ext_vector_type(4)));
-    typedef v4i16 __attribute__((address_space(3))) * lds_v4i16_ptr;
-    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_ptr)(vlane + (16 * N + 8 * H) * 256)));
-}
-// V rows at or past `vlim` have weights of 0 and may hold NaN.
-template <int N>
-__device__ inline void mask_v_operand(uint2 (&va)[2], int vlim, int half) {
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-        const int tok = 16 * N + 8 * g + 4 * half;
-        va[g].x &= (tok < vlim ? 0xffffu : 0u) | (tok + 1 < vlim ? 0xffff0000u : 0u);
-        va[g].y &= (tok + 2 < vlim ? 0xffffu : 0u) | (tok + 3 < vlim ? 0xffff0000u : 0u);
-    }
-}
-__device__ inline bf16x8 v_operand(const uint2 (&va)[2]) {
-    const uint4 aw = {va[0].x, va[0].y, va[1].x, va[1].y};
-    return __builtin_bit_cast(bf16x8, aw);
-}
-__device__ inline bf16x8 four_words(const uint32_t (&w)[8], int n) {
-    const uint4 v = {w[4 * n], w[4 * n + 1], w[4 * n + 2], w[4 * n + 3]};
-    return __builtin_bit_cast(bf16x8, v);
-}
-// Dims 16 J + 8 * half .. +7 of a row with XOR-permuted chunks; c: the row.
-template <int J>
-__device__ inline bf16x8 read_k_operand(const unsigned char *krow, int half, int c) {
-    return *reinterpret_cast<const bf16x8 *>(krow + (((2 * J + half) ^ (c & 15)) << 4));
-}
-
-// 16 bytes per lane from global memory straight into LDS, to lds_addr + 16 * lane (lds_addr uniform), and a second 1 KiB
-// from and to 1 KiB further on.  The compiler does not see these accesses: barriers order them against LDS reads,
-// wait_for() counts them.
-__device__ inline void load_rows(const void *base, uint32_t off0, uint32_t off1_minus_1k, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
-                 :: "s"(lds_addr), "v"(off0), "v"(off1_minus_1k), "s"(base) : "memory");
-}
-__device__ inline void load_lane_to_lds(const void *addr, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(addr) : "memory");
-}
-// Waits until at most LOADS of the wavefront's loads (and stores) and LDS of its LDS reads are under way.
-template <int LOADS, int LDS>
-__device__ inline void wait_for() {
-    static_assert(LOADS < 64 && LDS < 16, "fields of the wait instruction");
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((LOADS & 15) | (LOADS >> 4) << 14 | 7 << 4 | LDS << 8);
-    asm volatile("" ::: "memory");
-}
-__device__ inline void barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-// Nothing moves across this point when the compiler orders the instructions of a turn.
-#define KVC_PIN() __builtin_amdgcn_sched_barrier(0)
+using namespace prefill32;
 
 // Chunk of the turn (one matrix instruction each) in which the arithmetic of score e starts: argument, exponential,
 // rounding and pair sum, sum, one chunk after the other.  Score e: register 2 (e / 4) + e % 2 of group (e / 2) % 2.
@@ -257,7 +165,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void pa_prefill_wide_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
-    uint16_t *__restrict__ out, PrefillParams p, int query_tiles) {
+    uint16_t *__restrict__ out, PrefillParams p) {
     constexpr int kHeads = 4;
     constexpr int kWaveRows = 64 / kHeads;         // query rows of a wavefront
     constexpr int kTileRows = 4 * kWaveRows;       // and of the workgroup
@@ -274,7 +182,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     const int chunk = blockIdx.x % chunks, index = blockIdx.x / chunks;
     const int head0 = chunk * kHeads;
     const int kvh = head0 / p.group;
-    const int n = index % p.num_seqs, qtile = query_tiles - 1 - index / p.num_seqs;
+    const int n = index % p.num_seqs, qtile = p.max_query_tiles - 1 - index / p.num_seqs;
     const int S = context_lens[n], qs = q_start[n], Qn = q_start[n + 1] - qs;
     if (qtile * kTileRows >= Qn || Qn > S) return;  // uniform over the workgroup
     const int last_pos = S - Qn + min(Qn, (qtile + 1) * kTileRows) - 1;  // position of the workgroup's last query row
@@ -551,7 +459,7 @@ hipError_t launch_prefill_wide(const void *q, const void *k_cache, const void *v
     const auto kernel = p.block_size < 8 ? pa_prefill_wide_kernel<true> : pa_prefill_wide_kernel<false>;
     kernel<<<dim3(unsigned(grid)), dim3(256), 0, stream>>>(static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
                                                            static_cast<const uint16_t *>(v_cache), block_tables, context_lens,
-                                                           q_start, static_cast<uint16_t *>(out), p, p.max_query_tiles);
+                                                           q_start, static_cast<uint16_t *>(out), p);
     return hipGetLastError();
 }
 
