@@ -720,10 +720,8 @@ int kvc_paged_attention_prefill(const void *q, const void *k_cache, const void *
         return e == hipSuccess ? KVC_OK : hip_failed(e);
     }
     if (tile_grid > kMaxGrid) return KVC_ERR_BAD_SHAPE;
-    // 32x32 tiles need a positive scale (their max is taken over raw scores); KVC_KERNEL_MFMA asks
-    // for the 16x16-tile kernel whatever the shape.  They hold the bytes of a block in 32 bits.
-    const bool tiles32 = p.scale_log2e > 0.0f && desc->kernel != KVC_KERNEL_MFMA &&
-                         int64_t(desc->block_size) * desc->num_kv_heads * 256 < (int64_t(1) << 32);
+    // KVC_KERNEL_MFMA asks for the 16x16-tile kernel whatever the shape
+    const bool tiles32 = desc->kernel != KVC_KERNEL_MFMA && kvc::prefill_tiles32(p);
     const hipError_t e = tiles32 ? kvc::launch_prefill_mfma32(q, k_cache, v_cache, block_tables, context_lens, q_start,
                                                               out, p, total_q, static_cast<hipStream_t>(hip_stream))
                                  : kvc::launch_prefill_mfma(q, k_cache, v_cache, block_tables, context_lens, q_start,

@@ -22,6 +22,12 @@ struct PrefillParams {
     float scale_log2e;
 };
 
+// Whether 32x32 tiles serve a call at head_dim 128: their max is taken over raw scores, so the scale has to be positive, and
+// they hold the bytes of a block in 32 bits.  Others go to the kernel of 16x16 tiles.
+inline bool prefill_tiles32(const PrefillParams &p) {
+    return p.scale_log2e > 0.0f && int64_t(p.block_size) * p.num_kv_heads * 256 < (int64_t(1) << 32);
+}
+
 // Query tiles of the longest sequence and workgroups of a launch on 32-column wavefronts: 64 rows of two heads, or 128 of one.
 inline int prefill32_tiles(const PrefillParams &p) {
     const int rows64 = 2 / p.heads_per_chunk;

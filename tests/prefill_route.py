@@ -19,6 +19,7 @@ static PrefillParams params(const int *v) {
 extern "C" {
 int wide(const int *v, long long total_q) { return prefill_wide(params(v), total_q); }
 int by_units(const int *v) { return prefill_by_units(params(v)); }
+int tiles32(const int *v, float scale) { PrefillParams p = params(v); p.scale_log2e = scale; return prefill_tiles32(p); }
 int split(const int *v) { return prefill_split(params(v)); }
 int split_steps() { return kMinSplitSteps; }
 void places(int blocks, int group, int kv_heads, int *out) {

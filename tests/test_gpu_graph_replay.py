@@ -90,3 +90,47 @@ def test_decode_iteration_graph_replays_match_eager_and_oracle(oracle_mod):
         for i, b in enumerate(victims):
             assert np.array_equal(swapped[0, i].view(np.uint16), host_k[b]) and \
                 np.array_equal(swapped[1, i].view(np.uint16), host_v[b]), (step, i)
+
+
+# 64 columns per wavefront; 32 with two heads, ranked; split; heads placed by units (a test on the host asks the library)
+PREFILLS = {"wide": (64, 8, [2000], [2000]), "ranked": (32, 8, [1300, 900, 700], [300, 300, 200]), "split": (8, 2, [2000, 1700], [100, 64]),
+            "units": (24, 8, [200] * 22, [130] * 22)}
+
+
+@pytest.mark.parametrize("kind", sorted(PREFILLS))
+def test_prefill_graph_replays_match_eager(kind):
+    """One call recorded, replayed on inputs and contexts rewritten in place, with eager calls between the replays."""
+    import paper_2503_13773_amd as K
+    from test_gpu_prefill import make
+    hq, hkv, lens, qlens = PREFILLS[kind]
+    w, q, qs = make(1600 + hq, lens, qlens, hq, hkv)
+    k, v, qd = dev_tensor(w.k_cache, W.BF16), dev_tensor(w.v_cache, W.BF16), dev_tensor(q, W.BF16)
+    tables, ctx, starts = (torch.from_numpy(x).cuda() for x in (w.block_tables, w.context_lens.astype(np.int32), qs))
+    out = torch.empty_like(qd)
+
+    def call():
+        K.paged_attention_prefill(qd, k, v, tables, ctx, starts, w.scale, max(qlens), out)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for step in range(3):
+        for x in (qd, k, v):
+            x.copy_(torch.randn(x.shape, generator=gen, device="cuda"))
+        ctx.copy_(torch.tensor([max(n - 3 * step, r) for n, r in zip(lens, qlens)], dtype=torch.int32))
+        print(f"[case] prefill graph replay {kind} {step}", flush=True)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = out_bits(out).copy()
+        out.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        assert np.isfinite(out_to_f64(out)).all() and np.array_equal(replayed, out_bits(out)), step

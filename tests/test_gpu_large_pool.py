@@ -104,3 +104,27 @@ def test_long_prefill_beyond_4_gib():
                                     torch.from_numpy(qs).cuda(), w.scale, lens[0])
     torch.cuda.synchronize()
     assert np.abs(out_to_f64(out) - exact(w, q, qs)).max() <= BF16_TOL
+
+
+@pytest.mark.parametrize("heads", [65535, 65536])     # blocks of one head's 64 KiB below 4 GiB and of 4 GiB: 32x32 and 16x16 tiles
+def test_prefill_on_blocks_around_4_gib(heads):
+    import paper_2503_13773_amd as K
+    if torch.cuda.get_device_properties(0).total_memory < 64e9:
+        pytest.skip("needs 64 GB of device memory")
+    rows, tokens, scale = 20, 35, 128 ** -0.5
+    gen = torch.Generator(device="cuda").manual_seed(heads)
+    shape = (2, heads, 256, 128)
+    k, v = (torch.full(shape, float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    for cache in (k, v):                                      # block 1 is used
+        cache[1, :, :tokens] = torch.randn((heads, tokens, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    q = torch.randn((rows, heads, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    ints = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    print(f"[case] prefill, {heads} heads on blocks of 256", flush=True)
+    out = K.paged_attention_prefill(q, k, v, ints(1).reshape(1, 1), ints(tokens), ints(0, rows), scale, rows)
+    torch.cuda.synchronize()
+    hidden = torch.arange(tokens, device="cuda")[None] > torch.arange(tokens - rows, tokens, device="cuda")[:, None]
+    for h in range(0, heads, 8192):
+        kd, vd = (cache[1, h:h + 8192, :tokens].float() for cache in (k, v))
+        score = q[:, h:h + 8192].float().transpose(0, 1).contiguous() @ kd.transpose(1, 2).contiguous() * scale
+        ref = torch.softmax(score.masked_fill(hidden, float("-inf")), dim=2) @ vd
+        assert float((out[:, h:h + 8192].float().transpose(0, 1) - ref).abs().max()) <= BF16_TOL, h

@@ -45,6 +45,12 @@ def test_odd_groups_place_long_launches_by_units(route, hq, hkv, qlens, units):
     assert bool(route.by_units(prefill_route.values(hq, hkv, qlens, max(qlens)))) == units
 
 
+@pytest.mark.parametrize("heads,bs,scale,yes", [(65535, 256, 0.1, True), (65536, 256, 0.1, False), (131071, 128, 0.1, True),
+                                                (131072, 128, 0.1, False), (8, 16, 0.1, True), (8, 16, 0.0, False), (8, 16, -0.1, False)])
+def test_blocks_of_4_gib_and_other_scales_take_16x16_tiles(route, heads, bs, scale, yes):
+    assert bool(route.tiles32(prefill_route.values(heads, heads, [40], bs, bs), ctypes.c_float(scale))) == yes
+
+
 @pytest.mark.parametrize("hq,hkv,qlens,tokens,bs,yes", [
     (32, 8, [64], 1568, 16, False), (32, 8, [64], 1569, 16, True), (32, 8, [64], 1200, 16, False),   # 49 and 50 steps
     (32, 8, [16 * 64], 4000, 16, True), (32, 8, [16 * 64 + 1], 4000, 16, False),                     # workgroups
@@ -86,6 +92,13 @@ def test_shapes_of_the_device_tests_reach_the_kernel_of_64_columns(route):
     assert wide(route, *T.SPECIAL[:2], T.SPECIAL[2])
     assert [wide(route, hq, hkv, qlens) for hq, hkv, _, qlens in B.SHAPES].count(True) >= 1
     assert wide(route, *P.WIDE)
+
+
+def test_replayed_prefills_are_of_the_kinds_they_name(route):
+    import test_gpu_graph_replay as G
+    for kind, (hq, hkv, lens, qlens) in G.PREFILLS.items():
+        v = prefill_route.values(hq, hkv, qlens, (-(-max(lens) // 16) + 1) * 16)
+        assert [wide(route, hq, hkv, qlens), bool(route.split(v)), bool(route.by_units(v))] == [kind == k for k in ("wide", "split", "units")]
 
 
 # both sides of every line of the rule, with the shapes that were slower on 64 columns
