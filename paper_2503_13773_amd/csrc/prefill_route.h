@@ -89,15 +89,20 @@ constexpr HeadPlace head_place(int block, int blocks, int group, int kv_heads) {
 // query heads and 64 rows per workgroup, one workgroup per compute unit.  It reads half the LDS operands per score, but nothing hides a
 // tile's start and end (15000 cycles against 1390 per 32 tokens), and with one workgroup per compute unit the rounds in which
 // the tiles go round the device show.  us, 32 columns / 64 columns, in brackets the workgroups per compute unit:
-//   One request.  Up to 1.6 rounds tiles stand alone; between 1.65 and 2 a long and a short one share a compute unit
+//   One request, or several of nearly equal rows (on average 97 % of the longest).  Up to 1.6 rounds tiles stand alone; between 1.65 and 2 a long and a short one share a compute unit
 //     evenly; past 2 they do not; from 3.4 on there are enough of them.  32 / 8 heads: 3000 tokens [1.5] 75.9 / 77.0, 3500
 //     [1.7] 98.9 / 93.6, 4096 [2.0] 126.1 / 121.2, 4600 [2.3] 159.2 / 161.2, 5000 [2.5] 186.0 / 190.9, 6500 [3.2] 299.5 / 299.9,
 //     7300 [3.6] 374.8 / 367.4, 12000 [5.9] 980 / 960, 16384 [8] 1803 / 1768; 64 / 8: 2048 [2.0] 74.3 / 72.0, 2500 [2.5]
 //     108.7 / 112.2, 3000 [2.9] 148.9 / 151.1, 3600 [3.6] 208.2 / 205.6, 8000 [7.8] 882 / 864; 16 / 2: 6500 [1.6] 161.1 / 161.6, 7300
 //     [1.8] 199.6 / 188.7, 10500 [2.6] 389.5 / 394.7, 16384 [4] 904 / 876; 48 / 4: 3500 [2.6] 142.2 / 147.9, 4600 [3.4] 233.6 /
 //     229.8; 12 / 1: 11000 [2.02] 342 / 326.  Of tiles of fewer than 32 (64 rows each) the starts and ends are too large a
-//     share: 128 / 16, 1750 (28 tiles) [3.5] 111.6 / 112.8, 2048 (32) [4] 146.0 / 142.7.
-//   Several.  They leave an uneven end more often, so that it takes seven rounds, and 55 tiles in the longest, or 32 with 64
+//     share: 128 / 16, 1750 (28 tiles) [3.5] 111.6 / 112.8, 2048 (32) [4] 146.0 / 142.7.  Equal requests, 32 / 8: two of 4096 [4.0]
+//     246.8 / 238.3, four of 4096 [8] 489 / 472; 64 / 8, two of 4096 [8] 489 / 470; 16 / 2, two of 3600 [1.8] 103.5 / 99.8, of 5000
+//     [2.5] 186.7 / 191.3, three of 3600 [2.6] 150.0 / 153.7, eight of 5000 [9.8] 718 / 696; 8 / 2, six of 5000 [3.7] 273.8 /
+//     267.5; with an average of 95 % 16 / 2, three of 5000, and 32 / 8, two of 5000, lose 4 and 2 %.  Below 55
+//     tiles only groups of 8 and 16: equal rows can be chunks of unequal contexts, which only the device knows (32 / 8, two
+//     chunks of 2048 at 16000 [2] 697 / 715).
+//   Several of unequal rows.  They leave an uneven end more often, so that it takes seven rounds, and 55 tiles in the longest, or 32 with 64
 //     heads and more, whose workgroups of 32 columns spread a KV head over more XCDs.  32 / 8: six of 3600 [8.3] 437 / 417, of
 //     2048 [4.7] 157.6 / 161.5, eight of 2048 [6.6] 229.6 / 252.9, five of 4096 [8.3] 473 / 468; 64 / 8: four of 2048 [7.3] 259.6 /
 //     254.5, of 1500 [5.3] 150.8 / 153.9, eight of 2048 [13] 487 / 446; 48 / 4, six of 3600 [12] 665 / 619.  Where heads times
@@ -117,8 +122,9 @@ inline bool prefill_wide(const PrefillParams &p, int64_t total_q) {
     const int chunks = p.num_q_heads / 4;
     const int64_t rounds100 = 100 * chunks * ((total_q + 63) / 64) / kNumCUs;
     const bool small = p.block_size < 8, many_heads = chunks >= 16;
-    if (p.num_seqs == 1)
-        return p.max_query_tiles >= 32 && ((rounds100 >= 165 && rounds100 <= 205) || rounds100 >= (small ? 300 : 340));
+    if (p.num_seqs == 1 || 100 * total_q >= 97 * int64_t(p.num_seqs) * p.max_query_tiles * 64)
+        return p.max_query_tiles >= (p.num_seqs == 1 || p.group % 8 == 0 ? 32 : 55) &&
+               ((rounds100 >= 165 && rounds100 <= 205) || rounds100 >= (small ? 300 : 340));
     if (p.num_seqs == 2 && chunks == 2) return p.max_query_tiles >= 55 && rounds100 >= 165;
     const int64_t tile_row = int64_t(chunks) * p.num_seqs;  // workgroups of one query tile of all requests
     if (small)

@@ -108,11 +108,14 @@ def test_replayed_prefills_are_of_the_kinds_they_name(route):
     (32, 8, [109 * 64], True), (32, 8, [108 * 64], False), (32, 8, [16384], True),                            # of 3.4
     (64, 8, [32 * 64], True), (96, 8, [31 * 64], False), (128, 16, [31 * 64], False), (128, 16, [32 * 64], True),  # 32 tiles
     (64, 8, [2500], False), (16, 2, [6500], False), (16, 2, [7300], True),
-    (32, 8, [3500] * 4, False), (32, 8, [4900] * 4, False), (32, 8, [4096] * 5, True),                        # heads times requests
-    (64, 8, [4096] * 2, False), (64, 8, [4096] * 3, True), (16, 2, [6500] * 2, False), (24, 2, [5000] * 2, False),
-    (32, 8, [55 * 64] * 6, True), (32, 8, [54 * 64] * 6, False), (64, 8, [32 * 64] * 4, True), (64, 8, [31 * 64] * 4, False),  # tiles
+    (32, 8, [3500, 3000, 3400, 2900], False), (32, 8, [4900, 4000, 4800, 4100], False), (32, 8, [4096, 3700] * 3, True),  # heads times requests
+    (64, 8, [4096, 3500], False), (64, 8, [4096, 3500, 4000], True), (16, 2, [6500, 5000], False), (24, 2, [5000, 4500], False),
+    (64, 8, [4096] * 2, True), (16, 2, [3600] * 2, True), (16, 2, [5000] * 2, False), (32, 8, [4096] * 2, True),  # equal rows
+    (32, 8, [100 * 64, 94 * 64], True), (32, 8, [100 * 64, 93 * 64], False), (32, 8, [2048] * 2, False), (32, 2, [2048] * 2, True),
+    (32, 8, [55 * 64, 50 * 64] * 5, True), (32, 8, [54 * 64, 50 * 64] * 5, False),                              # tiles
+    (64, 8, [32 * 64, 30 * 64] * 2, True), (64, 8, [31 * 64, 29 * 64] * 3, False),
     (64, 8, [32 * 64] * 3 + [16 * 64], True), (64, 8, [32 * 64] * 3 + [15 * 64], False),                      # seven rounds
-    (8, 2, [8000] * 2, True), (8, 1, [5000] * 2, False), (8, 2, [54 * 64] * 2, False),                        # two of eight heads
+    (8, 2, [8000, 6000], True), (8, 1, [5000, 4000], False), (8, 2, [54 * 64] * 2, False),                    # two of eight heads
     (128, 8, [8000] * 3 + [10] * 4, False), (128, 8, [8000] * 4 + [10] * 3, True),                            # a mean of half
     (24, 8, [8000], False), (40, 8, [8000], False), (48, 8, [8000], False)])                                  # groups
 def test_which_calls_take_64_columns(route, hq, hkv, qlens, yes):
@@ -121,10 +124,10 @@ def test_which_calls_take_64_columns(route, hq, hkv, qlens, yes):
 
 @pytest.mark.parametrize("hq,hkv,qlens,yes", [
     (32, 8, [5000], False), (32, 8, [95 * 64], False), (32, 8, [96 * 64], True), (32, 8, [65 * 64], True), (32, 8, [66 * 64], False),
-    (32, 8, [4096] * 3, True), (32, 8, [45 * 64] * 6, True), (32, 8, [44 * 64] * 6, False),
-    (32, 8, [45 * 64, 44 * 64], False), (32, 8, [45 * 64] * 2, True),                       # 2.8 rounds
-    (16, 2, [8000] * 2, False), (16, 2, [8000] * 3, True), (8, 2, [9000] * 4, False),       # XCDs of their own
-    (64, 8, [3600, 2700], False), (64, 8, [56 * 64] * 2, True), (64, 8, [2600] * 3, True), (64, 8, [31 * 64] * 3, False),
+    (32, 8, [4096, 3500, 3800], True), (32, 8, [45 * 64, 40 * 64] * 3, True), (32, 8, [44 * 64, 40 * 64] * 3, False),
+    (32, 8, [46 * 64, 43 * 64], False), (32, 8, [47 * 64, 43 * 64], True),                    # 2.8 rounds
+    (16, 2, [8000, 7000], False), (16, 2, [8000, 7000, 7500], True), (8, 2, [9000, 8000] * 2, False),  # XCDs of their own
+    (64, 8, [3600, 2700], False), (64, 8, [58 * 64, 54 * 64], True), (64, 8, [2600, 2300, 2400], True), (64, 8, [31 * 64] * 3, False),
     (24, 8, [8000], False)])
 @pytest.mark.parametrize("bs", [1, 4])
 def test_which_calls_take_64_columns_on_blocks_of_few_tokens(route, hq, hkv, qlens, yes, bs):
@@ -132,5 +135,5 @@ def test_which_calls_take_64_columns_on_blocks_of_few_tokens(route, hq, hkv, qle
 
 
 def test_blocks_of_8_tokens_and_more_are_judged_alike(route):
-    for shape in [(32, 8, [6500]), (32, 8, [4096] * 3), (64, 8, [2600] * 3), (64, 8, [2600] * 5)]:
+    for shape in [(32, 8, [6500]), (32, 8, [4096, 3500, 3800]), (64, 8, [2600, 2300, 2400]), (64, 8, [2600] * 5)]:
         assert len({wide(route, *shape, bs) for bs in (8, 16, 256)}) == 1
