@@ -18,7 +18,8 @@
 // workgroup walks the context in steps of 32 tokens (the 32 rows of a score tile).
 //
 // What bounds it.  Two wavefronts of a SIMD read 128 KiB of operands from LDS per step of a compute
-// unit, 1024 cycles of its bandwidth against 1024 matrix cycles; a step of both takes about 1450.
+// unit, 1024 cycles of its bandwidth against 1024 matrix cycles; a step of both takes about 1450 cycles
+// with its rows in L2, 1600 (four chunks of 512 rows) to 1850 (2048 tokens) where they often are not.
 // One alone is bound by its own issue, about 130 instructions of 4 to 5 cycles (8 for an
 // exponential), and takes about 950 cycles for 512 matrix cycles.  A turn holds three steps: the
 // scores of the next, the weights of this one, V . P of the one before, so that the softmax
