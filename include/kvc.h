@@ -256,8 +256,8 @@ KVC_API int kvc_validate_attention_inputs(const int32_t *block_tables, const int
  *                 computed).
  * Every shape the descriptor allows is served: bf16 with head_dim 128 and group <= 16 runs on
  * the matrix cores (any block size): on 32x32 tiles when the scale is positive (two heads of a KV
- * head per wavefront for even group sizes, one head otherwise), on 16x16 tiles for other scales or
- * when desc->kernel is KVC_KERNEL_MFMA; bf16 with head_dim 64 runs on 32x32 tiles with the softmax
+ * head per wavefront for even group sizes, one head otherwise), on 16x16 tiles for other scales, blocks of
+ * 4 GiB and more (all KV heads of one block) or when desc->kernel is KVC_KERNEL_MFMA; bf16 with head_dim 64 runs on 32x32 tiles with the softmax
  * weights kept to 16 bits (any group size, any scale), except one query row per sequence, launches of a
  * few rows, batches that are mostly decode steps and bounds far above the rows there are; these and
  * everything else (fp32, larger groups at head_dim 128) run on the vector ALUs, one workgroup per query
