@@ -204,7 +204,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void pa_prefill_m
         head0 = at.head, kvh = at.kv_head, index = at.index;
     } else {
         const int chunks = p.num_q_heads / HEADS;
-        head0 = int(blockIdx.x % chunks) * HEADS, index = blockIdx.x / chunks;
+        head0 = chunk_place(blockIdx.x % chunks, chunks, p.group / HEADS) * HEADS, index = blockIdx.x / chunks;
         kvh = head0 / p.group;
     }
 

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void pa_prefill_d64_kernel(
     // `fold_at` on the shortest first (grids that are resident at once: a long and a short one share a compute unit)
     const int chunks = p.num_q_heads / HEADS;
     const int item = blockIdx.x;
-    const int chunk = item % chunks;
+    const int chunk = chunk_place(item % chunks, chunks, p.group / HEADS);
     const int n = (item / chunks) % p.num_seqs;
     const int order = item / (chunks * p.num_seqs);
     const int qtile = order < fold_at ? query_tiles - 1 - order : order - fold_at;

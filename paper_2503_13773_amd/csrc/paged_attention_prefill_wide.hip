@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 
     const int chunks = p.num_q_heads / kHeads;
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order), the longest query tiles first
-    const int chunk = blockIdx.x % chunks, index = blockIdx.x / chunks;
+    const int chunk = chunk_place(blockIdx.x % chunks, chunks, p.group / kHeads), index = blockIdx.x / chunks;
     const int head0 = chunk * kHeads;
     const int kvh = head0 / p.group;
     const int n = index % p.num_seqs, qtile = p.max_query_tiles - 1 - index / p.num_seqs;

@@ -85,6 +85,16 @@ constexpr HeadPlace head_place(int block, int blocks, int group, int kv_heads) {
     return {kv_head, kv_head * group + member, unit / kv_heads};
 }
 
+// The head chunk (the heads of one workgroup) of workgroup `b` among the `chunks` of a query tile; `sharing` of them attend
+// over one KV head.  The device hands neighbouring workgroups to its 8 XCDs in turn: chunks in multiples of eight are dealt
+// out so that those of a KV head are neighbours on one XCD, whose L2 then fetches its rows once, and every XCD
+// keeps its share of each tile.  32 / 8 heads, us, in plain order / so: two of 4096 216.7 / 210.2, six of 2000 148.5 / 145.6,
+// of 400 19.7 / 19.0, four chunks of 512 rows at 4000 106.6 / 105.8; heads of 64, four of 1999 107.8 / 106.0.  Heads that share
+// nothing gain nothing (32 / 32, two of 3000 122.2 / 123.0).
+constexpr int chunk_place(int b, int chunks, int sharing) {
+    return sharing > 1 && (chunks & 7) == 0 ? (b & 7) * (chunks >> 3) + (b >> 3) : b;
+}
+
 // Whether the kernel of 64-column wavefronts (paged_attention_prefill_wide.hip) takes a call: groups that 4 divides, four
 // query heads and 64 rows per workgroup, one workgroup per compute unit.  It reads half the LDS operands per score, but nothing hides a
 // tile's start and end (15000 cycles against 1390 per 32 tokens), and with one workgroup per compute unit the rounds in which

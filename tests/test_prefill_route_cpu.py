@@ -137,3 +137,14 @@ def test_which_calls_take_64_columns_on_blocks_of_few_tokens(route, hq, hkv, qle
 def test_blocks_of_8_tokens_and_more_are_judged_alike(route):
     for shape in [(32, 8, [6500]), (32, 8, [4096, 3500, 3800]), (64, 8, [2600, 2300, 2400]), (64, 8, [2600] * 5)]:
         assert len({wide(route, *shape, bs) for bs in (8, 16, 256)}) == 1
+
+
+@pytest.mark.parametrize("chunks,sharing", [(16, 2), (8, 1), (32, 4), (24, 6), (40, 5), (64, 8), (12, 2), (7, 7), (16, 1), (2, 2)])
+def test_head_chunks_of_a_kv_head_are_on_one_xcd(route, chunks, sharing):
+    at = np.array([route.chunk(b, chunks, sharing) for b in range(chunks)])
+    assert sorted(at) == list(range(chunks))
+    if sharing > 1 and chunks % 8 == 0:
+        for x in range(8):  # neighbours, so no more KV heads than that many chunks can hold
+            assert (np.diff(at[x::8]) == 1).all() and len(at[x::8]) == chunks // 8
+    else:
+        assert (at == np.arange(chunks)).all()
