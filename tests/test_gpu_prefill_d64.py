@@ -108,3 +108,33 @@ def test_infinities_stay_with_the_rows_that_see_them(oracle_mod):
         assert np.array_equal(np.isfinite(got), fine)
         assert (np.abs(got - ref)[fine] <= bound(ref)[fine]).all()
         assert np.array_equal(got[~fine], ref[~fine], equal_nan=True)
+
+
+@pytest.mark.parametrize("hq,hkv,bs", [(8, 2, 16), (3, 1, 8), (8, 2, 64), (4, 2, 4)])
+def test_windows_of_row_places(oracle_mod, hq, hkv, bs):
+    """The places of 64 steps (4096 tokens) are looked up at once, and a turn asks four steps ahead: contexts that end around
+    the points where the next 64 are fetched, and in the second and third window."""
+    lens = [4096 - 256, 4096 - 255, 4095, 4096, 4097, 4096 + 257, 8192 - 192, 8193, 9000]
+    qlens = [40, 70, 33, 64, 65, 40, 130, 20, 90]
+    w, q, qs = make(770 + bs, lens, qlens, hq, hkv, bs=bs, d=64)
+    poison(w)
+    print(f"[case] prefill d64 windows {hq}/{hkv} bs={bs}", flush=True)
+    got, ref = out_to_f64(run(w, q, qs, max(qlens))), reference(oracle_mod, w, q, qs)
+    assert np.isfinite(got).all()
+    assert (np.abs(got - ref) <= bound(ref)).all()
+
+
+def test_reference_point_moves_in_every_turn(oracle_mod):
+    """Scores that rise along the context move the reference point of the weights again and again, by less and by more than
+    the weights of a step can hold, in turns that hold the scores of two steps."""
+    for up in (0.02, 1.0, 40.0):
+        w, q, qs = make(780, [700, 333], [700, 40], 4, 2, d=64)
+        bits = lambda x: (np.ascontiguousarray(x, np.float32).view(np.uint32) >> 16).astype(np.uint16)
+        q[...] = bits(np.full(q.shape, 1.0))
+        for n, length in enumerate(w.context_lens.tolist()):
+            for t in range(length):
+                w.k_cache[w.block_tables[n, t // w.block_size], :, t % w.block_size] = bits(np.full((2, 64), up * t / 64))
+        print(f"[case] prefill d64 rising {up}", flush=True)
+        got, ref = out_to_f64(run(w, q, qs, 700)), reference(oracle_mod, w, q, qs)
+        # a score of magnitude s has an absolute error of about s * 2^-22 in fp32, relative error of its weight
+        assert (np.abs(got - ref) <= bound(ref) + 6 * (up * 700) * w.scale * 2.0 ** -22 * 4).all()
