@@ -148,8 +148,9 @@ KVC_API size_t kvc_paged_attention_decode_workspace_bytes(const kvc_attn_desc *d
  *   - Split-K: a long context is cut into pieces whose (max, sum, accumulator) partials go
  *     through the workspace.  The balanced kernel (KVC_KERNEL_MFMA_BALANCED, what AUTO picks for
  *     bf16 / head_dim 128 and for larger calls at head_dim 64) is ONE launch: the last wavefront or
- *     workgroup to finish a piece of a cut context merges its partials and writes the row.  The other
- *     kernels are followed by a merge launch where a context can span more than one partition.
+ *     workgroup to finish a piece of a cut context merges its partials and writes the row.  So is the
+ *     vector-ALU kernel up to 64 partitions a context and 1024 pairs of a sequence and the heads of a
+ *     workgroup.  Otherwise a merge launch follows where a context can span more than one partition.
  *   - `workspace`: device memory, 256-byte aligned, at least
  *     kvc_paged_attention_decode_workspace_bytes(desc); may be NULL when that is 0.  Its first
  *     4096 bytes hold arrival counters that must be 0 when a call starts:
@@ -172,8 +173,8 @@ KVC_API int kvc_paged_attention_decode_workspace_init(void *workspace, size_t wo
 
 /* The launches of kvc_paged_attention_decode on their own (same arguments, same checks), for
  * callers that time or schedule them separately.  Running partial then merge on one stream
- * equals kvc_paged_attention_decode; with the balanced kernel partial is the whole call and
- * merge launches nothing. */
+ * equals kvc_paged_attention_decode, also where that is one launch of the vector-ALU kernel; with
+ * the balanced kernel partial is the whole call and merge launches nothing. */
 KVC_API int kvc_paged_attention_decode_partial(const void *q, const void *k_cache, const void *v_cache,
                                        const int32_t *block_tables, const int32_t *context_lens,
                                        float scale, void *out, const kvc_attn_desc *desc,

@@ -21,6 +21,7 @@ struct AttnParams {
     int partition_tokens;   // split-K partition length, multiple of 16
     int max_partitions;     // partitions per sequence the grid and workspace provide for
     int head_chunk;         // vector-ALU kernel: query heads a workgroup processes (divides group)
+    int merge_here;         // vector-ALU kernel: the last partition of a row to finish merges it (1), or a launch of its own does (0)
     int k_via_lds;          // MFMA kernel: stage K tiles through LDS (1) or load them in operand layout (0)
     int min_chunk_tiles;    // balanced kernel: smallest number of tiles (16 tokens, 32 at head_dim 64) a worker (few rows: a workgroup) takes
     int max_context_len;    // context lengths are clamped to this (the bound every size is derived from)
@@ -28,8 +29,8 @@ struct AttnParams {
     float scale_log2e;      // scale * log2(e), for the base-2 softmax of the MFMA kernel
 };
 
-// Workspace layout.  The first kWorkspaceHeaderBytes hold the arrival counters of the
-// balanced kernel (int32 [workers], 0 between calls); no kernel writes anything else there.
+// Workspace layout.  The first kWorkspaceHeaderBytes hold the arrival counters of the balanced kernel (int32 [workers]) or
+// of the vector-ALU kernel (int32 [num_seqs][num_q_heads / head_chunk]), 0 between calls; no kernel writes anything else there.
 // Fixed-partition kernels: acc [num_seqs][num_q_heads][max_partitions][head_dim] fp32, then
 // ml [num_seqs][num_q_heads][max_partitions][2] fp32 (running max, running sum).
 // Balanced kernel: acc [workers][2][group][head_dim] fp32, ml [workers][2][group][2] fp32

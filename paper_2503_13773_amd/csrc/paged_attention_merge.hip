@@ -2,21 +2,17 @@
 // (max, sum, un-normalised accumulator) triples of every (sequence, query head) whose
 // context was split, normalise and cast.
 //
-//   M = max_p m_p;  out = sum_p w_p acc_p / sum_p w_p l_p,  w_p = exp(m_p - M)
-//
-// (exp is base 2 when the partial kernel worked in base-2 units.)  One wavefront per
-// (sequence, head).  Lane i first fetches (m, l) of partial i, so all weights of up to 64
-// partials come from one load and one wavefront max/sum; that load is issued speculatively
-// together with the loads of the context length and the partial count, so the kernel is two
-// memory round trips deep.  The accumulator rows are then streamed with the weight broadcast
-// from its lane, lanes striding over head_dim (coalesced 256/512-byte reads, 8 rows in flight).
+// One wavefront per (sequence, head); the arithmetic is pa_merge_row.h.  (m, l) of the first 64 partials are loaded
+// speculatively together with the context length, so the kernel is two memory round trips deep.
 //
 // The number of partials of a row is ceil(context_len / partition_tokens); rows finished by
 // the partial kernel (one partial, or an empty context) are skipped.  The balanced kernel
-// merges inside its own launch and does not use this one.
+// merges inside its own launch and does not use this one, nor does the vector-ALU kernel where it
+// counts the partitions of a row.
 #include <math.h>
 
 #include "kvc_internal.h"
+#include "pa_merge_row.h"
 
 namespace kvc {
 
@@ -53,46 +49,13 @@ __global__ __launch_bounds__(kThreads) void pa_merge_kernel(const int32_t *__res
     if (nparts <= 1) return;
     nparts = min(nparts, p.max_partitions);
 
-    float M = lane < nparts ? ml0.x : -INFINITY;
-    for (int i = lane + 64; i < nparts; i += 64) M = fmaxf(M, ml[2 * i]);
+    float a[DPL];
+    const float L = merge_row<DPL, BASE2, 8>(
+        ml0, nparts, lane, [&](int i) { return *reinterpret_cast<const float2 *>(ml + 2 * i); },
+        [&](int i, float (&x)[DPL]) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-
-    float L = 0.f, a[DPL];
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) a[j] = 0.f;
-    for (int c0 = 0; c0 < nparts; c0 += 64) {
-        const int i = c0 + lane;
-        float w = 0.f;
-        if (i < nparts) {
-            const float2 v = c0 == 0 ? ml0 : *reinterpret_cast<const float2 *>(ml + 2 * i);
-            const float x = v.x - M;
-            w = BASE2 ? __builtin_amdgcn_exp2f(x) : expf(x);
-            L = fmaf(w, v.y, L);
-        }
-        const int nt = min(64, nparts - c0);
-        int t = 0;
-        for (; t + 8 <= nt; t += 8) {  // 8 accumulator rows in flight
-            float x[8][DPL];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) x[u][j] = acc[size_t(c0 + t + u) * D + j];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float wt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), t + u));
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) a[j] = fmaf(wt, x[u][j], a[j]);
-            }
-        }
-        for (; t < nt; ++t) {
-            const float wt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), t));
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) a[j] = fmaf(wt, acc[size_t(c0 + t) * D + j], a[j]);
-        }
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) L += __shfl_xor(L, off);
+            for (int j = 0; j < DPL; ++j) x[j] = acc[size_t(i) * D + j];
+        }, a);
 #pragma unroll
     for (int j = 0; j < DPL; ++j) store_out(out + size_t(row) * D + lane * DPL + j, a[j] / L);
 }

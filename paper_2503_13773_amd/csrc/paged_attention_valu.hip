@@ -5,7 +5,8 @@
 // max and sum, reading K and V through the block table (block-allocated KV cache:
 // paper Section 1 and 3.3.1).  It serves any supported shape: fp32 tensors, blocks of 1 or 2
 // tokens, groups above 16, and at head_dim 64 the calls too small for the matrix-core kernels; other bf16
-// shapes normally take those.
+// shapes normally take those.  A context of several partitions is merged by the workgroup that finishes its last one
+// (p.merge_here), or by the merge launch.
 //
 // Mapping: a token row of K or V is D*sizeof(T) bytes = LR lanes x 16 bytes, so one
 // wavefront load covers TPL = 64/LR tokens, fully coalesced.  Each group of LR lanes
@@ -25,6 +26,7 @@
 #include <type_traits>
 
 #include "kvc_internal.h"
+#include "pa_merge_row.h"
 
 namespace kvc {
 
@@ -90,9 +92,23 @@ __device__ inline float sum_over_row(float x) {  // LR = 8, 16 or 32 lanes of a 
     return x;
 }
 
-constexpr int kUnroll = 4;  // tokens per lane group per loop trip (8 x 16-byte loads in flight)
+// Partials that another workgroup of the launch may merge travel by device-scope accesses, which go to the point of coherence
+// of the XCDs' caches by themselves.
+__device__ inline void store_device(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <int N>
+__device__ inline void load_device(const float *p, float (&x)[N]) {
+    if constexpr (N == 2) {
+        const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x[0] = __uint_as_float(uint32_t(u));
+        x[1] = __uint_as_float(uint32_t(u >> 32));
+    } else {
+        x[0] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
 
-template <typename T, int D, int GC, bool PREFILL, int WAVES>
+// UNROLL: tokens per lane group and loop trip (twice as many 16-byte loads in flight).  MERGE: the last partition of a row to
+// finish merges it (an instance of its own: as a branch the code cost launches of one partition 0.03 us).
+template <typename T, int D, int GC, bool PREFILL, int WAVES, int UNROLL, bool MERGE>
 __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const T *__restrict__ q, const T *__restrict__ k_cache, const T *__restrict__ v_cache,
     const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens,
@@ -160,7 +176,7 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const int32_t *table = block_tables + size_t(tseq) * p.max_blocks_per_seq;
     const size_t head_stride = size_t(p.block_size) * D;               // elements per (block, kv head)
     const size_t block_stride = head_stride * p.num_kv_heads;
-    constexpr int CH = TPL * kUnroll;                                   // tokens per wavefront per trip
+    constexpr int CH = TPL * UNROLL;                                   // tokens per wavefront per trip
 
     // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load the last one again, whose V
     // must not meet the weight 0, where it is an infinity.  One head per workgroup: every trip asks, which is shortest (fp32
@@ -168,10 +184,10 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     // 128, four heads, 24 x 256 15.6 us, asked in every trip 16.7).
     auto trip = [&](auto may_end, int base) __attribute__((always_inline)) {
         constexpr bool MAY_END = decltype(may_end)::value;
-        float kf[kUnroll][EPL], vf[kUnroll][EPL];
-        bool valid[kUnroll];
+        float kf[UNROLL][EPL], vf[UNROLL][EPL];
+        bool valid[UNROLL];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < UNROLL; ++u) {
             const int t = base + u * TPL + tg;
             valid[u] = !MAY_END || t < tok1;
             const int tc = valid[u] ? t : tok1 - 1;  // clamp: never touch a table entry or slot past the context
@@ -183,16 +199,16 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         }
         if (MAY_END && base + CH > tok1) {
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u)
+            for (int u = 0; u < UNROLL; ++u)
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) vf[u][e] = valid[u] ? vf[u][e] : 0.f;
         }
 #pragma unroll
         for (int g = 0; g < GC; ++g) {
-            float s[kUnroll];
+            float s[UNROLL];
             float mx = -INFINITY;
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < UNROLL; ++u) {
                 float d = 0.f;
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) d = fmaf(qf[g][e], kf[u][e], d);
@@ -212,7 +228,7 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
 #pragma unroll
             for (int e = 0; e < EPL; ++e) pv[e] = 0.f;
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < UNROLL; ++u) {
                 const float pu = E::exp_(s[u] - m_ref);
                 psum += pu;
 #pragma unroll
@@ -289,11 +305,47 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
             out[row * D + d] = E::to_out(A / L);
         } else {
             const size_t slot = row * p.max_partitions + part;
-            ws.acc[slot * D + d] = A;
+            if (MERGE) store_device(ws.acc + slot * D + d, A); else ws.acc[slot * D + d] = A;
             if (d == 0) {
-                ws.ml[slot * 2] = M;
-                ws.ml[slot * 2 + 1] = L;
+                if (MERGE) {
+                    store_device(ws.ml + slot * 2, M);
+                    store_device(ws.ml + slot * 2 + 1, L);
+                } else {
+                    ws.ml[slot * 2] = M;
+                    ws.ml[slot * 2 + 1] = L;
+                }
             }
+        }
+    }
+    if constexpr (MERGE) {
+        if (single) return;
+        // The workgroup that counts the last partition of its heads merges all of them.  The count may become visible only
+        // after the partial: every wavefront waits for its own stores, then all meet.  Nobody waits for anybody.
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        __shared__ int s_last;
+        const int nparts = (ctx + p.partition_tokens - 1) / p.partition_tokens;
+        int32_t *const counter = ws.cnt + seq * chunks + hc;
+        if (tid == 0) s_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nparts - 1;
+        __syncthreads();
+        if (!s_last) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // the fetches stay behind the count
+        if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        constexpr int DPL = D / 64;
+        for (int g = wave; g < GC; g += WAVES) {
+            const size_t row = size_t(seq) * p.num_q_heads + head0 + g, slot0 = row * p.max_partitions;
+            auto ml_of = [&](int i) {
+                float v[2];
+                load_device<2>(ws.ml + (slot0 + i) * 2, v);
+                return float2{v[0], v[1]};
+            };
+            float a[DPL];
+            const float L = merge_row<DPL, false, 16>(
+                lane < nparts ? ml_of(lane) : float2{-INFINITY, 0.f}, nparts, lane, ml_of,
+                [&](int i, float (&x)[DPL]) { load_device<DPL>(ws.acc + (slot0 + i) * D + lane * DPL, x); }, a);
+#pragma unroll
+            for (int j = 0; j < DPL; ++j) out[row * D + lane * DPL + j] = E::to_out(a[j] / L);
         }
     }
 }
@@ -302,18 +354,42 @@ template <typename T, int D, bool PREFILL>
 hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v, const int32_t *bt,
                             const int32_t *cl, const int32_t *qs, int num_tables, int max_query_len,
                             void *out, Workspace ws, const AttnParams &p, int grid, hipStream_t stream) {
-#define KVC_LAUNCH_WAVES(GC, WAVES)                                                               \
-    pa_partial_valu_kernel<T, D, GC, PREFILL, WAVES><<<dim3(grid), dim3(64 * WAVES), 0, stream>>>(\
-        static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v), bt, cl, \
-        qs, num_tables, max_query_len, static_cast<T *>(out), ws, p)
-    // Up to one workgroup per compute unit: sixteen wavefronts instead of four where the registers allow it and the
-    // merge in LDS is small (fp32, 24 x 256 tokens: 8 heads of 64 7.2 -> 6.4 us, 8 of 128 10.8 -> 8.7 us; four
-    // heads of 64 per workgroup 9.3 -> 9.7 us, so those stay at four).
+#define KVC_LAUNCH_AS(GC, WAVES, UNROLL, MERGE)                                                                       \
+    pa_partial_valu_kernel<T, D, GC, PREFILL, WAVES, UNROLL, MERGE><<<dim3(grid), dim3(64 * WAVES), 0, stream>>>(     \
+        static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v), bt, cl, qs, num_tables,     \
+        max_query_len, static_cast<T *>(out), ws, p)
+#define KVC_LAUNCH_WAVES(GC, WAVES, UNROLL)                                                                          \
+    do {                                                                                                             \
+        if (!PREFILL && p.merge_here) KVC_LAUNCH_AS(GC, WAVES, UNROLL, !PREFILL);                                    \
+        else KVC_LAUNCH_AS(GC, WAVES, UNROLL, false);                                                                \
+    } while (0)
+    if constexpr (!PREFILL) {
+        // A head per workgroup: the fewer trips a partition takes the better, as long as the workgroups of the launch fit the
+        // device at once.  Up to one workgroup a compute unit, fp32 takes sixteen wavefronts, with twice the tokens in a trip
+        // where four do not cover the partition (rows of 512 bytes: 5 x 1000 tokens, 16 / 4 heads, 15.0 -> 13.8 us, 4 x 256, 8 / 8,
+        // 6.0 -> 5.8).  Up to two, and bf16 throughout, eight, where four would make two trips (fp32 of 128, 16 / 4
+        // heads, 24 x 200 12.0 -> 11.4; bf16 of 64, 14 / 2 heads, 4 x 1500 7.6 -> 7.4; one trip, fp32 of 64, 12 / 12
+        // heads, 24 x 100 4.22 with four, 4.29 with eight).
+        if (gc == 1 && grid <= 2 * kNumCUs) {
+            constexpr int kTrip = 4 * (64 / (D * int(sizeof(T)) / 16));  // tokens of a wavefront
+            if constexpr (sizeof(T) == 4) {
+                if (grid <= kNumCUs) {
+                    if (p.partition_tokens > 16 * kTrip) KVC_LAUNCH_WAVES(1, 16, 8); else KVC_LAUNCH_WAVES(1, 16, 4);
+                    return hipGetLastError();
+                }
+            }
+            if (p.partition_tokens >= 2 * kWaves * kTrip) KVC_LAUNCH_WAVES(1, 8, 4); else KVC_LAUNCH_WAVES(1, kWaves, 4);
+            return hipGetLastError();
+        }
+    }
+    // Several heads, up to one workgroup per compute unit: sixteen wavefronts instead of four where the registers allow it and
+    // the merge in LDS is small (fp32, 24 x 256 tokens, 8 heads of 128 10.8 -> 8.7 us; four heads of 64 per workgroup 9.3 ->
+    // 9.7 us, so those stay at four).
     constexpr bool kWide = !PREFILL && sizeof(T) == 4;
 #define KVC_LAUNCH_VALU(GC)                                                                       \
     do {                                                                                          \
-        constexpr int kMany = kWide && (GC == 1 || (D == 128 && GC <= 4)) ? 16 : kWaves;          \
-        if (grid <= kNumCUs) KVC_LAUNCH_WAVES(GC, kMany); else KVC_LAUNCH_WAVES(GC, kWaves);      \
+        constexpr int kMany = kWide && D == 128 && GC <= 4 ? 16 : kWaves;                         \
+        if (grid <= kNumCUs) KVC_LAUNCH_WAVES(GC, kMany, 4); else KVC_LAUNCH_WAVES(GC, kWaves, 4); \
     } while (0)
     switch (gc) {
         case 8: KVC_LAUNCH_VALU(8); break;
@@ -322,6 +398,7 @@ hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v,
         default: KVC_LAUNCH_VALU(1); break;
     }
 #undef KVC_LAUNCH_VALU
+#undef KVC_LAUNCH_AS
 #undef KVC_LAUNCH_WAVES
     return hipGetLastError();
 }

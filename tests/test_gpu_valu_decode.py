@@ -40,3 +40,33 @@ def test_where_heads_part(oracle_mod, dtype, d, hq, hkv, nseq, cap, limit):
     print(f"[case] valu {dtype} D={d} {hq}/{hkv} nseq={nseq} cap={cap} of {limit} pairs", flush=True)
     got = out_to_f64(run_gpu(w, kernel=1, max_context_len=cap))
     assert np.abs(got - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
+
+
+# up to 64 partitions and 1024 counter words (sequence, heads of a workgroup) the last partition of a row merges it; above, a
+# launch of its own does
+@pytest.mark.parametrize("dtype,d,hq,hkv,nseq,cap,pt", [
+    (W.F32, 64, 4, 4, 3, 1024, 16), (W.F32, 64, 4, 4, 3, 1040, 16), (W.F32, 128, 16, 4, 5, 700, 16), (W.F32, 128, 8, 1, 30, 300, 32),
+    (W.BF16, 64, 6, 2, 9, 500, 32), (W.BF16, 128, 4, 4, 7, 260, 16), (W.F32, 64, 8, 8, 128, 64, 16), (W.F32, 64, 8, 8, 129, 64, 16),
+    (W.F32, 64, 32, 8, 40, 550, 0), (W.BF16, 64, 16, 16, 2, 5000, 0)])
+def test_the_last_partition_merges_the_row(oracle_mod, dtype, d, hq, hkv, nseq, cap, pt):
+    import paper_2503_13773_amd as K
+    import torch
+    from gpu_util import to_device
+    lens = np.random.default_rng(1400 + nseq + cap).integers(0, cap + 1, nseq)
+    lens[:4] = [cap, 0, 17, 16][:nseq]
+    w = custom(1400 + nseq, dtype=dtype, lens=lens, hq=hq, hkv=hkv, d=d, bs=16)
+    t = to_device(w)
+    desc = K.attn_desc(t["q"], t["k"], t["tables"], max_context_len=cap, kernel=1, partition_tokens=pt)
+    ws = K.new_workspace(desc)
+    print(f"[case] valu merge {dtype} D={d} {hq}/{hkv} nseq={nseq} cap={cap} pt={pt}", flush=True)
+    apart = torch.full_like(t["q"], float("nan"))
+    K.paged_attention_decode_partial(t["q"], t["k"], t["v"], t["tables"], t["lens"], w.scale, apart, desc, ws)
+    K.paged_attention_decode_merge(t["lens"], apart, desc, ws)
+    assert np.abs(out_to_f64(apart) - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
+    for _ in range(5):
+        ws[4096:].fill_(0xff)  # NaN in every slot: a partial fetched before it was written shows
+        got = torch.full_like(t["q"], float("nan"))
+        K.paged_attention_decode(t["q"], t["k"], t["v"], t["tables"], t["lens"], w.scale, got, desc=desc, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got, apart)
+        assert not ws[:4096].any()

@@ -93,6 +93,33 @@ def test_pieces_are_published_before_they_are_counted(tmp_path):
     assert checked >= 3, sorted(kernels)
 
 
+def test_partitions_are_published_before_they_are_counted(tmp_path):
+    """The vector-ALU kernel where the last partition of a row merges it: as in the kernel of few rows."""
+    kernels, name = {}, None
+    for ln in _assembly(tmp_path, os.path.join(B.CSRC, "paged_attention_valu.hip")):
+        m = re.match(r"^(_ZN\S*pa_partial_valu_kernel\S*):", ln)
+        if m:
+            name = m.group(1)
+            kernels[name] = []
+        elif ln.startswith(".Lfunc_end"):
+            name = None
+        elif name is not None:
+            kernels[name].append(ln.strip())
+    checked = 0
+    for name, body in kernels.items():
+        adds = [i for i, ln in enumerate(body) if ln.startswith("global_atomic_add")]
+        for i in adds:
+            before = [j for j in range(i) if body[j].startswith("global_store") and "sc1" in body[j]]
+            assert len(before) >= 2, name                   # accumulator, and maximum and sum
+            between = body[before[-1] + 1:i]
+            waits = [j for j, ln in enumerate(between) if re.match(r"s_waitcnt\b.*vmcnt\(0\)", ln)]
+            assert waits, f"{name}: no wait for the partition's stores before `{body[i]}`"
+            assert any(ln.startswith("s_barrier") for ln in between[waits[0]:]), \
+                f"{name}: no barrier between the wait for the partition's stores and `{body[i]}`"
+            checked += 1
+    assert checked >= 16, sorted(kernels)
+
+
 def test_score_products_of_the_wide_prefill_need_no_wait_states(tmp_path):
     """The wide prefill kernel's score products are inline asm, for which the compiler inserts no wait states: operands
     must not come from a vector instruction one or two before, and the scores of a product must not be touched by a
