@@ -11,6 +11,7 @@
 #include <math.h>
 
 #include "kvc_internal.h"
+#include "pa_lanes.h"
 
 namespace kvc {
 
@@ -28,8 +29,7 @@ __device__ inline float merge_row(float2 ml0, int nparts, int lane, Ml ml, Acc a
     fetch(0);
     float M = lane < nparts ? ml0.x : -INFINITY;
     for (int i = lane + 64; i < nparts; i += 64) M = fmaxf(M, ml(i).x);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    M = lanes::wave_max(M);
 
     float L = 0.f;
 #pragma unroll
@@ -55,9 +55,7 @@ __device__ inline float merge_row(float2 ml0, int nparts, int lane, Ml ml, Acc a
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) L += __shfl_xor(L, off);
-    return L;
+    return lanes::wave_sum(L);
 }
 
 }  // namespace kvc

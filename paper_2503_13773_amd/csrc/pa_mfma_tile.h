@@ -5,7 +5,7 @@
 //       A operand: lane holds K[token r][32j + 8*quad .. +7]; B operand: the same dims of
 //       Q[head r] (zero for r >= group size).
 //   softmax over the C layout: lane holds S[token 4*quad + i][head r], i < 4.  The max over
-//       the tile's tokens is 3 in-lane max + 2 cross-quad shuffles; exp2 with
+//       the tile's tokens is 3 in-lane max + 2 exchanges between quads; exp2 with
 //       scale*log2(e) folded into the scores.
 //   O^T[dim][head] += V^T[128 x 16] . P^T[16 x 16]       8 x v_mfma_f32_16x16x16_bf16
 //       B operand P^T is exactly the C layout of S (tokens 4*quad + i, head r): no data
@@ -27,6 +27,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include "pa_lanes.h"
 
 namespace kvc {
 namespace mfma {
@@ -70,8 +72,7 @@ struct HeadStateN {
     }
     // sum l over the 4 quads (the max is already common to them)
     __device__ inline void finish() {
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = lanes::sum_over_rows(l);
     }
 };
 using HeadState = HeadStateN<8>;
@@ -127,8 +128,7 @@ __device__ inline void compute_tile(HeadState &st, const bf16x8 (&ka)[4], uint4 
         }
     }
     float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = lanes::max_over_rows(mx);
     const float m_new = fmaxf(st.m, mx);  // finite: every tile has at least one valid token
     const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
     st.m = m_new;
@@ -207,8 +207,7 @@ __device__ inline void compute_tile(HeadStateN<4> &st, const uint4 (&kr)[4], uin
         }
     }
     float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = lanes::max_over_rows(mx);
     const float m_new = fmaxf(st.m, mx);
     const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
     st.m = m_new;
@@ -272,8 +271,7 @@ __device__ inline void compute_tile_groups(HeadState (&st)[NG], const bf16x8 (&k
 #pragma unroll
         for (int i = 0; i < 4; ++i) sv[i] = (4 * quad + i < limit) ? s[i] * scale_log2e : -INFINITY;
         float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        mx = lanes::max_over_rows(mx);
         const float m_new = fmaxf(st[g].m, mx);
         const float alpha = __builtin_amdgcn_exp2f(st[g].m - m_new);
         st[g].m = m_new;

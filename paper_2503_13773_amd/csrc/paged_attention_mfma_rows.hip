@@ -16,12 +16,14 @@
 //       last piece merges all of them, 512 threads wide, in slot order (so the bits of the result do not
 //       depend on who came last), writes the row and resets the counter.  Nobody waits for anybody.
 //
-// Measured against the balanced kernel, launches back to back, 32 / 8 heads of 128: one sequence of 300 tokens 9.2 ->
-// 7.3 us, 3217 tokens 15.0 -> 12.0 us (13 MB: 2.1 us of streaming; a call whose rows are all one piece takes
-// 5.5 to 8 us, the exchange of pieces about 2.5 us), 8000 tokens 24.8 -> 15.0 us, 32000 tokens 68 -> 28.8 us.
+// Measured against the balanced kernel, launches back to back, 32 / 8 heads of 128: one sequence of 3217 tokens 15.0 ->
+// 10.7 us (13 MB: 2.1 us of streaming; the exchange of pieces takes about 2.5 us), 8000 tokens 24.8 -> 14 us, 32000
+// tokens 68 -> 28 us.
 //
 // Every wavefront works out the placement by itself: lane n holds the length of sequence n, sums and
-// prefixes are a few cross-lane steps, no LDS and no barrier before the first loads.
+// prefixes are a few steps inside the vector ALU, no LDS and no barrier before the first loads (by shuffles, stamps of one sequence
+// of 3217 tokens, us from entry: placed 1.8, first loads 2.7, tiles consumed 4.0, wavefronts merged 5.4, stored 5.9,
+// counted 6.9, pieces fetched and weighed 9.4, written 10.6).
 #include <math.h>
 
 #include "kvc_internal.h"
@@ -42,16 +44,8 @@ constexpr int kMaxPieces = kMaxRowPieces;
 // 8.0 us against 8.4 us; 32 tiles 9.1 us against 8.5 us (head_dim 64: 16 tiles 7.0 / 8.1, 24 tiles 8.3 / 8.2).
 constexpr int kWholeTiles = kRowWholeTiles;
 
-__device__ inline int wave_sum(int x) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-    return uniform(x);
-}
-__device__ inline int wave_max(int x) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x = max(x, __shfl_xor(x, off));
-    return uniform(x);
-}
+using lanes::wave_max;
+using lanes::wave_sum;
 
 // Loads of one tile: entry(u) = pool index of its unit u (a tile is 1 << (kTokensLog2 - unit_log2) of them).  k_off / v_off:
 // this lane's place inside a unit, in elements.  UNIFORM: units of 16 tokens and more, so that all lanes of a
@@ -190,12 +184,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
         }
         const int P = lo;
         const int pieces = (t + P - 1) / P;
-        int incl = pieces;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            if (lane >= off) incl += v;
-        }
+        const int incl = lanes::prefix_sum(pieces);
         const int excl = incl - pieces;
         const int idx = b / Hkv;
         pc = Piece{0, b - idx * Hkv, 0, 0, 0, 0, 0};
@@ -368,13 +357,9 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         if (wave + j * kRowWaves < G) {  // wavefront-uniform
-            float top = pml[j].x;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+            const float top = wave_max(pml[j].x);
             const float wgt = lane < pc.pieces ? __builtin_amdgcn_exp2f(pml[j].x - top) : 0.f;
-            float sum = wgt * pml[j].y;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+            const float sum = wave_sum(wgt * pml[j].y);
             s_w[lane * G + wave + j * kRowWaves] = wgt;
             if (lane == 0) s_ml[0][wave + j * kRowWaves].y = sum;
         }

@@ -296,12 +296,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
             local[i] = sum;
             sum += t;
         }
-        int inc = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(inc, off);
-            if (lane >= off) inc += v;
-        }
+        const int inc = lanes::prefix_sum(sum);
         if (lane == 63) s_wave_tot[wave] = inc;
         if (HD == 64 && tid == 0) s_most = kShortRow;
         __syncthreads();
