@@ -11,10 +11,14 @@
 // Mapping: a token row of K or V is D*sizeof(T) bytes = LR lanes x 16 bytes, so one
 // wavefront load covers TPL = 64/LR tokens, fully coalesced.  Each group of LR lanes
 // keeps its own online-softmax state over the tokens it sees (no cross-lane traffic in
-// the loop beyond the LR-lane dot-product reduction); the TPL groups, then the four
-// wavefronts (sixteen in launches of at most a workgroup per compute unit, where the registers
-// allow it), are merged with the log-sum-exp rule at the end.  Scores and softmax are in
+// the loop beyond the LR-lane dot-product reduction); the TPL groups, then the four to sixteen
+// wavefronts, are merged with the log-sum-exp rule at the end.  Scores and softmax are in
 // natural-log units, accumulation in fp32.
+//
+// What bounds small launches is the chain of one workgroup, and in it the instructions that are run once: they come from L2,
+// so a merge written out for sixteen wavefronts in every thread, or an exponential (fp32: fifteen instructions) where one lane's
+// would do, costs more than it computes.  fp32, 8 / 8 heads of 64, us: 4 x 256 tokens 4.9 with the groups merged pair by pair,
+// 4.6 by one maximum and one exponential, 4.3 with a lane weighing each wavefront; 1 x 40 3.7 / 3.5 / 3.2.
 //
 // PREFILL variant (causal attention of several query positions per sequence, the recompute
 // path of Section 2.5 / 3.5, for the calls the matrix-core prefill kernels do not take): a
@@ -130,7 +134,31 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const int head0 = hc * GC;
     const int kvh = head0 / p.group;
     const int tid = threadIdx.x;
-    int ctx, tseq = seq;  // context length of this item, and the sequence whose table it walks
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int tg = lane / LR, c = lane % LR;
+    const int tok0 = part * p.partition_tokens;
+    constexpr int CH = TPL * UNROLL;  // tokens per wavefront per trip
+
+    // Table entries of the tokens of a trip.  They are requested before the context length is known, or under the K and V
+    // loads of the trip before (not with eight tokens a lane group, which leave no registers); entries past the context are
+    // read but never used.
+    constexpr bool kAhead = UNROLL == 4;
+    int blk[UNROLL];
+    const int32_t *table = nullptr;
+    auto look_up = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            blk[u] = table[min((base + u * TPL + tg) >> p.block_size_log2, p.max_blocks_per_seq - 1)];
+    };
+    int base = tok0 + wave * CH;
+    float qf[GC][EPL];
+    auto load_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < GC; ++g)
+            E::load16(q + (size_t(seq) * p.num_q_heads + head0 + g) * D + c * EPL, qf[g]);
+    };
+
+    int ctx;  // context length of this item
     if (PREFILL) {
         // seq is a row of q: largest n with q_start[n] <= row (sequences without rows are skipped)
         int lo = 0, hi = num_tables;
@@ -138,11 +166,14 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
             const int mid = (lo + hi) >> 1;
             if (q_start[mid] <= seq) lo = mid; else hi = mid;
         }
-        tseq = lo;
         const int i = seq - q_start[lo], Qn = q_start[lo + 1] - q_start[lo], S = context_lens[lo];
         if (Qn > S || i >= max_query_len) return;
         ctx = S - Qn + i + 1;
+        table = block_tables + size_t(lo) * p.max_blocks_per_seq;
     } else {
+        table = block_tables + size_t(seq) * p.max_blocks_per_seq;
+        if (kAhead) look_up(base);
+        load_q();
         ctx = min(context_lens[seq], p.max_context_len);
     }
 
@@ -152,17 +183,12 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
                 out[(size_t(seq) * p.num_q_heads + head0) * D + i] = E::to_out(0.f);
         return;
     }
-    const int tok0 = part * p.partition_tokens;
     if (tok0 >= ctx) return;
     const int tok1 = min(ctx, tok0 + p.partition_tokens);
-
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int tg = lane / LR, c = lane % LR;
-
-    float qf[GC][EPL];
-#pragma unroll
-    for (int g = 0; g < GC; ++g)
-        E::load16(q + (size_t(seq) * p.num_q_heads + head0 + g) * D + c * EPL, qf[g]);
+    if (PREFILL) {
+        if (kAhead) look_up(base);
+        load_q();
+    }
 
     float m[GC], l[GC], acc[GC][EPL];
 #pragma unroll
@@ -173,13 +199,11 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
     }
 
-    const int32_t *table = block_tables + size_t(tseq) * p.max_blocks_per_seq;
     const size_t head_stride = size_t(p.block_size) * D;               // elements per (block, kv head)
     const size_t block_stride = head_stride * p.num_kv_heads;
-    constexpr int CH = TPL * UNROLL;                                   // tokens per wavefront per trip
 
-    // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load the last one again, whose V
-    // must not meet the weight 0, where it is an infinity.  One head per workgroup: every trip asks, which is shortest (fp32
+    // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load from block 0 (or the
+    // last token again), whose V must not meet the weight 0, where it is an infinity or NaN.  One head per workgroup: every trip asks, which is shortest (fp32
     // of 64, 4 x 256 tokens 5.06 us, with the last trip apart 5.18); several: the last trip is code of its own (fp32 of
     // 128, four heads, 24 x 256 15.6 us, asked in every trip 16.7).
     auto trip = [&](auto may_end, int base) __attribute__((always_inline)) {
@@ -190,13 +214,14 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         for (int u = 0; u < UNROLL; ++u) {
             const int t = base + u * TPL + tg;
             valid[u] = !MAY_END || t < tok1;
-            const int tc = valid[u] ? t : tok1 - 1;  // clamp: never touch a table entry or slot past the context
-            const int blk = table[tc >> p.block_size_log2];
+            const int tc = kAhead || valid[u] ? t : tok1 - 1;
+            const int block = !kAhead ? table[tc >> p.block_size_log2] : valid[u] ? blk[u] : 0;
             const int slot = tc & (p.block_size - 1);
-            const size_t off = size_t(blk) * block_stride + kvh * head_stride + size_t(slot) * D + c * EPL;
+            const size_t off = size_t(block) * block_stride + kvh * head_stride + size_t(slot) * D + c * EPL;
             E::load16(k_cache + off, kf[u]);
             E::load16(v_cache + off, vf[u]);
         }
+        if (kAhead && base + WAVES * CH < tok1) look_up(base + WAVES * CH);  // wavefront-uniform
         if (MAY_END && base + CH > tok1) {
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u)
@@ -240,7 +265,6 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
             m[g] = m_new;
         }
     };
-    int base = tok0 + wave * CH;
     if constexpr (GC == 1) {
         for (; base < tok1; base += WAVES * CH) trip(std::true_type{}, base);
     } else {
@@ -248,24 +272,25 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         if (base < tok1) trip(std::true_type{}, base);
     }
 
-    // merge the TPL lane groups of this wavefront (log-sum-exp rule)
-#pragma unroll
-    for (int off = LR; off < 64; off <<= 1) {
-#pragma unroll
-        for (int g = 0; g < GC; ++g) {
-            const float m_o = __shfl_xor(m[g], off);
-            const float l_o = __shfl_xor(l[g], off);
-            const float M = fmaxf(m[g], m_o);
-            const float M_ref = M == -INFINITY ? 0.f : M;
-            const float a = E::exp_(m[g] - M_ref), b = E::exp_(m_o - M_ref);
-            l[g] = l[g] * a + l_o * b;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) {
-                const float acc_o = __shfl_xor(acc[g][e], off);
-                acc[g][e] = acc[g][e] * a + acc_o * b;
-            }
-            m[g] = M;
+    // merge the TPL lane groups of this wavefront (log-sum-exp rule): the maximum of all, one exponential, sums
+    auto over_groups = [](float x, auto op) __attribute__((always_inline)) {
+        if constexpr (LR <= 8) x = op(x, lanes::permuted<lanes::kRor8>(x));
+        if constexpr (LR <= 16) {
+            const lanes::Pair<float> a = lanes::pair_of<16>(x);
+            x = op(a.first, a.second);
         }
+        const lanes::Pair<float> b = lanes::pair_of<32>(x);
+        return op(b.first, b.second);
+    };
+    auto add = [](float a, float b) { return a + b; };
+#pragma unroll
+    for (int g = 0; g < GC; ++g) {
+        const float M = over_groups(m[g], [](float a, float b) { return fmaxf(a, b); });
+        const float a = E::exp_(m[g] - (M == -INFINITY ? 0.f : M));
+        l[g] = over_groups(l[g] * a, add);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] = over_groups(acc[g][e] * a, add);
+        m[g] = M;
     }
 
     // merge the wavefronts through LDS
@@ -288,18 +313,17 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     __syncthreads();
 
     const bool single = ctx <= p.partition_tokens;  // the whole context sat in this partition
-    for (int i = tid; i < GC * D; i += 64 * WAVES) {
-        const int g = i / D, d = i % D;
-        float M = sm_m[0][g];
+    // a wavefront takes 64 dims of a head; lane w weighs wavefront w's part
+    for (int i = wave; i < GC * (D / 64); i += WAVES) {
+        const int g = i / (D / 64), d = i % (D / 64) * 64 + lane;
+        const float m_w = lane < WAVES ? sm_m[lane % WAVES][g] : -INFINITY;
+        const float M = lanes::wave_max(m_w);
+        const float w_w = E::exp_(m_w - (M == -INFINITY ? 0.f : M));  // M = -inf: every score of the partition is
+        const float L = lanes::wave_sum(lane < WAVES ? w_w * sm_l[lane % WAVES][g] : 0.f);
+        float A = 0.f;
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][g]);
-        float L = 0.f, A = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            const float wgt = E::exp_(sm_m[w][g] - (M == -INFINITY ? 0.f : M));  // -inf: every score of the partition is
-            L = fmaf(wgt, sm_l[w][g], L);
-            A = fmaf(wgt, sm_acc[w][g][d], A);
-        }
+        for (int w = 0; w < WAVES; ++w)
+            A = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_w), w)), sm_acc[w][g][d], A);
         const size_t row = size_t(seq) * p.num_q_heads + head0 + g;
         if (single) {
             out[row * D + d] = E::to_out(A / L);
