@@ -17,7 +17,7 @@
 //       depend on who came last), writes the row and resets the counter.  Nobody waits for anybody.
 //
 // Measured against the balanced kernel, launches back to back, 32 / 8 heads of 128: one sequence of 3217 tokens 15.0 ->
-// 10.7 us (13 MB: 2.1 us of streaming; the exchange of pieces takes about 2.5 us), 8000 tokens 24.8 -> 14 us, 32000
+// 10.0 us (13 MB: 2.1 us of streaming; the exchange of pieces takes about 2.5 us), 8000 tokens 24.8 -> 14 us, 32000
 // tokens 68 -> 28 us.
 //
 // Every wavefront works out the placement by itself: lane n holds the length of sequence n, sums and
@@ -25,6 +25,8 @@
 // of 3217 tokens, us from entry: placed 1.8, first loads 2.7, tiles consumed 4.0, wavefronts merged 5.4, stored 5.9,
 // counted 6.9, pieces fetched and weighed 9.4, written 10.6).
 #include <math.h>
+
+#include <algorithm>
 
 #include "kvc_internal.h"
 #include "pa_mfma_tile.h"
@@ -46,6 +48,29 @@ constexpr int kWholeTiles = kRowWholeTiles;
 
 using lanes::wave_max;
 using lanes::wave_sum;
+
+// Divisions by numbers the host knows, as multiplications: an integer division is some forty instructions, and here it would stand
+// between two round trips to memory (32 / 8 heads of 128, us: 1 x 700 tokens 7.9 / 7.5, 1 x 3217 10.65 / 9.95, 4 x 2000 9.5 / 9.1).
+struct Divisors {
+    uint32_t room, slack;       // 2^32 / room and 2^32 / (room - num_seqs), rounded up
+    int rooms;                  // room: pieces per KV head that the grid holds
+    uint32_t kv_heads16;        // 2^16 / num_kv_heads, rounded up: exact below 2^16 / num_kv_heads
+    uint32_t group16;           // 2^16 / group, rounded up: exact below 2^16 / group
+    uint32_t vectors20;         // 2^20 / (group * HD / 4), rounded up: exact below 2^20 / that
+};
+// x / d, recip = 2^32 / d rounded up: the product is never too small and at most one too large (d = 1 does not fit)
+__device__ inline int divided(int x, int d, uint32_t recip) {
+    if (d == 1) return x;
+    const int q = int(__umulhi(uint32_t(x), recip));
+    return q - (q * d > x);
+}
+// x / d where that is at most a few hundred
+__device__ inline int divided_small(int x, int d, float recip) {
+    int q = int(float(x) * recip);
+    const int rem = x - q * d;
+    q += (rem >= d) - (rem < 0);
+    return q;
+}
 
 // Loads of one tile: entry(u) = pool index of its unit u (a tile is 1 << (kTokensLog2 - unit_log2) of them).  k_off / v_off:
 // this lane's place inside a unit, in elements.  UNIFORM: units of 16 tokens and more, so that all lanes of a
@@ -134,7 +159,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, uint16_t *__restrict__ out, Workspace ws,
-    AttnParams p, int unit_log2, int units_per_block_log2, Schedule sched) {
+    AttnParams p, Divisors by, int unit_log2, int units_per_block_log2, Schedule sched) {
     using TS = Shape<HD>;
     constexpr int kTokens = TS::kTokens, NV = TS::kVecs;
     constexpr int kMaxUnits = kTokens / 4;
@@ -173,20 +198,24 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
         const int t = (ctx + kTokens - 1) >> TS::kTokensLog2;
         const int total = wave_sum(t), longest = wave_max(t);
         empty_seq = b < nseq && __builtin_amdgcn_readlane(ctx, b < nseq ? b : 0) == 0;
-        const int room = int(gridDim.x) / Hkv;  // pieces per KV head the grid holds: at least 2 * num_seqs
+        const int room = by.rooms;  // pieces per KV head the grid holds: at least 2 * num_seqs
         // rows of up to kWholeTiles tiles are not cut if the grid allows: the exchange costs more than it saves
         const int least = longest <= kWholeTiles ? longest : p.min_chunk_tiles;
-        int lo = max(max(max(least, 1), (total + room - 1) / room), (longest + kMaxPieces - 1) / kMaxPieces);
-        int hi = max(lo, (total + room - nseq - 1) / (room - nseq));  // sum ceil(t / P) <= total / P + num_seqs
+        int lo = max(max(max(least, 1), divided(total + room - 1, room, by.room)), (longest + kMaxPieces - 1) / kMaxPieces);
+        // sum ceil(t / P) <= total / P + num_seqs
+        int hi = max(lo, divided(total + room - nseq - 1, room - nseq, by.slack));
+        auto pieces_of = [&](int len) __attribute__((always_inline)) {  // no row has more than kMaxPieces
+            return divided_small(t + len - 1, len, __builtin_amdgcn_rcpf(float(len)));
+        };
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (wave_sum((t + mid - 1) / mid) <= room) hi = mid; else lo = mid + 1;
+            if (wave_sum(pieces_of(mid)) <= room) hi = mid; else lo = mid + 1;
         }
         const int P = lo;
-        const int pieces = (t + P - 1) / P;
+        const int pieces = pieces_of(P);
         const int incl = lanes::prefix_sum(pieces);
         const int excl = incl - pieces;
-        const int idx = b / Hkv;
+        const int idx = int((uint32_t(b) * by.kv_heads16) >> 16);
         pc = Piece{0, b - idx * Hkv, 0, 0, 0, 0, 0};
         const uint64_t at = __ballot(pieces > 0 && excl <= idx && idx < incl);
         if (at) {
@@ -282,8 +311,8 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
     }
     __syncthreads();
     const int nv4 = G * HD / 4;
-    const int f = tid % nv4, share = tid / nv4;  // share: which pieces a thread merges in the second step
-    const int head = f % G, vq = f / G;
+    const int share = int((uint32_t(tid) * by.vectors20) >> 20), f = tid - share * nv4;  // share: which pieces a thread merges in the second step
+    const int vq = int((uint32_t(f) * by.group16) >> 16), head = f - vq * G;
     uint16_t *dst = out + (size_t(pc.n) * p.num_q_heads + pc.kvh * G + head) * HD + HD / 4 * (vq & 3) + 4 * (vq >> 2);
     auto write_out = [&](const float4 &a, float L) __attribute__((always_inline)) {
         const float inv = 1.0f / L;
@@ -332,7 +361,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
     if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // thread (share, f) takes the pieces share, share + shares, ... of vector f; the shares of a vector meet in LDS
-    const int shares = kRowThreads / nv4;
+    const int shares = int((uint32_t(kRowThreads) * by.vectors20) >> 20);
     const bool active = share < shares;
     float *const s_w = s_mem;                                                   // [64 pieces][G] weights
     float4 *const s_part = reinterpret_cast<float4 *>(s_mem + kMaxPieces * 16);  // [shares][nv4]
@@ -394,7 +423,7 @@ template <int HD, int MODE, bool UNIFORM>
 __global__ __launch_bounds__(64 * kWholeWaves, HD == 128 ? 2 : 3) void pa_whole_mfma_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
-    const int32_t *__restrict__ context_lens, uint16_t *__restrict__ out, AttnParams p, int unit_log2,
+    const int32_t *__restrict__ context_lens, uint16_t *__restrict__ out, AttnParams p, uint32_t group16, int unit_log2,
     int units_per_block_log2, Schedule sched) {
     using TS = Shape<HD>;
     constexpr int kTokens = TS::kTokens, NV = TS::kVecs;
@@ -472,7 +501,7 @@ __global__ __launch_bounds__(64 * kWholeWaves, HD == 128 ? 2 : 3) void pa_whole_
     __syncthreads();
     const int nv4 = G * HD / 4;
     for (int f = tid; f < nv4; f += 64 * kWholeWaves) {
-        const int head = f % G, vq = f / G;  // as in the kernel above
+        const int vq = int((uint32_t(f) * group16) >> 16), head = f - vq * G;  // as in the kernel above
         float M = -INFINITY, L = 0.f;
         float4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -506,7 +535,11 @@ hipError_t launch_rows_mfma(const void *q, const void *k_cache, const void *v_ca
 #define KVC_LAUNCH_ROWS(HD, MODE)                                                                                 \
     pa_rows_mfma_kernel<HD, MODE><<<dim3(grid), dim3(kRowThreads), 0, stream>>>(                                  \
         static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache), \
-        block_tables, context_lens, static_cast<uint16_t *>(out), ws, p, unit_log2, p.block_size_log2 - unit_log2, sched)
+        block_tables, context_lens, static_cast<uint16_t *>(out), ws, p, by, unit_log2, p.block_size_log2 - unit_log2, sched)
+    auto recip = [](uint64_t one, int d) { return uint32_t(std::min<uint64_t>((one + d - 1) / d, UINT32_MAX)); };  // d = 1: not used
+    const int room = grid / p.num_kv_heads;
+    const Divisors by{recip(uint64_t(1) << 32, room), recip(uint64_t(1) << 32, room - p.num_seqs), room, recip(1 << 16, p.num_kv_heads),
+                      recip(1 << 16, p.group), recip(1 << 20, p.group * head_dim / 4)};
     if (head_dim == 64) KVC_LAUNCH_ROWS(64, kDirect);  // stateless calls only
     else if (mode == kDirect) KVC_LAUNCH_ROWS(128, kDirect);
     else if (mode == kBuild) KVC_LAUNCH_ROWS(128, kBuild);
@@ -524,7 +557,8 @@ hipError_t launch_whole_mfma(const void *q, const void *k_cache, const void *v_c
 #define KVC_LAUNCH_WHOLE(HD, MODE, UNIFORM)                                                                                \
     pa_whole_mfma_kernel<HD, MODE, UNIFORM><<<dim3(p.num_kv_heads, p.num_seqs), dim3(64 * kWholeWaves), 0, stream>>>( \
         static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache), \
-        block_tables, context_lens, static_cast<uint16_t *>(out), p, unit_log2, p.block_size_log2 - unit_log2, sched)
+        block_tables, context_lens, static_cast<uint16_t *>(out), p, uint32_t(((1 << 16) + p.group - 1) / p.group), unit_log2, \
+        p.block_size_log2 - unit_log2, sched)
     const bool uniform_units = p.block_size >= 16;
     if (mode == kBuild) KVC_LAUNCH_WHOLE(128, kBuild, false);
     else if (head_dim == 64 && uniform_units) KVC_LAUNCH_WHOLE(64, kDirect, true);  // stateless calls only

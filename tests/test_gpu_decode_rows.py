@@ -54,6 +54,15 @@ def test_many_pieces_and_full_grids(oracle_mod, d, lens, hq, hkv):
     check(custom(920 + len(lens) + d, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=d, bs=16), oracle_mod, f"{lens[:4]}")
 
 
+# numbers of heads and sequences that the placement and the merge divide by: one to 128 KV heads, one piece to spare or
+# none per KV head, groups of any size
+@pytest.mark.parametrize("hq,hkv,lens", [(128, 128, [1000]), (86, 43, [700, 513]), (15, 3, [2000] * 7 + [33]), (65, 13, [900, 40, 600]), (11, 11, [600] * 11),
+                                         (77, 7, [5000, 17]), (26, 2, [3000, 100, 0, 700, 650]), (127, 127, [600])])
+def test_heads_and_sequences_of_any_number(oracle_mod, hq, hkv, lens):
+    for d in (128, 64):
+        check(custom(930 + hq + d, dtype=W.BF16, lens=lens, hq=hq, hkv=hkv, d=d, bs=16), oracle_mod, f"{hq}/{hkv} {lens[:4]}")
+
+
 def test_bound_far_above_the_lengths(oracle_mod):
     w = custom(940, dtype=W.BF16, lens=[70, 300, 5], hq=8, hkv=2, d=128, bs=16, lmax=4096)
     check(w, oracle_mod, "loose", max_context_len=65536)
