@@ -144,19 +144,28 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
     }
 
     constexpr int kMergeBatch = 16 / PV;  // partials of a row fetched together (64 registers per row)
+    // They are handled four at a time: the code of those behind the row's last four is neither run nor fetched, which is what a
+    // merge spends most of its time on (stamps of the last workers: 1.2 us from the last partial's arrival to the end at
+    // head_dim 128, 1.8 at 64, with code for sixteen and eight; 48 lognormal sequences, 32 / 8 heads of 64, 19.5 -> 18.8 us).
+    constexpr int kGroup = kMergeBatch < 4 ? kMergeBatch : 4;
     float2 ml[2][kMergeBatch];
     float4 x[2][kMergeBatch][PV];
     auto issue = [&](int w, int c0) __attribute__((always_inline)) {
         if (active) {
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; ++u) {
-                // wavefront-uniform: nothing is fetched past the row's partials, nor this worker's own
-                if (c0 + u >= row[w].cnt || c0 + u == row[w].own) continue;
-                const int slot = slot_of_partial(row[w].j0, c0 + u);
-                ml[w][u] = load2_device_scope(ml_buf, slot_ml(slot, G, hd));
+            for (int g = 0; g < kMergeBatch; g += kGroup) {
+                if (c0 + g < row[w].cnt) {
 #pragma unroll
-                for (int vv = 0; vv < PV; ++vv)
-                    x[w][u][vv] = load4_device_scope(acc_buf, slot_vec<HD>(slot, G, PV * sub + vv, quad, hd));
+                    for (int u = g; u < g + kGroup; ++u) {
+                        // wavefront-uniform: nothing is fetched past the row's partials, nor this worker's own
+                        if (c0 + u >= row[w].cnt || c0 + u == row[w].own) continue;
+                        const int slot = slot_of_partial(row[w].j0, c0 + u);
+                        ml[w][u] = load2_device_scope(ml_buf, slot_ml(slot, G, hd));
+#pragma unroll
+                        for (int vv = 0; vv < PV; ++vv)
+                            x[w][u][vv] = load4_device_scope(acc_buf, slot_vec<HD>(slot, G, PV * sub + vv, quad, hd));
+                    }
+                }
             }
         }
     };
@@ -181,18 +190,23 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
             if (c0 > 0) issue(w, c0);
             float mc = M;
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; ++u) {
-                if (c0 + u == row[w].own) {  // wavefront-uniform
-                    ml[w][u] = own_ml[w];
+            for (int g = 0; g < kMergeBatch; g += kGroup) {
+                if (c0 + g < cnt) {  // wavefront-uniform
 #pragma unroll
-                    for (int vv = 0; vv < PV; ++vv) x[w][u][vv] = own_x[w][vv];
-                }
-                if (c0 + u >= cnt) {         // past the row's partials: weight 0 below
-                    ml[w][u] = float2{-INFINITY, 0.f};
+                    for (int u = g; u < g + kGroup; ++u) {
+                        if (c0 + u == row[w].own) {
+                            ml[w][u] = own_ml[w];
 #pragma unroll
-                    for (int vv = 0; vv < PV; ++vv) x[w][u][vv] = float4{0.f, 0.f, 0.f, 0.f};
+                            for (int vv = 0; vv < PV; ++vv) x[w][u][vv] = own_x[w][vv];
+                        }
+                        if (c0 + u >= cnt) {  // past the row's partials: weight 0 below
+                            ml[w][u] = float2{-INFINITY, 0.f};
+#pragma unroll
+                            for (int vv = 0; vv < PV; ++vv) x[w][u][vv] = float4{0.f, 0.f, 0.f, 0.f};
+                        }
+                        mc = fmaxf(mc, ml[w][u].x);  // finite: every partial holds at least one token
+                    }
                 }
-                mc = fmaxf(mc, ml[w][u].x);  // finite: every partial holds at least one token
             }
             const float alpha = __builtin_amdgcn_exp2f(M - mc);
             M = mc;
@@ -200,15 +214,20 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
 #pragma unroll
             for (int vv = 0; vv < PV; ++vv) { a[vv].x *= alpha; a[vv].y *= alpha; a[vv].z *= alpha; a[vv].w *= alpha; }
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; ++u) {
-                const float wgt = c0 + u < cnt ? __builtin_amdgcn_exp2f(ml[w][u].x - M) : 0.f;
-                L = fmaf(wgt, ml[w][u].y, L);
+            for (int g = 0; g < kMergeBatch; g += kGroup) {
+                if (c0 + g < cnt) {
 #pragma unroll
-                for (int vv = 0; vv < PV; ++vv) {
-                    a[vv].x = fmaf(wgt, x[w][u][vv].x, a[vv].x);
-                    a[vv].y = fmaf(wgt, x[w][u][vv].y, a[vv].y);
-                    a[vv].z = fmaf(wgt, x[w][u][vv].z, a[vv].z);
-                    a[vv].w = fmaf(wgt, x[w][u][vv].w, a[vv].w);
+                    for (int u = g; u < g + kGroup; ++u) {
+                        const float wgt = __builtin_amdgcn_exp2f(ml[w][u].x - M);
+                        L = fmaf(wgt, ml[w][u].y, L);
+#pragma unroll
+                        for (int vv = 0; vv < PV; ++vv) {
+                            a[vv].x = fmaf(wgt, x[w][u][vv].x, a[vv].x);
+                            a[vv].y = fmaf(wgt, x[w][u][vv].y, a[vv].y);
+                            a[vv].z = fmaf(wgt, x[w][u][vv].z, a[vv].z);
+                            a[vv].w = fmaf(wgt, x[w][u][vv].w, a[vv].w);
+                        }
+                    }
                 }
             }
         }
