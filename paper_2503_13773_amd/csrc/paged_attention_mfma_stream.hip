@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         if (MODE == kBuild && lane < kPlanInts) sched.plans[size_t(worker) * kPlanInts + lane] = 0;
     };
     const int seq_units = uniform(s_pref[nseq]), T = seq_units * Hkv;
-    const int workers = gridDim.x * kWaves;
+    constexpr int workers = kNumCUs * kWaves;  // the grid's
     // The smallest range keeps the pieces of a row at about 32, whose lengths the host bounds; at head_dim 64 the lengths
     // themselves put a loose bound right (no row is longer than all of them together): 16 / 16 heads, four sequences of up to
     // 8000 tokens under a bound of 32000 39.9 -> 26.4 us.
@@ -402,6 +402,15 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         load_q_operand(qb, q + (size_t(n) * p.num_q_heads + c.kvh * G + (r < G ? r : 0)) * HD, quad, active);
     };
 
+    // x / d for 0 <= x < 2^30 with a quotient below 2^20, recip within an ulp of 1 / d: the float product is off by less
+    // than one, so one correction step either way makes it exact - a handful of instructions against the forty of an integer
+    // division, five times, on the path every wavefront walks before it can request its first tile (0.1 to 0.2 us a call)
+    auto quotient = [](int x, int d, float recip) __attribute__((always_inline)) {
+        int qt = int(float(x) * recip);
+        const int rem = x - qt * d;
+        qt += (rem >= d) - (rem < 0);
+        return qt;
+    };
     // ---- place the worker: largest n with s_pref[n] * Hkv <= f0 (that sequence is not empty)
     RowCursor first;
     int first_tile;
@@ -447,7 +456,9 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         first.pref = uniform(s_pref[lo]);
         const int units = uniform(s_pref[lo + 1]) - first.pref;  // per KV head
         first.tiles = units - kRowCost;
-        first.kvh = (f0 - first.pref * Hkv) / units;
+        const float recip = __builtin_amdgcn_rcpf(float(units));
+        first.kvh = quotient(f0 - first.pref * Hkv, units, recip);  // below Hkv
+        if (Hkv >= 1 << 20) first.kvh = (f0 - first.pref * Hkv) / units;
         first_tile = (f0 - first.pref * Hkv) - first.kvh * units;
         if (first_tile >= first.tiles) {  // the range starts in the row's cost units: begin with the next row
             first = next_row(first);
@@ -471,17 +482,8 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
             c = next_row(c);
             t0 = 0;
         }
-        // x / C for 0 <= x < 2^30 with a quotient below 2^16 (a worker index): the float product
-        // is off by less than one, so one correction step either way makes it exact - a handful
-        // of instructions against the forty of an integer division, four times, on the path
-        // every wavefront walks before it can request its first tile
-        const float inv_c = 1.0f / float(C);
-        auto div_c = [&](int x) __attribute__((always_inline)) {
-            int qt = int(float(x) * inv_c);
-            const int rem = x - qt * C;
-            qt += (rem >= C) - (rem < 0);
-            return qt;
-        };
+        const float inv_c = __builtin_amdgcn_rcpf(float(C));
+        auto div_c = [&](int x) __attribute__((always_inline)) { return quotient(x, C, inv_c); };  // the index of a worker
         if (first_tile > 0) {
             const int row_f = first.pref * Hkv + first.kvh * (first.tiles + kRowCost);
             h_n = first.n; h_kvh = first.kvh; h_j0 = div_c(row_f);
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         }                               // else: T piece, stays in `st`
     };
 
-    const uint32_t slots = 2u * gridDim.x * kWaves;
+    constexpr uint32_t slots = 2u * kNumCUs * kWaves;
     const __amdgpu_buffer_rsrc_t acc_buf = raw_buffer(ws.acc, slots * uint32_t(G * HD) * 4u);
     const __amdgpu_buffer_rsrc_t ml_buf = raw_buffer(ws.ml, slots * uint32_t(G) * 8u);
     auto store_partial = [&](int slot, const typename TS::State &x) __attribute__((always_inline)) {
