@@ -3,7 +3,7 @@
 //
 // Written for head_dim 128 and 16-token tiles below; at head_dim 64 a tile is 32 tokens, the same 8 KiB of
 // K and V, so ranges, loads in flight and row costs are the same (48 sequences, lognormal, 32 / 8 heads, 73 MB:
-// 19.9 us; on the vector ALUs with a merge launch 32.9 us).
+// 18.6 us; on the vector ALUs with a merge launch 32.9 us).
 //
 // The serving traces this path sees have heavily skewed context lengths (a lognormal mix:
 // median ~700 tokens, tail to 4096), and the whole batch is only ~30 us of HBM streaming.
