@@ -110,7 +110,8 @@ typedef struct {
     int32_t max_partitions;    /* partitions per sequence the grid provides for (balanced kernel:
                                   partial slots per wavefront) */
     int32_t partial_grid;      /* workgroups of the partial kernel */
-    int32_t merge_grid;        /* workgroups of the merge kernel (0: not launched) */
+    int32_t merge_grid;        /* workgroups of kvc_paged_attention_decode_merge (0: launches nothing);
+                                  the whole call may do without that launch, see below */
     int32_t reserved;
     uint64_t workspace_bytes;
 } kvc_attn_plan_info;
