@@ -199,14 +199,18 @@ bool prefill_d64_ok(const kvc::PrefillParams &p, int total_q, int max_query_len)
 // A workgroup of the vector-ALU kernel takes as many heads of a KV head as its registers hold, which reads K and V
 // once for all of them; a launch of few workgroups spends its time on the chain of one of them, which is
 // shorter with a head each.  The line, in (query head, partition) pairs, and both sides, us with the heads together / one each:
-//   four or eight heads: fp32, 16 / 4 heads, 4 x 256 tokens, 64 pairs, of 64 9.0 / 5.1, of 128 12.9 / 7.0; 4 x 1000, 256 pairs,
+//   four heads: fp32, 16 / 4 heads, 4 x 256 tokens, 64 pairs, of 64 9.0 / 5.1, of 128 12.9 / 7.0; 4 x 1000, 256 pairs,
 //     18.1 / 14.1; 4 x 2000, 512 pairs, 19.6 / 21.7; bf16 of 128, 40 / 2 heads, 1 x 2300, 360 pairs, 15.0 / 10.4, but with four heads per KV
 //     head, whose reads meet less often in the caches, 32 / 8, 1 x 2560, 320 pairs, 14.9 / 14.5, 1 x 3000, 384 pairs, 15.0 / 16.1
 //     (one partition, 12 x 100, 384 pairs, 8.1 / 5.0);
+//   eight heads lose most: fp32, 16 / 2 heads, 9 x 700, 432 pairs, of 64 16.2 / 10.4, of 128 28.3 / 15.8; 64 / 8, 10 x 250, 640 pairs, 13.4 /
+//     9.8 and 25.5 / 16.6; 16 / 2, 20 x 512, 640 pairs, 16.2 / 11.5 and 28.9 / 18.1; 14 x 1000, 896 pairs, 16.4 / 14.7 and 30.1 / 24.1, but 64 x 250, 1024
+//     pairs, 13.7 / 14.5 and 27.3 / 24.5, 64 / 8, 24 x 250, 1536 pairs, 14.2 / 19.1 and 28.0 / 34.2; bf16 of 128, 16 / 2, 30 x 250, 480 pairs, 14.6 / 9.7;
 //   two heads lose less together: rows of 256 bytes and more, 16 / 8 heads, 16 x 256, 256 pairs, 7.6 / 5.9 (fp32 of 64), 7.9 / 7.3
 //     (bf16 of 128), 20 x 256, 320 pairs, 7.7 / 10.5 and 7.9 / 10.6; rows of 128 bytes (bf16 of 64) 8 x 700, 384 pairs, 9.3 / 8.6.
 int64_t few_row_parts(const kvc_attn_desc &d, int heads, int64_t parts) {
     const bool wide_rows = d.head_dim * (d.dtype == KVC_F32 ? 4 : 2) >= 256;
+    if (heads == 8) return 768;
     if (heads == 2 && wide_rows) return 256;
     return d.dtype == KVC_BF16 && wide_rows && d.num_q_heads == 4 * d.num_kv_heads && parts > 1 ? 320 : 384;
 }

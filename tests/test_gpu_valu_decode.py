@@ -70,3 +70,19 @@ def test_the_last_partition_merges_the_row(oracle_mod, dtype, d, hq, hkv, nseq, 
         torch.cuda.synchronize()
         assert torch.equal(got, apart)
         assert not ws[:4096].any()
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,nseq,cap", [(W.F32, 64, 16, 2, 24, 512), (W.F32, 64, 16, 2, 25, 512), (W.F32, 128, 64, 8, 12, 256),
+                                                     (W.F32, 128, 64, 8, 13, 256), (W.BF16, 128, 32, 4, 8, 700), (W.BF16, 64, 8, 1, 33, 700)])
+def test_where_eight_heads_part(oracle_mod, dtype, d, hq, hkv, nseq, cap):
+    """Eight heads of a KV head together from 768 (head, partition) pairs on."""
+    import paper_2503_13773_amd as K
+    lens = np.random.default_rng(1450 + nseq).integers(0, cap + 1, nseq)
+    lens[0] = cap
+    w = custom(1450 + nseq + d, dtype=dtype, lens=lens, hq=hq, hkv=hkv, d=d, bs=16, lmax=64)
+    code, pairs = K.KVC_F32 if dtype == W.F32 else K.KVC_BF16, nseq * hq * -(-cap // 256)
+    plan = K.attn_plan(K.AttnDesc(nseq, hq, hkv, d, 16, 64, 64, code, cap, 0, 1, 0))
+    assert plan.partial_grid == (pairs if pairs <= 768 else pairs // 8)
+    print(f"[case] valu eight heads {dtype} D={d} {hq}/{hkv} nseq={nseq} cap={cap}", flush=True)
+    got = out_to_f64(run_gpu(w, kernel=1, max_context_len=cap))
+    assert np.abs(got - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
