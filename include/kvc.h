@@ -141,9 +141,11 @@ KVC_API size_t kvc_paged_attention_decode_workspace_bytes(const kvc_attn_desc *d
  * t % block_size, KV head h / group.  (Decode step of an iteration-level scheduler over
  * block-based KV allocation: Section 1, Section 3.1, Section 3.3.)
  *
- *   - Table entries at index >= ceil(context_len / block_size) are never dereferenced, and
- *     pool contents at slots >= context_len in the last block never reach `out` (NaN there
- *     is fine).  One block id may appear in many rows (shared prefix).
+ *   - Table entries at index >= ceil(context_len / block_size) may be read (every row has
+ *     max_blocks_per_seq of them) but are never dereferenced: no block is touched for a sequence
+ *     that its first ceil(context_len / block_size) entries do not name.  Pool contents at
+ *     slots >= context_len in the last block never reach `out` (NaN there is fine).  One
+ *     block id may appear in many rows (shared prefix).
  *   - context_lens[n] == 0 writes a row of zeros.
  *   - Accumulation is fp32; bf16 output is rounded to nearest even.
  *   - Split-K: a long context is cut into pieces whose (max, sum, accumulator) partials go

@@ -140,8 +140,8 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     constexpr int CH = TPL * UNROLL;  // tokens per wavefront per trip
 
     // Table entries of the tokens of a trip.  They are requested before the context length is known, or under the K and V
-    // loads of the trip before (not with eight tokens a lane group, which leave no registers); entries past the context are
-    // read but never used.
+    // loads of the trip before (not with eight tokens a lane group, which leave no registers); entries past the context may be
+    // read, inside the table's row, but are never used.
     constexpr bool kAhead = UNROLL == 4;
     int blk[UNROLL];
     const int32_t *table = nullptr;
@@ -202,20 +202,21 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const size_t head_stride = size_t(p.block_size) * D;               // elements per (block, kv head)
     const size_t block_stride = head_stride * p.num_kv_heads;
 
-    // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load from block 0 (or the
-    // last token again), whose V must not meet the weight 0, where it is an infinity or NaN.  One head per workgroup: every trip asks, which is shortest (fp32
+    // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load the trip's first token again (or
+    // the last one), whose V must not meet the weight 0, where it is an infinity or NaN.  One head per workgroup: every trip asks, which is shortest (fp32
     // of 64, 4 x 256 tokens 5.06 us, with the last trip apart 5.18); several: the last trip is code of its own (fp32 of
     // 128, four heads, 24 x 256 15.6 us, asked in every trip 16.7).
     auto trip = [&](auto may_end, int base) __attribute__((always_inline)) {
         constexpr bool MAY_END = decltype(may_end)::value;
         float kf[UNROLL][EPL], vf[UNROLL][EPL];
         bool valid[UNROLL];
+        const int first_block = kAhead ? __builtin_amdgcn_readfirstlane(blk[0]) : 0;  // of token `base`, which is inside the context
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const int t = base + u * TPL + tg;
             valid[u] = !MAY_END || t < tok1;
-            const int tc = kAhead || valid[u] ? t : tok1 - 1;
-            const int block = !kAhead ? table[tc >> p.block_size_log2] : valid[u] ? blk[u] : 0;
+            const int tc = valid[u] ? t : kAhead ? base : tok1 - 1;
+            const int block = !kAhead ? table[tc >> p.block_size_log2] : valid[u] ? blk[u] : first_block;
             const int slot = tc & (p.block_size - 1);
             const size_t off = size_t(block) * block_stride + kvh * head_stride + size_t(slot) * D + c * EPL;
             E::load16(k_cache + off, kf[u]);
