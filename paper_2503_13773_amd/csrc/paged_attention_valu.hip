@@ -111,8 +111,9 @@ __device__ inline void load_device(const float *p, float (&x)[N]) {
 }
 
 // UNROLL: tokens per lane group and loop trip (twice as many 16-byte loads in flight).  MERGE: the last partition of a row to
-// finish merges it (an instance of its own: as a branch the code cost launches of one partition 0.03 us).
-template <typename T, int D, int GC, bool PREFILL, int WAVES, int UNROLL, bool MERGE>
+// finish merges it (an instance of its own: as a branch the code cost launches of one partition 0.03 us).  AHEAD: table entries
+// are requested ahead of their use (see below).
+template <typename T, int D, int GC, bool PREFILL, int WAVES, int UNROLL, bool MERGE, bool AHEAD>
 __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const T *__restrict__ q, const T *__restrict__ k_cache, const T *__restrict__ v_cache,
     const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens,
@@ -139,10 +140,8 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const int tok0 = part * p.partition_tokens;
     constexpr int CH = TPL * UNROLL;  // tokens per wavefront per trip
 
-    // Table entries of the tokens of a trip.  They are requested before the context length is known, or under the K and V
-    // loads of the trip before (not with eight tokens a lane group, which leave no registers); entries past the context may be
-    // read, inside the table's row, but are never used.
-    constexpr bool kAhead = UNROLL == 4;
+    // AHEAD: the table entries of the tokens of a trip are requested before the context length is known, or under the K and V
+    // loads of the trip before; entries past the context may be read, inside the table's row, but are never used.
     int blk[UNROLL];
     const int32_t *table = nullptr;
     auto look_up = [&](int base) __attribute__((always_inline)) {
@@ -172,8 +171,10 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         table = block_tables + size_t(lo) * p.max_blocks_per_seq;
     } else {
         table = block_tables + size_t(seq) * p.max_blocks_per_seq;
-        if (kAhead) look_up(base);
-        load_q();
+        if (AHEAD) {
+            look_up(base);
+            load_q();
+        }
         ctx = min(context_lens[seq], p.max_context_len);
     }
 
@@ -185,8 +186,8 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     }
     if (tok0 >= ctx) return;
     const int tok1 = min(ctx, tok0 + p.partition_tokens);
-    if (PREFILL) {
-        if (kAhead) look_up(base);
+    if (PREFILL || !AHEAD) {
+        if (AHEAD) look_up(base);
         load_q();
     }
 
@@ -210,19 +211,19 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
         constexpr bool MAY_END = decltype(may_end)::value;
         float kf[UNROLL][EPL], vf[UNROLL][EPL];
         bool valid[UNROLL];
-        const int first_block = kAhead ? __builtin_amdgcn_readfirstlane(blk[0]) : 0;  // of token `base`, which is inside the context
+        const int first_block = AHEAD ? __builtin_amdgcn_readfirstlane(blk[0]) : 0;  // of token `base`, which is inside the context
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const int t = base + u * TPL + tg;
             valid[u] = !MAY_END || t < tok1;
-            const int tc = valid[u] ? t : kAhead ? base : tok1 - 1;
-            const int block = !kAhead ? table[tc >> p.block_size_log2] : valid[u] ? blk[u] : first_block;
+            const int tc = valid[u] ? t : AHEAD ? base : tok1 - 1;
+            const int block = !AHEAD ? table[tc >> p.block_size_log2] : valid[u] ? blk[u] : first_block;
             const int slot = tc & (p.block_size - 1);
             const size_t off = size_t(block) * block_stride + kvh * head_stride + size_t(slot) * D + c * EPL;
             E::load16(k_cache + off, kf[u]);
             E::load16(v_cache + off, vf[u]);
         }
-        if (kAhead && base + WAVES * CH < tok1) look_up(base + WAVES * CH);  // wavefront-uniform
+        if (AHEAD && base + WAVES * CH < tok1) look_up(base + WAVES * CH);  // wavefront-uniform
         if (MAY_END && base + CH > tok1) {
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u)
@@ -375,19 +376,39 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     }
 }
 
+// Whether table entries are requested ahead of their use.  That takes a round trip out of the chain of a workgroup; the registers
+// that hold them cost loads in flight or, with four heads in bf16, a wavefront per SIMD.  Both sides, us, at their use / ahead:
+//   eight heads: decode, bf16 of 64, 64 / 8 heads, eight of up to 13689 tokens 113.2 / 92.0, fp32 of 128, 8 / 1, eight of up to 2920
+//     37.6 / 30.7; prefill, bf16 of 64, 64 / 8, 9 x 1 row of up to 1151 50.6 / 33.1;
+//   four: decode, bf16 of 128, 32 / 8, blocks of one, 175 of up to 49 16.5 / 19.0, fp32 of 64, 32 / 8, 42 of up to 1174 26.2 / 31.0;
+//     prefill, bf16 of 128, 40 / 2, 9 x 8 rows of up to 695 35.0 / 51.7;
+//   two: decode, bf16 99 : 98, fp32 of 128 above two workgroups a compute unit 100 : 105; prefill, bf16 100 : 101;
+//   one: fp32 100 : 99; bf16 the same in calls of few workgroups, 34 / 2 heads of 64, blocks of two, 68 of up to 6009 165 / 183.
+// Prefill of two or four heads in fp32 goes by the launch: up to two workgroups a compute unit long contexts win (16 / 4 heads of 64, 352
+// workgroups at 1671 tokens 100.5 / 81.6, 32 / 16 of 128, 480 at 1835 177 / 142; from about 400 tokens on), short ones and larger launches
+// lose (16 / 8 of 128, 448 at 82 8.6 / 9.3, 1376 at 274 37.8 / 44.6).
+constexpr bool ahead_of_use(size_t bytes, int heads, bool prefill) {
+    return heads == 8 || (bytes == 4 ? heads == 1 : heads == 2 && !prefill);
+}
+
 template <typename T, int D, bool PREFILL>
 hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v, const int32_t *bt,
                             const int32_t *cl, const int32_t *qs, int num_tables, int max_query_len,
                             void *out, Workspace ws, const AttnParams &p, int grid, hipStream_t stream) {
-#define KVC_LAUNCH_AS(GC, WAVES, UNROLL, MERGE)                                                                       \
-    pa_partial_valu_kernel<T, D, GC, PREFILL, WAVES, UNROLL, MERGE><<<dim3(grid), dim3(64 * WAVES), 0, stream>>>(     \
+#define KVC_LAUNCH_AS(GC, WAVES, UNROLL, MERGE, AHEAD)                                                                \
+    pa_partial_valu_kernel<T, D, GC, PREFILL, WAVES, UNROLL, MERGE, AHEAD><<<dim3(grid), dim3(64 * WAVES), 0, stream>>>( \
         static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v), bt, cl, qs, num_tables,     \
         max_query_len, static_cast<T *>(out), ws, p)
 #define KVC_LAUNCH_WAVES(GC, WAVES, UNROLL)                                                                          \
     do {                                                                                                             \
-        if (!PREFILL && p.merge_here) KVC_LAUNCH_AS(GC, WAVES, UNROLL, !PREFILL);                                    \
-        else KVC_LAUNCH_AS(GC, WAVES, UNROLL, false);                                                                \
+        constexpr bool kAhead = UNROLL == 4 && ahead_of_use(sizeof(T), GC, PREFILL);                                 \
+        constexpr bool kEither = PREFILL && sizeof(T) == 4 && (GC == 2 || GC == 4);                                  \
+        if (!PREFILL && p.merge_here) KVC_LAUNCH_AS(GC, WAVES, UNROLL, !PREFILL, kAhead);                            \
+        else if (kEither && few_long) KVC_LAUNCH_AS(GC, WAVES, UNROLL, false, kEither || kAhead);                    \
+        else KVC_LAUNCH_AS(GC, WAVES, UNROLL, false, kAhead);                                                        \
     } while (0)
+    // prefill: up to two workgroups a compute unit, and tables that can hold several trips
+    [[maybe_unused]] const bool few_long = grid <= 2 * kNumCUs && int64_t(p.max_blocks_per_seq) * p.block_size >= 512;
     if constexpr (!PREFILL) {
         // A head per workgroup: the fewer trips a partition takes the better, as long as the workgroups of the launch fit the
         // device at once.  Up to one workgroup a compute unit, fp32 takes sixteen wavefronts, with twice the tokens in a trip
