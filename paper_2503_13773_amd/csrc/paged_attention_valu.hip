@@ -315,17 +315,8 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     __syncthreads();
 
     const bool single = ctx <= p.partition_tokens;  // the whole context sat in this partition
-    // a wavefront takes 64 dims of a head; lane w weighs wavefront w's part
-    for (int i = wave; i < GC * (D / 64); i += WAVES) {
-        const int g = i / (D / 64), d = i % (D / 64) * 64 + lane;
-        const float m_w = lane < WAVES ? sm_m[lane % WAVES][g] : -INFINITY;
-        const float M = lanes::wave_max(m_w);
-        const float w_w = E::exp_(m_w - (M == -INFINITY ? 0.f : M));  // M = -inf: every score of the partition is
-        const float L = lanes::wave_sum(lane < WAVES ? w_w * sm_l[lane % WAVES][g] : 0.f);
-        float A = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-            A = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_w), w)), sm_acc[w][g][d], A);
+    // m, sum and dim d of the accumulator of head g, over all wavefronts
+    auto put = [&](int g, int d, float M, float L, float A) __attribute__((always_inline)) {
         const size_t row = size_t(seq) * p.num_q_heads + head0 + g;
         if (single) {
             out[row * D + d] = E::to_out(A / L);
@@ -341,6 +332,39 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
                     ws.ml[slot * 2 + 1] = L;
                 }
             }
+        }
+    };
+    // Weights of the wavefronts: by a lane each, for all 64 dims of a wavefront's share, where the exponential is the long one and a
+    // few workgroups' chain is what counts (fp32 of 64, 8 / 8 heads, 4 x 256 tokens 4.6 -> 4.3 us); else every thread its own, which has no
+    // chain over the lanes (bf16 of 64, 61 x 91 tokens, 16 / 16 heads, 5.06 with a lane each, 4.88 so; decode up to 512 workgroups 0.97;
+    // eight heads 0.98; prefill 0.98).
+    if constexpr (sizeof(T) == 4 && GC < 8 && !PREFILL) {
+        for (int i = wave; i < GC * (D / 64); i += WAVES) {
+            const int g = i / (D / 64), d = i % (D / 64) * 64 + lane;
+            const float m_w = lane < WAVES ? sm_m[lane % WAVES][g] : -INFINITY;
+            const float M = lanes::wave_max(m_w);
+            const float w_w = E::exp_(m_w - (M == -INFINITY ? 0.f : M));  // M = -inf: every score of the partition is
+            const float L = lanes::wave_sum(lane < WAVES ? w_w * sm_l[lane % WAVES][g] : 0.f);
+            float A = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w)
+                A = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_w), w)), sm_acc[w][g][d], A);
+            put(g, d, M, L, A);
+        }
+    } else {
+        for (int i = tid; i < GC * D; i += 64 * WAVES) {
+            const int g = i / D, d = i % D;
+            float M = sm_m[0][g];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][g]);
+            float L = 0.f, A = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const float wgt = E::exp_(sm_m[w][g] - (M == -INFINITY ? 0.f : M));
+                L = fmaf(wgt, sm_l[w][g], L);
+                A = fmaf(wgt, sm_acc[w][g][d], A);
+            }
+            put(g, d, M, L, A);
         }
     }
     if constexpr (MERGE) {
