@@ -17,23 +17,18 @@ namespace kvc {
 
 // ml0 = (m, l) of partial `lane` where that is below nparts.  ml(i): those of partial i; acc(i, x): this lane's dims of
 // its accumulator.  On return a holds the merged accumulator and the result is a[j] / the returned sum.  BATCH accumulator
-// rows are in flight, the first of them under the loads and the maximum of ml0.  nparts is the same in all lanes.  MANY: whole
-// batches have code of their own without a branch per row (more than 64 partials, 16 / 4 heads of 64 in fp32, one sequence of 30000 tokens,
-// us, 28.1 without it, 24.9 with; where partials are few the code to fetch costs more: three of them, 5.5 without, 6.0 with).
-template <int DPL, bool BASE2, int BATCH, bool MANY, class Ml, class Acc>
+// rows are in flight.  FEW: a row at a time may be missing from a batch, and the first batch goes out ahead of the maximum, which is
+// the least code to fetch (three partials, fp32 of 64, 5.5 us, with whole batches apart 6.0); otherwise whole batches have code of
+// their own (118 partials, 16 / 4 heads of 64 and of 128, one sequence, 28.5 and 42.5 us as FEW, 23.9 and 35.8 so).
+template <int DPL, bool BASE2, int BATCH, bool FEW, class Ml, class Acc>
 __device__ inline float merge_row(float2 ml0, int nparts, int lane, Ml ml, Acc acc, float (&a)[DPL]) {
     float x[BATCH][DPL];
     auto fetch = [&](int t) __attribute__((always_inline)) {
-        if (MANY && t + BATCH <= nparts) {
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) acc(t + u, x[u]);
-            return;
-        }
 #pragma unroll
         for (int u = 0; u < BATCH; ++u)
-            if (t + u < nparts) acc(t + u, x[u]);
+            if (!FEW || t + u < nparts) acc(t + u, x[u]);
     };
-    if (!MANY || nparts <= 64) fetch(0);
+    if (FEW) fetch(0);
     float M = lane < nparts ? ml0.x : -INFINITY;
     for (int i = lane + 64; i < nparts; i += 64) M = fmaxf(M, ml(i).x);
     M = lanes::wave_max(M);
@@ -51,22 +46,30 @@ __device__ inline float merge_row(float2 ml0, int nparts, int lane, Ml ml, Acc a
             L = fmaf(w, v.y, L);
         }
         const int nt = min(64, nparts - c0);
-        for (int t = 0; t < nt; t += BATCH) {
-            if (c0 + t > 0 || (MANY && nparts > 64)) fetch(c0 + t);
-            auto add = [&](int u) __attribute__((always_inline)) {
-                const float wt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), t + u));
+        auto add = [&](int t, const float (&row)[DPL]) __attribute__((always_inline)) {
+            const float wt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), t));
 #pragma unroll
-                for (int j = 0; j < DPL; ++j) a[j] = fmaf(wt, x[u][j], a[j]);
-            };
-            if (MANY && t + BATCH <= nt) {
+            for (int j = 0; j < DPL; ++j) a[j] = fmaf(wt, row[j], a[j]);
+        };
+        if constexpr (FEW) {
+            for (int t = 0; t < nt; t += BATCH) {
+                if (c0 + t > 0) fetch(c0 + t);
 #pragma unroll
-                for (int u = 0; u < BATCH; ++u) add(u);
-                continue;
+                for (int u = 0; u < BATCH; ++u) {
+                    if (t + u >= nt) break;
+                    add(t + u, x[u]);
+                }
             }
+        } else {
+            int t = 0;
+            for (; t + BATCH <= nt; t += BATCH) {
+                fetch(c0 + t);
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                if (t + u >= nt) break;
-                add(u);
+                for (int u = 0; u < BATCH; ++u) add(t + u, x[u]);
+            }
+            for (; t < nt; ++t) {
+                acc(c0 + t, x[0]);
+                add(t, x[0]);
             }
         }
     }

@@ -391,7 +391,7 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
                 return float2{v[0], v[1]};
             };
             float a[DPL];
-            const float L = merge_row<DPL, false, 16, false>(
+            const float L = merge_row<DPL, false, 16, true>(
                 lane < nparts ? ml_of(lane) : float2{-INFINITY, 0.f}, nparts, lane, ml_of,
                 [&](int i, float (&x)[DPL]) { load_device<DPL>(ws.acc + (slot0 + i) * D + lane * DPL, x); }, a);
 #pragma unroll

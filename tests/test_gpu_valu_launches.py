@@ -3,7 +3,8 @@ import numpy as np
 import pytest
 
 import kvc_workloads as W
-from gpu_util import F32_TOL, out_to_f64
+from gpu_util import F32_TOL, out_to_f64, run_gpu, tol_of
+from test_gpu_attention import custom
 from test_gpu_prefill import make, run
 from test_gpu_prefill_d64 import reference
 
@@ -28,3 +29,13 @@ def test_prefill_of_two_and_four_heads(oracle_mod, d, hq, hkv, rows, longest, bs
     got, ref = out_to_f64(run(w, q, qs, max(qlens))), reference(oracle_mod, w, q, qs)
     assert np.isfinite(got).all()
     assert np.abs(got - ref).max() <= F32_TOL
+
+
+# more partials than a wavefront weighs at once: whole batches of eight and what is left, in the first 64 and behind
+@pytest.mark.parametrize("dtype,d,kernel", [(W.F32, 64, 1), (W.F32, 128, 1), (W.BF16, 64, 1), (W.BF16, 128, 2)])
+@pytest.mark.parametrize("cap", [1040, 1041, 1152, 1160, 2049, 3200])
+def test_merges_of_many_partials(oracle_mod, dtype, d, kernel, cap):
+    w = custom(1700 + cap + d, dtype=dtype, lens=[cap, 1025, 0, 16, 1024, 33], hq=6, hkv=2, d=d, bs=16)
+    print(f"[case] merge of {cap / 16} partials {dtype} D={d} kernel={kernel}", flush=True)
+    got = out_to_f64(run_gpu(w, kernel=kernel, partition_tokens=16, max_context_len=cap))
+    assert np.abs(got - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
