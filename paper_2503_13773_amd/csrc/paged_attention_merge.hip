@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kThreads) void pa_merge_kernel(const int32_t *__res
                                                             T *__restrict__ out, Workspace ws,
                                                             AttnParams p) {
     constexpr int DPL = D / 64;  // dims per lane
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int row = blockIdx.x * kWaves + wave;  // seq * num_q_heads + head
     if (row >= p.num_seqs * p.num_q_heads) return;
     const int seq = row / p.num_q_heads;
@@ -47,15 +47,16 @@ __global__ __launch_bounds__(kThreads) void pa_merge_kernel(const int32_t *__res
     if (lane < p.max_partitions) ml0 = *reinterpret_cast<const float2 *>(ml + 2 * lane);
     int nparts = (ctx + p.partition_tokens - 1) / p.partition_tokens;  // <= 1: finished already, or empty
     if (nparts <= 1) return;
-    nparts = min(nparts, p.max_partitions);
+    nparts = __builtin_amdgcn_readfirstlane(min(nparts, p.max_partitions));
 
-    float a[DPL];
-    const float L = merge_row<DPL, BASE2, 8, false>(
-        ml0, nparts, lane, [&](int i) { return *reinterpret_cast<const float2 *>(ml + 2 * i); },
-        [&](int i, float (&x)[DPL]) {
+    float a[DPL], L;
+    auto ml_of = [&](int i) { return *reinterpret_cast<const float2 *>(ml + 2 * i); };
+    auto acc_of = [&](int i, float (&x)[DPL]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < DPL; ++j) x[j] = acc[size_t(i) * D + j];
-        }, a);
+        for (int j = 0; j < DPL; ++j) x[j] = acc[size_t(i) * D + j];
+    };
+    if (nparts <= 64) L = merge_row<DPL, BASE2, 16, true>(ml0, nparts, lane, ml_of, acc_of, a);
+    else L = merge_row<DPL, BASE2, 8, false>(ml0, nparts, lane, ml_of, acc_of, a);
 #pragma unroll
     for (int j = 0; j < DPL; ++j) store_out(out + size_t(row) * D + lane * DPL + j, a[j] / L);
 }
