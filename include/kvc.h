@@ -152,8 +152,9 @@ KVC_API size_t kvc_paged_attention_decode_workspace_bytes(const kvc_attn_desc *d
  *     through the workspace.  The balanced kernel (KVC_KERNEL_MFMA_BALANCED, what AUTO picks for
  *     bf16 / head_dim 128 and for larger calls at head_dim 64) is ONE launch: the last wavefront or
  *     workgroup to finish a piece of a cut context merges its partials and writes the row.  So is the
- *     vector-ALU kernel up to 64 partitions a context and 1024 pairs of a sequence and the heads of a
- *     workgroup.  Otherwise a merge launch follows where a context can span more than one partition.
+ *     vector-ALU kernel where a context has few partitions or the call many rows (up to 64 partitions a
+ *     context and 1024 pairs of a sequence and the heads of a workgroup).  Otherwise a merge launch
+ *     follows where a context can span more than one partition.
  *   - `workspace`: device memory, 256-byte aligned, at least
  *     kvc_paged_attention_decode_workspace_bytes(desc); may be NULL when that is 0.  Its first
  *     4096 bytes hold arrival counters that must be 0 when a call starts:

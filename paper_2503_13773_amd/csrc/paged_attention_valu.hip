@@ -427,7 +427,8 @@ hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v,
     do {                                                                                                             \
         constexpr bool kAhead = UNROLL == 4 && ahead_of_use(sizeof(T), GC, PREFILL);                                 \
         constexpr bool kEither = PREFILL && sizeof(T) == 4 && (GC == 2 || GC == 4);                                  \
-        if (!PREFILL && p.merge_here) KVC_LAUNCH_AS(GC, WAVES, UNROLL, !PREFILL, kAhead);                            \
+        constexpr bool kMerge = !PREFILL && GC < 8;                                                                  \
+        if (kMerge && p.merge_here) KVC_LAUNCH_AS(GC, WAVES, UNROLL, kMerge, kAhead);                                \
         else if (kEither && few_long) KVC_LAUNCH_AS(GC, WAVES, UNROLL, false, kEither || kAhead);                    \
         else KVC_LAUNCH_AS(GC, WAVES, UNROLL, false, kAhead);                                                        \
     } while (0)
