@@ -142,8 +142,7 @@ bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
 //     are: bounds of 300 to 512, 256 x 250 39.3 / 35.8, 256 x 150 27.3 / 25.5, 256 x 16 7.6 / 11.6; 64 / 8 heads 512 x 150 54.1 / 54.2,
 //     512 x 16 13.9 / 23.9; 1024 x 150 97 / 99, 1024 x 16 23 / 42: no more than 2048 rows;
 //   head_dim 64: 1 x 500 7.0 / 5.5, 64 x 500 17.9 / 12.4, 20 x 1000 12.8 / 10.7; 14 / 2 heads on the vector ALUs before:
-//     128 x 500 36.2 / 8.2; but one head per KV head and many rows of one partition on the vector ALUs: 12 / 12 heads 42 x 100 4.25 /
-//     4.26, 64 x 100 4.5 / 5.1, 83 x 150 6.7 / 8.1.
+//     128 x 500 36.2 / 8.2; but one head per KV head and many rows of one partition on the vector ALUs: 12 / 12 heads 64 x 100 4.3 / 5.1, 83 x 150 7.6 / 8.1 (up to 640 rows they lead by a tenth at most: 12 / 12 42 x 100 3.9 / 4.3, 16 / 16 10 x 256 3.8 / 4.05).
 bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
     const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
     if (d.partition_tokens != 0 || d.num_seqs < 1 || d.num_seqs > kvc::kMaxStreamSeqs) return false;
@@ -154,11 +153,12 @@ bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
 
 // At head_dim 64 the balanced kernel serves calls that KVC_KERNEL_AUTO brings without a split of the caller's
 // own: whole rows, few rows, and ranges; the vector ALUs keep what they do as fast.  In us, there / here:
-//   few rows about as long as the launch takes a head per workgroup (few_row_parts): 14 / 2 heads 1 x 1000 8.0 / 8.5, 1 x 4000 7.4 /
-//     8.8, 4 x 2000, 448 pairs, 9.6 / 8.8; 16 / 8 heads 1 x 2000 7.1 / 9.0, 1 x 8000, 512 pairs, 9.2 / 11.7, 4 x 4000, 1024 pairs,
-//     11.4 / 11.7, but 4 x 250 under a bound of 4096 6.7 / 5.8; 32 / 8 heads 1 x 2000 7.4 / 8.9, 1 x 4000,
-//     512 pairs, 10.3 / 9.8; one head per KV head, where they read nothing twice, to 1024 pairs: 12 / 12 heads 1 x 4000 7.4 / 10.7,
-//     4 x 4000, 768 pairs, 12.3 / 14.2, 4 x 8000 20.1 / 20.6 (but 128 rows fill the device here: 16 / 16 heads 8 x 1500 15.0 / 13.9);
+//   few rows, by (query head, partition) pairs.  Groups of four and more to 384: 32 / 8 heads 1 x 1536, 192 pairs, 6.5 / 7.8, 2 x 1536 7.8 / 8.6, 1 x
+//     4096, 512 pairs, 9.3 / 8.8; 14 / 2 1 x 1792 6.5 / 7.5, 4 x 2048, 448 pairs, 7.8 / 7.9, 6 x 1792, 588 pairs, 9.9 / 8.2; 16 / 2 1 x 6144
+//     8.2 / 8.3, 8 x 1280, 640 pairs, 10.7 / 8.3 (but 16 x 512 in whole rows, 14 / 2 7.3 / 5.4).  Two heads to 512, 16 / 8 2 x 1536 6.5 / 8.6, 8 / 4 16 x
+//     1024 8.0 / 9.0, with about a tenth left above: 16 / 8 4 x 4096, 1024 pairs, 9.8 / 10.9, 6 x 2816 11.7 / 11.0.  One head per KV head,
+//     where they read nothing twice, to 1024: 12 / 12 2 x 4096 7.9 / 10.5, 8 x 2048, 768 pairs, 11.9 / 15.6, 1 x 21760 19.7 / 17.4, 16 / 16 2 x
+//     8192, 1024 pairs, 16.0 / 15.8 (but 128 rows fill the device here: 16 / 16 heads 8 x 1500 15.0 / 13.9);
 //   more rows below 2^17 tokens x KV heads: 102 k 9.7 / 11.9, 128 k 14.0 / 11.8, 524 k 39.3 / 25.2, 1 M 33.1 / 20.1 (one head per KV head: 128 rows
 //     of 1500 15.5 / 14.2, 12 / 12 heads 16 x 2000 18.8 / 18.6, 64 x 2000 52.6 / 53.1, 64 x 4000 114 / 98).
 bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
@@ -175,14 +175,13 @@ bool balanced64_ok(const kvc_attn_desc &d, int max_ctx) {
 // or 128 rows of a sequence, two workgroups a compute unit; one on the vector ALUs takes one row for as many heads as
 // it holds (valu_head_chunk: 1 for odd groups, else 2, 4 or 8).  The vector ALUs keep (us there / on the matrix cores)
 //   launches of at most two workgroups a compute unit with one head each, or one with two: 14 / 2 heads, one sequence of
-//     400 tokens, 2 rows 5.9 / 8.2, 32 rows 7.2 / 8.6, 64 rows 9.3 / 8.9; of 1500, 2 rows 12.0 / 17.2, 32 rows 16.2 / 17.6; 16 / 8 heads
-//     of 1500, 2 rows 15.8 / 17.4, four sequences of 16 rows 20.1 / 17.2 (with four heads each, 32 / 8, 1 to 8 x 2 rows
-//     17 to 19 / 12 to 13);
+//     400 tokens, 2 rows 5.9 / 7.4, 32 rows 6.9 / 7.8, 64 rows 9.2 / 8.2; of 1500, 2 rows 12.1 / 14.9, 32 rows 14.9 / 15.0; 16 / 8 heads
+//     of 1500, 2 rows 15.7 / 15.0, four sequences of 16 rows 20.1 / 14.8 (with four heads each, 32 / 8, 1 x 2 rows 24.1 / 15.1);
 //   batches that are mostly decode steps, one row each, and a few longer ones, where K and V of a sequence are read
-//     once per head chunk by either: 32 / 8 heads, 128 sequences of 800, one of 64 rows and the rest of one 46.7 / 60.6, half of
-//     them of two 48.8 / 57.0; 24 / 8 heads of 200 28.1 / 41.2 and 28.4 / 40.1; at 1.75 rows on average 26.5 / 26.5, at 3 35 / 28.  Two heads per
-//     workgroup lose their lead earlier: 16 / 8 heads of 800, 1.0 rows 30.4 / 33.6, 1.2 rows 14.4 / 13.6.  Eight heads are too
-//     few workgroups: 16 / 1 heads, 128 of 800 at 1.5 rows 50.0 / 38.8;
+//     once per head chunk by either: 32 / 8 heads, 128 sequences of 800, a fifth of them of two rows and the rest of one 42.8 / 48.5, half of
+//     them 48.9 / 48.8, three quarters 57.2 / 48.8; 24 / 8 heads of 200, half of them, 29.3 / 39.5 (of 800 90 / 69).  Two heads per
+//     workgroup lose their lead earlier: 16 / 8 heads of 800, 1.2 rows on average 37.5 / 34.4.  Eight heads are too
+//     few workgroups: 16 / 1 heads, 64 of 1500 at 1.6 rows 46.2 / 33.0;
 //   tiles most of which would be empty: a workgroup without rows still costs 1.2 ns (4096 sequences of 2 rows with a bound of
 //     8000 575 / 11000);
 //   and what a launch cannot hold: HIP refuses 2^32 threads and more.
@@ -198,16 +197,15 @@ bool prefill_d64_ok(const kvc::PrefillParams &p, int total_q, int max_query_len)
 
 // A workgroup of the vector-ALU kernel takes as many heads of a KV head as its registers hold, which reads K and V
 // once for all of them; a launch of few workgroups spends its time on the chain of one of them, which is
-// shorter with a head each.  The line, in (query head, partition) pairs, and both sides, us with the heads together / one each:
-//   four heads: fp32, 16 / 4 heads, 4 x 256 tokens, 64 pairs, of 64 9.0 / 5.1, of 128 12.9 / 7.0; 4 x 1000, 256 pairs,
-//     18.1 / 14.1; 4 x 2000, 512 pairs, 19.6 / 21.7; bf16 of 128, 40 / 2 heads, 1 x 2300, 360 pairs, 15.0 / 10.4, but with four heads per KV
-//     head, whose reads meet less often in the caches, 32 / 8, 1 x 2560, 320 pairs, 14.9 / 14.5, 1 x 3000, 384 pairs, 15.0 / 16.1
-//     (one partition, 12 x 100, 384 pairs, 8.1 / 5.0);
-//   eight heads lose most: fp32, 16 / 2 heads, 9 x 700, 432 pairs, of 64 16.2 / 10.4, of 128 28.3 / 15.8; 64 / 8, 10 x 250, 640 pairs, 13.4 /
-//     9.8 and 25.5 / 16.6; 16 / 2, 20 x 512, 640 pairs, 16.2 / 11.5 and 28.9 / 18.1; 14 x 1000, 896 pairs, 16.4 / 14.7 and 30.1 / 24.1, but 64 x 250, 1024
-//     pairs, 13.7 / 14.5 and 27.3 / 24.5, 64 / 8, 24 x 250, 1536 pairs, 14.2 / 19.1 and 28.0 / 34.2; bf16 of 128, 16 / 2, 30 x 250, 480 pairs, 14.6 / 9.7;
-//   two heads lose less together: rows of 256 bytes and more, 16 / 8 heads, 16 x 256, 256 pairs, 7.6 / 5.9 (fp32 of 64), 7.9 / 7.3
-//     (bf16 of 128), 20 x 256, 320 pairs, 7.7 / 10.5 and 7.9 / 10.6; rows of 128 bytes (bf16 of 64) 8 x 700, 384 pairs, 9.3 / 8.6.
+// shorter with a head each.  The line, in (query head, partition) pairs, and both sides (us with the heads together / one each, or the
+// quotient over contexts of 100 to 5000 tokens):
+//   four heads, together : one each by pairs: fp32 of 64 1.65 at 256, 1.02 at 384, 0.76 at 448; fp32 of 128 1.50, 0.96, 0.83; bf16 of 64 1.45, 1.31,
+//     1.27; bf16 of 128 1.62, 1.01, 1.00, but in several partitions with four heads per KV head, whose reads meet less often in the
+//     caches, 32 / 8, 1 x 2560, 320 pairs, 14.9 / 14.5, 1 x 3000, 384 pairs, 15.0 / 16.1 (one partition, 12 x 100, 384 pairs, 8.1 / 5.0);
+//   eight heads: 1.6 (fp32 of 64 1.4) at 384, fp32 of 64 1.02 at 672 to 768 and 0.84 above, fp32 of 128 0.98 and 0.90, bf16 of 128
+//     1.01 and 0.81, bf16 of 64 1.27 and 1.04;
+//   two heads lose less together: rows of 256 bytes and more, fp32 of 64 1.23 at 256, 0.93 at 352 to 384, bf16 of 128 1.24 and 0.89; fp32 of 128
+//     crosses before that (1.04 at 200, 0.73 at 256); rows of 128 bytes (bf16 of 64) 1.03 at 384, 1.00 at 512.
 int64_t few_row_parts(const kvc_attn_desc &d, int heads, int64_t parts) {
     const bool wide_rows = d.head_dim * (d.dtype == KVC_F32 ? 4 : 2) >= 256;
     if (heads == 8) return 768;

@@ -1,5 +1,5 @@
-"""The vector-ALU decode kernel around its launch shapes: one head or several per workgroup (384 (head, partition)
-pairs), four or sixteen wavefronts (256 workgroups), rows of 128, 256 and 512 bytes (sums over 8, 16 and 32 lanes)."""
+"""The vector-ALU decode kernel around its launch shapes: one head or several per workgroup (256 to 768 (head,
+partition) pairs), four or sixteen wavefronts (256 workgroups), rows of 128, 256 and 512 bytes (sums over 8, 16 and 32 lanes)."""
 import numpy as np
 import pytest
 
@@ -42,8 +42,7 @@ def test_where_heads_part(oracle_mod, dtype, d, hq, hkv, nseq, cap, limit):
     assert np.abs(got - oracle_mod.attention_of_workload(w, num_threads=8)).max() <= tol_of(w)
 
 
-# up to 64 partitions and 1024 counter words (sequence, heads of a workgroup) the last partition of a row merges it; above, a
-# launch of its own does
+# rows merged by their last partition (few partitions, or many rows, up to 64 and 1024) or by a launch of its own: the same bits
 @pytest.mark.parametrize("dtype,d,hq,hkv,nseq,cap,pt", [
     (W.F32, 64, 4, 4, 3, 1024, 16), (W.F32, 64, 4, 4, 3, 1040, 16), (W.F32, 128, 16, 4, 5, 700, 16), (W.F32, 128, 8, 1, 30, 300, 32),
     (W.BF16, 64, 6, 2, 9, 500, 32), (W.BF16, 128, 4, 4, 7, 260, 16), (W.F32, 64, 8, 8, 128, 64, 16), (W.F32, 64, 8, 8, 129, 64, 16),
@@ -75,7 +74,7 @@ def test_the_last_partition_merges_the_row(oracle_mod, dtype, d, hq, hkv, nseq, 
 @pytest.mark.parametrize("dtype,d,hq,hkv,nseq,cap", [(W.F32, 64, 16, 2, 24, 512), (W.F32, 64, 16, 2, 25, 512), (W.F32, 128, 64, 8, 12, 256),
                                                      (W.F32, 128, 64, 8, 13, 256), (W.BF16, 128, 32, 4, 8, 700), (W.BF16, 64, 8, 1, 33, 700)])
 def test_where_eight_heads_part(oracle_mod, dtype, d, hq, hkv, nseq, cap):
-    """Eight heads of a KV head together from 768 (head, partition) pairs on."""
+    """Eight heads of a KV head together above 768 (head, partition) pairs."""
     import paper_2503_13773_amd as K
     lens = np.random.default_rng(1450 + nseq).integers(0, cap + 1, nseq)
     lens[0] = cap
