@@ -128,6 +128,12 @@ __device__ inline uint32_t finite_only(uint32_t w) {
     return ((w & 0x7f80u) == 0x7f80u ? 0u : w & 0xffffu) | ((w & 0x7f800000u) == 0x7f800000u ? 0u : w & 0xffff0000u);
 }
 
+// a * b rounded, also where a subtraction follows: the compiler makes one fused operation of __fmul_rn(a, b) - c.
+__device__ inline float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 __device__ inline float top_of(const floatx16 &x) {
     const float a = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[8]));
     return fmaxf(a, max3(max3(x[9], x[10], x[11]), max3(x[12], x[13], x[14]), x[15]));
@@ -183,7 +189,7 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2], floatx16 &x, float &lsu
         }
         if (huge != 0) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) x[v] = __fmul_rn(x[v], scale);
+            for (int v = 0; v < 16; ++v) x[v] = rounded_product(x[v], scale);
             factor = 1.f;
         }
     }
@@ -414,7 +420,7 @@ __global__ __launch_bounds__(kBlockThreads, 4) void pa_prefill_d64_kernel(
         // so large that the factor itself would overflow the product is rounded first.
         if (huge != 0) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) x[v] = __fmul_rn(x[v], scale) - m;
+            for (int v = 0; v < 16; ++v) x[v] = rounded_product(x[v], scale) - m;
         } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) x[v] = __builtin_fmaf(x[v], scale, -m);
