@@ -197,7 +197,7 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2], floatx16 &x, float &lsu
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = 0.f;
     uint32_t hi[8], lo[8];
-    float rest[16];
+    float rest[16], sum;
     static_for<0, 14>([&](auto chunk) __attribute__((always_inline)) {
         constexpr int T = decltype(chunk)::value;
         KVC_PIN();
@@ -222,8 +222,9 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2], floatx16 &x, float &lsu
             }
             if constexpr (pair_chunk(I) + 2 == T) {
                 hi[I] = upper_parts(x[A], x[B]);
-                lsum += x[A] + x[B];
-                asm volatile("" : "+v"(hi[I]), "+v"(lsum));
+                const float both = x[A] + x[B];
+                sum = I == 0 ? both : sum + both;
+                asm volatile("" : "+v"(hi[I]), "+v"(sum));
                 rest[A] = rest_of(x[A]);
             }
             if constexpr (pair_chunk(I) + 3 == T) {
@@ -234,6 +235,7 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2], floatx16 &x, float &lsu
         });
     });
     KVC_PIN();
+    lsum += sum;  // once a step, as a step by itself does: weights far below the sum so far add up before they meet it
     x = s;
 }
 

@@ -1,9 +1,10 @@
 """Scores and weights of head_dim 64 prefill at the ends of their ranges: reference points beyond 2^20, where the product of a
-score and the scale is rounded before the reference point is taken off."""
+score and the scale is rounded before the reference point is taken off, and sums of weights far below their total."""
 import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import out_to_f64
 from test_gpu_prefill import make, run
@@ -42,3 +43,29 @@ def test_reference_points_beyond_2_to_the_20(oracle_mod, scale, hq, hkv, bs, seg
     got, ref = out_to_f64(run(w, q, qs, max(qlens))), reference(oracle_mod, w, q, qs)
     assert np.isfinite(got).all()
     assert (np.abs(got - ref) <= bound(ref)).all()
+
+
+def test_many_small_weights_reach_the_sum():
+    """2^23 tokens that weigh 2^-26 beside four that weigh 1: a pair of them is lost on a running sum of 1 (half an ulp is 2^-24),
+    the sixteen of a lane's step are not.  Tokens 0, 4, 32 and 36 weigh 1, one for every lane that sums a column, their V is 0, that of
+    all others 1; the output is one rounding to bf16 (2^-9) of S / (4 + S)."""
+    import paper_2503_13773_amd as K
+    bs, blocks, hq = 256, 1 << 15, 4
+    k = torch.zeros((2, 1, bs, 64), dtype=torch.bfloat16, device="cuda")
+    v = torch.ones_like(k)
+    k[:, :, :, 0] = -26.0
+    for t in (0, 4, 32, 36):
+        k[0, :, t, 0] = 0.0
+        v[0, :, t] = 0.0
+    q = torch.zeros((2, hq, 64), dtype=torch.bfloat16, device="cuda")
+    q[:, :, 0] = 1.0
+    tables = torch.ones((1, blocks), dtype=torch.int32, device="cuda")
+    tables[0, 0] = 0
+    lens = torch.tensor([bs * blocks], dtype=torch.int32, device="cuda")
+    starts = torch.tensor([0, 2], dtype=torch.int32, device="cuda")
+    print(f"[case] prefill d64 small weights, {bs * blocks} tokens", flush=True)
+    got = out_to_f64(K.paged_attention_prefill(q, k, v, tables, lens, starts, float(np.float32(np.log(2.0))), 2))
+    for row in range(2):
+        small = (bs * blocks - 1 + row - 4) * 2.0 ** -26
+        ref = small / (4 + small)
+        assert np.abs(got[row] - ref).max() <= ref * 2.0 ** -8
