@@ -142,7 +142,8 @@ bool smaller_calls_need_balanced(const kvc_attn_desc &d, int max_ctx) {
 //     are: bounds of 300 to 512, 256 x 250 39.3 / 35.8, 256 x 150 27.3 / 25.5, 256 x 16 7.6 / 11.6; 64 / 8 heads 512 x 150 54.1 / 54.2,
 //     512 x 16 13.9 / 23.9; 1024 x 150 97 / 99, 1024 x 16 23 / 42: no more than 2048 rows;
 //   head_dim 64: 1 x 500 7.0 / 5.5, 64 x 500 17.9 / 12.4, 20 x 1000 12.8 / 10.7; 14 / 2 heads on the vector ALUs before:
-//     128 x 500 36.2 / 8.2; but one head per KV head and many rows of one partition on the vector ALUs: 12 / 12 heads 64 x 100 4.3 / 5.1, 83 x 150 7.6 / 8.1 (up to 640 rows they lead by a tenth at most: 12 / 12 42 x 100 3.9 / 4.3, 16 / 16 10 x 256 3.8 / 4.05).
+//     128 x 500 36.2 / 8.2; but one head per KV head and many rows of one partition on the vector ALUs: 12 / 12 heads
+//     64 x 100 4.3 / 5.1, 83 x 150 7.6 / 8.1 (up to 640 rows they lead by a tenth at most: 42 x 100 3.9 / 4.3, 16 / 16 10 x 256 3.8 / 4.05).
 bool whole_ok(const kvc_attn_desc &d, int max_ctx) {
     const int64_t rows = int64_t(d.num_seqs) * d.num_kv_heads;
     if (d.partition_tokens != 0 || d.num_seqs < 1 || d.num_seqs > kvc::kMaxStreamSeqs) return false;

@@ -153,15 +153,12 @@ __device__ inline void multiply(floatx16 &acc, const uint4 &a, uint32_t b0, uint
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, uint4{b0, b1, b2, b3}), acc, 0, 0, 0);
 }
 
-// Chunk of the turn in which the arithmetic of pair i starts: arguments, exponentials, upper parts and sum, rests, one chunk
-// after the other.
-constexpr int pair_chunk(int i) { return i; }
-
 // One turn of a wavefront that sees all tokens of its step and the next, with the raw scores of step s in x:
 //     chunks  0 ..  3   S of step s + 1
 //     chunks  6 ..  9   O += V . weights of tokens 0 .. 15 of step s, upper parts, then rests
 //     chunks 10 .. 13   of tokens 16 .. 31
-// and the softmax arithmetic of step s spread over chunks 0 .. 10.
+// and the softmax arithmetic of step s spread over chunks 0 .. 10: that of pair i starts in chunk i, and its arguments, exponentials,
+// upper parts and sum, rests take a chunk each.
 __device__ inline void pipeline_turn(floatx16 (&acc)[2], floatx16 &x, float &lsum, float &m, uint64_t &huge, const bf16x8 (&qb)[4],
                                      const unsigned char *k_next, const int (&koff)[2], const unsigned char *const (&v_cur)[2], float scale) {
     bf16x8 ka[4];
@@ -212,22 +209,22 @@ __device__ inline void pipeline_turn(floatx16 (&acc)[2], floatx16 &x, float &lsu
         if constexpr (T == 6 || T == 7) va[1][T - 6] = read_v_operand(v_cur[T - 6], 1);
         static_for<0, 8>([&](auto pair) __attribute__((always_inline)) {
             constexpr int I = decltype(pair)::value, A = 2 * I, B = A + 1;
-            if constexpr (pair_chunk(I) == T) {
+            if constexpr (I == T) {
                 x[A] = __builtin_fmaf(x[A], factor, -m);
                 x[B] = __builtin_fmaf(x[B], factor, -m);
             }
-            if constexpr (pair_chunk(I) + 1 == T) {
+            if constexpr (I + 1 == T) {
                 x[A] = __builtin_amdgcn_exp2f(x[A]);
                 x[B] = __builtin_amdgcn_exp2f(x[B]);
             }
-            if constexpr (pair_chunk(I) + 2 == T) {
+            if constexpr (I + 2 == T) {
                 hi[I] = upper_parts(x[A], x[B]);
                 const float both = x[A] + x[B];
                 sum = I == 0 ? both : sum + both;
                 asm volatile("" : "+v"(hi[I]), "+v"(sum));
                 rest[A] = rest_of(x[A]);
             }
-            if constexpr (pair_chunk(I) + 3 == T) {
+            if constexpr (I + 3 == T) {
                 rest[B] = rest_of(x[B]);
                 lo[I] = pack_bf16(rest[A], rest[B]);
                 asm volatile("" : "+v"(lo[I]));
