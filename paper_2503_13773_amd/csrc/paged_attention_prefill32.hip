@@ -186,7 +186,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void pa_prefill_m
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
     const uint16_t *__restrict__ v_cache, const int32_t *__restrict__ block_tables,
     const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
-    uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at, int fold_ranked, int rank_from, int by_units) {
+    uint16_t *__restrict__ out, PrefillParams p, int query_tiles, int fold_at, int fold_ranked, int rank_from, int by_units, int spread) {
     constexpr int kParts = SPLIT ? 2 : 1;
     __shared__ __attribute__((aligned(1024))) unsigned char s_kv[kParts][2 * kRing][kStageBytes];
     constexpr int kWaveRows = 32 / HEADS;           // query rows of a wavefront: column c = kWaveRows * head + row
@@ -197,14 +197,14 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void pa_prefill_m
     // that share a compute unit are then a long and a short one.  With a context of `rank_from` tokens or more in
     // the batch (0: never) the same order is taken over the tiles of all sequences by the steps they walk,
     // which only the device knows.
-    // by_units (all workgroups, or 0): blockIdx.x places the head by head_place() instead.
+    // by_units (all workgroups, or 0): blockIdx.x places the head by head_place() instead.  spread: chunk_spread() of the chunks.
     int head0, kvh, index;
     if (HEADS == 1 && by_units > 0) {
         const HeadPlace at = head_place(blockIdx.x, by_units, p.group, p.num_kv_heads);
         head0 = at.head, kvh = at.kv_head, index = at.index;
     } else {
         const int chunks = p.num_q_heads / HEADS;
-        head0 = chunk_place(blockIdx.x % chunks, chunks, p.group / HEADS) * HEADS, index = blockIdx.x / chunks;
+        head0 = chunk_at(blockIdx.x % chunks, spread) * HEADS, index = blockIdx.x / chunks;
         kvh = head0 / p.group;
     }
 
@@ -618,9 +618,10 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k_cache, const void 
     const int fold_ranked = grid <= 2 * kNumCUs ? std::max(1, std::min(int(items), kNumCUs / chunks)) : int(items);
     const int by_units = prefill_by_units(p) ? int(grid) : 0;
     const dim3 g{unsigned(grid)}, b(split ? 512 : 256);
+    const int spread = chunk_spread(chunks, p.group / heads);
 #define KVC_LAUNCH(SMALL, HEADS, SPLIT)                                                                        \
     pa_prefill_mfma32_kernel<SMALL, HEADS, SPLIT><<<g, b, 0, stream>>>(qq, kk, vv, block_tables, context_lens, \
-                                                                       q_start, oo, p, query_tiles, fold_at, fold_ranked, rank_from, by_units)
+                                                                       q_start, oo, p, query_tiles, fold_at, fold_ranked, rank_from, by_units, spread)
     if (small && heads == 2) KVC_LAUNCH(true, 2, false);
     else if (small) KVC_LAUNCH(true, 1, false);
     else if (heads == 2 && split) KVC_LAUNCH(false, 2, true);

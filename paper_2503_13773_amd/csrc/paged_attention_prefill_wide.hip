@@ -165,7 +165,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void pa_prefill_wide_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     const int32_t *__restrict__ block_tables, const int32_t *__restrict__ context_lens, const int32_t *__restrict__ q_start,
-    uint16_t *__restrict__ out, PrefillParams p) {
+    uint16_t *__restrict__ out, PrefillParams p, int spread) {
     constexpr int kHeads = 4;
     constexpr int kWaveRows = 64 / kHeads;         // query rows of a wavefront
     constexpr int kTileRows = 4 * kWaveRows;       // and of the workgroup
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 
     const int chunks = p.num_q_heads / kHeads;
     // blockIdx.x = head chunk + chunks * (seq + num_seqs * order), the longest query tiles first
-    const int chunk = chunk_place(blockIdx.x % chunks, chunks, p.group / kHeads), index = blockIdx.x / chunks;
+    const int chunk = chunk_at(blockIdx.x % chunks, spread), index = blockIdx.x / chunks;
     const int head0 = chunk * kHeads;
     const int kvh = head0 / p.group;
     const int n = index % p.num_seqs, qtile = p.max_query_tiles - 1 - index / p.num_seqs;
@@ -459,7 +459,7 @@ hipError_t launch_prefill_wide(const void *q, const void *k_cache, const void *v
     const auto kernel = p.block_size < 8 ? pa_prefill_wide_kernel<true> : pa_prefill_wide_kernel<false>;
     kernel<<<dim3(unsigned(grid)), dim3(256), 0, stream>>>(static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
                                                            static_cast<const uint16_t *>(v_cache), block_tables, context_lens,
-                                                           q_start, static_cast<uint16_t *>(out), p);
+                                                           q_start, static_cast<uint16_t *>(out), p, chunk_spread(p.num_q_heads / 4, p.group / 4));
     return hipGetLastError();
 }
 
