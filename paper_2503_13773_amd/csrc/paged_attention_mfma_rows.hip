@@ -31,6 +31,7 @@
 #include "kvc_internal.h"
 #include "pa_mfma_tile.h"
 #include "pa_partials.h"
+#include "pa_quotient.h"
 
 namespace kvc {
 
@@ -63,13 +64,6 @@ __device__ inline int divided(int x, int d, uint32_t recip) {
     if (d == 1) return x;
     const int q = int(__umulhi(uint32_t(x), recip));
     return q - (q * d > x);
-}
-// x / d where that is at most a few hundred
-__device__ inline int divided_small(int x, int d, float recip) {
-    int q = int(float(x) * recip);
-    const int rem = x - q * d;
-    q += (rem >= d) - (rem < 0);
-    return q;
 }
 
 // Loads of one tile: entry(u) = pool index of its unit u (a tile is 1 << (kTokensLog2 - unit_log2) of them).  k_off / v_off:
@@ -205,7 +199,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void pa_rows_mfma_kernel(
         // sum ceil(t / P) <= total / P + num_seqs
         int hi = max(lo, divided(total + room - nseq - 1, room - nseq, by.slack));
         auto pieces_of = [&](int len) __attribute__((always_inline)) {  // no row has more than kMaxPieces
-            return divided_small(t + len - 1, len, __builtin_amdgcn_rcpf(float(len)));
+            return quotient(t + len - 1, len, __builtin_amdgcn_rcpf(float(len)));
         };
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;

@@ -67,6 +67,7 @@
 #include "kvc_internal.h"
 #include "pa_mfma_tile.h"
 #include "pa_partials.h"
+#include "pa_quotient.h"
 
 namespace kvc {
 
@@ -402,15 +403,6 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         load_q_operand(qb, q + (size_t(n) * p.num_q_heads + c.kvh * G + (r < G ? r : 0)) * HD, quad, active);
     };
 
-    // x / d for 0 <= x < 2^30 with a quotient below 2^20, recip within an ulp of 1 / d: the float product is off by less
-    // than one, so one correction step either way makes it exact - a handful of instructions against the forty of an integer
-    // division, five times, on the path every wavefront walks before it can request its first tile (0.1 to 0.2 us a call)
-    auto quotient = [](int x, int d, float recip) __attribute__((always_inline)) {
-        int qt = int(float(x) * recip);
-        const int rem = x - qt * d;
-        qt += (rem >= d) - (rem < 0);
-        return qt;
-    };
     // ---- place the worker: largest n with s_pref[n] * Hkv <= f0 (that sequence is not empty)
     RowCursor first;
     int first_tile;
@@ -457,8 +449,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
         const int units = uniform(s_pref[lo + 1]) - first.pref;  // per KV head
         first.tiles = units - kRowCost;
         const float recip = __builtin_amdgcn_rcpf(float(units));
-        first.kvh = quotient(f0 - first.pref * Hkv, units, recip);  // below Hkv
-        if (Hkv >= 1 << 20) first.kvh = (f0 - first.pref * Hkv) / units;
+        first.kvh = quotient_wide(f0 - first.pref * Hkv, units, recip);  // below Hkv, which nothing else limits
         first_tile = (f0 - first.pref * Hkv) - first.kvh * units;
         if (first_tile >= first.tiles) {  // the range starts in the row's cost units: begin with the next row
             first = next_row(first);
@@ -483,7 +474,7 @@ __global__ __launch_bounds__(kThreads, 1) void pa_stream_mfma_kernel(
             t0 = 0;
         }
         const float inv_c = __builtin_amdgcn_rcpf(float(C));
-        auto div_c = [&](int x) __attribute__((always_inline)) { return quotient(x, C, inv_c); };  // the index of a worker
+        auto div_c = [&](int x) __attribute__((always_inline)) { return quotient(x, C, inv_c); };  // the index of a worker (by float: 0.1 to 0.2 us a call)
         if (first_tile > 0) {
             const int row_f = first.pref * Hkv + first.kvh * (first.tiles + kRowCost);
             h_n = first.n; h_kvh = first.kvh; h_j0 = div_c(row_f);
