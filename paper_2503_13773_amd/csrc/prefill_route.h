@@ -91,12 +91,10 @@ constexpr HeadPlace head_place(int block, int blocks, int group, int kv_heads) {
 // keeps its share of each tile.  32 / 8 heads, us, in plain order / so: two of 4096 216.7 / 210.2, six of 2000 148.5 / 145.6,
 // of 400 19.7 / 19.0, four chunks of 512 rows at 4000 106.6 / 105.8; heads of 64, four of 1999 107.8 / 106.0.  Heads that share
 // nothing gain nothing (32 / 32, two of 3000 122.2 / 123.0).
-// At head_dim 128 the host says how many chunks an XCD holds (0: plain order): worked out in the kernel that took 0.05 us of a call (15 / 5
-// heads, two chunks of 5 rows, 6.89 us without, 6.99 with), also where nothing is dealt out.  At head_dim 64 the other arguments arrive later
-// with one more (32 / 8 heads, 18 rows, 4.53 us as it is, 4.87 with it), and the kernel works it out.
+// The host says how many chunks an XCD holds (0: plain order): worked out in the kernel that took 0.05 us of a call at head_dim 128 (15 / 5
+// heads, two chunks of 5 rows, 6.89 us without, 6.99 with), also where nothing is dealt out.
 constexpr int chunk_spread(int chunks, int sharing) { return sharing > 1 && (chunks & 7) == 0 ? chunks >> 3 : 0; }
 constexpr int chunk_at(int b, int spread) { return spread > 0 ? (b & 7) * spread + (b >> 3) : b; }
-constexpr int chunk_place(int b, int chunks, int sharing) { return chunk_at(b, chunk_spread(chunks, sharing)); }
 
 // Whether the kernel of 64-column wavefronts (paged_attention_prefill_wide.hip) takes a call: groups that 4 divides, four
 // query heads and 64 rows per workgroup, one workgroup per compute unit.  It reads half the LDS operands per score, but nothing hides a

@@ -22,7 +22,7 @@ int by_units(const int *v) { return prefill_by_units(params(v)); }
 int tiles32(const int *v, float scale) { PrefillParams p = params(v); p.scale_log2e = scale; return prefill_tiles32(p); }
 int split(const int *v) { return prefill_split(params(v)); }
 int split_steps() { return kMinSplitSteps; }
-int chunk(int b, int chunks, int sharing) { return chunk_place(b, chunks, sharing); }
+int chunk(int b, int chunks, int sharing) { return chunk_at(b, chunk_spread(chunks, sharing)); }
 void places(int blocks, int group, int kv_heads, int *out) {
     for (int b = 0; b < blocks; ++b) {
         const HeadPlace at = head_place(b, blocks, group, kv_heads);
