@@ -16,8 +16,9 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 template <class T>
 __device__ inline uint32_t bits(T x) { return __builtin_bit_cast(uint32_t, x); }
 
-// DPP controls: permutations of a quad, rotations and mirrors of a row of 16 lanes, shifts along a row.
-constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kRor4 = 0x124, kRor8 = 0x128, kShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+// DPP controls: permutations of a quad, mirrors of 8 and 16 lanes, rotations of a row of 16, shifts along it, its last lane to the next rows.
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kMirror8 = 0x141, kMirror16 = 0x140, kRor4 = 0x124, kRor8 = 0x128, kShr = 0x110, kBcast15 = 0x142,
+              kBcast31 = 0x143;
 template <int CTRL, int ROWS = 0xf, class T>
 __device__ inline T permuted(T x) {  // 0 in lanes that nothing is moved to
     return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, ROWS == 0xf));
@@ -34,6 +35,16 @@ __device__ inline Pair<T> pair_of(T x) {
                               : __builtin_amdgcn_permlane16_swap(bits(x), bits(x), false, false);
     const uint32_t first = b[0], second = b[1];
     return {__builtin_bit_cast(T, first), __builtin_bit_cast(T, second)};
+}
+
+// op over lanes l and l ^ 32.
+__device__ inline float max_over_halves(float x) {
+    const Pair<float> b = pair_of<32>(x);
+    return fmaxf(b.first, b.second);
+}
+__device__ inline float sum_over_halves(float x) {
+    const Pair<float> b = pair_of<32>(x);
+    return b.first + b.second;
 }
 
 // op over lanes l, l ^ 16, l ^ 32 and l ^ 48.

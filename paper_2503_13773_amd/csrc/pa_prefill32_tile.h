@@ -30,16 +30,8 @@ __device__ inline void static_for(const F &f) {
 }
 
 // The value lane l ^ 32 holds, next to this lane's: one swap of the two 32-lane halves.
-__device__ inline float max_over_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ inline float sum_over_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
+using lanes::max_over_halves;
+using lanes::sum_over_halves;
 
 // A operands of O^T += V^T . P^T straight from LDS.  The transposing read hands lane i of a
 // 16-lane block the i-th 16-bit element of each of the four 16-element groups that lanes

@@ -67,7 +67,6 @@ constexpr int kPreTiles = 1;   // tiles of the next step whose K operands are re
 constexpr int kVRow = D + 16;                     // padded V row in LDS (288 bytes): see the transpose reads
 constexpr int kVStepElems = kStepTokens * kVRow;
 
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // Online-softmax state of one head: 16 query rows (columns r) x 128 dims; lane (quad, r) holds
 // O[row r][16*e + 4*quad + j] in acc[e][j] (MFMA number e covers dims 16e .. 16e+15).
@@ -87,14 +86,8 @@ struct PrefillState {
 // max over the four lanes that share r (lane = 16*quad + r): the two row swaps exchange 16-lane
 // rows between the two copies of the operand, no LDS round trip.
 __device__ inline float max_over_quads(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const float a0 = __uint_as_float(a[0]), a1 = __uint_as_float(a[1]);
-    const float y = a0 > a1 ? a0 : a1;  // inputs are never NaN; a select needs no quieting moves
-    const unsigned w = __float_as_uint(y);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-    const float b0 = __uint_as_float(b[0]), b1 = __uint_as_float(b[1]);
-    return b0 > b1 ? b0 : b1;
+    // inputs are never NaN; a select needs no quieting moves
+    return lanes::over_rows(x, [](float a, float b) { return a > b ? a : b; });
 }
 
 // K operands of one 16-token tile from LDS (sk_tile: [16 tokens][128], 16-byte chunks

@@ -51,7 +51,6 @@ using mfma::bf16x8;
 using mfma::pack_bf16;
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kDim = 64;
 constexpr int kRowBytes = kDim * 2;
@@ -72,16 +71,8 @@ __device__ inline void static_for(const F &f) {
 // Nothing moves across this point when the compiler orders the instructions of a turn.
 #define KVC_PIN() __builtin_amdgcn_sched_barrier(0)
 
-__device__ inline float max_over_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ inline float sum_over_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const u32x2 b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
+using lanes::max_over_halves;
+using lanes::sum_over_halves;
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
 // 16 bytes per lane from global memory to LDS at lds_addr + 16 * lane (lds_addr uniform).  Not seen by the

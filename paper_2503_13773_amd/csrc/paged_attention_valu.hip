@@ -78,20 +78,15 @@ struct Elem<uint16_t> {  // bfloat16 bit patterns
 // workgroups waits for in every step (one sequence of 256 tokens, fp32, 16 / 4 heads of 128: 14.6 -> 10.4 us).
 // Prefill has wavefronts enough to hide it and keeps the shuffles, which leave the vector ALU free (fp32, 1000 rows,
 // 32 / 8 heads of 128: 503 us with shuffles, 566 us with permutations).
-template <int CTRL>
-__device__ inline float permuted(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
 template <int LR>
 __device__ inline float sum_over_row(float x) {  // LR = 8, 16 or 32 lanes of a token row
-    x += permuted<0xb1>(x);   // quad_perm [1, 0, 3, 2]
-    x += permuted<0x4e>(x);   // quad_perm [2, 3, 0, 1]
-    x += permuted<0x141>(x);  // row_half_mirror
-    if constexpr (LR > 8) x += permuted<0x140>(x);  // row_mirror
+    x += lanes::permuted<lanes::kXor1>(x);
+    x += lanes::permuted<lanes::kXor2>(x);
+    x += lanes::permuted<lanes::kMirror8>(x);
+    if constexpr (LR > 8) x += lanes::permuted<lanes::kMirror16>(x);
     if constexpr (LR > 16) {
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-        const u32x2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        x = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+        const lanes::Pair<float> b = lanes::pair_of<16>(x);
+        x = b.first + b.second;
     }
     return x;
 }
