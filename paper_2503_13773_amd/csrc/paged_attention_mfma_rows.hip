@@ -17,8 +17,8 @@
 //       depend on who came last), writes the row and resets the counter.  Nobody waits for anybody.
 //
 // Measured against the balanced kernel, launches back to back, 32 / 8 heads of 128: one sequence of 3217 tokens 15.0 ->
-// 10.0 us (13 MB: 2.1 us of streaming; the exchange of pieces takes about 2.5 us), 8000 tokens 24.8 -> 14 us, 32000
-// tokens 68 -> 28 us.
+// 10.3 us (13 MB: 2.1 us of streaming; the exchange of pieces takes about 2.5 us), 8000 tokens 24.8 -> 12.7 us, 32000
+// tokens 68 -> 25.9 us.
 //
 // Every wavefront works out the placement by itself: lane n holds the length of sequence n, sums and
 // prefixes are a few steps inside the vector ALU, no LDS and no barrier before the first loads (by shuffles, stamps of one sequence

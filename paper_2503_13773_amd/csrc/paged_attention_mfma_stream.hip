@@ -3,7 +3,7 @@
 //
 // Written for head_dim 128 and 16-token tiles below; at head_dim 64 a tile is 32 tokens, the same 8 KiB of
 // K and V, so ranges, loads in flight and row costs are the same (48 sequences, lognormal, 32 / 8 heads, 73 MB:
-// 18.6 us; on the vector ALUs with a merge launch 32.9 us).
+// 18.7 us; on the vector ALUs with a merge launch 32.9 us).
 //
 // The serving traces this path sees have heavily skewed context lengths (a lognormal mix:
 // median ~700 tokens, tail to 4096), and the whole batch is only ~30 us of HBM streaming.
@@ -147,7 +147,7 @@ __device__ inline void merge_cut_rows(__amdgpu_buffer_rsrc_t acc_buf, __amdgpu_b
     constexpr int kMergeBatch = 16 / PV;  // partials of a row fetched together (64 registers per row)
     // They are handled four at a time: the code of those behind the row's last four is neither run nor fetched, which is what a
     // merge spends most of its time on (stamps of the last workers: 1.2 us from the last partial's arrival to the end at
-    // head_dim 128, 1.8 at 64, with code for sixteen and eight; 48 lognormal sequences, 32 / 8 heads of 64, 19.5 -> 18.8 us).
+    // head_dim 128, 1.8 at 64, with code for sixteen and eight; 48 lognormal sequences, 32 / 8 heads of 64, 19.5 -> 18.7 us).
     constexpr int kGroup = kMergeBatch < 4 ? kMergeBatch : 4;
     float2 ml[2][kMergeBatch];
     float4 x[2][kMergeBatch][PV];

@@ -19,7 +19,9 @@
 //
 // What bounds it.  Two wavefronts of a SIMD read 128 KiB of operands from LDS per step of a compute
 // unit, 1024 cycles of its bandwidth against 1024 matrix cycles; a step of both takes about 1450 cycles
-// with its rows in L2, 1600 (four chunks of 512 rows) to 1850 (2048 tokens) where they often are not.
+// in long launches, 1600 in four chunks of 512 rows and 1850 at 2048 tokens.  Rows that are not in L2 are
+// not what the chunks wait for: with the heads of a KV head on one XCD their launch misses 0.81 M times
+// instead of 1.52 M, and takes the same time (matrix pipes busy 55 % of the cycles, 1.80 GHz).
 // One alone is bound by its own issue, about 130 instructions of 4 to 5 cycles (8 for an
 // exponential), and takes about 950 cycles for 512 matrix cycles.  A turn holds three steps: the
 // scores of the next, the weights of this one, V . P of the one before, so that the softmax

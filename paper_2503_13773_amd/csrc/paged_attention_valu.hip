@@ -199,9 +199,9 @@ __global__ __launch_bounds__(64 * WAVES) void pa_partial_valu_kernel(
     const size_t block_stride = head_stride * p.num_kv_heads;
 
     // A trip of a wavefront.  MAY_END: it may reach past the end; the lanes of tokens there load the trip's first token again (or
-    // the last one), whose V must not meet the weight 0, where it is an infinity or NaN.  One head per workgroup: every trip asks, which is shortest (fp32
-    // of 64, 4 x 256 tokens 5.06 us, with the last trip apart 5.18); several: the last trip is code of its own (fp32 of
-    // 128, four heads, 24 x 256 15.6 us, asked in every trip 16.7).
+    // the last one), whose V must not meet the weight 0, where it is an infinity or NaN.  One head per workgroup: every trip asks, which is
+    // the least code in the shortest calls (fp32 of 64, 8 / 8 heads, 1 x 40 tokens 3.3 us, with the last trip apart 3.6; 4 x 256 4.49 and
+    // 4.40); several: the last trip is code of its own (fp32 of 128, four heads, 40 x 256 25.2 us, asked in every trip 26.9).
     auto trip = [&](auto may_end, int base) __attribute__((always_inline)) {
         constexpr bool MAY_END = decltype(may_end)::value;
         float kf[UNROLL][EPL], vf[UNROLL][EPL];
@@ -449,19 +449,19 @@ hipError_t launch_for_chunk(int gc, const void *q, const void *k, const void *v,
         }
     }
     // Several heads, up to one workgroup per compute unit: sixteen wavefronts instead of four where the registers allow it and
-    // the merge in LDS is small (fp32, 24 x 256 tokens, 8 heads of 128 10.8 -> 8.7 us; four heads of 64 per workgroup 9.3 ->
-    // 9.7 us, so those stay at four).
+    // the merge in LDS is small (fp32, 24 x 256 tokens, four heads of 64 per workgroup 9.3 us with four, 9.7 with sixteen, so
+    // those stay at four).
     constexpr bool kWide = !PREFILL && sizeof(T) == 4;
 #define KVC_LAUNCH_VALU(GC)                                                                       \
     do {                                                                                          \
-        constexpr int kMany = kWide && D == 128 && GC <= 4 ? 16 : kWaves;                         \
+        constexpr int kMany = kWide && D == 128 && GC < 8 ? 16 : kWaves;                          \
         if (grid <= kNumCUs) KVC_LAUNCH_WAVES(GC, kMany, 4); else KVC_LAUNCH_WAVES(GC, kWaves, 4); \
     } while (0)
     switch (gc) {
         case 8: KVC_LAUNCH_VALU(8); break;
         case 4: KVC_LAUNCH_VALU(4); break;
         case 2: KVC_LAUNCH_VALU(2); break;
-        default: KVC_LAUNCH_VALU(1); break;
+        default: KVC_LAUNCH_WAVES(1, kWaves, 4); break;  // prefill, and more than two workgroups a compute unit
     }
 #undef KVC_LAUNCH_VALU
 #undef KVC_LAUNCH_AS
