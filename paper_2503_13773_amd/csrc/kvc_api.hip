@@ -353,18 +353,18 @@ int check_workspace(const Plan &pl, void *workspace, size_t workspace_bytes, kvc
 }
 
 // Whether the vector-ALU kernel merges the partitions of a context itself: a counter word for each (sequence, heads of a
-// workgroup), and no more partials than a wavefront holds weights of at once.  It saves the second launch for a count and a fetch, us
-// in two launches / one: fp32, 12 / 12 heads of 64, 7 x 607 tokens 7.4 / 6.8, 16 / 4 of 128, 5 x 1000 18.5 / 17.7; bf16 of 64, 14 / 2, 4 x 1500
-// 7.6 / 7.6.  The last workgroup of a row fetches that row's partials alone, after its own are published, while the launch
-// spreads all of them; so few rows of many partitions, which all end at about the same time, do better in two launches: bf16 of 64, 16 / 16, 1 x
-// 8192, 32 partitions, 9.1 / 12.4, 14 / 2, 1 x 6144 8.1 / 9.9; fp32, 16 / 4 of 64, 1 x 4096 7.8 / 9.3.  In all, one launch : two
-// is 0.96 up to 8 partitions (bf16 4) and from 32 rows on (bf16 64), and 1.02 with less of both, up to 1.27.  Eight heads, which four
-// wavefronts merge in two turns: 1.02 (64 / 8 heads of 64, 2 x 4096, bf16 13.1 / 16.1, fp32 17.9 / 20.5).
+// workgroup), and no more partials than a wavefront holds weights of at once.  It saves the second launch for a count and a fetch, us in two
+// launches / one: fp32, 12 / 12 heads of 64, 7 x 607 tokens 7.4 / 6.8, 16 / 4 of 128, 5 x 1000 18.5 / 17.7; bf16 of 64, 14 / 2, 4 x 1500 7.6 /
+// 7.6, 4 of up to 587 under a bound of 1174 6.4 / 5.9.  The last workgroup of a row fetches that row's partials alone, after its own are
+// published, while the launch spreads all of them; so few rows of many partitions, which all end at about the same time, do better in two
+// launches: bf16 of 64, 16 / 16, 1 x 8192, 32 partitions, 9.1 / 12.4, 14 / 2, 1 x 6144 8.1 / 9.9; fp32, 16 / 4 of 64, 1 x 4096 7.8 / 9.3.  In
+// all, one launch : two is 0.96 up to 8 partitions (bf16 6) and from 32 rows on (bf16 64), and 1.02 with less of both, up to 1.27.  Eight
+// heads, which four wavefronts merge in two turns: 1.02 (64 / 8 heads of 64, 2 x 4096, bf16 13.1 / 16.1, fp32 17.9 / 20.5).
 bool merges_itself(const kvc_attn_desc &d, const Plan &pl) {
     const int64_t rows = int64_t(d.num_seqs) * (d.num_q_heads / std::max(pl.head_chunk, 1));
     const bool wide = d.dtype == KVC_F32;
     return pl.kernel == KVC_KERNEL_VALU && pl.head_chunk < 8 && pl.max_partitions > 1 && pl.max_partitions <= 64 &&
-           (pl.max_partitions <= (wide ? 8 : 4) || rows >= (wide ? 32 : 64)) &&
+           (pl.max_partitions <= (wide ? 8 : 6) || rows >= (wide ? 32 : 64)) &&
            rows <= int64_t(kvc::kWorkspaceHeaderBytes / sizeof(int32_t));
 }
 
